@@ -8,10 +8,7 @@
 //                 the blocks arrive by global->LDS DMA through a ring of four 64-key
 //                 tiles, three tiles ahead; the waves run freely between one s_barrier
 //                 per tile, so the two waves of a SIMD fill each other's MFMA and VALU
-//                 gaps.  An item may name a second, earlier tile of the same sequence and
-//                 KV head, which the work-group computes afterwards (whole prompts with
-//                 many tiles per CU: half as many work-group starts).
-//                 For an fp8 cache a chunk of few tiles converts the codes on their way
+//                 gaps.  For an fp8 cache a chunk of few tiles converts the codes on their way
 //                 into LDS (through registers, two stages); a chunk of many tiles reads a
 //                 bf16 copy of its sequence that kv_stage_kernel makes first, through the
 //                 same DMA pipeline as a bf16 cache.
@@ -261,7 +258,8 @@ __device__ __forceinline__ void run_wide_staged(const AttnParams& p, const WorkI
   constexpr int ESZ = FP8 ? 1 : 2;
   using Raw = typename RawChunk<FP8>::type;
 
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
   const int lane = tid & 63, half = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, it.n_blocks};
@@ -520,7 +518,8 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
   constexpr int UPB = BLK_LDS / 1024;     // units per block
   constexpr int NI = 2 * UPW;             // DMA instructions per wave per tile
 
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
   const int lane = tid & 63, half = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, it.n_blocks};
@@ -817,7 +816,8 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   constexpr int WAVE_LDS = 2 * NSTEP * 1024 + (FP8 ? 512 : 0);  // per-wave LDS: K planes then V planes (= NACC * 256); fp8: two sets of block images
   using Raw = typename RawChunk<FP8>::type;
 
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
   const int lane = tid & 63, half = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, it.n_blocks};
@@ -1081,21 +1081,52 @@ constexpr int attn_lds_bytes() {
   constexpr int wide_lds = 4 * 2 * 4 * 16 * D * 2;  // stages x (K + V tile of 64 keys)
   constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * 64 * 4;
   constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
-  static_assert(lds + 64 <= 160 * 1024, "LDS budget (the buffers and the 64-byte mailbox of the item loop)");
+  static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
   return lds;
 }
 
-// Index of the next work item for a work-group that runs on XCD `xcc`, or -1 when every
-// queue is empty: the own queue first, then the others in ring order (a queue's head only
-// grows, so a queue found empty stays empty).
-__device__ __forceinline__ int take_item(const AttnParams& p, int xcc) {
-  for (int k = 0; k < kQueues; ++k) {
-    const int y = (xcc + k) & (kQueues - 1);
-    if (p.q_len[y] == 0) continue;
-    const int idx = __hip_atomic_fetch_add(p.q_heads + y * kCounterStride, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (idx < p.q_len[y]) return p.q_base[y] + idx;
+// Behind the kernels' LDS buffers: two mailboxes of 16 ints (an item's record; the item loop
+// alternates between them, so one barrier per item separates writing and reading), then for
+// lane k = 0 .. 7 the dynamic part of queue (xcc + k) mod 8 as (items, first item).
+constexpr int kLoopLdsBytes = 2 * 64 + 2 * 4 * kQueues;
+
+// Items of queue x that are handed out without a ticket: work-group b starts with item b / 8
+// of queue b mod 8 (the dispatcher deals work-groups to the XCDs in turn), so the first
+// items of a launch need no atomic, and a launch with no more items than work-groups needs
+// none at all.
+__device__ __forceinline__ int static_items(const AttnParams& p, int x) {
+  return min(p.q_len[x], ((int)gridDim.x - x + kQueues - 1) / kQueues);
+}
+
+// Index of the next work item for a work-group of XCD `xcc`, or -1 when every queue is
+// empty: the own queue first, then the others in ring order (a queue's head only grows, so
+// a queue found empty stays empty).  One memory round trip takes the ticket of the own
+// queue (lane 0) and looks at the heads of the other seven (lanes 1 .. 7), so finding out
+// that nothing is left costs one round trip and not eight: measured on a decode batch that
+// gives every CU one item, 4.2 us -> 1.3 us between a work-group's last item and its end.
+__device__ __forceinline__ int take_item(const AttnParams& p, const int* dyn, int xcc, int lane) {
+  int len = 0, base = 0, head = 0;
+  if (lane < kQueues) {
+    len = dyn[2 * lane];
+    base = dyn[2 * lane + 1];
   }
-  return -1;
+  if (__builtin_amdgcn_ballot_w64(len > 0) == 0) return -1;
+  int* const q = p.q_heads + ((xcc + lane) & (kQueues - 1)) * kCounterStride;
+  if (len > 0) {
+    if (lane == 0) head = __hip_atomic_fetch_add(q, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else head = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  bool ticket = lane == 0;  // this lane's head is a ticket, not a look
+  for (;;) {
+    const unsigned long long open = __builtin_amdgcn_ballot_w64(head < len);
+    if (open == 0) return -1;
+    const int l = __builtin_ctzll(open);
+    if (__builtin_amdgcn_readlane((int)ticket, l)) return __builtin_amdgcn_readlane(base + head, l);
+    if (lane == l) {
+      head = __hip_atomic_fetch_add(q, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ticket = true;
+    }
+  }
 }
 
 // The work-groups of a launch stay resident, one per CU (the LDS they use allows no second
@@ -1109,27 +1140,41 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
   static_assert(kQueues == 8, "XCC_ID is masked to three bits");
   // hardware register XCC_ID (id 20), bits 3:0: the XCD this work-group runs on
   const int xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (kQueues - 1);
-  int* const mailbox = reinterpret_cast<int*>(smem + attn_lds_bytes<D, FP8>());  // 16 ints behind the kernels' buffers
-  for (;;) {
+  int* const mailboxes = reinterpret_cast<int*>(smem + attn_lds_bytes<D, FP8>());
+  int* const dyn = mailboxes + 32;
+  int next = -1;  // wave 0: the item this work-group starts with
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    const int y = (xcc + lane) & (kQueues - 1);
+#pragma unroll
+    for (int x = 0; x < kQueues; ++x) {
+      const int n_static = static_items(p, x), i = blockIdx.x / kQueues;
+      if ((blockIdx.x & (kQueues - 1)) == (unsigned)x && i < n_static) next = p.q_base[x] + i;
+      if (lane < kQueues && x == y) {
+        dyn[2 * lane] = p.q_len[x] - n_static;
+        dyn[2 * lane + 1] = p.q_base[x] + n_static;
+      }
+    }
+  }
+  for (int turn = 0;; turn ^= 1) {
+    int* const mailbox = mailboxes + 16 * turn;
     // wave 0 takes the next item and posts its record; lanes 0-15 fetch one dword each
     if (threadIdx.x < 64) {
-      int idx = 0;
-      if (threadIdx.x == 0) idx = take_item(p, xcc);
-      idx = __builtin_amdgcn_readfirstlane(idx);
+      const int idx = next >= 0 ? next : take_item(p, dyn, xcc, threadIdx.x);
+      next = -1;
       if (threadIdx.x < 16) {
         int v = threadIdx.x == 9 ? -1 : 0;  // field 9 = WorkItem::wide; -1: nothing left
         if (idx >= 0) v = reinterpret_cast<const int*>(p.items + idx)[threadIdx.x];
         mailbox[threadIdx.x] = v;
       }
     }
-    __syncthreads();
+    __syncthreads();  // the record is there, and every wave is done with the last item's LDS
     WorkItem it;
     {
       int* f = reinterpret_cast<int*>(&it);
 #pragma unroll
       for (int i = 0; i < 16; ++i) f[i] = __builtin_amdgcn_readfirstlane(mailbox[i]);
     }
-    __syncthreads();  // the mailbox may be rewritten, and the item's LDS buffers reused, from here on
     if (it.wide < 0) break;
     if (it.n_tok <= 0 || it.n_heads <= 0) continue;
     if (it.wide) {
@@ -1142,18 +1187,17 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
     } else {
       run_narrow<D, FP8>(p, it, smem);
     }
-    __syncthreads();  // every wave is done with this item's LDS before the next one's fetches land
   }
   // No queue has an item left for this work-group.  The last work-group of the launch to get
   // here (every other one has taken its last ticket) zeroes the heads for the next launch.
   if (threadIdx.x == 0) {
     int* const done = p.q_heads + kQueues * kCounterStride;
-    const unsigned finished = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned finished = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (finished == gridDim.x - 1) {
 #pragma unroll
       for (int x = 0; x < kQueues; ++x)
         __hip_atomic_store(p.q_heads + x * kCounterStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(done, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -1268,7 +1312,7 @@ template <int D, bool FP8>
 int prepare_typed() {
   auto kern = attn_mixed_kernel<D, FP8>;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             attn_lds_bytes<D, FP8>() + 64) == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
+                             attn_lds_bytes<D, FP8>() + kLoopLdsBytes) == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
 }
 
 // Launches of one call, in order: the fp8 copy (if any sequence has one), the main kernel, the
@@ -1277,7 +1321,7 @@ int prepare_typed() {
 // differences are kernel durations without the launch latency around them.
 template <int D, bool FP8>
 int launch_typed(const AttnLaunch& a, const AttnParams& p) {
-  constexpr int lds = attn_lds_bytes<D, FP8>() + 64;
+  constexpr int lds = attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
   hipStream_t s = static_cast<hipStream_t>(a.stream);
   const Plan& pl = *a.plan;
   auto ev = [&](int i) { return static_cast<hipEvent_t>(a.ev[i]); };
