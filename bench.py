@@ -4,7 +4,7 @@
 A step is one pass of the whole path over one synthetic batch: ingest of the
 transferred prefixes of the continuation chunks (cronus_kv_append), append of the
 iteration's new K/V rows (cronus_kv_append), and the mixed attention
-(cronus_attn_mixed: work decomposition, chunk tiles, decode spans, merge).  Inputs are
+(cronus_attn_mixed: work decomposition, chunk tiles, decode spans and their merge).  Inputs are
 resident in HBM before the timed region.  Prints ONE JSON line.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--no-extra]
@@ -90,10 +90,10 @@ def time_workload(name, steps, warmup, trial=0):
     gc.collect()
     gc.disable()
     try:
-        # four events per timed step: start/stop of the main kernel's own dispatch, start of the
-        # call's first kernel if that is the fp8 copy, stop of its last if that is the merge
+        # three events per timed step: start/stop of the main kernel's own dispatch (which also merges
+        # the results of key spans), start of the call's first kernel if that is the fp8 copy
         ev = B.HipEvents()
-        quads = [tuple(ev.create() for _ in range(4)) for _ in range(steps)]
+        quads = [tuple(ev.create() for _ in range(3)) for _ in range(steps)]
         for q in quads:  # first use of an event is slow (lazy allocation): keep it out of the timed region
             B.cronus_profile_events(*q)
             it.attention()
@@ -119,8 +119,7 @@ def time_workload(name, steps, warmup, trial=0):
         gc.enable()
     B.cronus_profile_events(None, None)
     main_ms = np.array([ev.elapsed_ms(q[0], q[1]) for q in quads])
-    span_ms = np.array([ev.elapsed_ms(q[2] if stats["copy_blocks"] else q[0], q[3] if stats["merge_groups"] else q[1])
-                        for q in quads])
+    span_ms = np.array([ev.elapsed_ms(q[2] if stats["copy_blocks"] else q[0], q[1]) for q in quads])
     for q in quads:
         for e in q:
             ev.destroy(e)
@@ -141,7 +140,7 @@ def time_workload(name, steps, warmup, trial=0):
         "kv_tokens_per_s": int(batch.kv_lens.sum()) / (ms_per_step * 1e-3),
         "ms_per_step": ms_per_step,
         # the whole attention of a call on the device: first kernel's start to last kernel's end
-        # (fp8 copy, main kernel, merge, and the gaps between them)
+        # (fp8 copy, main kernel, and the gap between them)
         "attn_ms": span_mean, "attn_ms_median": float(np.median(span_ms)), "attn_ms_min": float(span_ms.min()),
         # the main kernel alone (what a profiler's kernel trace lists as attn_mixed_kernel)
         "attn_kernel_ms": main_mean, "attn_kernel_ms_median": float(np.median(main_ms)),
@@ -160,9 +159,9 @@ def time_workload(name, steps, warmup, trial=0):
         "append_algorithmic_bytes": append_bytes,
         "plan": stats,
         # achieved = the call's algorithmic work / mean duration of ALL its attention kernels (span
-        # above), so the copy and merge kernels are charged; frac_main_kernel_only divides by the
+        # above), so the copy kernel is charged; frac_main_kernel_only divides by the
         # main kernel's own duration, the figure a kernel trace's average reproduces
-        "roofline": {"bound": bound, "kernel": "attn_mixed_kernel (+ kv_stage_kernel, attn_merge_kernel of the same call)",
+        "roofline": {"bound": bound, "kernel": "attn_mixed_kernel (+ kv_stage_kernel of the same call)",
                      "achieved": rate(span_mean), "peak": peak, "unit": unit, "frac": rate(span_mean) / peak,
                      "frac_median": rate(float(np.median(span_ms))) / peak,
                      "frac_main_kernel_only": rate(main_mean) / peak,

@@ -181,8 +181,8 @@ size_t cronus_attn_mixed_workspace_bytes(const cronus_kv_cache* cache, const int
  * cronus_attn_mixed_plan_stats - how the work decomposition (mixed batch of section
  * 4.4 turned into tiles) would look for these lengths.  stats (host, int64[6]):
  * [0] work items launched, [1] of those that are wide (chunk) tiles, [2] split partial
- * results, [3] rows merged from partials, [4] work-groups of the merge kernel (0: it is
- * not launched), [5] cache blocks converted by the fp8 copy kernel (0: it is not
+ * results, [3] rows merged from partials, [4] groups of up to 32 such rows (0: nothing is
+ * split; the main kernel merges them itself), [5] cache blocks converted by the fp8 copy kernel (0: it is not
  * launched).  Returns a cronus_status.
  */
 int cronus_attn_mixed_plan_stats(const cronus_kv_cache* cache, const int32_t* prefix_lens,
@@ -272,12 +272,12 @@ int cronus_balancer_split(const cronus_balancer_model* model, int64_t l_in, int6
  * cronus_attn_mixed launches its main attention kernel with them as the start and stop
  * events of that dispatch (hipExtLaunchKernel), on that call's stream:
  * hipEventElapsedTime(main_start, main_stop) is then the duration of that one kernel (within
- * a few microseconds of what a profiler's kernel trace shows for it).  A call may launch two
- * more kernels: the fp8 copy before the main kernel (cronus_attn_mixed_plan_stats [5] > 0) and
- * the merge after it ([4] > 0).  first_start, if set, becomes the start event of the copy
- * kernel when there is one, and last_stop the stop event of the merge kernel when there is
- * one; otherwise they are left untouched.  The whole attention of a call thus spans from
- * (copy ? first_start : main_start) to (merge ? last_stop : main_stop).  Pass four NULLs to
+ * a few microseconds of what a profiler's kernel trace shows for it).  A call may launch one
+ * more kernel: the fp8 copy before the main kernel (cronus_attn_mixed_plan_stats [5] > 0).
+ * first_start, if set, becomes the start event of the copy kernel when there is one; last_stop,
+ * if set, is recorded on the stream behind the main kernel when the call merges results of key
+ * spans ([4] > 0); otherwise they are left untouched.  The main kernel does that merging, so
+ * the whole attention of a call spans from (copy ? first_start : main_start) to main_stop.  Pass four NULLs to
  * switch it off (the default).  Process-wide; not meant for concurrent callers.
  */
 void cronus_profile_events(void* main_start, void* main_stop, void* first_start, void* last_stop);

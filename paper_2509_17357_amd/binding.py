@@ -107,7 +107,7 @@ def version() -> int:
 def cronus_profile_events(main_start: int | None, main_stop: int | None, first_start: int | None = None,
                           last_stop: int | None = None) -> None:
     """Events of the main kernel's dispatch; optionally the start of the call's first kernel
-    (when that is the fp8 copy) and the stop of its last kernel (when that is the merge)."""
+    (when that is the fp8 copy), and an event behind the main kernel of a call that merges key spans."""
     lib().cronus_profile_events(ctypes.c_void_p(main_start), ctypes.c_void_p(main_stop),
                                 ctypes.c_void_p(first_start), ctypes.c_void_p(last_stop))
 

@@ -16,8 +16,8 @@
 //                 keys; the 8 waves split the span and stream K/V from the paged pools
 //                 through private LDS (bf16: the chunk each lane needs, 16 bytes; fp8:
 //                 whole blocks, from which the lanes pick their 8-byte chunks).
-// Items that cover a span only leave (O, m, l) partial results, which the merge kernel
-// combines.
+// Items that cover a span only leave (O, m, l) partial results; the wave whose result of a
+// row group arrives last combines them (arrive_last below): there is no merge launch.
 //
 // Both compute S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, so a
 // lane owns one query row (column of S^T): its softmax statistics are lane-local
@@ -69,7 +69,6 @@ struct AttnParams {
   const float* v_scale;
   const int* block_tables;
   const WorkItem* items;
-  const MergeItem* merges;
   float* partials;
   const StageSeq* stage_seqs;   // fp8 cache: sequences with a bf16 copy of their K/V in the workspace
   unsigned char* stage_k;       // the copy: [block][Hkv][16 x D bf16], chunk layout as in the cache
@@ -79,6 +78,7 @@ struct AttnParams {
   int n_q_heads;
   int n_kv_heads;
   float scale_log2e;  // sm_scale * log2(e)
+  int* merge_counters;  // kMaxMergeGroups x kWaves arrivals of spans; all zero between launches
   int* q_heads;       // head of queue x at q_heads[x * kCounterStride], finished work-groups at
                       // q_heads[kQueues * kCounterStride]; all zero when the kernel starts and when it ends
   int q_base[kQueues];
@@ -222,27 +222,96 @@ __device__ __forceinline__ void store_row_bf16(unsigned short* row_ptr, const f3
     }
 }
 
-// Leave one lane's share of an unfinished row in a partial-result slot (O[32][D] fp32,
-// then m[32] in log2 units, then l[32]): `row` is the row's index inside the slot, lt the
-// row sum over both lanes of the row.
+// Partial results of key spans.  A slot holds 32 rows: O (32 x D fp32; a wide tile's wave
+// writes it in the order of its registers, a narrow item row by row), then (m in log2 units,
+// l) of every row.  Every XCD has its own L2, so the slots are written and read with agent
+// scope (relaxed 8-byte atomics: plain stores that write through and loads that do not hit a
+// stale line), which costs no cache write-back or invalidation.
+typedef unsigned long long u64;
+__device__ __forceinline__ void put_pair(float* p, float a, float b) {
+  __hip_atomic_store(reinterpret_cast<u64*>(p), (u64)__float_as_uint(a) | ((u64)__float_as_uint(b) << 32), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x2 get_pair(const float* p) {
+  const u64 v = __hip_atomic_load(reinterpret_cast<const u64*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return f32x2{__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32))};
+}
+
+// To be called by a whole wave after it has stored its partial result of a row group:
+// true for the wave that is the last of the group's n_split spans to get here, which then
+// combines all of them.  The wave's stores are acknowledged before its arrival is counted,
+// and the last arrival is known before the first load of the others' results is issued.
+// The last one puts the counter back to zero for the next launch.
+__device__ __forceinline__ bool arrive_last(int* counter, int n_split, int lane) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  int before = 0;
+  if (lane == 0) before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const bool last = __builtin_amdgcn_readfirstlane(before) == n_split - 1;
+  if (last && lane == 0) __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::: "memory");
+  return last;
+}
+// The counter of one wave's share of a merge group.
+__device__ __forceinline__ int* merge_counter(const AttnParams& p, const WorkItem& it, int wave) {
+  return p.merge_counters + (it.merge_key & (kMaxMergeGroups - 1)) * kWaves + wave;
+}
+__device__ __forceinline__ int merge_splits(const WorkItem& it) { return it.merge_key / kMaxMergeGroups; }
+
+// Largest running reference (log2 units) that the spans of a row group left for one row;
+// ml: the row's (m, l) pair in the first span's slot.
+__device__ __forceinline__ float merge_max(const float* ml, size_t step, int n_split) {
+  float mt = kNeg * 4.f;
+  for (int s0 = 0; s0 < n_split; s0 += 4) {  // four loads in flight
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = get_pair(ml + min(s0 + k, n_split - 1) * step)[0];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) mt = fmaxf(mt, v[k]);
+  }
+  return mt;
+}
+
+// A wave's share (32 rows) of a wide tile that was cut into spans: store the partial result,
+// and, as the last wave of the row group to arrive, combine the spans in order:
+// O = sum_s O_s 2^(m_s - M), l = sum_s l_s 2^(m_s - M), M = max_s m_s.  Returns whether o
+// and lt now hold the finished rows.
 template <int NDB, int D>
-__device__ __forceinline__ void store_partial_row(float* slot, int row, const f32x16 (&o)[NDB], float m_log2,
-                                                  float lt, int half) {
-  float* orow = slot + row * D;
+__device__ __forceinline__ bool merge_wide_rows(const AttnParams& p, const WorkItem& it, int wave, int lane,
+                                                f32x16 (&o)[NDB], float m_log2, float& lt) {
+  constexpr size_t kSlot = (size_t)kNarrowRows * (D + 2);
+  const int half = lane >> 5, c32 = lane & 31;
+  float* ps = p.partials + (size_t)(it.partial + wave) * kSlot;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      f32x4 lo4 = {o[db][8 * j], o[db][8 * j + 1], o[db][8 * j + 2], o[db][8 * j + 3]};
-      f32x4 hi4 = {o[db][8 * j + 4], o[db][8 * j + 5], o[db][8 * j + 6], o[db][8 * j + 7]};
-      float* dp = orow + 32 * db + 16 * j + 8 * half;
-      *reinterpret_cast<f32x4*>(dp) = lo4;
-      *reinterpret_cast<f32x4*>(dp + 4) = hi4;
+    for (int i = 0; i < 8; ++i) put_pair(ps + ((db * 8 + i) * 64 + lane) * 2, o[db][2 * i], o[db][2 * i + 1]);
+  if (half == 0) put_pair(ps + kNarrowRows * D + 2 * c32, m_log2, lt);
+  const int n_split = merge_splits(it);
+  if (!arrive_last(merge_counter(p, it, wave), n_split, lane)) return false;
+  const float* base = p.partials + (size_t)(it.first_partial + wave) * kSlot;
+  const size_t step = kSlot * kWaves;
+  const float* ml = base + kNarrowRows * D + 2 * c32;
+  const float mt = merge_max(ml, step, n_split);
+  lt = 0.f;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+  for (int s = 0; s < n_split; ++s) {
+    const float* sp = base + s * step + 2 * lane;
+    f32x2 v[NDB * 8];
+    const f32x2 st = get_pair(ml + s * step);
+#pragma unroll
+    for (int k = 0; k < NDB * 8; ++k) v[k] = get_pair(sp + k * 128);
+    const float w = __builtin_amdgcn_exp2f(st[0] - mt);
+    lt += st[1] * w;
+#pragma unroll
+    for (int k = 0; k < NDB * 8; ++k) {
+      o[k / 8][2 * (k & 7)] += v[k][0] * w;
+      o[k / 8][2 * (k & 7) + 1] += v[k][1] * w;
     }
-  if (half == 0) {
-    slot[kNarrowRows * D + row] = m_log2;
-    slot[kNarrowRows * D + kNarrowRows + row] = lt;
   }
+  return true;
 }
 
 // ---------------------------------------- wide (chunk) tile, staged through registers
@@ -405,13 +474,9 @@ __device__ __forceinline__ void run_wide_staged(const AttnParams& p, const WorkI
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
     const int r = row_base + qt * 32 + c32;
-    const float lt = pair_sum(l[qt]);
+    float lt = pair_sum(l[qt]);
+    if (it.partial >= 0 && (!wave_active || !merge_wide_rows<NDB, D>(p, it, wave, lane, o[qt], m[qt] * c, lt))) continue;
     if (r < rows_valid) {
-      if (it.partial >= 0) {
-        float* ps = p.partials + (long long)(it.partial + wave) * (kNarrowRows * (D + 2));
-        store_partial_row<NDB, D>(ps, c32, o[qt], m[qt] * c, lt, half);
-        continue;
-      }
       const int t = r / gi_n, gi = r - t * gi_n;
       unsigned short* op = p.out + ((long long)(si.q_off + it.q_tok0 + t) * p.n_q_heads + it.head0 + gi) * D;
       store_row_bf16<NDB>(op, o[qt], vmul / lt, half);
@@ -765,15 +830,11 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
   wait_vmcnt<0>();  // fetches past the item's last tile are still landing in LDS
   __builtin_amdgcn_s_barrier();
 
-  const float lt = pair_sum(l);
+  float lt = pair_sum(l);
+  if (it.partial >= 0 && (!wave_has_rows || !merge_wide_rows<NDB, D>(p, it, wave, lane, o, m * c, lt))) return;
   if (row_base + c32 < rows_valid) {
-    if (it.partial >= 0) {
-      float* ps = p.partials + (long long)(it.partial + wave) * (kNarrowRows * (D + 2));
-      store_partial_row<NDB, D>(ps, c32, o, m * c, lt, half);
-    } else {
-      unsigned short* op = p.out + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D;
-      store_row_bf16<NDB>(op, o, vmul / lt, half);
-    }
+    unsigned short* op = p.out + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D;
+    store_row_bf16<NDB>(op, o, vmul / lt, half);
   }
 }
 
@@ -1027,50 +1088,101 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     }
   }
 
-  // combine the waves (each covered different keys) pairwise, in log2(waves) rounds: a
-  // wave that is a source of the coming round parks its accumulators in its own LDS
-  // planes (its reads of them are complete), the wave kWaves/2, then /4, ... below it
-  // folds them into its own
-  float* xo = reinterpret_cast<float*>(smem + wave * WAVE_LDS) + lane;        // [NACC][64]
-  float* xs = reinterpret_cast<float*>(smem + kWaves * WAVE_LDS) + lane;      // [kWaves][2][64]
-  auto park = [&]() {
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) xo[(db * 16 + i) * 64] = o[db][i];
-    xs[(wave * 2) * 64] = m;
-    xs[(wave * 2 + 1) * 64] = l;
-  };
-  if (wave >= kWaves / 2) park();
-#pragma unroll 1
-  for (int n = kWaves / 2; n >= 1; n >>= 1) {
-    __syncthreads();
-    if (wave < n) {
-      const int w2 = wave + n;
-      const float* w = reinterpret_cast<const float*>(smem + w2 * WAVE_LDS) + lane;
-      const float mo = xs[(w2 * 2) * 64], lo = xs[(w2 * 2 + 1) * 64];
-      const float mn = fmaxf(m, mo);
-      const float a0 = __builtin_amdgcn_exp2f((m - mn) * c), a1 = __builtin_amdgcn_exp2f((mo - mn) * c);
+  // Combine the waves, which covered different keys: each parks the valid rows of its O in
+  // its own LDS planes (its reads of them are complete) and its (m, l), and after one barrier
+  // four dims of a row belong to one thread, which adds up the waves.  16-byte units of a row
+  // are swizzled by the row, so that lanes that write different rows hit different banks.
+  // (A pairwise fold of the waves' registers in three rounds took 2.5 us of a decode's span;
+  // only G of the 32 columns of the MFMA tile are rows there.)
+  constexpr int U = D / 4;
+  static_assert(kNarrowRows * D * 4 <= WAVE_LDS, "a wave parks 32 rows in its planes");
+  float* xs = reinterpret_cast<float*>(smem + kWaves * WAVE_LDS);  // [kWaves][32] (m in log2 units, l)
+  {
+    const float lt = pair_sum(l);
+    if (c32 < rows_valid) {
+      f32x4* xo = reinterpret_cast<f32x4*>(smem + wave * WAVE_LDS) + c32 * U;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[db][i] = o[db][i] * a0 + w[(db * 16 + i) * 64] * a1;
-      l = l * a0 + lo * a1;
-      m = mn;
-      if (2 * wave >= n) park();  // n/2 <= wave < n: a source of the next round
+        for (int i = 0; i < 4; ++i) {
+          const int unit = 8 * db + 4 * (i >> 1) + 2 * half + (i & 1);
+          xo[unit ^ (c32 & (U - 1))] = f32x4{o[db][4 * i], o[db][4 * i + 1], o[db][4 * i + 2], o[db][4 * i + 3]};
+        }
+      if (half == 0) {
+        xs[(wave * kNarrowRows + c32) * 2] = m * c;
+        xs[(wave * kNarrowRows + c32) * 2 + 1] = lt;
+      }
     }
   }
-  if (wave == 0) {
-    float lt = pair_sum(l);
-    if (c32 < rows_valid) {
-      if (it.partial < 0) {
-        const float vmul = FP8 ? p.v_scale[it.kv_head] : 1.0f;
-        unsigned short* op =
-            p.out + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D;
-        store_row_bf16<NDB>(op, o, vmul / lt, half);
-      } else {
-        float* ps = p.partials + (long long)it.partial * (kNarrowRows * (D + 2));
-        store_partial_row<NDB, D>(ps, c32, o, m * c, lt, half);  // running maximum in log2 units
+  __syncthreads();
+  // the last waves take the first rows: wave 0 is on its way to the next item's record
+  const int mt = tid ^ (kThreads - 64);
+  constexpr size_t kSlot = (size_t)kNarrowRows * (D + 2);
+  const float vmul = FP8 ? p.v_scale[it.kv_head] : 1.0f;
+  auto store_out = [&](int row, int u, f32x4 acc, float f) {
+    const int t = row / gi_n, gi = row - t * gi_n;
+    unsigned short* op = p.out + ((long long)(si.q_off + it.q_tok0 + t) * p.n_q_heads + it.head0 + gi) * D + 4 * u;
+    *reinterpret_cast<u32x2*>(op) = u32x2{pack_bf16(acc[0] * f, acc[1] * f), pack_bf16(acc[2] * f, acc[3] * f)};
+  };
+  for (int e = mt; e < rows_valid * U; e += kThreads) {
+    const int row = e / U, u = e % U;
+    float ms[kWaves], ls[kWaves], mx = kNeg * 4.f;
+    f32x4 ov[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      ms[w] = xs[(w * kNarrowRows + row) * 2];
+      ls[w] = xs[(w * kNarrowRows + row) * 2 + 1];
+      ov[w] = reinterpret_cast<const f32x4*>(smem + w * WAVE_LDS)[row * U + (u ^ (row & (U - 1)))];
+    }
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, ms[w]);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float lsum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float a = __builtin_amdgcn_exp2f(ms[w] - mx);
+      acc += ov[w] * a;
+      lsum += ls[w] * a;
+    }
+    if (it.partial < 0) {
+      store_out(row, u, acc, vmul / lsum);
+    } else {
+      float* ps = p.partials + (size_t)it.partial * kSlot;
+      put_pair(ps + row * D + 4 * u, acc[0], acc[1]);
+      put_pair(ps + row * D + 4 * u + 2, acc[2], acc[3]);
+      if (u == 0) put_pair(ps + kNarrowRows * D + 2 * row, mx, lsum);
+    }
+  }
+  // a wave's rows are complete as soon as that wave of every span has arrived
+  const int mwave = kWaves - 1 - wave;
+  if (it.partial >= 0 && mwave * 64 < rows_valid * U) {
+    const int n_split = merge_splits(it);
+    if (arrive_last(merge_counter(p, it, mwave), n_split, lane)) {
+      const float* base = p.partials + (size_t)it.first_partial * kSlot;
+      for (int e = mt; e < rows_valid * U; e += kThreads) {
+        const int row = e / U, u = e % U;
+        const float* ml = base + kNarrowRows * D + 2 * row;
+        const float* op = base + row * D + 4 * u;
+        const float mx = merge_max(ml, kSlot, n_split);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float lsum = 0.f;
+        for (int s0 = 0; s0 < n_split; s0 += 4) {  // twelve loads in flight
+          f32x2 st[4], lo[4], hi[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const size_t off = min(s0 + k, n_split - 1) * kSlot;
+            st[k] = get_pair(ml + off);
+            lo[k] = get_pair(op + off);
+            hi[k] = get_pair(op + off + 2);
+          }
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float a = s0 + k < n_split ? __builtin_amdgcn_exp2f(st[k][0] - mx) : 0.f;
+            acc += f32x4{lo[k][0], lo[k][1], hi[k][0], hi[k][1]} * a;
+            lsum += st[k][1] * a;
+          }
+        }
+        store_out(row, u, acc, vmul / lsum);
       }
     }
   }
@@ -1079,7 +1191,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
 template <int D, bool FP8>
 constexpr int attn_lds_bytes() {
   constexpr int wide_lds = 4 * 2 * 4 * 16 * D * 2;  // stages x (K + V tile of 64 keys)
-  constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * 64 * 4;
+  constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * kNarrowRows * 4;
   constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
   static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
   return lds;
@@ -1235,79 +1347,6 @@ __global__ __launch_bounds__(kStageThreads) void kv_stage_kernel(AttnParams p) {
   }
 }
 
-// Combine the partial results of a row group that was split over key spans:
-// out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s (m in log2 units).
-// D/4 threads share a row (four dims each); a work-group of 256 threads covers 1024/D rows
-// per pass and keeps all passes of the item's (at most 32) rows in flight at once, so the
-// loads of a span for every row are issued together: the kernel is bound by memory
-// latency (a row's spans are combined in span order, the sums depend on each other).
-constexpr int kMergeThreads = 256;
-template <int D, bool FP8>
-__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) {
-  constexpr int TPR = D / 4, RPP = kMergeThreads / TPR, NPASS = kNarrowRows / RPP;
-  static_assert(NPASS * RPP == kNarrowRows, "a merge item has at most kNarrowRows rows");
-  const MergeItem mi = p.merges[blockIdx.x];
-  const int dq = threadIdx.x % TPR;
-  const size_t slot = (size_t)kNarrowRows * (D + 2);
-  const size_t step = slot * (size_t)mi.stride;
-  const float vmul = FP8 ? p.v_scale[mi.kv_head] : 1.0f;
-  const float* base = p.partials + (size_t)mi.first_partial * slot;
-  // pass k covers rows k * RPP ..; a pass past the item's last row is skipped as a whole
-  // (decodes have G rows), inside a pass the rows past the last repeat it (loaded, never stored)
-  int row[NPASS];
-#pragma unroll
-  for (int k = 0; k < NPASS; ++k) row[k] = min((int)threadIdx.x / TPR + k * RPP, mi.n_rows - 1);
-  float mt[NPASS];
-#pragma unroll
-  for (int k = 0; k < NPASS; ++k) mt[k] = kNeg * 4.f;
-  for (int s = 0; s < mi.n_split; ++s) {
-#pragma unroll
-    for (int k = 0; k < NPASS; ++k)
-      if (k * RPP < mi.n_rows) mt[k] = fmaxf(mt[k], base[s * step + kNarrowRows * D + row[k]]);
-  }
-  f32x4 acc[NPASS];
-  float ls[NPASS];
-#pragma unroll
-  for (int k = 0; k < NPASS; ++k) {
-    acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-    ls[k] = 0.f;
-  }
-  for (int s = 0; s < mi.n_split; ++s) {
-    const float* ps = base + s * step;
-    float ms[NPASS], lsp[NPASS];
-    f32x4 o4[NPASS];
-#pragma unroll
-    for (int k = 0; k < NPASS; ++k) {
-      if (k * RPP < mi.n_rows) {
-        ms[k] = ps[kNarrowRows * D + row[k]];
-        o4[k] = *reinterpret_cast<const f32x4*>(ps + row[k] * D + 4 * dq);
-        lsp[k] = ps[kNarrowRows * D + kNarrowRows + row[k]];
-      } else {
-        ms[k] = 0.f;
-        o4[k] = f32x4{0.f, 0.f, 0.f, 0.f};
-        lsp[k] = 0.f;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NPASS; ++k) {
-      const float w = __builtin_amdgcn_exp2f(ms[k] - mt[k]);
-      acc[k] += o4[k] * w;
-      ls[k] += lsp[k] * w;
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < NPASS; ++k) {
-    const int r = (int)threadIdx.x / TPR + k * RPP;
-    if (r >= mi.n_rows) continue;
-    const int tr = mi.row0 + r;
-    const int t = tr / mi.n_heads, gi = tr - t * mi.n_heads;
-    unsigned short* op = p.out + ((long long)(mi.q_off + mi.q_tok0 + t) * p.n_q_heads + mi.head0 + gi) * D + 4 * dq;
-    const float f = vmul / ls[k];
-    u32x2 w2 = {pack_bf16(acc[k][0] * f, acc[k][1] * f), pack_bf16(acc[k][2] * f, acc[k][3] * f)};
-    *reinterpret_cast<u32x2*>(op) = w2;
-  }
-}
-
 template <int D, bool FP8>
 int prepare_typed() {
   auto kern = attn_mixed_kernel<D, FP8>;
@@ -1315,8 +1354,7 @@ int prepare_typed() {
                              attn_lds_bytes<D, FP8>() + kLoopLdsBytes) == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
 }
 
-// Launches of one call, in order: the fp8 copy (if any sequence has one), the main kernel, the
-// merge (if any item was split).  prepare_attn_kernels() must have run on this device.  The
+// Launches of one call, in order: the fp8 copy (if any sequence has one), the main kernel.  prepare_attn_kernels() must have run on this device.  The
 // optional events of a.ev become start/stop events of these dispatches themselves, so their
 // differences are kernel durations without the launch latency around them.
 template <int D, bool FP8>
@@ -1344,14 +1382,8 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p) {
       hipLaunchKernelGGL(kern, dim3((unsigned)pl.n_workgroups), dim3(kThreads), lds, s, p);
     if (hipGetLastError() != hipSuccess) return CRONUS_ERR_HIP;
   }
-  if (pl.n_merge > 0) {
-    if (timed && a.ev[3])
-      hipExtLaunchKernelGGL((attn_merge_kernel<D, FP8>), dim3((unsigned)pl.n_merge), dim3(kMergeThreads), 0, s, nullptr,
-                            ev(3), 0, p);
-    else
-      hipLaunchKernelGGL((attn_merge_kernel<D, FP8>), dim3((unsigned)pl.n_merge), dim3(kMergeThreads), 0, s, p);
-    if (hipGetLastError() != hipSuccess) return CRONUS_ERR_HIP;
-  }
+  // results of key spans are merged by the main kernel itself; the outer stop event follows it
+  if (pl.n_merge > 0 && timed && a.ev[3] && hipEventRecord(ev(3), s) != hipSuccess) return CRONUS_ERR_HIP;
   return CRONUS_OK;
 }
 
@@ -1427,9 +1459,9 @@ int launch_attn(const AttnLaunch& a) {
   p.block_tables = a.block_tables;
   const unsigned char* image = static_cast<const unsigned char*>(a.plan_image);
   p.items = reinterpret_cast<const WorkItem*>(image + pl.off_items);
-  p.merges = reinterpret_cast<const MergeItem*>(image + pl.off_merge);
   p.partials = reinterpret_cast<float*>(ws + pl.off_partials);
   p.q_heads = a.queue_set;
+  p.merge_counters = a.queue_set + (kQueues + 1) * kCounterStride;
   for (int x = 0; x < kQueues; ++x) {
     p.q_base[x] = pl.q_base[x];
     p.q_len[x] = pl.q_len[x];

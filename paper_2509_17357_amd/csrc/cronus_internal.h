@@ -17,7 +17,10 @@ constexpr int kWideKvTile = 64;     // keys staged in LDS per step of a wide (ch
 constexpr int kNarrowKvStep = 32 * kWaves;  // keys covered by the waves of a narrow item per step
 constexpr int kQueues = 8;          // work queues of a launch: one per XCD of an MI355X (each XCD has its own L2)
 constexpr int kCounterStride = 16;  // int32 between the queue heads of a set: one 64-byte line each
-constexpr int kQueueSetInts = (kQueues + 1) * kCounterStride;  // a set: the heads, then the count of finished work-groups
+// Row groups whose results are merged from key spans, per launch at most: each has kWaves arrival
+// counters in the set.  A launch that would split more has thousands of items without splitting.
+constexpr int kMaxMergeGroups = 4096;
+constexpr int kQueueSetInts = (kQueues + 1) * kCounterStride + kMaxMergeGroups * kWaves;  // a set: the heads, the count of finished work-groups, the arrival counters
 constexpr int kQueueSets = 9;       // sets of queue heads per device: one per plan buffer of the ring, one for the static entry point
 
 // Per-sequence record of the batch (section 4.4: one iteration = chunks + decodes).
@@ -45,11 +48,14 @@ struct WorkItem {
   // copy of the sequence's record, so that a work-group needs one dependent load less
   // before it can address Q and the block table
   int32_t prefix_len, chunk_len, q_off, n_blocks;
-  int32_t reserved[2];  // zero
+  // partial >= 0: first partial slot of the item's row group, and n_split * kMaxMergeGroups +
+  // the group's index among those of the launch
+  int32_t first_partial, merge_key;
 };
 static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
-// Rows whose partial results (split over key spans) are combined by the merge kernel:
+// Rows whose partial results (split over key spans) are combined, for inspection (the kernels
+// find what they need in the work items):
 // rows row0 .. row0 + n_rows - 1 of the tile (row r = token r / n_heads, head r % n_heads);
 // span s left them in partial slot first_partial + s * stride, at slot rows 0 .. n_rows - 1.
 // A narrow item fills one slot (stride 1, row0 0); a split wide tile fills kWaves slots
@@ -99,7 +105,7 @@ struct Plan {
   size_t off_partials = 0, off_stage_k = 0, off_stage_v = 0, total_bytes = 0;
 };
 
-// Number of floats of one partial slot: O[32][D], m[32], l[32].
+// Number of floats of one partial slot: O (32 x D), then (m, l) of 32 rows.
 inline size_t partial_floats(int head_dim) { return (size_t)kNarrowRows * (head_dim + 2); }
 
 // Rows per wide tile for a head shape (must match the kernel instance that is launched).

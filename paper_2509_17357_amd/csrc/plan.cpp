@@ -35,7 +35,7 @@ struct Scratch {
   std::vector<MergeItem> merges;
   std::vector<StageSeq> stages;
   std::vector<int32_t> queue[kXcds];  // item references: >= 0 wide index, < 0 ~narrow index
-  struct Tile { int32_t t0, nt, kv_total, n_split, per, first_partial; float cost_per_key; };
+  struct Tile { int32_t t0, nt, kv_total, n_split, per, first_partial, merge_key; float cost_per_key; };
   std::vector<Tile> tiles;
   std::vector<int32_t> order, bucket_start;
   struct Run { int32_t begin, len; float shortest; };  // a contiguous run of one group's tiles in a queue
@@ -245,6 +245,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   sc.merges.clear();
   sc.stages.clear();
   int64_t n_partials = 0, n_merge_rows = 0, n_stage_blocks = 0;
+  int32_t n_merge_groups = 0;
   // fp8 cache: a chunk of many tiles reads each key of its sequence that many times; its
   // K/V is then converted to bf16 once (into the workspace) and the tiles run on the bf16
   // pipeline (measured on the chunks of the 70B-shaped batch: 7.66 -> 6.6 ms of attention).
@@ -261,16 +262,25 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     if (n_split > 1 && kv_total - (long long)(n_split - 1) * span <= span / 4) --n_split;  // no sliver spans
     const int per = (int)(((kv_total + n_split - 1) / n_split + kNarrowKvStep - 1) / kNarrowKvStep * kNarrowKvStep);
     n_split = (kv_total + per - 1) / per;
+    int per_item = per;
+    if (n_split > 1 && n_merge_groups == kMaxMergeGroups) {  // no arrival counters left
+      n_split = 1;
+      per_item = kv_total;
+    }
+    const int32_t first_partial = (int32_t)n_partials, merge_key = n_split * kMaxMergeGroups + n_merge_groups;
     if (n_split > 1) {
+      ++n_merge_groups;
       sc.merges.push_back(MergeItem{(int32_t)n_partials, n_split, s, kvh, head0, nh, q_tok0, n_tok, 0, n_tok * nh, 1, 0});
       n_merge_rows += (int64_t)n_tok * nh;
     }
     for (int i = 0; i < n_split; ++i) {
       WorkItem w{};
       w.seq = s; w.kv_head = kvh; w.head0 = head0; w.n_heads = nh; w.q_tok0 = q_tok0; w.n_tok = n_tok;
-      w.kv_begin = i * per;
-      w.kv_end = std::min(kv_total, (i + 1) * per);
+      w.kv_begin = i * per_item;
+      w.kv_end = std::min(kv_total, (i + 1) * per_item);
       w.partial = n_split > 1 ? (int32_t)(n_partials++) : -1;
+      w.first_partial = first_partial;
+      w.merge_key = merge_key;
       w.wide = 0;
       sc.narrow.push_back(w);
     }
@@ -317,11 +327,14 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
           int n_split = 1;
           if (wide_piece_keys > 0 && kv_total > wide_piece_keys + wide_piece_keys / 2)
             n_split = (kv_total + wide_piece_keys - 1) / wide_piece_keys;
+          if (n_merge_groups == kMaxMergeGroups) n_split = 1;  // no arrival counters left
           const int per = ((kv_total + n_split - 1) / n_split + kWideKvTile - 1) / kWideKvTile * kWideKvTile;
           n_split = (kv_total + per - 1) / per;
           const int rows = nt * nh;
           int32_t first_partial = -1;
+          const int32_t merge_key = n_split * kMaxMergeGroups + n_merge_groups;
           if (n_split > 1) {
+            ++n_merge_groups;
             first_partial = (int32_t)n_partials;
             for (int wv = 0; wv * kNarrowRows < rows; ++wv)
               sc.merges.push_back(MergeItem{first_partial + wv, n_split, s, kvh, head0, nh, t0, nt,
@@ -329,7 +342,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
             n_merge_rows += rows;
             n_partials += (int64_t)n_split * kWaves;
           }
-          sc.tiles.push_back(Scratch::Tile{t0, nt, kv_total, n_split, per, first_partial, (wide_rows / 128.0f) * rows_frac});
+          sc.tiles.push_back(Scratch::Tile{t0, nt, kv_total, n_split, per, first_partial, merge_key, (wide_rows / 128.0f) * rows_frac});
           max_split = std::max(max_split, n_split);
         }
         // One group per span index: the spans i of all tiles of this (sequence, KV head) cover
@@ -344,6 +357,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
             w.kv_begin = i * t.per;
             w.kv_end = std::min(t.kv_total, (i + 1) * t.per);
             w.partial = t.n_split > 1 ? t.first_partial + i * kWaves : -1;
+            w.first_partial = t.first_partial;
+            w.merge_key = t.merge_key;
             w.wide = wide_tag;
             const float cost = (float)(w.kv_end - w.kv_begin) * t.cost_per_key;
             sc.wide.push_back(w);

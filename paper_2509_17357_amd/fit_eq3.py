@@ -62,7 +62,7 @@ def time_batch(batch, steps, warmup):
     it.ensure_workspace()
     stats = B.cronus_attn_mixed_plan_stats(it.cache, batch.prefix_lens, batch.chunk_lens)
     ev = B.HipEvents()
-    quads = [tuple(ev.create() for _ in range(4)) for _ in range(steps)]
+    quads = [tuple(ev.create() for _ in range(3)) for _ in range(steps)]
     for q in quads[:max(warmup, 1)]:
         B.cronus_profile_events(*q)
         it.append_new()
@@ -84,7 +84,7 @@ def time_batch(batch, steps, warmup):
         torch.cuda.synchronize()
         groups.append((time.perf_counter() - t0) * 1e3 / per_group)
     B.cronus_profile_events(None, None)
-    span = [ev.elapsed_ms(q[2] if stats["copy_blocks"] else q[0], q[3] if stats["merge_groups"] else q[1]) for q in quads[:k]]
+    span = [ev.elapsed_ms(q[2] if stats["copy_blocks"] else q[0], q[1]) for q in quads[:k]]
     for q in quads:
         for e in q:
             ev.destroy(e)
