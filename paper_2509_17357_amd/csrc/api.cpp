@@ -2,9 +2,12 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 #include "cronus_internal.h"
@@ -82,30 +85,41 @@ int prepare_device_locked(int* device) {
 }
 
 // The work list is written into pinned, device-mapped host memory and the kernels read it
-// from there (each work-group one 64-byte item; the merge kernel its record): no copy
-// sits between the caller's previous work on the stream and the attention kernel (a
-// stream-ordered copy of these few KB took about 25 us of otherwise idle stream time on
-// MI355X).  A slot is reused only after the kernels of the call that used it finished.
+// from there (each work-group one 64-byte item): no copy sits between the caller's previous
+// work on the stream and the attention kernel (a stream-ordered copy of these few KB took
+// about 25 us of otherwise idle stream time on MI355X).  A slot is reused only after the
+// kernels of the call that used it are done with it: the main kernel's last work-group stores
+// the call's number in front of the plan image.  (An event recorded behind the kernels cost
+// the host 1.5 us a call and the stream 5 us before its next kernel.)
 struct Slot {
   void* host = nullptr;
   void* dev = nullptr;   // the same memory as the device sees it
   size_t cap = 0;
-  hipEvent_t done = nullptr;
-  bool pending = false;
+  uint32_t call = 0;     // number of the last call that used the slot
+  enum { kFree, kPending, kLost } state = kFree;  // kLost: nothing tells when its kernels are done
 };
+constexpr size_t kSlotHeader = 256;  // bytes in front of the plan image: the number of the last finished call
 void* g_ev[4] = {nullptr, nullptr, nullptr, nullptr};
 
 constexpr int kSlots = 8;
 static_assert(kQueueSets == kSlots + 1, "one set of queue heads per plan buffer, one for the static entry point");
-Slot g_slots[kMaxDevices][kSlots];  // a ring per device: the events that guard reuse belong to a device
+Slot g_slots[kMaxDevices][kSlots];  // a ring per device: a slot's memory is mapped for one
 int g_next[kMaxDevices] = {0};
 
 Slot* acquire_slot(int dev, size_t bytes) {
+  bytes += kSlotHeader;
   Slot* s = &g_slots[dev][g_next[dev]];
   g_next[dev] = (g_next[dev] + 1) % kSlots;
-  if (s->pending) {
-    if (hipEventSynchronize(s->done) != hipSuccess) return nullptr;
-    s->pending = false;
+  if (s->state == Slot::kLost) return nullptr;
+  if (s->state == Slot::kPending) {
+    // seven more calls have been enqueued since: the wait is for a host that runs ahead of the GPU
+    const volatile uint32_t* done = static_cast<const volatile uint32_t*>(s->host);
+    for (int spin = 0; *done != s->call; ++spin) {
+      if (spin < 4096) __builtin_ia32_pause();
+      else std::this_thread::sleep_for(std::chrono::microseconds(2));
+    }
+    std::atomic_thread_fence(std::memory_order_acquire);
+    s->state = Slot::kFree;
   }
   if (s->cap < bytes) {
     if (s->host) (void)hipHostFree(s->host);
@@ -120,9 +134,20 @@ Slot* acquire_slot(int dev, size_t bytes) {
       return nullptr;
     }
     s->cap = cap;
+    *static_cast<volatile uint32_t*>(s->host) = s->call;
   }
-  if (!s->done && hipEventCreateWithFlags(&s->done, hipEventDisableTiming) != hipSuccess) return nullptr;
   return s;
+}
+
+// A captured call runs when its graph does, and again with every replay.
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (stream == nullptr) return false;  // the default stream cannot be captured
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -257,15 +282,21 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, co
   if (int rc = prepare_device_locked(&dev)) return rc;
   Slot* slot = acquire_slot(dev, plan.image_bytes);
   if (!slot) return CRONUS_ERR_HIP;
-  write_plan(&plan, slot->host);
+  unsigned char* const host = static_cast<unsigned char*>(slot->host);
+  unsigned char* const dev_mem = static_cast<unsigned char*>(slot->dev);
+  write_plan(&plan, host + kSlotHeader);
   // the set of queue heads that belongs to this plan buffer: free again when the buffer is
   const int set = (int)(slot - g_slots[dev]);
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, slot->dev, &plan, hip_stream,
-               g_dev[dev].queue_sets + set * kQueueSetInts, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
-  const int rc = launch_attn(a);
-  // whatever was launched may still read the slot
-  if (hipEventRecord(slot->done, stream) != hipSuccess) return CRONUS_ERR_HIP;
-  slot->pending = true;
+  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, &plan, hip_stream,
+               g_dev[dev].queue_sets + set * kQueueSetInts, reinterpret_cast<uint32_t*>(dev_mem), ++slot->call,
+               {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+  slot->state = is_capturing(stream) ? Slot::kLost : Slot::kPending;
+  bool main_launched = false;
+  const int rc = launch_attn(a, &main_launched);
+  if (!main_launched && slot->state == Slot::kPending) {
+    (void)hipStreamSynchronize(stream);  // an earlier kernel of the call may read the slot
+    slot->state = Slot::kFree;
+  }
   return rc;
 }
 
@@ -300,8 +331,9 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   // (The heads of the work queues, which must, live in their own small array, and every
   // launch leaves them zero.)
   AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, base + plan.image_bytes, base, &plan,
-               hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
-  return launch_attn(a);
+               hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+  bool main_launched = false;
+  return launch_attn(a, &main_launched);
 }
 
 void cronus_profile_events(void* main_start, void* main_stop, void* first_start, void* last_stop) {

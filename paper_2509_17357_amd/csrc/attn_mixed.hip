@@ -81,6 +81,8 @@ struct AttnParams {
   int* merge_counters;  // kMaxMergeGroups x kWaves arrivals of spans; all zero between launches
   int* q_heads;       // head of queue x at q_heads[x * kCounterStride], finished work-groups at
                       // q_heads[kQueues * kCounterStride]; all zero when the kernel starts and when it ends
+  unsigned* done_flag;  // host memory: receives done_value when the launch has read its last item, or nullptr
+  unsigned done_value;
   int q_base[kQueues];
   int q_len[kQueues];
 };
@@ -1301,7 +1303,10 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
     }
   }
   // No queue has an item left for this work-group.  The last work-group of the launch to get
-  // here (every other one has taken its last ticket) zeroes the heads for the next launch.
+  // here (every other one has taken its last ticket, and its stores to the arrival counters
+  // are acknowledged) zeroes the heads for the next launch and tells the host.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
   if (threadIdx.x == 0) {
     int* const done = p.q_heads + kQueues * kCounterStride;
     const unsigned finished = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1310,6 +1315,10 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
       for (int x = 0; x < kQueues; ++x)
         __hip_atomic_store(p.q_heads + x * kCounterStride, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (p.done_flag) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __hip_atomic_store(p.done_flag, p.done_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
     }
   }
 }
@@ -1358,7 +1367,7 @@ int prepare_typed() {
 // optional events of a.ev become start/stop events of these dispatches themselves, so their
 // differences are kernel durations without the launch latency around them.
 template <int D, bool FP8>
-int launch_typed(const AttnLaunch& a, const AttnParams& p) {
+int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) {
   constexpr int lds = attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
   hipStream_t s = static_cast<hipStream_t>(a.stream);
   const Plan& pl = *a.plan;
@@ -1381,6 +1390,7 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p) {
     else
       hipLaunchKernelGGL(kern, dim3((unsigned)pl.n_workgroups), dim3(kThreads), lds, s, p);
     if (hipGetLastError() != hipSuccess) return CRONUS_ERR_HIP;
+    *main_launched = true;
   }
   // results of key spans are merged by the main kernel itself; the outer stop event follows it
   if (pl.n_merge > 0 && timed && a.ev[3] && hipEventRecord(ev(3), s) != hipSuccess) return CRONUS_ERR_HIP;
@@ -1445,7 +1455,7 @@ int prepare_attn_kernels() {
   return prepare_typed<64, true>();
 }
 
-int launch_attn(const AttnLaunch& a) {
+int launch_attn(const AttnLaunch& a, bool* main_launched) {
   const cronus_kv_cache& c = *a.cache;
   const Plan& pl = *a.plan;
   unsigned char* ws = static_cast<unsigned char*>(a.workspace);
@@ -1461,6 +1471,8 @@ int launch_attn(const AttnLaunch& a) {
   p.items = reinterpret_cast<const WorkItem*>(image + pl.off_items);
   p.partials = reinterpret_cast<float*>(ws + pl.off_partials);
   p.q_heads = a.queue_set;
+  p.done_flag = a.done_flag;
+  p.done_value = a.done_value;
   p.merge_counters = a.queue_set + (kQueues + 1) * kCounterStride;
   for (int x = 0; x < kQueues; ++x) {
     p.q_base[x] = pl.q_base[x];
@@ -1475,8 +1487,8 @@ int launch_attn(const AttnLaunch& a) {
   p.n_kv_heads = c.num_kv_heads;
   p.scale_log2e = a.sm_scale * 1.4426950408889634f;
   const bool fp8 = c.kv_dtype == CRONUS_KV_FP8_E4M3;
-  if (c.head_dim == 128) return fp8 ? launch_typed<128, true>(a, p) : launch_typed<128, false>(a, p);
-  if (c.head_dim == 64) return fp8 ? launch_typed<64, true>(a, p) : launch_typed<64, false>(a, p);
+  if (c.head_dim == 128) return fp8 ? launch_typed<128, true>(a, p, main_launched) : launch_typed<128, false>(a, p, main_launched);
+  if (c.head_dim == 64) return fp8 ? launch_typed<64, true>(a, p, main_launched) : launch_typed<64, false>(a, p, main_launched);
   return CRONUS_ERR_UNSUPPORTED;
 }
 

@@ -132,16 +132,20 @@ struct AttnLaunch {
   const Plan* plan;
   void* stream;
   int* queue_set;  // device; this call's set of queue heads (kQueueSetInts ints, all zero between launches)
+  uint32_t* done_flag;  // device-visible host memory; receives done_value when the main kernel is done with the plan
+                        // image and the queue set, or nullptr
+  uint32_t done_value;
   // optional hipEvent_t handles (measurement aid): [0], [1] start and stop of the main
   // kernel's dispatch; [2] start of the call's first kernel when that is another one (the
-  // fp8 copy); [3] stop of its last kernel when that is another one (the merge)
+  // fp8 copy); [3] recorded behind the main kernel when that merges results of key spans
   void* ev[4];
 };
 
 // One-time set-up of the attention kernels on the current device (dynamic LDS limits);
 // call before the first launch_attn() there.
 int prepare_attn_kernels();
-int launch_attn(const AttnLaunch& a);
+// *main_launched: whether the main kernel, which reports the end of the call, has been enqueued.
+int launch_attn(const AttnLaunch& a, bool* main_launched);
 
 // The no-allocation variant's device memory: a static array in the library's device image
 // (attn_mixed.hip).  static_scratch_resolve() looks up its address on the current device
