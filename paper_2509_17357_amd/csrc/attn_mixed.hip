@@ -46,6 +46,9 @@ static __device__ __align__(256) unsigned char scratch[cronus::kStaticScratchByt
 // back to zero, so that no launch has to be preceded by a reset.
 static __device__ __align__(256) int queue_sets[cronus::kQueueSets * cronus::kQueueSetInts];
 
+// The record of "no item left": field 9 is WorkItem::wide.
+static __device__ const int no_item[16] = {0, 0, 0, 0, 0, 0, 0, 0, 0, -1, 0, 0, 0, 0, 0, 0};
+
 namespace cronus {
 namespace {
 
@@ -316,6 +319,110 @@ __device__ __forceinline__ bool merge_wide_rows(const AttnParams& p, const WorkI
   return true;
 }
 
+// ------------------------------------------------------------------ work queues
+template <int D, bool FP8>
+constexpr int attn_lds_bytes() {
+  constexpr int wide_lds = 4 * 2 * 4 * 16 * D * 2;  // stages x (K + V tile of 64 keys)
+  constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * kNarrowRows * 4;
+  constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
+  static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
+  return lds;
+}
+
+// Behind the kernels' LDS buffers: two mailboxes of 16 ints (an item's record; the item loop
+// alternates between them, so one barrier per item separates writing and reading), then for
+// lane k = 0 .. 7 the dynamic part of queue (xcc + k) mod 8 as (items, first item).
+constexpr int kLoopLdsBytes = 2 * 64 + 2 * 4 * kQueues;
+
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+
+// Items of queue x that are handed out without a ticket: work-group b starts with item b / 8
+// of queue b mod 8 (the dispatcher deals work-groups to the XCDs in turn), so the first
+// items of a launch need no atomic, and a launch with no more items than work-groups needs
+// none at all.
+__device__ __forceinline__ int static_items(const AttnParams& p, int x) {
+  return min(p.q_len[x], ((int)gridDim.x - x + kQueues - 1) / kQueues);
+}
+
+// What wave 0 needs to take the next item, and the mailbox that the next record goes to.
+// LDS is accessed through asm here: transfers of K/V tiles may be in flight (see lds_read4).
+struct Feed {
+  unsigned mail;   // LDS byte address of the mailboxes; the table of queues is 128 bytes further
+  unsigned turn;   // 0 or 64: the mailbox of the next record
+  int xcc;
+  int left;        // wave 0: items that the own queue had left when this work-group last asked, 0 once it had none
+};
+
+// Taking an item has two steps, so that the memory round trip between them can be hidden:
+// request() takes the ticket of the own queue (lane 0) and looks at the heads of the other
+// seven (lanes 1 .. 7), so finding out that nothing is left costs one round trip and not
+// eight (measured on a decode batch that gives every CU one item, 4.2 us -> 1.3 us between a
+// work-group's last item and its end); resolve() finds the item: of the own queue, else of
+// the others in ring order (a queue's head only grows, so a queue found empty stays empty).
+// Wave 0 only.
+struct QueuePart {
+  int len, base;
+};
+__device__ __forceinline__ QueuePart queue_part(const Feed& f, int lane) {
+  u32x2 q;
+  asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(q)
+               : "v"(f.mail + 128 + 8 * (lane & (kQueues - 1)))
+               : "memory");
+  return QueuePart{lane < kQueues ? (int)q[0] : 0, (int)q[1]};
+}
+__device__ __forceinline__ int* queue_head(const AttnParams& p, const Feed& f, int lane) {
+  return p.q_heads + ((f.xcc + lane) & (kQueues - 1)) * kCounterStride;
+}
+__device__ __forceinline__ int request_item(const AttnParams& p, const Feed& f, int lane) {
+  const int len = queue_part(f, lane).len;
+  int head = 0;
+  if (__builtin_amdgcn_ballot_w64(len > 0) != 0 && len > 0) {
+    int* const h = queue_head(p, f, lane);
+    if (lane == 0) head = __hip_atomic_fetch_add(h, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else head = __hip_atomic_load(h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return head;
+}
+__device__ __forceinline__ int resolve_item(const AttnParams& p, Feed& f, int head, int lane) {
+  const QueuePart q = queue_part(f, lane);
+  f.left = max(0, __builtin_amdgcn_readfirstlane(q.len - head - 1));
+  bool ticket = lane == 0;  // this lane's head is a ticket, not a look
+  for (;;) {
+    const unsigned long long open = __builtin_amdgcn_ballot_w64(head < q.len);
+    if (open == 0) return -1;
+    const int l = __builtin_ctzll(open);
+    if (__builtin_amdgcn_readlane((int)ticket, l)) return __builtin_amdgcn_readlane(q.base + head, l);
+    if (lane == l) {
+      head = __hip_atomic_fetch_add(queue_head(p, f, lane), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ticket = true;
+    }
+  }
+}
+constexpr int kNotYet = -2;  // WorkItem::wide of a mailbox that waits for its record
+// Copies the record of item idx (idx < 0: a record whose field 9, WorkItem::wide, is -1) to the
+// mailbox.  By DMA: the transfer passes no register, so only the wait for it (vmcnt, then a
+// barrier for the other waves) has to be placed.
+__device__ __forceinline__ void fetch_record(const AttnParams& p, const Feed& f, int idx, int lane) {
+  typedef const __attribute__((address_space(1))) int global_int;
+  global_int* r = idx >= 0 ? (global_int*)(p.items + idx) : (global_int*)no_item;
+  if (lane < 16) __builtin_amdgcn_global_load_lds(r + lane, (lds_byte*)(f.mail + f.turn), 4, 0, 0);
+}
+// The record in the mailbox (posted, and a barrier passed), one dword per lane of each 16;
+// then as scalars.
+__device__ __forceinline__ int read_mail(const Feed& f, unsigned turn, int lane) {
+  int v;
+  asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(f.mail + turn + 4 * (lane & 15)) : "memory");
+  return v;
+}
+__device__ __forceinline__ WorkItem unpack_record(int rec) {
+  WorkItem it;
+  int* f = reinterpret_cast<int*>(&it);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) f[i] = __builtin_amdgcn_readlane(rec, i);
+  return it;
+}
+
 // ---------------------------------------- wide (chunk) tile, staged through registers
 // Used for the fp8 cache: codes are converted to bf16 once, on their way into LDS.
 template <int D, bool FP8, int QT>
@@ -488,8 +595,6 @@ __device__ __forceinline__ void run_wide_staged(const AttnParams& p, const WorkI
 
 
 // ------------------------------------- wide (chunk) tile, bf16 cache: DMA-fed pipeline
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -562,6 +667,53 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// Read the NOPS 1-KiB operand planes of this lane (plane n at addr + 1024 n).
+template <int NOPS>
+__device__ __forceinline__ void lds_read_planes(u32x4 (&x)[NOPS], unsigned addr) {
+  static_assert(NOPS == 4 || NOPS == 8, "D = 64 or 128");
+  if constexpr (NOPS == 8) lds_read8<0, 1024, 2048, 3072, 4096, 5120, 6144, 7168>(x, addr);
+  else lds_read4<0, 1024, 2048, 3072>(x[0], x[1], x[2], x[3], addr);
+}
+
+// Row r of a tile = (token r / g, head r % g), r < 256 and g = heads per item <= 32:
+// the quotient as (r * row_magic(g)) >> 16.  With M = 65536 / g + d, 0 < d <= 2, the product
+// exceeds r * 65536 / g by at most 2 * 255 < 65536 / 32, so the floor is that of r / g.
+__device__ __forceinline__ unsigned row_magic(int g) {
+  return (unsigned)__builtin_amdgcn_readfirstlane((int)(65536.0f * __builtin_amdgcn_rcpf((float)g)) + 1);
+}
+
+// Q enters and the output leaves a wide tile through LDS, in a region of the wave's own
+// (32 rows x D bf16), so that global memory sees whole rows: one instruction moves 64 / (D/8)
+// rows of D/8 16-byte chunks.  (Lanes that own a row each read or wrote 64 separate 16-byte
+// pieces per instruction, which kept the address path busy for 1.2 us per Q and 1.7 us per
+// output of a 256-row tile.)  Chunk ch of row r is stored at chunk position ch ^ swz(r), so
+// that the per-row accesses of the operands hit every bank once.
+template <int D>
+struct RowTile {
+  static constexpr int CPR = D / 8;        // chunks per row
+  static constexpr int RPI = 64 / CPR;     // rows per instruction
+  static constexpr int NINS = 32 / RPI;    // instructions for 32 rows
+  static __device__ __forceinline__ int swz(int row) { return (D == 128 ? row : row >> 1) & (CPR - 1); }
+  // LDS offset of chunk `half` of a row; that of chunk 2 s + half is this value ^ 32 s (the
+  // wave's rows start at a multiple of a row's size).
+  static __device__ __forceinline__ unsigned row_chunk(int row, int half) {
+    return (unsigned)(row * (2 * D) + ((half ^ swz(row)) * 16));
+  }
+  // Byte offset of the chunk that lane `lane` moves in instruction n, relative to the tile's
+  // first token: row (clamped to the tile) -> token and head.
+  static __device__ __forceinline__ unsigned offset(int n, int lane, int row_base, int rows_valid, unsigned magic, int g,
+                                                    int n_q_heads) {
+    const unsigned r = (unsigned)min(row_base + n * RPI + lane / CPR, rows_valid - 1);
+    const unsigned t = __umul24(r, magic) >> 16;
+    const unsigned ch = (unsigned)((lane % CPR) ^ swz(lane / CPR) ^ swz(n * RPI));
+    return r * (2 * D) + __umul24(t, (unsigned)(n_q_heads - g) * (2 * D)) + ch * 16;
+  }
+};
+template <int OFF>
+__device__ __forceinline__ void lds_write_b128(unsigned addr, u32x4 v) {
+  asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "i"(OFF) : "memory");
+}
+
 // Schedule per wave (n = number of 32-key sub-tiles, S(u) = K(u) Q^T, P(u) = softmax
 // numerators), software-pipelined by one sub-tile so that the MFMA pipe has the S(u+1)
 // products to work on while the VALU computes the softmax of S(u):
@@ -571,54 +723,120 @@ __device__ __forceinline__ void static_for(F&& f) {
 // fetching 1/8 of a tile; one s_barrier per tile publishes a landed tile and frees the
 // stage of the tile before last.  Between barriers the 8 waves run freely, so the two
 // waves of a SIMD fill each other's VALU and MFMA gaps.
+// Consecutive wide items of a work-group are chained while its queue is well filled: during
+// the last kLead tiles of an item wave 0 takes the next item's ticket and has its record
+// copied to the mailbox, every wave requests its table entries when the last tile opens, and
+// the next item's first K/V tiles and its Q are requested before the finished output is
+// normalised and stored.  Between two items of whole prompts (24 prompts of 100 .. 2000 tokens,
+// 3272 items of 576 keys in the median) 6.2 us passed without products, 3.3 us do now; an
+// iteration over them took 358 -> 344 us.  Launches bound by the power limit gain less (large
+// chunks behind prefixes 876 -> 873 us): what is not idle any more lowers the clock.
+// Returns whether the next item's record is in mailbox f.turn, published by a barrier.
 // COPY: the item's sequence belongs to an fp8 cache and its K/V is read from the bf16 copy
 // that kv_stage_kernel made for this launch (blocks it.wide - 2 .. in logical order, no
 // table); the scale of K enters the exponent constant, that of V the normalisation.
 template <int D, bool COPY>
-__device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem& it, unsigned char* smem) {
+__device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, unsigned char* smem) {
   constexpr int NSTEP = D / 16, NDB = D / 32;
   constexpr int BLK_LDS = 16 * D * 2;     // bytes of one (block, head)
   constexpr int KT_BYTES = 4 * BLK_LDS;   // K (or V) tile: 64 keys
   constexpr int STAGE = 2 * KT_BYTES;
   constexpr int kStages = 4, kAhead = kStages - 1;
+  constexpr int kLead = 6;                // tiles of an item that are left when the next item is asked for
   constexpr int UPW = D / 64;             // 1-KiB units of K (and of V) each wave fetches per tile
   constexpr int UPB = BLK_LDS / 1024;     // units per block
   constexpr int NI = 2 * UPW;             // DMA instructions per wave per tile
+  using Rows = RowTile<D>;
+  static_assert(Rows::NINS == NSTEP && 2 * STAGE == kWaves * 32 * D * 2, "Q of a tile fills two stages");
 
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
-  const int lane = tid & 63, half = lane >> 5, c32 = lane & 31;
+  int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, it.n_blocks};
-  const int gi_n = it.n_heads;
-  const int rows_valid = it.n_tok * gi_n;
   const int row_base = wave * 32;
-  const bool wave_has_rows = row_base < rows_valid;
-  // key positions are counted from the item's first key (a multiple of the tile size)
-  const int kv_len = si.prefix_len + si.chunk_len - it.kv_begin;
-  const int pos0 = si.prefix_len + it.q_tok0 - it.kv_begin;
-  float c = p.scale_log2e, vmul = 1.0f;
-  if constexpr (COPY) {
-    c *= p.k_scale[it.kv_head];
-    vmul = p.v_scale[it.kv_head];
-  }
   const unsigned char* const k_src = COPY ? p.stage_k : p.k_pool;
   const unsigned char* const v_src = COPY ? p.stage_v : p.v_pool;
-  const int wave_min_limit = pos0 + min(row_base, rows_valid - 1) / gi_n;
-  const int wave_max_limit = wave_has_rows ? pos0 + min(row_base + 31, rows_valid - 1) / gi_n : -1;
+  const long long head_stride = (long long)BLK_LDS;
+  lds_byte* const lds0 = (lds_byte*)smem;
+  const unsigned lds_base = (unsigned)(unsigned long long)lds0;
+  // the wave's own rows (Q on its way in, the output on its way out): in stages 2 and 3
+  const unsigned own_off = 2 * STAGE + wave * (32 * D * 2);
 
-  const int r = min(row_base + c32, rows_valid - 1);
-  const int t_row = r / gi_n, gi_row = r - t_row * gi_n;
-  const int limit = pos0 + t_row;
-  // Q is requested first and waited for only after the first K/V tiles have been
-  // requested too: one memory latency, not two, before the first product
-  u32x4 qraw[NSTEP];
-  {
-    const unsigned short* qp =
-        p.q + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D + 8 * half;
+  // ---- DMA of tile j: this wave moves UPW units of K and of V, all inside one block
+  const int blk_w = (wave * UPW) / UPB, part_w = (wave * UPW) % UPB;
+  // lane i: physical block of this wave's share of tile (j + i) of an item
+  auto table_entries = [&](const WorkItem& w, int j) {
+    const int blk0 = w.kv_begin >> 4;
+    const int b = min(4 * (j + lane) + blk_w, w.n_blocks - 1 - blk0);
+    if constexpr (COPY) return w.wide - 2 + blk0 + b;  // blocks of the copy are in logical order
+    else return p.block_tables[(long long)w.seq * p.max_blocks + blk0 + b];
+  };
+  // instruction q = 2 x + is_v of tile j, whose block is lane j & 63 of bt
+  auto issue_part = [&](int j, int q, int bt, int kv_head) {
+    const long long b = __builtin_amdgcn_readlane(bt, j & 63);
+    const long long goff = (b * p.n_kv_heads + kv_head) * head_stride + part_w * 1024;
+    lds_byte* dst = lds0 + (j % kStages) * STAGE + blk_w * BLK_LDS + part_w * 1024;
+    const int x = q >> 1;
+    if (q & 1) dma_1k(v_src + goff + x * 1024, dst + KT_BYTES + x * 1024, lane);
+    else dma_1k(k_src + goff + x * 1024, dst + x * 1024, lane);
+  };
+  auto issue_tile = [&](int j, int bt, int kv_head) {
 #pragma unroll
-    for (int s = 0; s < NSTEP; ++s) qraw[s] = *reinterpret_cast<const u32x4*>(qp + 16 * s);
+    for (int q = 0; q < NI; ++q) issue_part(j, q, bt, kv_head);
+  };
+  auto tiles_of = [](const WorkItem& w) { return (w.kv_end - w.kv_begin + kWideKvTile - 1) / kWideKvTile; };
+  // Q of an item, by DMA into the wave's own rows
+  auto issue_q = [&](const WorkItem& w, int lane) {
+    const unsigned magic = row_magic(w.n_heads);
+    const unsigned char* qp =
+        reinterpret_cast<const unsigned char*>(p.q + ((long long)(w.q_off + w.q_tok0) * p.n_q_heads + w.head0) * D);
+#pragma unroll
+    for (int n = 0; n < NSTEP; ++n) {
+      __builtin_amdgcn_global_load_lds(
+          qp + Rows::offset(n, lane, row_base, w.n_tok * w.n_heads, magic, w.n_heads, p.n_q_heads),
+          lds0 + own_off + n * 1024, 16, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto chains = [](const WorkItem& w) { return COPY ? w.wide >= 2 : w.wide == 1; };
+
+  // The record of the item being computed is read from its mailbox again where it is needed
+  // (the mailbox is written next for the item after the next one): scalars that live through
+  // the loops would be spilled.
+  auto current = [&]() { return unpack_record(read_mail(feed, feed.turn ^ 64, lane)); };
+  // the first item's table entries, first tiles and Q are requested here, a chained item's below
+  int bt_reg, younger;  // younger: memory operations issued after the item's Q
+  {
+    const WorkItem it = current();
+    bt_reg = table_entries(it, 0);
+    asm volatile("" : "+v"(bt_reg));
+    issue_tile(0, bt_reg, it.kv_head);
+    issue_q(it, lane);
+    if (tiles_of(it) > 1) issue_tile(1, bt_reg, it.kv_head);
+    younger = tiles_of(it) > 1 ? NI : 0;
   }
+
+  for (;;) {
+  asm volatile("" : "+v"(lane));  // lane terms are recomputed per item
+  const int half = lane >> 5, c32 = lane & 31, pr = perm32(c32);
+  const WorkItem it = current();
+  const int kv_head = it.kv_head;
+  const int gi_n = it.n_heads;
+  const int rows_valid = it.n_tok * gi_n;
+  const bool wave_has_rows = row_base < rows_valid;
+  const unsigned magic = row_magic(gi_n);
+  auto token_of = [&](int row) { return (int)(((unsigned)row * magic) >> 16); };
+  // key positions are counted from the item's first key (a multiple of the tile size)
+  const int kv_len = it.prefix_len + it.chunk_len - it.kv_begin;
+  const int pos0 = it.prefix_len + it.q_tok0 - it.kv_begin;
+  float c = p.scale_log2e;
+  if constexpr (COPY) c *= p.k_scale[kv_head];
+  const int wave_min_limit = __builtin_amdgcn_readfirstlane(pos0 + token_of(min(row_base, rows_valid - 1)));
+  const int wave_max_limit =
+      wave_has_rows ? __builtin_amdgcn_readfirstlane(pos0 + token_of(min(row_base + 31, rows_valid - 1))) : -1;
+  const int limit = pos0 + token_of(min(row_base + c32, rows_valid - 1));
+  const int n_sub = (it.kv_end - it.kv_begin + 31) >> 5;
+  const int n_tiles = tiles_of(it);
   f32x16 o[NDB];
   float m = kNeg, l = 0.f;
 #pragma unroll
@@ -626,51 +844,27 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
 #pragma unroll
     for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
 
-  const int blk0 = it.kv_begin >> 4;
-  const int* bt = p.block_tables + (long long)it.seq * p.max_blocks + blk0;
-  const int copy_blk0 = it.wide - 2 + blk0;  // COPY: the copy's block of the span's first key
-  const long long head_stride = (long long)BLK_LDS;
-  const int n_sub = (it.kv_end - it.kv_begin + 31) >> 5;
-  const int last_blk = si.n_blocks - 1 - blk0;
-  const int pr = perm32(c32);
-
-  // ---- DMA of tile j: this wave moves UPW units of K and of V, all inside one block
-  const int blk_w = (wave * UPW) / UPB, part_w = (wave * UPW) % UPB;
-  lds_byte* const lds0 = (lds_byte*)smem;
-  int bt_reg = 0;  // lane i: physical block of this wave's share of tile (64*k + i)
-  auto issue_tile = [&](int j) {
-    if ((j & 63) == 0) {
-      if constexpr (COPY) bt_reg = copy_blk0 + min(4 * (j + lane) + blk_w, last_blk);
-      else bt_reg = bt[min(4 * (j + lane) + blk_w, last_blk)];
-      asm volatile("" : "+v"(bt_reg));
-    }
-    const long long b = __builtin_amdgcn_readlane(bt_reg, j & 63);
-    const long long goff = (b * p.n_kv_heads + it.kv_head) * head_stride + part_w * 1024;
-    lds_byte* dst = lds0 + (j % kStages) * STAGE + blk_w * BLK_LDS + part_w * 1024;
-#pragma unroll
-    for (int x = 0; x < UPW; ++x) {
-      dma_1k(k_src + goff + x * 1024, dst + x * 1024, lane);
-      dma_1k(v_src + goff + x * 1024, dst + KT_BYTES + x * 1024, lane);
-    }
+  // ---- the next item, step by step: wave 0 takes a ticket, fetches the record and posts it;
+  // then every wave requests its table entries
+  // An item is reserved ahead only while the own queue holds another one for every CU of the
+  // XCD: near the end of a launch a work-group that is done earlier should get it.  (Reserved
+  // always: a paper-shaped iteration of 104 tiles next to 49 decodes 89 -> 95 us.)
+  int head = 0;
+  bool early = false, asked = false;  // wave 0: a ticket was requested ahead; the record is on its way or there
+  auto ask_next = [&]() {
+    fetch_record(p, feed, resolve_item(p, feed, head, lane), lane);
+    asked = true;
   };
-  // one of the NI instructions of tile j (q = 2 x + is_v), for spreading a tile's fetch
-  // over the two sub-tile steps of a period
-  auto issue_part = [&](int j, int q) {
-    if (q == 0 && (j & 63) == 0) {
-      if constexpr (COPY) bt_reg = copy_blk0 + min(4 * (j + lane) + blk_w, last_blk);
-      else bt_reg = bt[min(4 * (j + lane) + blk_w, last_blk)];
-      asm volatile("" : "+v"(bt_reg));
-    }
-    const long long b = __builtin_amdgcn_readlane(bt_reg, j & 63);
-    const long long goff = (b * p.n_kv_heads + it.kv_head) * head_stride + part_w * 1024;
-    lds_byte* dst = lds0 + (j % kStages) * STAGE + blk_w * BLK_LDS + part_w * 1024;
-    const int x = q >> 1;
-    if (q & 1) dma_1k(v_src + goff + x * 1024, dst + KT_BYTES + x * 1024, lane);
-    else dma_1k(k_src + goff + x * 1024, dst + x * 1024, lane);
+  int bt_next = 0;
+  bool known = false;  // the next record is there, and its table entries have been requested
+  auto look_ahead = [&]() {
+    const WorkItem w = unpack_record(read_mail(feed, feed.turn, lane));
+    if (w.wide == kNotYet) return;
+    if (chains(w)) bt_next = table_entries(w, 0);
+    known = true;
   };
 
   // ---- LDS operand reads (byte addresses)
-  const unsigned lds_base = (unsigned)(unsigned long long)lds0;
   const unsigned k_lane = lds_base + (pr >> 4) * BLK_LDS + (half * 16 + (pr & 15)) * 16;
   const unsigned v_lane = lds_base + KT_BYTES + (half * D + pr) * 16;
   u32x4 ka[NSTEP], va[NSTEP];
@@ -697,21 +891,56 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[st]), qreg[st], s, 0, 0, 0);
   };
 
-  // ---- prologue: first tiles in flight, tile 0 landed everywhere, S(0), K(1) on its way
+  // ---- prologue: Q and the first tiles are in flight; tile 0 landed everywhere and Q in
+  // registers, S(0), K(1) on its way
+  if (younger == NSTEP) wait_vmcnt<NSTEP>();
+  else if (younger == NI) wait_vmcnt<NI>();
+  else wait_vmcnt<0>();
+  {
+    const unsigned a = lds_base + own_off + Rows::row_chunk(c32, half);
+    u32x4 q[NSTEP];
+    static_for<0, NSTEP>([&](auto I) {
+      constexpr int st = decltype(I)::value;
+      lds_issue1<0>(q[st], a ^ (32 * st));
+    });
+    lds_land<0>(q);
 #pragma unroll
-  for (int j = 0; j < kAhead; ++j) issue_tile(j);
-#pragma unroll
-  for (int s = 0; s < NSTEP; ++s) {
-    asm volatile("" : "+v"(qraw[s]));  // the wait for Q sits here, not inside the pipeline
-    qreg[s] = as_bf16x8(qraw[s]);
+    for (int st = 0; st < NSTEP; ++st) qreg[st] = as_bf16x8(q[st]);
   }
-  wait_vmcnt<NI * (kAhead - 1)>();
   __builtin_amdgcn_s_barrier();
+  if (wave == 0)
+    asm volatile("ds_write_b32 %0, %1 offset:36" ::"v"(feed.mail + feed.turn), "v"(kNotYet) : "memory");
+  if (n_tiles > 2) issue_tile(2, bt_reg, kv_head);
   f32x16 s_even, s_odd;  // S(u) of even / odd sub-tiles
+  // written only where this wave sees a sub-tile: without a definition here the registers
+  // would count as live from the item before
+  asm volatile("" : "=v"(s_even), "=v"(s_odd), "=v"(pp[0]), "=v"(pp[1]));
   read_k(0);
   if (active(0)) qk(s_even);
   if (n_sub > 1) read_k(1);
 
+  auto next_entries = [&](int j) {
+    if ((j & 63) == 0) {
+      bt_reg = table_entries(current(), j);
+      asm volatile("" : "+v"(bt_reg));
+    }
+  };
+  // Tile k opens: this wave's share of it has landed (the tile after it may still be in
+  // flight); the barrier publishes it and tells that every wave is done reading tile k - 2,
+  // whose stage the next fetch overwrites.
+  auto open_tile = [&](int k) {
+    if (k + 1 < n_tiles) wait_vmcnt<NI>(); else wait_vmcnt<0>();
+    // the record comes over PCIe: tiles pass between its request and its use.  An item of
+    // three tiles and more asks at the second last of them at the latest, so the wait above
+    // has landed the record when the last one opens.
+    if (early && !asked && k >= n_tiles - (kLead - 1)) ask_next();
+    __builtin_amdgcn_s_barrier();
+    if (k == n_tiles - 1 && n_tiles >= 3) look_ahead();
+    if (k + 2 < n_tiles) {
+      next_entries(k + 2);
+      issue_tile(k + 2, bt_reg, kv_head);
+    }
+  };
   // one sub-tile: s_cur = S(u) is consumed, s_nxt receives S(u+1)
   auto step = [&](int u, f32x16& s_cur, f32x16& s_nxt, bool opens_tile) {
     const int sub_base = 32 * u;
@@ -721,12 +950,7 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
     read_v(u);
     if (u + 2 < n_sub) {
       if (opens_tile) {
-        // K(u+2) opens tile u/2 + 1: this wave's share of it has landed (the tile after it
-        // may still be in flight); the barrier publishes it and tells that every wave is
-        // done reading tile u/2 - 1, whose stage the next fetch overwrites
-        wait_vmcnt<NI>();
-        __builtin_amdgcn_s_barrier();
-        issue_tile((u >> 1) + kAhead);
+        open_tile((u >> 1) + 1);
       }
       read_k(u + 2);
     }
@@ -753,13 +977,8 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
   // chain and the numerators of S(u) that go with it; each slot of the second block one
   // LDS read of K(u+2) and one O product.  An operand is thus requested NSTEP MFMA slots
   // before its use, and LDS sees single reads, not bursts of eight per wave.
-  auto tile_sync = [&](int jn) {
-    wait_vmcnt<NI>();
-    __builtin_amdgcn_s_barrier();
-    issue_part(jn, 0);
-    issue_part(jn, 1);
-  };
-  auto fast_step = [&](int u, f32x16& s_cur, f32x16& s_nxt, bool opens_tile) {
+  // fetch: the tile after next exists and is fetched here; otherwise open_tile decides.
+  auto fast_step = [&](int u, f32x16& s_cur, f32x16& s_nxt, bool opens_tile, bool fetch) {
     const int jn = (u >> 1) + kAhead;
     const unsigned av = v_lane + ((u >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
     const unsigned ak = k_lane + (((u + 2) >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
@@ -801,11 +1020,17 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
       tile_sum = softmax_exp_part(s_cur, c, m, pp);
     }
     l += tile_sum;
-    if (opens_tile) {
-      tile_sync(jn);
+    if (!fetch) {
+      if (opens_tile) open_tile((u >> 1) + 1);
+    } else if (opens_tile) {
+      wait_vmcnt<NI>();
+      __builtin_amdgcn_s_barrier();
+      next_entries(jn);
+      issue_part(jn, 0, bt_reg, kv_head);
+      issue_part(jn, 1, bt_reg, kv_head);
     } else if constexpr (UPW > 1) {
-      issue_part(jn, 2);
-      issue_part(jn, 3);
+      issue_part(jn, 2, bt_reg, kv_head);
+      issue_part(jn, 3, bt_reg, kv_head);
     }
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NSTEP>([&](auto I) {
@@ -819,24 +1044,96 @@ __device__ __forceinline__ void run_wide_dma(const AttnParams& p, const WorkItem
   // sub-tile u is "whole" for this wave when u + 1 is too: 32 (u + 1) + 31 <= wave_min_limit
   int n_fast = wave_has_rows ? min(n_sub - 2, (wave_min_limit + 1) / 32 - 1) : 0;
   n_fast = max(n_fast, 0) & ~1;
+  const int n_fetch = min(n_fast, max(2 * (n_tiles - kLead), 0));
   int u = 0;
+  for (; u < n_fetch; u += 2) {
+    fast_step(u, s_even, s_odd, true, true);
+    fast_step(u + 1, s_odd, s_even, false, true);
+  }
+  if (wave == 0 && feed.left >= 2 * (int)(gridDim.x / kQueues)) {
+    early = true;
+    head = request_item(p, feed, lane);
+  }
   for (; u < n_fast; u += 2) {
-    fast_step(u, s_even, s_odd, true);
-    fast_step(u + 1, s_odd, s_even, false);
+    fast_step(u, s_even, s_odd, true, false);
+    fast_step(u + 1, s_odd, s_even, false, false);
   }
   lds_land<0>(ka);  // the steps below expect K(u+1) in registers
   for (; u < n_sub; u += 2) {
     step(u, s_even, s_odd, true);
     if (u + 1 < n_sub) step(u + 1, s_odd, s_even, false);
   }
-  wait_vmcnt<0>();  // fetches past the item's last tile are still landing in LDS
-  __builtin_amdgcn_s_barrier();
+  if (early && n_tiles < 3) {
+    if (!asked) ask_next();
+    wait_vmcnt<0>();
+  }
+  __builtin_amdgcn_s_barrier();  // every wave is done with the item's K/V; the next record is there
 
+  // ---- the next item's first tiles, then this item's output, with the next item's Q in between
+  if (!known) look_ahead();
+  asm volatile("" : "+v"(bt_next));  // landed, whichever way the work goes on
+  bool chained, posted;
+  {
+    const WorkItem nx = unpack_record(read_mail(feed, feed.turn, lane));
+    posted = nx.wide != kNotYet;
+    chained = chains(nx);
+    if (chained) {
+      bt_reg = bt_next;
+      issue_tile(0, bt_reg, nx.kv_head);
+      if (tiles_of(nx) > 1) issue_tile(1, bt_reg, nx.kv_head);
+    }
+  }
+  asm volatile("" : "+v"(lane));
+  const WorkItem fin = current();
+  const int fin_rows = fin.n_tok * fin.n_heads;
   float lt = pair_sum(l);
-  if (it.partial >= 0 && (!wave_has_rows || !merge_wide_rows<NDB, D>(p, it, wave, lane, o, m * c, lt))) return;
-  if (row_base + c32 < rows_valid) {
-    unsigned short* op = p.out + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D;
-    store_row_bf16<NDB>(op, o, vmul / lt, half);
+  const bool finished =
+      fin.partial < 0 || (row_base < fin_rows && merge_wide_rows<NDB, D>(p, fin, wave, lane, o, m * c, lt));
+  u32x4 w[NSTEP];
+#pragma unroll
+  for (int n = 0; n < NSTEP; ++n) asm volatile("" : "=v"(w[n]));  // as for s_even
+  if (finished) {
+    float mul = 1.0f / lt;
+    if constexpr (COPY) mul = p.v_scale[fin.kv_head] / lt;
+    const unsigned a = lds_base + own_off + Rows::row_chunk(lane & 31, lane >> 5);
+    static_for<0, NSTEP>([&](auto I) {
+      constexpr int ch = decltype(I)::value;  // dims 16 ch + 8 half + 0..7
+      u32x4 x;
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+        x[y] = pack_bf16(o[ch / 2][8 * (ch & 1) + 2 * y] * mul, o[ch / 2][8 * (ch & 1) + 2 * y + 1] * mul);
+      lds_write_b128<0>(a ^ (32 * ch), x);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    lds_read_planes<NSTEP>(w, lds_base + own_off + lane * 16);
+  }
+  // Q before the output stores, so that the wait for Q is not a wait for them
+  if (chained) {
+    asm volatile("" ::: "memory");
+    issue_q(unpack_record(read_mail(feed, feed.turn, lane)), lane);
+    asm volatile("" ::: "memory");
+    feed.turn ^= 64;
+  }
+  younger = 0;
+  if (finished) {
+    unsigned char* const op =
+        reinterpret_cast<unsigned char*>(p.out + ((long long)(fin.q_off + fin.q_tok0) * p.n_q_heads + fin.head0) * D);
+    const unsigned fin_magic = row_magic(fin.n_heads);
+    auto put = [&](int n) {
+      *reinterpret_cast<u32x4*>(op + Rows::offset(n, lane, row_base, fin_rows, fin_magic, fin.n_heads, p.n_q_heads)) = w[n];
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (row_base + 32 <= fin_rows) {
+#pragma unroll
+      for (int n = 0; n < NSTEP; ++n) put(n);
+      younger = NSTEP;
+    } else {
+#pragma unroll
+      for (int n = 0; n < NSTEP; ++n)
+        if (row_base + n * Rows::RPI + lane / Rows::CPR < fin_rows) put(n);
+    }
+  }
+  if (!chained) return posted;
   }
 }
 
@@ -863,14 +1160,6 @@ __device__ __forceinline__ void lds_read4_b64(u32x2 (&x)[4], unsigned addr) {
       : "memory");
 }
 
-// Read the NOPS 1-KiB operand planes of this lane (plane n at addr + 1024 n).
-template <int NOPS>
-__device__ __forceinline__ void lds_read_planes(u32x4 (&x)[NOPS], unsigned addr) {
-  static_assert(NOPS == 4 || NOPS == 8, "D = 64 or 128");
-  if constexpr (NOPS == 8) lds_read8<0, 1024, 2048, 3072, 4096, 5120, 6144, 7168>(x, addr);
-  else lds_read4<0, 1024, 2048, 3072>(x[0], x[1], x[2], x[3], addr);
-}
-
 template <int D, bool FP8>
 __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& it, unsigned char* smem) {
   constexpr int NSTEP = D / 16, NDB = D / 32;
@@ -894,17 +1183,8 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   const int r = min(c32, rows_valid - 1);
   const int t_row = r / gi_n, gi_row = r - t_row * gi_n;
   const int limit = pos0 + t_row;
-  // Q is requested here and waited for after the first block-table entries and K/V
-  // chunks have been requested as well (pin_q below): the latencies overlap, and the wait
-  // is not left to the streaming loop, where it would be a wait for every load in flight
   bf16x8 qreg[NSTEP];
   u32x4 qraw[NSTEP];
-  {
-    const unsigned short* qp =
-        p.q + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D + 8 * half;
-#pragma unroll
-    for (int s = 0; s < NSTEP; ++s) qraw[s] = *reinterpret_cast<const u32x4*>(qp + 16 * s);
-  }
   auto pin_q = [&]() {
 #pragma unroll
     for (int s = 0; s < NSTEP; ++s) {
@@ -927,6 +1207,30 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   const int pr = perm32(c32);
   const long long k_lane_off = (long long)(half * 16 + (pr & 15)) * 8 * ESZ;
   const long long v_lane_off = (long long)(half * D + pr) * 8 * ESZ;
+  // Block-table entries of this wave's next 32 sub-tiles live in one register (two lanes per
+  // sub-tile) and are picked with readlane: a table load inside the loop would have to wait
+  // behind every DMA load in flight.  The first ones are requested before Q, and Q is waited
+  // for after the first K/V chunks have been requested as well (pin_q): the latencies overlap,
+  // and the wait for Q is not left to the streaming loop, where it would be a wait for every
+  // load in flight.
+  int bt_reg = 0;
+  auto load_table = [&](int j0) {
+    const int uu = wave + kWaves * (j0 + (lane >> 1));
+    bt_reg = bt[min(((it.kv_begin + 32 * uu) >> 4) + (lane & 1), last_blk)];
+  };
+  auto pin_table = [&]() { asm volatile("" : "+v"(bt_reg)); };  // wait for them here, not at each use
+  load_table(0);
+  asm volatile("" ::: "memory");
+  // Lanes without a row of their own ask for nothing (a decode has G valid rows of 32).
+#pragma unroll
+  for (int s = 0; s < NSTEP; ++s) qraw[s] = u32x4{0, 0, 0, 0};
+  if (c32 < rows_valid) {
+    const unsigned short* qp =
+        p.q + ((long long)(si.q_off + it.q_tok0 + t_row) * p.n_q_heads + it.head0 + gi_row) * D + 8 * half;
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) qraw[s] = *reinterpret_cast<const u32x4*>(qp + 16 * s);
+  }
+  asm volatile("" ::: "memory");
 
   auto compute_s = [&](const u32x4 (&kop)[NSTEP], f32x16& s) {
 #pragma unroll
@@ -961,15 +1265,6 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     // so LDS only serves as storage for loads in flight (no registers are tied up).
     lds_byte* wl = (lds_byte*)smem + wave * WAVE_LDS;
     const unsigned rd_addr = (unsigned)(unsigned long long)wl + lane * 16;  // LDS byte address
-    // Block-table entries of this wave's next 32 sub-tiles live in one register (two
-    // lanes per sub-tile) and are picked with readlane: a table load inside the loop
-    // would have to wait behind every DMA load in flight.
-    int bt_reg = 0;
-    auto load_table = [&](int j0) {
-      const int uu = wave + kWaves * (j0 + (lane >> 1));
-      bt_reg = bt[min(((it.kv_begin + 32 * uu) >> 4) + (lane & 1), last_blk)];
-      asm volatile("" : "+v"(bt_reg));  // wait for it here, not at each use
-    };
     auto issue_k = [&](int j) {
       const long long b0 = __builtin_amdgcn_readlane(bt_reg, 2 * (j & 31));
       const long long b1 = __builtin_amdgcn_readlane(bt_reg, 2 * (j & 31) + 1);
@@ -990,7 +1285,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     };
     const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;  // sub-tiles wave, wave+4, ...
     if (n_iter > 0) {
-      load_table(0);
+      pin_table();
       issue_k(0);
       issue_v(0);
     }
@@ -1004,7 +1299,10 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
       lds_read_planes<NSTEP>(kop, rd_addr);
       compute_s(kop, s);
       if (has_next) {
-        if (((j + 1) & 31) == 0) load_table(j + 1);
+        if (((j + 1) & 31) == 0) {
+          load_table(j + 1);
+          pin_table();
+        }
         issue_k(j + 1);  // the K planes are free again
       }
       softmax(s, pp, u);
@@ -1028,14 +1326,11 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     const unsigned wl_addr = (unsigned)(unsigned long long)wl;
     const unsigned k_rd = wl_addr + (pr >> 4) * (BLKB + 128) + (half * 16 + (pr & 15)) * 8;
     const unsigned v_rd = wl_addr + KSET + (half * D + pr) * 8;
-    int bt_reg = 0;
-    auto load_table = [&](int j0) {
-      const int uu = wave + kWaves * (j0 + (lane >> 1));
-      bt_reg = bt[min(((it.kv_begin + 32 * uu) >> 4) + (lane & 1), last_blk)];
-      asm volatile("" : "+v"(bt_reg));
-    };
     auto issue = [&](int j) {
-      if ((j & 31) == 0) load_table(j);
+      if ((j & 31) == 0) {
+        if (j) load_table(j);
+        pin_table();
+      }
       lds_byte* set = wl + (j & 1) * SET;
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) {
@@ -1190,59 +1485,6 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   }
 }
 
-template <int D, bool FP8>
-constexpr int attn_lds_bytes() {
-  constexpr int wide_lds = 4 * 2 * 4 * 16 * D * 2;  // stages x (K + V tile of 64 keys)
-  constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * kNarrowRows * 4;
-  constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
-  static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
-  return lds;
-}
-
-// Behind the kernels' LDS buffers: two mailboxes of 16 ints (an item's record; the item loop
-// alternates between them, so one barrier per item separates writing and reading), then for
-// lane k = 0 .. 7 the dynamic part of queue (xcc + k) mod 8 as (items, first item).
-constexpr int kLoopLdsBytes = 2 * 64 + 2 * 4 * kQueues;
-
-// Items of queue x that are handed out without a ticket: work-group b starts with item b / 8
-// of queue b mod 8 (the dispatcher deals work-groups to the XCDs in turn), so the first
-// items of a launch need no atomic, and a launch with no more items than work-groups needs
-// none at all.
-__device__ __forceinline__ int static_items(const AttnParams& p, int x) {
-  return min(p.q_len[x], ((int)gridDim.x - x + kQueues - 1) / kQueues);
-}
-
-// Index of the next work item for a work-group of XCD `xcc`, or -1 when every queue is
-// empty: the own queue first, then the others in ring order (a queue's head only grows, so
-// a queue found empty stays empty).  One memory round trip takes the ticket of the own
-// queue (lane 0) and looks at the heads of the other seven (lanes 1 .. 7), so finding out
-// that nothing is left costs one round trip and not eight: measured on a decode batch that
-// gives every CU one item, 4.2 us -> 1.3 us between a work-group's last item and its end.
-__device__ __forceinline__ int take_item(const AttnParams& p, const int* dyn, int xcc, int lane) {
-  int len = 0, base = 0, head = 0;
-  if (lane < kQueues) {
-    len = dyn[2 * lane];
-    base = dyn[2 * lane + 1];
-  }
-  if (__builtin_amdgcn_ballot_w64(len > 0) == 0) return -1;
-  int* const q = p.q_heads + ((xcc + lane) & (kQueues - 1)) * kCounterStride;
-  if (len > 0) {
-    if (lane == 0) head = __hip_atomic_fetch_add(q, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else head = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  bool ticket = lane == 0;  // this lane's head is a ticket, not a look
-  for (;;) {
-    const unsigned long long open = __builtin_amdgcn_ballot_w64(head < len);
-    if (open == 0) return -1;
-    const int l = __builtin_ctzll(open);
-    if (__builtin_amdgcn_readlane((int)ticket, l)) return __builtin_amdgcn_readlane(base + head, l);
-    if (lane == l) {
-      head = __hip_atomic_fetch_add(q, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ticket = true;
-    }
-  }
-}
-
 // The work-groups of a launch stay resident, one per CU (the LDS they use allows no second
 // one), and work through the queues: the hardware dispatcher hands out work-groups strictly
 // in index order and stalls on the first XCD without a free CU, which couples the per-XCD
@@ -1250,14 +1492,14 @@ __device__ __forceinline__ int take_item(const AttnParams& p, const int* dyn, in
 // item when it is done with the last, whichever XCD's queue still has one.
 template <int D, bool FP8>
 __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
-  extern __shared__ __align__(16) unsigned char smem[];
+  extern __shared__ __align__(1024) unsigned char smem[];
   static_assert(kQueues == 8, "XCC_ID is masked to three bits");
   // hardware register XCC_ID (id 20), bits 3:0: the XCD this work-group runs on
   const int xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (kQueues - 1);
-  int* const mailboxes = reinterpret_cast<int*>(smem + attn_lds_bytes<D, FP8>());
-  int* const dyn = mailboxes + 32;
+  int* const dyn = reinterpret_cast<int*>(smem + attn_lds_bytes<D, FP8>() + 128);
+  Feed feed{(unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>(), 0, xcc, 0};
   int next = -1;  // wave 0: the item this work-group starts with
-  if (threadIdx.x < 64) {
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
     const int lane = threadIdx.x;
     const int y = (xcc + lane) & (kQueues - 1);
 #pragma unroll
@@ -1270,33 +1512,34 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
       }
     }
   }
-  for (int turn = 0;; turn ^= 1) {
-    int* const mailbox = mailboxes + 16 * turn;
-    // wave 0 takes the next item and posts its record; lanes 0-15 fetch one dword each
-    if (threadIdx.x < 64) {
-      const int idx = next >= 0 ? next : take_item(p, dyn, xcc, threadIdx.x);
+  bool posted = false;  // the next record is in the mailbox already
+  for (;;) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // recomputed per item
+    // wave 0 takes the next item and posts its record
+    if (!posted && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+      const int lane = tid;
+      if (next < 0) next = resolve_item(p, feed, request_item(p, feed, lane), lane);
+      else feed.left = __builtin_amdgcn_readfirstlane(queue_part(feed, lane).len);
+      fetch_record(p, feed, next, lane);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       next = -1;
-      if (threadIdx.x < 16) {
-        int v = threadIdx.x == 9 ? -1 : 0;  // field 9 = WorkItem::wide; -1: nothing left
-        if (idx >= 0) v = reinterpret_cast<const int*>(p.items + idx)[threadIdx.x];
-        mailbox[threadIdx.x] = v;
-      }
     }
     __syncthreads();  // the record is there, and every wave is done with the last item's LDS
-    WorkItem it;
-    {
-      int* f = reinterpret_cast<int*>(&it);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) f[i] = __builtin_amdgcn_readfirstlane(mailbox[i]);
-    }
+    const WorkItem it = unpack_record(read_mail(feed, feed.turn, tid & 63));
+    feed.turn ^= 64;
+    posted = false;
     if (it.wide < 0) break;
     if (it.n_tok <= 0 || it.n_heads <= 0) continue;
     if (it.wide) {
       if constexpr (FP8) {
-        if (it.wide >= 2) run_wide_dma<D, true>(p, it, smem);
-        else run_wide_staged<D, FP8, 1>(p, it, smem);
+        if (it.wide >= 2) {
+          posted = run_wide_dma<D, true>(p, feed, smem);
+        } else {
+          run_wide_staged<D, FP8, 1>(p, it, smem);
+        }
       } else {
-        run_wide_dma<D, false>(p, it, smem);
+        posted = run_wide_dma<D, false>(p, feed, smem);
       }
     } else {
       run_narrow<D, FP8>(p, it, smem);
