@@ -8,10 +8,9 @@
 //                 the blocks arrive by global->LDS DMA through a ring of four 64-key
 //                 tiles, three tiles ahead; the waves run freely between one s_barrier
 //                 per tile, so the two waves of a SIMD fill each other's MFMA and VALU
-//                 gaps.  For an fp8 cache a chunk of few tiles converts the codes on their way
-//                 into LDS (through registers, two stages); a chunk of many tiles reads a
-//                 bf16 copy of its sequence that kv_stage_kernel makes first, through the
-//                 same DMA pipeline as a bf16 cache.
+//                 gaps.  For an fp8 cache a chunk of few tiles converts the codes between a ring
+//                 of codes and three bf16 stages of the same pipeline; a chunk of many tiles
+//                 reads a bf16 copy of its sequence that kv_stage_kernel makes first.
 //   narrow item - at most 32 rows (a decode, or a short chunk) against a span of
 //                 keys; the 8 waves split the span and stream K/V from the paged pools
 //                 through private LDS (bf16: the chunk each lane needs, 16 bytes; fp8:
@@ -111,14 +110,13 @@ __device__ __forceinline__ unsigned int pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned int, __builtin_convertvector(f, bf16x2));
 }
 
-// 8 e4m3 codes -> 8 bf16 (exact).
+// 8 e4m3 codes -> 8 bf16 (exact: every e4m3 value is a bf16 value).
 __device__ __forceinline__ u32x4 fp8x8_to_bf16x8(u32x2 c) {
   u32x4 r;
-  f32x2 f;
-  f = __builtin_amdgcn_cvt_pk_f32_fp8(c[0], false); r[0] = pack_bf16(f[0], f[1]);
-  f = __builtin_amdgcn_cvt_pk_f32_fp8(c[0], true);  r[1] = pack_bf16(f[0], f[1]);
-  f = __builtin_amdgcn_cvt_pk_f32_fp8(c[1], false); r[2] = pack_bf16(f[0], f[1]);
-  f = __builtin_amdgcn_cvt_pk_f32_fp8(c[1], true);  r[3] = pack_bf16(f[0], f[1]);
+  r[0] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[0], 1.0f, false));
+  r[1] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[0], 1.0f, true));
+  r[2] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[1], 1.0f, false));
+  r[3] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[1], 1.0f, true));
   return r;
 }
 
@@ -133,18 +131,6 @@ __device__ __forceinline__ u32x4 zero_tail(u32x4 v, int kv0, int kv_len) {
     v[w] &= m;
   }
   return v;
-}
-
-template <bool FP8> struct RawChunk { using type = u32x4; };
-template <> struct RawChunk<true> { using type = u32x2; };
-
-template <bool FP8>
-__device__ __forceinline__ typename RawChunk<FP8>::type load_chunk(const unsigned char* p) {
-  return *reinterpret_cast<const typename RawChunk<FP8>::type*>(p);
-}
-template <bool FP8>
-__device__ __forceinline__ u32x4 to_bf16_chunk(typename RawChunk<FP8>::type c) {
-  if constexpr (FP8) return fp8x8_to_bf16x8(c); else return c;
 }
 
 // Online softmax update of one 32(q) x 32(key) S^T tile held as 16 accumulators per
@@ -322,7 +308,8 @@ __device__ __forceinline__ bool merge_wide_rows(const AttnParams& p, const WorkI
 // ------------------------------------------------------------------ work queues
 template <int D, bool FP8>
 constexpr int attn_lds_bytes() {
-  constexpr int wide_lds = 4 * 2 * 4 * 16 * D * 2;  // stages x (K + V tile of 64 keys)
+  constexpr int tile = 2 * 4 * 16 * D * 2;          // a K and V tile of 64 keys, bf16
+  constexpr int wide_lds = FP8 ? 3 * tile + 3 * tile / 2 : 4 * tile;  // stages (fp8: three, and three tiles of codes)
   constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * kNarrowRows * 4;
   constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
   static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
@@ -423,178 +410,7 @@ __device__ __forceinline__ WorkItem unpack_record(int rec) {
   return it;
 }
 
-// ---------------------------------------- wide (chunk) tile, staged through registers
-// Used for the fp8 cache: codes are converted to bf16 once, on their way into LDS.
-template <int D, bool FP8, int QT>
-__device__ __forceinline__ void run_wide_staged(const AttnParams& p, const WorkItem& it, unsigned char* smem) {
-  constexpr int NSTEP = D / 16, NDB = D / 32;
-  constexpr int BLK_LDS = 16 * D * 2;           // bytes of one (block, head) as bf16
-  constexpr int KT_BYTES = 4 * BLK_LDS;         // K (or V) tile: 64 keys
-  constexpr int STAGE = 2 * KT_BYTES;
-  constexpr int CH_PER_BLK = 2 * D;             // 8-element chunks per (block, head)
-  constexpr int PER = 8 * D / kThreads;         // chunks of K (and of V) each thread stages
-  constexpr int ESZ = FP8 ? 1 : 2;
-  using Raw = typename RawChunk<FP8>::type;
-
-  int tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
-  const int lane = tid & 63, half = lane >> 5, c32 = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, it.n_blocks};
-  const int gi_n = it.n_heads;
-  const int rows_valid = it.n_tok * gi_n;
-  const int row_base = wave * 32 * QT;
-  const bool wave_active = row_base < rows_valid;
-  const int kv_len = si.prefix_len + si.chunk_len;
-  const int pos0 = si.prefix_len + it.q_tok0;   // absolute position of the tile's first token
-  const float c = p.scale_log2e * (FP8 ? p.k_scale[it.kv_head] : 1.0f);
-
-  // causal limits of the rows this wave owns (rows past the tile repeat the last row)
-  const int wave_min_limit = pos0 + min(row_base, rows_valid - 1) / gi_n;
-  const int wave_max_limit = pos0 + min(row_base + 32 * QT - 1, rows_valid - 1) / gi_n;
-
-  bf16x8 qreg[QT][NSTEP];
-  int limit[QT];
-#pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    const int r = min(row_base + qt * 32 + c32, rows_valid - 1);
-    const int t = r / gi_n, gi = r - t * gi_n;
-    limit[qt] = pos0 + t;
-    const unsigned short* qp =
-        p.q + ((long long)(si.q_off + it.q_tok0 + t) * p.n_q_heads + it.head0 + gi) * D + 8 * half;
-#pragma unroll
-    for (int s = 0; s < NSTEP; ++s) qreg[qt][s] = as_bf16x8(*reinterpret_cast<const u32x4*>(qp + 16 * s));
-  }
-
-  f32x16 o[QT][NDB];
-  float m[QT], l[QT];
-#pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    m[qt] = kNeg;
-    l[qt] = 0.f;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) o[qt][db][i] = 0.f;
-  }
-
-  const int* bt = p.block_tables + (long long)it.seq * p.max_blocks;
-  const long long head_stride = (long long)16 * D * ESZ;  // bytes of one (block, head)
-  const int n_tiles = (it.kv_end - it.kv_begin + kWideKvTile - 1) / kWideKvTile;
-
-  Raw rk[PER], rv[PER];
-  int bt_next[PER];  // physical blocks of the tile that will be fetched next (looked up one tile early)
-  auto lookup_blocks = [&](int tile_base) {
-#pragma unroll
-    for (int n = 0; n < PER; ++n) {
-      const int bidx = (tile_base >> 4) + (tid + kThreads * n) / CH_PER_BLK;
-      bt_next[n] = bt[min(bidx, si.n_blocks - 1)];
-    }
-  };
-  auto stage_load = [&](int tile_base) {
-#pragma unroll
-    for (int n = 0; n < PER; ++n) {
-      const int id = tid + kThreads * n;
-      const int off = id % CH_PER_BLK;
-      const long long base = ((long long)bt_next[n] * p.n_kv_heads + it.kv_head) * head_stride + (long long)off * 8 * ESZ;
-      rk[n] = load_chunk<FP8>(p.k_pool + base);
-      rv[n] = load_chunk<FP8>(p.v_pool + base);
-    }
-  };
-  auto stage_store = [&](int buf, int tile_base) {
-    unsigned char* kb = smem + buf * STAGE;
-    unsigned char* vb = kb + KT_BYTES;
-    const bool tail = tile_base + kWideKvTile > kv_len;
-#pragma unroll
-    for (int n = 0; n < PER; ++n) {
-      const int id = tid + kThreads * n;
-      u32x4 kk = to_bf16_chunk<FP8>(rk[n]);
-      u32x4 vv = to_bf16_chunk<FP8>(rv[n]);
-      if (tail) {
-        const int blk = id / CH_PER_BLK, off = id - blk * CH_PER_BLK;
-        vv = zero_tail(vv, tile_base + 16 * blk + 8 * (off / D), kv_len);
-      }
-      *reinterpret_cast<u32x4*>(kb + id * 16) = kk;
-      *reinterpret_cast<u32x4*>(vb + id * 16) = vv;
-    }
-  };
-
-  const int pr = perm32(c32);
-  // byte offset of this lane's K chunk (step 0) inside a 32-key sub-tile, and of its V chunk (db 0)
-  const int k_lane_off = (pr >> 4) * BLK_LDS + (half * 16 + (pr & 15)) * 16;
-  const int v_lane_off = (half * D + pr) * 16;
-
-  lookup_blocks(it.kv_begin);
-  stage_load(it.kv_begin);
-  lookup_blocks(it.kv_begin + kWideKvTile);
-  int buf = 0;
-  for (int j = 0; j < n_tiles; ++j) {
-    const int tile_base = it.kv_begin + j * kWideKvTile;
-    stage_store(buf, tile_base);
-    __syncthreads();
-    if (j + 1 < n_tiles) {
-      stage_load(tile_base + kWideKvTile);
-      lookup_blocks(tile_base + 2 * kWideKvTile);
-    }
-    if (wave_active && tile_base <= wave_max_limit) {
-      const unsigned char* kb = smem + buf * STAGE;
-      const unsigned char* vb = kb + KT_BYTES;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int sub_base = tile_base + 32 * u;
-        if (sub_base > wave_max_limit) break;
-        const bool need_mask = sub_base + 31 > wave_min_limit;
-        f32x16 s[QT];
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s[qt][i] = 0.f;
-        const unsigned char* ksub = kb + u * 2 * BLK_LDS + k_lane_off;
-#pragma unroll
-        for (int st = 0; st < NSTEP; ++st) {
-          const bf16x8 a = as_bf16x8(*reinterpret_cast<const u32x4*>(ksub + st * 512));
-#pragma unroll
-          for (int qt = 0; qt < QT; ++qt)
-            s[qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[qt][st], s[qt], 0, 0, 0);
-        }
-        u32x4 pp[QT][2];
-#pragma unroll
-        for (int qt = 0; qt < QT; ++qt)
-          softmax_tile<NDB>(s[qt], need_mask, sub_base, half, limit[qt], c, m[qt], l[qt], o[qt], pp[qt]);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const unsigned char* vsub = vb + (u * 2 + t) * BLK_LDS + v_lane_off;
-#pragma unroll
-          for (int db = 0; db < NDB; ++db) {
-            const bf16x8 a = as_bf16x8(*reinterpret_cast<const u32x4*>(vsub + db * 512));
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt)
-              o[qt][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(pp[qt][t]), o[qt][db], 0, 0, 0);
-          }
-        }
-      }
-    }
-    buf ^= 1;
-  }
-
-  // epilogue: normalise and store, or leave this span's partial result for the merge
-  static_assert(QT == 1, "one partial slot per wavefront");
-  const float vmul = FP8 ? p.v_scale[it.kv_head] : 1.0f;
-#pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    const int r = row_base + qt * 32 + c32;
-    float lt = pair_sum(l[qt]);
-    if (it.partial >= 0 && (!wave_active || !merge_wide_rows<NDB, D>(p, it, wave, lane, o[qt], m[qt] * c, lt))) continue;
-    if (r < rows_valid) {
-      const int t = r / gi_n, gi = r - t * gi_n;
-      unsigned short* op = p.out + ((long long)(si.q_off + it.q_tok0 + t) * p.n_q_heads + it.head0 + gi) * D;
-      store_row_bf16<NDB>(op, o[qt], vmul / lt, half);
-    }
-  }
-}
-
-
-// ------------------------------------- wide (chunk) tile, bf16 cache: DMA-fed pipeline
+// ------------------------------------------------- wide (chunk) tile: DMA-fed pipeline
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -732,20 +548,32 @@ __device__ __forceinline__ void lds_write_b128(unsigned addr, u32x4 v) {
 // iteration over them took 358 -> 344 us.  Launches bound by the power limit gain less (large
 // chunks behind prefixes 876 -> 873 us): what is not idle any more lowers the clock.
 // Returns whether the next item's record is in mailbox f.turn, published by a barrier.
-// COPY: the item's sequence belongs to an fp8 cache and its K/V is read from the bf16 copy
-// that kv_stage_kernel made for this launch (blocks it.wide - 2 .. in logical order, no
-// table); the scale of K enters the exponent constant, that of V the normalisation.
-template <int D, bool COPY>
-__device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, unsigned char* smem) {
+// Where the K/V tiles come from:
+//  kPool   a bf16 cache;
+//  kCopy   the bf16 copy of an fp8 sequence that kv_stage_kernel made for this launch (blocks
+//          it.wide - 2 .. in logical order, no table);
+//  kCodes  an fp8 cache: the codes arrive by the same DMA in a ring of their own, three tiles
+//          ahead, and each wave converts the part that it fetched on its way into the stage of
+//          the tile after next (three bf16 stages; 16 more VALU instructions and 4 LDS writes per
+//          wave and 64 keys).  Before, the codes passed through registers between two barriers
+//          per tile, with the products of a sub-tile behind its softmax: 36 ns a key, 26 now (chunk of
+//          201 tokens behind 3000, G = 8, next to 48 decodes: 117.4 -> 111.4 us a pass).
+// For an fp8 cache the scale of K enters the exponent constant, that of V the normalisation.
+enum { kPool, kCopy, kCodes };
+template <int D, int MODE>
+__device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsigned char* smem) {
+  constexpr bool FP8 = MODE != kPool, CODES = MODE == kCodes;
   constexpr int NSTEP = D / 16, NDB = D / 32;
   constexpr int BLK_LDS = 16 * D * 2;     // bytes of one (block, head)
   constexpr int KT_BYTES = 4 * BLK_LDS;   // K (or V) tile: 64 keys
   constexpr int STAGE = 2 * KT_BYTES;
-  constexpr int kStages = 4, kAhead = kStages - 1;
+  constexpr int kStages = CODES ? 3 : 4, kAhead = 3;
+  // CODES: a ring of kRaw tiles of codes behind the stages; a wave converts what it fetched
+  constexpr int kRaw = 3, RAW = kStages * STAGE, RAW_TILE = STAGE / 2;
   constexpr int kLead = 6;                // tiles of an item that are left when the next item is asked for
   constexpr int UPW = D / 64;             // 1-KiB units of K (and of V) each wave fetches per tile
   constexpr int UPB = BLK_LDS / 1024;     // units per block
-  constexpr int NI = 2 * UPW;             // DMA instructions per wave per tile
+  constexpr int NI = CODES ? D / 64 : 2 * UPW;  // DMA instructions per wave per tile
   using Rows = RowTile<D>;
   static_assert(Rows::NINS == NSTEP && 2 * STAGE == kWaves * 32 * D * 2, "Q of a tile fills two stages");
 
@@ -754,26 +582,32 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row_base = wave * 32;
-  const unsigned char* const k_src = COPY ? p.stage_k : p.k_pool;
-  const unsigned char* const v_src = COPY ? p.stage_v : p.v_pool;
+  const unsigned char* const k_src = MODE == kCopy ? p.stage_k : p.k_pool;
+  const unsigned char* const v_src = MODE == kCopy ? p.stage_v : p.v_pool;
   const long long head_stride = (long long)BLK_LDS;
   lds_byte* const lds0 = (lds_byte*)smem;
   const unsigned lds_base = (unsigned)(unsigned long long)lds0;
-  // the wave's own rows (Q on its way in, the output on its way out): in stages 2 and 3
-  const unsigned own_off = 2 * STAGE + wave * (32 * D * 2);
+  // the wave's own rows (Q on its way in, the output on its way out): in the last two stages
+  const unsigned own_off = (kStages - 2) * STAGE + wave * (32 * D * 2);
 
-  // ---- DMA of tile j: this wave moves UPW units of K and of V, all inside one block
-  const int blk_w = (wave * UPW) / UPB, part_w = (wave * UPW) % UPB;
+  // ---- DMA of tile j: this wave moves UPW units of K and of V, all inside one block (codes:
+  // one block of K, waves 0 .. 3, or of V)
+  const int blk_w = CODES ? wave & 3 : (wave * UPW) / UPB, part_w = (wave * UPW) % UPB;
   // lane i: physical block of this wave's share of tile (j + i) of an item
   auto table_entries = [&](const WorkItem& w, int j) {
     const int blk0 = w.kv_begin >> 4;
     const int b = min(4 * (j + lane) + blk_w, w.n_blocks - 1 - blk0);
-    if constexpr (COPY) return w.wide - 2 + blk0 + b;  // blocks of the copy are in logical order
+    if constexpr (MODE == kCopy) return w.wide - 2 + blk0 + b;  // blocks of the copy are in logical order
     else return p.block_tables[(long long)w.seq * p.max_blocks + blk0 + b];
   };
   // instruction q = 2 x + is_v of tile j, whose block is lane j & 63 of bt
   auto issue_part = [&](int j, int q, int bt, int kv_head) {
     const long long b = __builtin_amdgcn_readlane(bt, j & 63);
+    if constexpr (CODES) {
+      dma_1k((wave < 4 ? k_src : v_src) + (b * p.n_kv_heads + kv_head) * (BLK_LDS / 2) + q * 1024,
+             lds0 + RAW + (j % kRaw) * RAW_TILE + (wave * NI + q) * 1024, lane);
+      return;
+    }
     const long long goff = (b * p.n_kv_heads + kv_head) * head_stride + part_w * 1024;
     lds_byte* dst = lds0 + (j % kStages) * STAGE + blk_w * BLK_LDS + part_w * 1024;
     const int x = q >> 1;
@@ -783,6 +617,23 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   auto issue_tile = [&](int j, int bt, int kv_head) {
 #pragma unroll
     for (int q = 0; q < NI; ++q) issue_part(j, q, bt, kv_head);
+  };
+  // CODES: the codes that instruction q of tile j brought, as bf16 into the tile's stage; each
+  // lane reads back the 16 codes (two chunks) it fetched, so only its wave's transfers have to
+  // have landed.  Complete when the wave's LDS operations are.
+  auto convert_part = [&](int j, int q) {
+    u32x4 r;
+    asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(r)
+                 : "v"(lds_base + RAW + (j % kRaw) * RAW_TILE + (wave * NI + q) * 1024 + lane * 16)
+                 : "memory");
+    const unsigned a = lds_base + (j % kStages) * STAGE + (wave >> 2) * KT_BYTES + blk_w * BLK_LDS + q * 2048 + lane * 32;
+    lds_write_b128<0>(a, fp8x8_to_bf16x8(u32x2{r[0], r[1]}));
+    lds_write_b128<16>(a, fp8x8_to_bf16x8(u32x2{r[2], r[3]}));
+  };
+  auto convert_tile = [&](int j) {
+#pragma unroll
+    for (int q = 0; q < NI; ++q) convert_part(j, q);
   };
   auto tiles_of = [](const WorkItem& w) { return (w.kv_end - w.kv_begin + kWideKvTile - 1) / kWideKvTile; };
   // Q of an item, by DMA into the wave's own rows
@@ -798,7 +649,7 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  auto chains = [](const WorkItem& w) { return COPY ? w.wide >= 2 : w.wide == 1; };
+  auto chains = [](const WorkItem& w) { return MODE == kCopy ? w.wide >= 2 : w.wide == 1; };
 
   // The record of the item being computed is read from its mailbox again where it is needed
   // (the mailbox is written next for the item after the next one): scalars that live through
@@ -814,6 +665,10 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
     issue_q(it, lane);
     if (tiles_of(it) > 1) issue_tile(1, bt_reg, it.kv_head);
     younger = tiles_of(it) > 1 ? NI : 0;
+    if (CODES && tiles_of(it) > 2) {
+      issue_tile(2, bt_reg, it.kv_head);
+      younger = 2 * NI;
+    }
   }
 
   for (;;) {
@@ -830,7 +685,7 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   const int kv_len = it.prefix_len + it.chunk_len - it.kv_begin;
   const int pos0 = it.prefix_len + it.q_tok0 - it.kv_begin;
   float c = p.scale_log2e;
-  if constexpr (COPY) c *= p.k_scale[kv_head];
+  if constexpr (FP8) c *= p.k_scale[kv_head];
   const int wave_min_limit = __builtin_amdgcn_readfirstlane(pos0 + token_of(min(row_base, rows_valid - 1)));
   const int wave_max_limit =
       wave_has_rows ? __builtin_amdgcn_readfirstlane(pos0 + token_of(min(row_base + 31, rows_valid - 1))) : -1;
@@ -894,8 +749,10 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   // ---- prologue: Q and the first tiles are in flight; tile 0 landed everywhere and Q in
   // registers, S(0), K(1) on its way
   if (younger == NSTEP) wait_vmcnt<NSTEP>();
+  else if (CODES && younger == 2 * NI) wait_vmcnt<2 * NI>();
   else if (younger == NI) wait_vmcnt<NI>();
   else wait_vmcnt<0>();
+  if constexpr (CODES) convert_tile(0);
   {
     const unsigned a = lds_base + own_off + Rows::row_chunk(c32, half);
     u32x4 q[NSTEP];
@@ -910,7 +767,19 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   __builtin_amdgcn_s_barrier();
   if (wave == 0)
     asm volatile("ds_write_b32 %0, %1 offset:36" ::"v"(feed.mail + feed.turn), "v"(kNotYet) : "memory");
-  if (n_tiles > 2) issue_tile(2, bt_reg, kv_head);
+  if constexpr (!CODES) {
+    if (n_tiles > 2) issue_tile(2, bt_reg, kv_head);
+  } else {
+    if (n_tiles > 3) issue_tile(3, bt_reg, kv_head);
+    if (n_tiles > 1) {
+      // tile 1 may be younger than Q (an item that is not chained: then tile 2 behind it, and tile 3)
+      if (younger != NSTEP) {
+        if (n_tiles > 3) wait_vmcnt<2 * NI>(); else wait_vmcnt<0>();
+      }
+      convert_tile(1);
+    }
+    if (n_tiles > 4) issue_tile(4, bt_reg, kv_head);
+  }
   f32x16 s_even, s_odd;  // S(u) of even / odd sub-tiles
   // written only where this wave sees a sub-tile: without a definition here the registers
   // would count as live from the item before
@@ -929,14 +798,28 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   // flight); the barrier publishes it and tells that every wave is done reading tile k - 2,
   // whose stage the next fetch overwrites.
   auto open_tile = [&](int k) {
-    if (k + 1 < n_tiles) wait_vmcnt<NI>(); else wait_vmcnt<0>();
+    if constexpr (CODES) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's part of tile k has been converted
+      if (k == n_tiles - 1) wait_vmcnt<0>();
+    } else {
+      if (k + 1 < n_tiles) wait_vmcnt<NI>(); else wait_vmcnt<0>();
+    }
     // the record comes over PCIe: tiles pass between its request and its use.  An item of
     // three tiles and more asks at the second last of them at the latest, so the wait above
     // has landed the record when the last one opens.
     if (early && !asked && k >= n_tiles - (kLead - 1)) ask_next();
     __builtin_amdgcn_s_barrier();
     if (k == n_tiles - 1 && n_tiles >= 3) look_ahead();
-    if (k + 2 < n_tiles) {
+    if constexpr (CODES) {
+      if (k + 1 < n_tiles) {
+        if (k + 3 < n_tiles) wait_vmcnt<2 * NI>(); else wait_vmcnt<0>();
+        convert_tile(k + 1);
+      }
+      if (k + 4 < n_tiles) {
+        next_entries(k + 4);
+        issue_tile(k + 4, bt_reg, kv_head);
+      }
+    } else if (k + 2 < n_tiles) {
       next_entries(k + 2);
       issue_tile(k + 2, bt_reg, kv_head);
     }
@@ -979,7 +862,7 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   // before its use, and LDS sees single reads, not bursts of eight per wave.
   // fetch: the tile after next exists and is fetched here; otherwise open_tile decides.
   auto fast_step = [&](int u, f32x16& s_cur, f32x16& s_nxt, bool opens_tile, bool fetch) {
-    const int jn = (u >> 1) + kAhead;
+    const int jn = (u >> 1) + (CODES ? kAhead + 2 : kAhead);  // the tile to fetch
     const unsigned av = v_lane + ((u >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
     const unsigned ak = k_lane + (((u + 2) >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
     // On entry the NSTEP reads of K(u+1) are in flight or landed and nothing else is.
@@ -1023,12 +906,25 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
     if (!fetch) {
       if (opens_tile) open_tile((u >> 1) + 1);
     } else if (opens_tile) {
-      wait_vmcnt<NI>();
-      __builtin_amdgcn_s_barrier();
-      next_entries(jn);
-      issue_part(jn, 0, bt_reg, kv_head);
+      if constexpr (CODES) {
+        // the writes of this wave's part of the tile are older than the NSTEP reads of V
+        asm volatile("s_waitcnt lgkmcnt(%0)" ::"i"(NSTEP) : "memory");
+        __builtin_amdgcn_s_barrier();
+        next_entries(jn);
+        wait_vmcnt<2 * NI>();
+        convert_part(jn - 3, 0);
+        issue_part(jn, 0, bt_reg, kv_head);
+      } else {
+        wait_vmcnt<NI>();
+        __builtin_amdgcn_s_barrier();
+        next_entries(jn);
+        issue_part(jn, 0, bt_reg, kv_head);
+        issue_part(jn, 1, bt_reg, kv_head);
+      }
+    } else if constexpr (CODES && NI > 1) {
+      convert_part(jn - 3, 1);
       issue_part(jn, 1, bt_reg, kv_head);
-    } else if constexpr (UPW > 1) {
+    } else if constexpr (!CODES && UPW > 1) {
       issue_part(jn, 2, bt_reg, kv_head);
       issue_part(jn, 3, bt_reg, kv_head);
     }
@@ -1081,6 +977,7 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
       bt_reg = bt_next;
       issue_tile(0, bt_reg, nx.kv_head);
       if (tiles_of(nx) > 1) issue_tile(1, bt_reg, nx.kv_head);
+      if (CODES && tiles_of(nx) > 2) issue_tile(2, bt_reg, nx.kv_head);
     }
   }
   asm volatile("" : "+v"(lane));
@@ -1094,7 +991,7 @@ __device__ __forceinline__ bool run_wide_dma(const AttnParams& p, Feed& feed, un
   for (int n = 0; n < NSTEP; ++n) asm volatile("" : "=v"(w[n]));  // as for s_even
   if (finished) {
     float mul = 1.0f / lt;
-    if constexpr (COPY) mul = p.v_scale[fin.kv_head] / lt;
+    if constexpr (FP8) mul = p.v_scale[fin.kv_head] / lt;
     const unsigned a = lds_base + own_off + Rows::row_chunk(lane & 31, lane >> 5);
     static_for<0, NSTEP>([&](auto I) {
       constexpr int ch = decltype(I)::value;  // dims 16 ch + 8 half + 0..7
@@ -1166,7 +1063,6 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   constexpr int ESZ = FP8 ? 1 : 2;
   constexpr int NACC = NDB * 16;
   constexpr int WAVE_LDS = 2 * NSTEP * 1024 + (FP8 ? 512 : 0);  // per-wave LDS: K planes then V planes (= NACC * 256); fp8: two sets of block images
-  using Raw = typename RawChunk<FP8>::type;
 
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
@@ -1534,12 +1430,12 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
     if (it.wide) {
       if constexpr (FP8) {
         if (it.wide >= 2) {
-          posted = run_wide_dma<D, true>(p, feed, smem);
+          posted = run_wide<D, kCopy>(p, feed, smem);
         } else {
-          run_wide_staged<D, FP8, 1>(p, it, smem);
+          posted = run_wide<D, kCodes>(p, feed, smem);
         }
       } else {
-        posted = run_wide_dma<D, false>(p, feed, smem);
+        posted = run_wide<D, kPool>(p, feed, smem);
       }
     } else {
       run_narrow<D, FP8>(p, it, smem);
