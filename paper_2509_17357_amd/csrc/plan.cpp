@@ -49,6 +49,15 @@ Scratch& scratch() {
 
 }  // namespace
 
+// A narrow item's keys in equal spans of at most `span` (and a quarter: no sliver spans), whole steps.
+struct NarrowSplit { int n, per; };
+static NarrowSplit split_of(long long kv_total, long long span) {
+  long long n = std::max<long long>(1, (kv_total + span - 1) / span);
+  if (n > 1 && kv_total - (n - 1) * span <= span / 4) --n;
+  const long long per = ((kv_total + n - 1) / n + kNarrowKvStep - 1) / kNarrowKvStep * kNarrowKvStep;
+  return NarrowSplit{(int)((kv_total + per - 1) / per), (int)per};
+}
+
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
                int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage) {
   const int D = cache->head_dim, Hq = cache->num_q_heads, Hkv = cache->num_kv_heads;
@@ -120,6 +129,26 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   span = (span + kNarrowKvStep - 1) / kNarrowKvStep * kNarrowKvStep;
   constexpr int kMaxSpanSteps = 16;  // spans are 2 .. 16 steps of kNarrowKvStep keys
   span = std::min<long long>(std::max<long long>(span, 2 * kNarrowKvStep), kMaxSpanSteps * kNarrowKvStep);
+  // Decodes alone whose spans are a few more than the CUs would pay a second round for those
+  // few: a longer span, up to twice as long, that needs one round is taken instead.  (16 decodes
+  // of 200 .. 3000 keys: 264 spans of at most 1024 keys on 256 CUs, 30.4 us; fewer of at most
+  // 1280, 28.1 us.)
+  if (wide_cost_total == 0) {
+    auto spans = [&](long long len) {
+      long long n = 0;
+      for (int s = 0; s < n_seqs; ++s)
+        if (chunk_lens[s] > 0)
+          n += split_of((long long)prefix_lens[s] + chunk_lens[s], len).n * Hkv * n_groups;
+      return n;
+    };
+    if (spans(span) > target_items)
+      for (long long len = span + kNarrowKvStep; len <= std::min<long long>(2 * span, kMaxSpanSteps * kNarrowKvStep);
+           len += kNarrowKvStep)
+        if (spans(len) <= target_items) {
+          span = len;
+          break;
+        }
+  }
 
   // A launch with few wide tiles (the paper's own iteration: one chunk of at most 512 tokens
   // = 64 tiles, section 5.1) lives or dies by how its spans pack onto the CUs next to the
@@ -141,13 +170,16 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   //    the wide items alone have run in rounds, or before the narrow items' K/V has streamed at
   //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, so the
   //    last wide item starts at about 0.77 of that time and the launch ends when it does.
+  //    Wide items on at most three quarters of the CUs are queued in front instead (below): the
+  //    launch cannot end before the longest of them, 10 us + 25.5 ns per key from its start.
   //    Next to streaming CUs a wide item takes 10 us + 16 ns per key (the clock is higher than
   //    under a chip-wide MFMA load), a narrow span 8 us + 6.7 ns per key, and a partial slot
   //    costs 21 ns (its traffic competes with the decodes'), the merge launch 4 us.
   if (wide_cost_total > 0 && wide_tiles <= 2LL * std::max(n_cus, 1)) {
     const int cus = std::max(n_cus, 1);
     struct Costs { double wide_us0, wide_us_key, narrow_us0, narrow_us_key, slot_us, merge_us0; };
-    const Costs chunk_dominated{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0}, decode_rich{10.0, 0.016, 8.0, 0.0067, 0.0206, 4.0};
+    const Costs chunk_dominated{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0}, decode_rich{10.0, 0.016, 8.0, 0.0067, 0.0206, 4.0},
+        at_once{10.0, 0.0255, 0.0, 0.0, 0.0, 0.0};
     const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77;
     constexpr int kMinCutPiece = 12 * kWideKvTile;
     long long longest = 0, n_narrow = 0;
@@ -166,9 +198,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     const double kv_elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1.0 : 2.0;
     const double hbm_us = (double)narrow_keys * 2.0 * D * kv_elem_bytes / hbm_bytes_per_us;  // K and V of every narrow key
     // items, summed and longest time of the wide items, and partial slots for a span length
-    struct WideSide { long long items, slots; double total_us, longest_us; };
+    struct WideSide { long long items, slots; double total_us, longest_us, longest_keys; };
     auto wide_side = [&](int piece, const Costs& c) {
-      WideSide w{0, 0, 0.0, 0.0};
+      WideSide w{0, 0, 0.0, 0.0, 0.0};
       for (int s = 0; s < n_seqs; ++s) {
         const long long P = prefix_lens[s], C = chunk_lens[s];
         if (C * group <= kNarrowRows) continue;
@@ -185,6 +217,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
           w.items += n_split * copies;
           w.total_us += us * (double)(n_split * copies);
           w.longest_us = std::max(w.longest_us, us);
+          w.longest_keys = std::max(w.longest_keys, height * (double)per);
           if (n_split > 1) w.slots += n_split * copies * kWaves;
         }
       }
@@ -224,6 +257,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         const double floor_us = std::max(std::max((w.total_us + narrow_total_us) / cus, hbm_us), wide_alone_us);
         const double ratio = narrow_total_us / w.total_us;
         if (ratio < 0.3) us = wide_alone_us + trailing_us();
+        else if (4 * w.items <= 3 * cus) us = std::max(floor_us, at_once.wide_us0 + at_once.wide_us_key * w.longest_keys);
         else if (ratio <= 10.0) us = std::max(floor_us, last_wide_start * floor_us + w.longest_us);
         else us = std::max(floor_us, w.longest_us);
       }
@@ -258,11 +292,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   int32_t q_off = 0;
 
   auto add_narrow = [&](int s, int kvh, int head0, int nh, int q_tok0, int n_tok, int kv_total) {
-    int n_split = (int)((kv_total + span - 1) / span);
-    if (n_split > 1 && kv_total - (long long)(n_split - 1) * span <= span / 4) --n_split;  // no sliver spans
-    const int per = (int)(((kv_total + n_split - 1) / n_split + kNarrowKvStep - 1) / kNarrowKvStep * kNarrowKvStep);
-    n_split = (kv_total + per - 1) / per;
-    int per_item = per;
+    const NarrowSplit split = split_of(kv_total, span);
+    int n_split = split.n;
+    int per_item = split.per;
     if (n_split > 1 && n_merge_groups == kMaxMergeGroups) {  // no arrival counters left
       n_split = 1;
       per_item = kv_total;
@@ -450,6 +482,13 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // step than with the spans last.  Where wide tiles dominate, the spans stay at the end
   // of the queue anyway.
   constexpr double kWideLead = 0.75;
+  // A queue whose wide items are at most three quarters of its XCD's CUs keeps them in front:
+  // they all start at once and the rest of the CUs stream beside them, and none is left to
+  // start late.  (A chunk of 463 tokens behind 2049 next to 49 decodes, 13 wide items a queue:
+  // 88.1 us interleaved, 80.0 with the wide items in front; fp8, a chunk of 201 behind 3000
+  // next to 48 decodes, 14 a queue: 110.7 -> 102.2; with as many wide items as CUs, the
+  // Llama-3-8B-shaped batch, interleaving is the better one.)
+  const size_t wide_at_once = (size_t)(3 * std::max(n_cus, 1) / (4 * kXcds));
   for (auto& q : sc.queue) {
     // microseconds per item, fitted to per-work-group timestamps of the Llama-3-8B-shaped
     // batch on MI355X (D = 128, bf16; only the ratio of the two kinds matters here)
@@ -467,7 +506,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       total[ref < 0] += time_of(ref);
       n_wide_q += ref >= 0;
     }
-    if (n_wide_q == 0 || n_wide_q == q.size() || total[1] < 0.3 * total[0] || total[0] < 0.1 * total[1]) continue;
+    if (n_wide_q <= wide_at_once || n_wide_q == q.size() || total[1] < 0.3 * total[0] || total[0] < 0.1 * total[1]) continue;
     sc.order.assign(q.begin(), q.end());  // wide refs first, then narrow refs
     size_t iw = 0, in = n_wide_q, k = 0;
     while (iw < n_wide_q || in < sc.order.size()) {
