@@ -324,8 +324,18 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   unsigned char* base = static_cast<unsigned char*>(g_dev[dev].static_scratch);
   static thread_local std::vector<unsigned char> image;  // host memory; grows to the largest plan seen
   image.resize(plan.image_bytes);
-  write_plan(&plan, image.data());
-  if (int rc = static_scratch_upload(base, image.data(), plan.image_bytes, hip_stream)) return rc;
+  // the compact list, when there is one and the scratch has room to stage it behind the rest
+  CompactPlan compact;
+  size_t compact_bytes = 0;
+  if (compact_plan(cache, &plan, &compact, image.data(), plan.image_bytes, &compact_bytes) &&
+      compact_bytes <= kStaticScratchBytes - plan.image_bytes - plan.total_bytes) {
+    if (int rc = static_scratch_expand(base + plan.off_items, base + plan.image_bytes + plan.total_bytes, compact, image.data(),
+                                       compact_bytes, hip_stream))
+      return rc;
+  } else {
+    write_plan(&plan, image.data());
+    if (int rc = static_scratch_upload(base, image.data(), plan.image_bytes, hip_stream)) return rc;
+  }
   // Nothing in the scratch has to start at zero: the kernels read the plan image that was just
   // stored and, of the partial slots, exactly the rows that items of this call write first.
   // (The heads of the work queues, which must, live in their own small array, and every

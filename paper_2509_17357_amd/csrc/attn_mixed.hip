@@ -1539,7 +1539,7 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
 // Plan upload of the no-allocation variant: the bytes travel as kernel arguments (copied by
 // the runtime at launch, so neither a pinned staging buffer nor a host-to-device copy is
 // needed), one work-group stores them.
-constexpr int kUploadVecs = 192;  // 3 KiB of payload per launch, inside the 4 KiB argument limit
+constexpr int kUploadVecs = 240;  // 3.75 KiB of payload per launch, inside the 4 KiB argument limit
 struct UploadChunk {
   u32x4 v[kUploadVecs];
 };
@@ -1548,7 +1548,39 @@ __global__ __launch_bounds__(256) void plan_upload_kernel(UploadChunk c, u32x4* 
   if (i < n_vec) dst[i] = c.v[i];
 }
 
+// Work items from the compact form of the list, one thread per item.  A list that fits in the
+// arguments is expanded by one launch (64 decodes, 512 items: 3 KiB, one launch where the
+// records took eleven of 2 us each); a longer one is uploaded first.
+__device__ __forceinline__ void expand_one(const CompactPlan& m, const unsigned char* src, WorkItem* items) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= m.n_items) return;
+  const unsigned char* refs = src + (size_t)m.n_units * sizeof(CompactUnit);
+  const uint32_t ref = m.ref_bytes == 2 ? reinterpret_cast<const uint16_t*>(refs)[i] : reinterpret_cast<const uint32_t*>(refs)[i];
+  items[i] = expand_item(m, reinterpret_cast<const CompactUnit*>(src), ref);
+}
+__global__ __launch_bounds__(256) void plan_expand_args_kernel(UploadChunk c, CompactPlan m, WorkItem* items) {
+  expand_one(m, reinterpret_cast<const unsigned char*>(&c), items);
+}
+__global__ __launch_bounds__(256) void plan_expand_kernel(const unsigned char* src, CompactPlan m, WorkItem* items) {
+  expand_one(m, src, items);
+}
+
 }  // namespace
+
+int static_scratch_expand(void* items, void* staging, const CompactPlan& m, const void* host_src, size_t bytes, void* stream) {
+  const dim3 grid((unsigned)((m.n_items + 255) / 256));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  WorkItem* out = static_cast<WorkItem*>(items);
+  if (bytes <= sizeof(UploadChunk)) {
+    UploadChunk c;
+    memcpy(&c, host_src, bytes);
+    hipLaunchKernelGGL(plan_expand_args_kernel, grid, dim3(256), 0, s, c, m, out);
+  } else {
+    if (int rc = static_scratch_upload(staging, host_src, bytes, stream)) return rc;
+    hipLaunchKernelGGL(plan_expand_kernel, grid, dim3(256), 0, s, static_cast<const unsigned char*>(staging), m, out);
+  }
+  return hipGetLastError() == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
+}
 
 int static_scratch_resolve(void** device_ptr) {
   void* ptr = nullptr;

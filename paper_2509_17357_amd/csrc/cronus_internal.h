@@ -54,6 +54,55 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
+// Compact form of the work list, for the entry point that uploads it as kernel arguments: the
+// items of one tile of a sequence differ only by KV head and key span, so an item is a number
+// (unit * n_kv_heads + kv_head) * max_split + span (2 bytes when all fit) and a unit holds the
+// rest.  expand_item() is the one definition of what an item then is: the device builds the
+// records with it, and the host accepts the compact form only if it gives back every record.
+#if defined(__HIP__)
+#define CRONUS_HOST_DEVICE __host__ __device__
+#else
+#define CRONUS_HOST_DEVICE
+#endif
+struct CompactUnit {
+  int32_t seq, prefix_len, chunk_len, q_off;
+  uint32_t tile;      // tile of the chunk | head group << 24
+  uint32_t per;       // keys per span | wide << 31
+  uint32_t partial;   // first partial slot of KV head 0 | slots per KV head << 16
+  uint32_t merge;     // merge group of KV head 0 | groups per KV head << 16
+};
+static_assert(sizeof(CompactUnit) == 32, "two 16-byte vectors");
+struct CompactPlan {
+  int32_t n_items, n_units, n_kv_heads, max_split;
+  int32_t group_heads, heads_per_kv, wide_tok, ref_bytes;  // ref_bytes: 2 or 4
+};
+CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
+  const uint32_t span = ref % (uint32_t)c.max_split, rest = ref / (uint32_t)c.max_split;
+  const int32_t kvh = (int32_t)(rest % (uint32_t)c.n_kv_heads);
+  const CompactUnit u = units[rest / (uint32_t)c.n_kv_heads];
+  const int32_t first_head = (int32_t)(u.tile >> 24) * c.group_heads, per = (int32_t)(u.per & 0x7fffffffu);
+  const bool wide = u.per >> 31;
+  WorkItem w;
+  w.seq = u.seq;
+  w.kv_head = kvh;
+  w.head0 = kvh * c.heads_per_kv + first_head;
+  w.n_heads = c.heads_per_kv - first_head < c.group_heads ? c.heads_per_kv - first_head : c.group_heads;
+  w.q_tok0 = (int32_t)(u.tile & 0xffffffu) * c.wide_tok;
+  w.n_tok = u.chunk_len - w.q_tok0 < c.wide_tok ? u.chunk_len - w.q_tok0 : c.wide_tok;
+  const int32_t kv_total = u.prefix_len + w.q_tok0 + w.n_tok, n_split = (kv_total - 1) / per + 1;
+  w.kv_begin = (int32_t)span * per;
+  w.kv_end = kv_total - w.kv_begin < per ? kv_total : w.kv_begin + per;
+  w.first_partial = (int32_t)(u.partial & 0xffffu) + kvh * (int32_t)(u.partial >> 16);
+  w.partial = n_split > 1 ? w.first_partial + (int32_t)span * (wide ? kWaves : 1) : -1;
+  w.merge_key = n_split * kMaxMergeGroups + (int32_t)(u.merge & 0xffffu) + kvh * (int32_t)(u.merge >> 16);
+  w.wide = wide;
+  w.prefix_len = u.prefix_len;
+  w.chunk_len = u.chunk_len;
+  w.q_off = u.q_off;
+  w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
+  return w;
+}
+
 // Rows whose partial results (split over key spans) are combined, for inspection (the kernels
 // find what they need in the work items):
 // rows row0 .. row0 + n_rows - 1 of the tile (row r = token r / n_heads, head r % n_heads);
@@ -119,6 +168,9 @@ int wide_rows_for(int head_dim, int kv_dtype);
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
                int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage = true);
 void write_plan(const Plan* plan, void* host_buf);
+// The same list in compact form ([CompactUnit x n_units | references], *bytes of buf used, a
+// multiple of 16), when it can be expressed (it holds every record) and fits in `capacity`.
+bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c, void* buf, size_t capacity, size_t* bytes);
 
 struct AttnLaunch {
   const cronus_kv_cache* cache;
@@ -158,6 +210,10 @@ int static_scratch_resolve(void** device_ptr);
 // static device array, zero when the library is loaded; every launch leaves its set zero).
 int queue_sets_resolve(int** device_ptr);
 int static_scratch_upload(void* dst, const void* host_src, size_t bytes, void* stream);
+// Enqueues the launches that build the work items of a compact list at `items` (device); a list
+// that does not fit in the arguments of one launch goes through `staging` (device, 16-byte
+// aligned, `bytes` bytes).
+int static_scratch_expand(void* items, void* staging, const CompactPlan& c, const void* host_src, size_t bytes, void* stream);
 int launch_kv_append(const cronus_kv_cache* cache, const void* k_src, const void* v_src,
                      const int32_t* cu_tokens, const int32_t* start_pos, const int32_t* block_tables,
                      int32_t max_blocks_per_seq, int32_t n_seqs, int32_t n_tokens, void* stream);

@@ -40,6 +40,8 @@ struct Scratch {
   std::vector<int32_t> order, bucket_start;
   struct Run { int32_t begin, len; float shortest; };  // a contiguous run of one group's tiles in a queue
   std::vector<Run> runs[kXcds];
+  int32_t wide_tok;                    // tokens per wide tile of the last plan
+  std::vector<int32_t> unit_base;      // compact_plan: first unit of every sequence
 };
 
 Scratch& scratch() {
@@ -271,6 +273,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   }
 
   Scratch& sc = scratch();
+  sc.wide_tok = wide_tok;
   sc.seqs.resize((size_t)n_seqs);
   sc.wide.clear();
   sc.narrow.clear();
@@ -574,6 +577,77 @@ void write_plan(const Plan* plan, void* host_buf) {
     std::memcpy(h + plan->off_merge, sc.merges.data(), sizeof(MergeItem) * sc.merges.size());
   }
   if (!sc.stages.empty()) std::memcpy(h + plan->off_stage, sc.stages.data(), sizeof(StageSeq) * sc.stages.size());
+}
+
+bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c, void* buf, size_t capacity, size_t* bytes) {
+  Scratch& sc = scratch();
+  const int Hkv = cache->num_kv_heads, G = cache->num_q_heads / Hkv;
+  const int group = std::min(G, kNarrowRows), n_groups = (G + group - 1) / group;
+  if (n_groups > 255) return false;
+  long long n_units = 0;
+  sc.unit_base.resize(sc.seqs.size());
+  for (size_t s = 0; s < sc.seqs.size(); ++s) {
+    sc.unit_base[s] = (int32_t)std::min<long long>(n_units, 1 << 30);
+    const long long tiles = (sc.seqs[s].chunk_len + sc.wide_tok - 1) / sc.wide_tok;
+    if (tiles >= 1 << 24) return false;
+    n_units += tiles * n_groups;
+  }
+  if (plan->n_items <= 0 || n_units > (long long)(capacity / sizeof(CompactUnit))) return false;
+  auto unit_of = [&](const WorkItem& w) {
+    const SeqInfo& si = sc.seqs[(size_t)w.seq];
+    const int32_t tiles = (si.chunk_len + sc.wide_tok - 1) / sc.wide_tok, g = (w.head0 - w.kv_head * G) / group;
+    return (size_t)(sc.unit_base[(size_t)w.seq] + g * tiles + w.q_tok0 / sc.wide_tok);
+  };
+  CompactUnit* units = static_cast<CompactUnit*>(buf);
+  std::memset(units, 0, (size_t)n_units * sizeof(CompactUnit));
+  uint32_t max_split = 1;
+  // the first span of KV head 0 fills a unit, that of KV head 1 shows the steps between heads
+  for (const auto* list : {&sc.wide, &sc.narrow})
+    for (const WorkItem& w : *list) {
+      if (w.kv_begin != 0 || w.kv_head > 1) continue;
+      CompactUnit& u = units[unit_of(w)];
+      const SeqInfo& si = sc.seqs[(size_t)w.seq];
+      const bool split = w.partial >= 0;
+      const uint32_t merge = (uint32_t)(w.merge_key % kMaxMergeGroups);
+      if (w.kv_head == 0) {
+        u = CompactUnit{w.seq, si.prefix_len, si.chunk_len, si.q_off,
+                        (uint32_t)(w.q_tok0 / sc.wide_tok) | (uint32_t)((w.head0 / group) << 24),
+                        (uint32_t)w.kv_end | (w.wide ? 1u << 31 : 0u), split ? (uint32_t)w.first_partial : 0u,
+                        split ? merge : 0u};
+        if (split) max_split = std::max(max_split, (uint32_t)(w.merge_key / kMaxMergeGroups));
+        if (u.partial > 0xffffu) return false;
+      } else if (split) {
+        const int64_t dp = (int64_t)w.first_partial - (u.partial & 0xffffu), dm = (int64_t)merge - (u.merge & 0xffffu);
+        if (dp < 0 || dp > 0xffff || dm < 0 || dm > 0xffff) return false;
+        u.partial |= (uint32_t)dp << 16;
+        u.merge |= (uint32_t)dm << 16;
+      }
+    }
+  const unsigned long long numbers = (unsigned long long)n_units * Hkv * max_split;
+  if (numbers > 0x7fffffffull) return false;
+  *c = CompactPlan{(int32_t)plan->n_items, (int32_t)n_units, Hkv, (int32_t)max_split, group, G, sc.wide_tok,
+                   numbers <= 0x10000ull ? 2 : 4};
+  const size_t off = (size_t)n_units * sizeof(CompactUnit);
+  *bytes = align_up(off + (size_t)plan->n_items * c->ref_bytes, 16);
+  if (*bytes > capacity) return false;
+  unsigned char* refs = static_cast<unsigned char*>(buf) + off;
+  size_t i = 0;
+  for (int x = 0; x < kQueues; ++x)
+    for (const int32_t q : sc.queue[x]) {
+      const WorkItem& w = q >= 0 ? sc.wide[(size_t)q] : sc.narrow[(size_t)~q];
+      const size_t unit = unit_of(w);
+      const uint32_t per = units[unit].per & 0x7fffffffu;
+      if (per == 0) return false;
+      const uint32_t ref = (uint32_t)((unit * (size_t)Hkv + w.kv_head) * max_split + (uint32_t)w.kv_begin / per);
+      const WorkItem e = expand_item(*c, units, ref);
+      if (e.seq != w.seq || e.kv_head != w.kv_head || e.head0 != w.head0 || e.n_heads != w.n_heads || e.q_tok0 != w.q_tok0 ||
+          e.n_tok != w.n_tok || e.kv_begin != w.kv_begin || e.kv_end != w.kv_end || e.partial != w.partial || e.wide != w.wide ||
+          (w.partial >= 0 && (e.first_partial != w.first_partial || e.merge_key != w.merge_key)))
+        return false;
+      if (c->ref_bytes == 2) reinterpret_cast<uint16_t*>(refs)[i++] = (uint16_t)ref;
+      else reinterpret_cast<uint32_t*>(refs)[i++] = ref;
+    }
+  return true;
 }
 
 }  // namespace cronus
