@@ -152,8 +152,8 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * memory and calls no allocating HIP routine.  The plan image and the partial results live in
  * a static device array inside the library (64 MiB, CRONUS_STATIC_SCRATCH_BYTES; every GPU
  * that the library runs on holds its own copy until the process ends); the work list reaches
- * it as kernel arguments of small upload launches (about one per 48 work items) on
- * `hip_stream`.  The first call on a device looks up that device's address of the array and
+ * it as kernel arguments on `hip_stream`, in a compact form that one launch expands (64 decodes
+ * of 8 KV heads: 3 KiB, that launch alone; more: one upload launch per 3.75 KiB before it).  The first call on a device looks up that device's address of the array and
  * sets the kernels' attributes (no allocation either).  On the host the planner keeps its
  * per-thread arrays (ordinary heap memory, grown to the largest batch the thread has planned).
  *   - CRONUS_ERR_WORKSPACE, nothing enqueued: the batch's plan image plus partial results
