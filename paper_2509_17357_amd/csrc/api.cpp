@@ -114,9 +114,17 @@ Slot* acquire_slot(int dev, size_t bytes) {
   if (s->state == Slot::kPending) {
     // seven more calls have been enqueued since: the wait is for a host that runs ahead of the GPU
     const volatile uint32_t* done = static_cast<const volatile uint32_t*>(s->host);
-    for (int spin = 0; *done != s->call; ++spin) {
-      if (spin < 4096) __builtin_ia32_pause();
-      else std::this_thread::sleep_for(std::chrono::microseconds(2));
+    const auto start = std::chrono::steady_clock::now();
+    for (int spin = 0; *done != s->call; spin += spin < 4096) {
+      if (spin < 4096) {
+        __builtin_ia32_pause();
+        continue;
+      }
+      std::this_thread::sleep_for(std::chrono::microseconds(2));
+      // A launch that a device error ended never reports; the wait must not last for ever.
+      if (std::chrono::steady_clock::now() - start > std::chrono::seconds(10)) {
+        if (hipDeviceSynchronize() != hipSuccess || *done != s->call) return nullptr;
+      }
     }
     std::atomic_thread_fence(std::memory_order_acquire);
     s->state = Slot::kFree;
