@@ -393,7 +393,7 @@ constexpr int kNotYet = -2;  // WorkItem::wide of a mailbox that waits for its r
 __device__ __forceinline__ void fetch_record(const AttnParams& p, const Feed& f, int idx, int lane) {
   typedef const __attribute__((address_space(1))) int global_int;
   global_int* r = idx >= 0 ? (global_int*)(p.items + idx) : (global_int*)no_item;
-  if (lane < 16) __builtin_amdgcn_global_load_lds(r + lane, (lds_byte*)(f.mail + f.turn), 4, 0, 0);
+  if (lane < 16) __builtin_amdgcn_global_load_lds(r + lane, (lds_byte*)(uintptr_t)(f.mail + f.turn), 4, 0, 0);
 }
 // The record in the mailbox (posted, and a barrier passed), one dword per lane of each 16;
 // then as scalars.
@@ -1559,7 +1559,11 @@ __device__ __forceinline__ void expand_one(const CompactPlan& m, const unsigned 
   items[i] = expand_item(m, reinterpret_cast<const CompactUnit*>(src), ref);
 }
 __global__ __launch_bounds__(256) void plan_expand_args_kernel(UploadChunk c, CompactPlan m, WorkItem* items) {
-  expand_one(m, reinterpret_cast<const unsigned char*>(&c), items);
+  // the arguments lie in host memory: one coalesced read of all of them, then LDS
+  __shared__ u32x4 list[kUploadVecs];
+  if (threadIdx.x < kUploadVecs) list[threadIdx.x] = c.v[threadIdx.x];
+  __syncthreads();
+  expand_one(m, reinterpret_cast<const unsigned char*>(list), items);
 }
 __global__ __launch_bounds__(256) void plan_expand_kernel(const unsigned char* src, CompactPlan m, WorkItem* items) {
   expand_one(m, src, items);
