@@ -131,26 +131,6 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   span = (span + kNarrowKvStep - 1) / kNarrowKvStep * kNarrowKvStep;
   constexpr int kMaxSpanSteps = 16;  // spans are 2 .. 16 steps of kNarrowKvStep keys
   span = std::min<long long>(std::max<long long>(span, 2 * kNarrowKvStep), kMaxSpanSteps * kNarrowKvStep);
-  // Decodes alone whose spans are a few more than the CUs would pay a second round for those
-  // few: a longer span, up to twice as long, that needs one round is taken instead.  (16 decodes
-  // of 200 .. 3000 keys: 264 spans of at most 1024 keys on 256 CUs, 30.4 us; fewer of at most
-  // 1280, 28.1 us.)
-  if (wide_cost_total == 0) {
-    auto spans = [&](long long len) {
-      long long n = 0;
-      for (int s = 0; s < n_seqs; ++s)
-        if (chunk_lens[s] > 0)
-          n += split_of((long long)prefix_lens[s] + chunk_lens[s], len).n * Hkv * n_groups;
-      return n;
-    };
-    if (spans(span) > target_items)
-      for (long long len = span + kNarrowKvStep; len <= std::min<long long>(2 * span, kMaxSpanSteps * kNarrowKvStep);
-           len += kNarrowKvStep)
-        if (spans(len) <= target_items) {
-          span = len;
-          break;
-        }
-  }
 
   // A launch with few wide tiles (the paper's own iteration: one chunk of at most 512 tokens
   // = 64 tiles, section 5.1) lives or dies by how its spans pack onto the CUs next to the
