@@ -980,6 +980,10 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
       if (CODES && tiles_of(nx) > 2) issue_tile(2, bt_reg, nx.kv_head);
     }
   }
+  // Nothing was posted: the item loop's wave 0 writes the next record to the mailbox that every
+  // wave has just read, so it may not get there before the last wave has read it.  (Every wave
+  // sees the same mailbox between the two barriers, so all of them come here or none.)
+  if (!posted) __builtin_amdgcn_s_barrier();
   asm volatile("" : "+v"(lane));
   const WorkItem fin = current();
   const int fin_rows = fin.n_tok * fin.n_heads;
