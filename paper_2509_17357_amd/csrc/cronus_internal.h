@@ -18,7 +18,7 @@ constexpr int kNarrowKvStep = 32 * kWaves;  // keys covered by the waves of a na
 constexpr int kQueues = 8;          // work queues of a launch: one per XCD of an MI355X (each XCD has its own L2)
 constexpr int kCounterStride = 16;  // int32 between the queue heads of a set: one 64-byte line each
 // Row groups whose results are merged from key spans, per launch at most: each has kWaves arrival
-// counters in the set.  A launch that would split more has thousands of items without splitting.
+// counters in the set.  A launch with more rows to split leaves its shortest ones whole (build_plan).
 constexpr int kMaxMergeGroups = 4096;
 constexpr int kQueueSetInts = (kQueues + 1) * kCounterStride + kMaxMergeGroups * kWaves;  // a set: the heads, the count of finished work-groups, the arrival counters
 constexpr int kQueueSets = 9;       // sets of queue heads per device: one per plan buffer of the ring, one for the static entry point

@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <utility>
 #include <vector>
 
 #include "cronus_internal.h"
@@ -42,6 +43,8 @@ struct Scratch {
   std::vector<Run> runs[kXcds];
   int32_t wide_tok;                    // tokens per wide tile of the last plan
   std::vector<int32_t> unit_base;      // compact_plan: first unit of every sequence
+  std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
+  std::vector<std::pair<int32_t, int32_t>> by_length;  // (-keys, sequence) of the narrow rows that are long enough to be cut
 };
 
 Scratch& scratch() {
@@ -274,11 +277,41 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   const bool fp8 = cache->kv_dtype == CRONUS_KV_FP8_E4M3 && allow_stage;  // candidates for the bf16 copy
   int32_t q_off = 0;
 
+  // More rows to cut than arrival counters: the longest are cut, the others stay whole.  A row
+  // that stays whole is then no longer than any of the nearly kMaxMergeGroups that are cut, so
+  // it is a small part of a CU's share of the launch (at most 1/15 at 256 CUs), and the queues
+  // take such rows first.  (With the counters dealt in batch order, 512 decodes of 8 k keys and
+  // a last one of 128 k left that one whole: 2190 -> 3916 us by the time_of estimates below.)
+  sc.whole.clear();
+  if ((long long)n_seqs * Hkv * n_groups + wide_tiles > kMaxMergeGroups) {
+    const long long copies = (long long)Hkv * n_groups;
+    long long cut_tiles = 0;
+    sc.by_length.clear();
+    for (int s = 0; s < n_seqs; ++s) {
+      const long long P = prefix_lens[s], C = chunk_lens[s];
+      if (C == 0) continue;
+      long long narrow_tok = C * group <= kNarrowRows ? C : 0;
+      if (narrow_tok == 0)
+        for (long long t0 = 0; t0 < C; t0 += wide_tok) {
+          const long long nt = std::min<long long>(wide_tok, C - t0);
+          if (nt * group <= kNarrowRows) narrow_tok = nt;
+          else cut_tiles += wide_piece_keys > 0 && P + t0 + nt > wide_piece_keys + wide_piece_keys / 2;
+        }
+      if (narrow_tok > 0 && split_of(P + C, span).n > 1) sc.by_length.push_back({(int32_t)-(P + C), s});
+    }
+    const size_t cuttable = (size_t)(std::max<long long>(0, kMaxMergeGroups - cut_tiles * copies) / copies);
+    if (sc.by_length.size() > cuttable) {
+      std::nth_element(sc.by_length.begin(), sc.by_length.begin() + (std::ptrdiff_t)cuttable, sc.by_length.end());
+      sc.whole.assign((size_t)n_seqs, 0);
+      for (size_t i = cuttable; i < sc.by_length.size(); ++i) sc.whole[(size_t)sc.by_length[i].second] = 1;
+    }
+  }
+
   auto add_narrow = [&](int s, int kvh, int head0, int nh, int q_tok0, int n_tok, int kv_total) {
     const NarrowSplit split = split_of(kv_total, span);
     int n_split = split.n;
     int per_item = split.per;
-    if (n_split > 1 && n_merge_groups == kMaxMergeGroups) {  // no arrival counters left
+    if (n_split > 1 && ((!sc.whole.empty() && sc.whole[(size_t)s]) || n_merge_groups == kMaxMergeGroups)) {
       n_split = 1;
       per_item = kv_total;
     }
@@ -342,7 +375,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
           int n_split = 1;
           if (wide_piece_keys > 0 && kv_total > wide_piece_keys + wide_piece_keys / 2)
             n_split = (kv_total + wide_piece_keys - 1) / wide_piece_keys;
-          if (n_merge_groups == kMaxMergeGroups) n_split = 1;  // no arrival counters left
+          if (n_merge_groups == kMaxMergeGroups) n_split = 1;  // no arrival counters left (more cut tiles than any MI355X launch has)
           const int per = ((kv_total + n_split - 1) / n_split + kWideKvTile - 1) / kWideKvTile * kWideKvTile;
           n_split = (kv_total + per - 1) / per;
           const int rows = nt * nh;
@@ -437,15 +470,22 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       for (int32_t j = 0; j < r.len; ++j) sc.queue[x][k++] = sc.order[(size_t)(r.begin + j)];
   }
   {  // narrow items by length, longest first: bucket sort on the number of kNarrowKvStep steps
+    // (a span has at most kMaxSpanSteps and a quarter; what is longer is a row left whole above,
+    // and those, in the first bucket, are sorted by their length)
     const size_t n = sc.narrow.size();
-    sc.bucket_start.assign(kMaxSpanSteps + 2, 0);
-    auto steps_of = [&](const WorkItem& w) {
-      return std::min(kMaxSpanSteps, (w.kv_end - w.kv_begin + kNarrowKvStep - 1) / kNarrowKvStep);
+    sc.bucket_start.assign(kMaxSpanSteps + 3, 0);
+    auto bucket_of = [&](const WorkItem& w) {
+      const int steps = (w.kv_end - w.kv_begin + kNarrowKvStep - 1) / kNarrowKvStep;
+      return (size_t)(steps > kMaxSpanSteps + kMaxSpanSteps / 4 ? 0 : kMaxSpanSteps + 1 - std::min(kMaxSpanSteps, steps));
     };
-    for (const WorkItem& w : sc.narrow) ++sc.bucket_start[(size_t)(kMaxSpanSteps - steps_of(w)) + 1];
-    for (int b = 0; b <= kMaxSpanSteps; ++b) sc.bucket_start[(size_t)b + 1] += sc.bucket_start[(size_t)b];
+    for (const WorkItem& w : sc.narrow) ++sc.bucket_start[bucket_of(w) + 1];
+    for (int b = 0; b <= kMaxSpanSteps + 1; ++b) sc.bucket_start[(size_t)b + 1] += sc.bucket_start[(size_t)b];
     sc.order.resize(n);
-    for (size_t i = 0; i < n; ++i) sc.order[(size_t)sc.bucket_start[(size_t)(kMaxSpanSteps - steps_of(sc.narrow[i]))]++] = (int32_t)i;
+    for (size_t i = 0; i < n; ++i) sc.order[(size_t)sc.bucket_start[bucket_of(sc.narrow[i])]++] = (int32_t)i;
+    std::stable_sort(sc.order.begin(), sc.order.begin() + sc.bucket_start[0], [&](int32_t a, int32_t b) {
+      const WorkItem &x = sc.narrow[(size_t)a], &y = sc.narrow[(size_t)b];
+      return x.kv_end - x.kv_begin > y.kv_end - y.kv_begin;
+    });
     for (size_t k = 0; k < n; ++k) {
       const int32_t i = sc.order[k];
       const WorkItem& w = sc.narrow[(size_t)i];
