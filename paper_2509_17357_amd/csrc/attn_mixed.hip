@@ -636,11 +636,23 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     for (int q = 0; q < NI; ++q) convert_part(j, q);
   };
   auto tiles_of = [](const WorkItem& w) { return (w.kv_end - w.kv_begin + kWideKvTile - 1) / kWideKvTile; };
-  // Q of an item, by DMA into the wave's own rows
+  // Q of an item into the wave's own rows: by DMA, which moves aligned 16-byte pieces.  The entry
+  // points accept bf16 rows at any address; rows that are not 16-byte aligned pass through
+  // registers (the wave's LDS operations are in order, so nothing waits for them but the reads).
   auto issue_q = [&](const WorkItem& w, int lane) {
     const unsigned magic = row_magic(w.n_heads);
     const unsigned char* qp =
         reinterpret_cast<const unsigned char*>(p.q + ((long long)(w.q_off + w.q_tok0) * p.n_q_heads + w.head0) * D);
+    if ((reinterpret_cast<uintptr_t>(p.q) & 15) != 0) {
+#pragma unroll 1
+      for (int n = 0; n < NSTEP; ++n) {
+        typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+        const u32x4 v = *reinterpret_cast<const u32x4_any*>(
+            qp + Rows::offset(n, lane, row_base, w.n_tok * w.n_heads, magic, w.n_heads, p.n_q_heads));
+        lds_write_b128<0>(lds_base + own_off + n * 1024 + lane * 16, v);
+      }
+      return;
+    }
 #pragma unroll
     for (int n = 0; n < NSTEP; ++n) {
       __builtin_amdgcn_global_load_lds(
