@@ -516,7 +516,8 @@ struct RowTile {
     return (unsigned)(row * (2 * D) + ((half ^ swz(row)) * 16));
   }
   // Byte offset of the chunk that lane `lane` moves in instruction n, relative to the tile's
-  // first token: row (clamped to the tile) -> token and head.
+  // first token: row (clamped to the tile) -> token and head.  The planner makes wide tiles only
+  // of tokens of less than 2^24 bytes.
   static __device__ __forceinline__ unsigned offset(int n, int lane, int row_base, int rows_valid, unsigned magic, int g,
                                                     int n_q_heads) {
     const unsigned r = (unsigned)min(row_base + n * RPI + lane / CPR, rows_valid - 1);

@@ -79,6 +79,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // tiles are slower again, and with the CUs already filled half tiles cost 1.5x the CU time.)
   constexpr int kMinPiece = 16 * kWideKvTile;  // no key span of a wide tile is shorter
   int wide_tok = std::max(1, wide_rows / group);
+  // A wide tile addresses its rows by 24-bit products of a token's bytes (Hq x D bf16); where
+  // those do not hold them, the chunk is cut into narrow items (64-bit addresses).
+  if ((long long)Hq * D * 2 >= 1 << 24) wide_tok = std::max(1, kNarrowRows / group);
   {
     long long full_tiles = 0, narrow_items = 0, longest = 0;
     for (int s = 0; s < n_seqs; ++s) {
