@@ -2,15 +2,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstring>
 #include <mutex>
-#include <thread>
 #include <vector>
 
 #include "cronus_internal.h"
+#include "plan_ring.h"
 
 namespace cronus {
 namespace {
@@ -84,51 +83,34 @@ int prepare_device_locked(int* device) {
   return CRONUS_OK;
 }
 
-// The work list is written into pinned, device-mapped host memory and the kernels read it
-// from there (each work-group one 64-byte item): no copy sits between the caller's previous
-// work on the stream and the attention kernel (a stream-ordered copy of these few KB took
-// about 25 us of otherwise idle stream time on MI355X).  A slot is reused only after the
-// kernels of the call that used it are done with it: the main kernel's last work-group stores
-// the call's number in front of the plan image.  (An event recorded behind the kernels cost
-// the host 1.5 us a call and the stream 5 us before its next kernel.)
-struct Slot {
-  void* host = nullptr;
-  void* dev = nullptr;   // the same memory as the device sees it
-  size_t cap = 0;
-  uint32_t call = 0;     // number of the last call that used the slot
-  enum { kFree, kPending, kLost } state = kFree;  // kLost: nothing tells when its kernels are done
-};
 constexpr size_t kSlotHeader = 256;  // bytes in front of the plan image: the number of the last finished call
 void* g_ev[4] = {nullptr, nullptr, nullptr, nullptr};
 
-constexpr int kSlots = 8;
 static_assert(kQueueSets == kSlots + 1, "one set of queue heads per plan buffer, one for the static entry point");
-Slot g_slots[kMaxDevices][kSlots];  // a ring per device: a slot's memory is mapped for one
-int g_next[kMaxDevices] = {0};
+PlanRing g_rings[kMaxDevices];  // a ring per device: a slot's memory is mapped for one
 
-Slot* acquire_slot(int dev, size_t bytes) {
-  bytes += kSlotHeader;
-  Slot* s = &g_slots[dev][g_next[dev]];
-  g_next[dev] = (g_next[dev] + 1) % kSlots;
-  if (s->state == Slot::kLost) return nullptr;
-  if (s->state == Slot::kPending) {
-    // seven more calls have been enqueued since: the wait is for a host that runs ahead of the GPU
-    const volatile uint32_t* done = static_cast<const volatile uint32_t*>(s->host);
-    const auto start = std::chrono::steady_clock::now();
-    for (int spin = 0; *done != s->call; spin += spin < 4096) {
-      if (spin < 4096) {
-        __builtin_ia32_pause();
-        continue;
-      }
-      std::this_thread::sleep_for(std::chrono::microseconds(2));
-      // A launch that a device error ended never reports; the wait must not last for ever.
-      if (std::chrono::steady_clock::now() - start > std::chrono::seconds(10)) {
-        if (hipDeviceSynchronize() != hipSuccess || *done != s->call) return nullptr;
-      }
-    }
-    std::atomic_thread_fence(std::memory_order_acquire);
-    s->state = Slot::kFree;
+// A captured call runs when its graph does, and again with every replay.
+bool is_capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (stream == nullptr) return false;  // the default stream cannot be captured
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
   }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// A plan buffer of at least `bytes` behind its header, or nullptr.  The caller holds g_mu through `lock`.
+Slot* acquire_slot(int dev, size_t bytes, hipStream_t stream, std::unique_lock<std::mutex>& lock) {
+  bytes += kSlotHeader;
+  Slot* s = wait_for_slot(g_rings[dev], lock, stream, std::chrono::seconds(10), [&] {
+    if (is_capturing(stream)) return StreamIs::kBusy;
+    const hipError_t e = hipStreamQuery(stream);
+    if (e == hipSuccess) return StreamIs::kDone;
+    (void)hipGetLastError();
+    return e == hipErrorNotReady ? StreamIs::kBusy : StreamIs::kFailed;
+  });
+  if (!s) return nullptr;
   if (s->cap < bytes) {
     if (s->host) (void)hipHostFree(s->host);
     s->host = s->dev = nullptr;
@@ -145,17 +127,6 @@ Slot* acquire_slot(int dev, size_t bytes) {
     *static_cast<volatile uint32_t*>(s->host) = s->call;
   }
   return s;
-}
-
-// A captured call runs when its graph does, and again with every replay.
-bool is_capturing(hipStream_t stream) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (stream == nullptr) return false;  // the default stream cannot be captured
-  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return st != hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -284,25 +255,28 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, co
   if (plan.n_items > 0x7fffffffLL) return CRONUS_ERR_INVALID_ARG;
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  std::lock_guard<std::mutex> lock(g_mu);
+  std::unique_lock<std::mutex> lock(g_mu);
   // everything that can fail without a launch comes first: kernel attributes, the plan buffer
   int dev = 0;
   if (int rc = prepare_device_locked(&dev)) return rc;
-  Slot* slot = acquire_slot(dev, plan.image_bytes);
+  Slot* slot = acquire_slot(dev, plan.image_bytes, stream, lock);
   if (!slot) return CRONUS_ERR_HIP;
   unsigned char* const host = static_cast<unsigned char*>(slot->host);
   unsigned char* const dev_mem = static_cast<unsigned char*>(slot->dev);
   write_plan(&plan, host + kSlotHeader);
   // the set of queue heads that belongs to this plan buffer: free again when the buffer is
-  const int set = (int)(slot - g_slots[dev]);
+  const int set = (int)(slot - g_rings[dev].slots);
   AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, &plan, hip_stream,
                g_dev[dev].queue_sets + set * kQueueSetInts, reinterpret_cast<uint32_t*>(dev_mem), ++slot->call,
                {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+  slot->stream = stream;
   slot->state = is_capturing(stream) ? Slot::kLost : Slot::kPending;
   bool main_launched = false;
   const int rc = launch_attn(a, &main_launched);
   if (!main_launched && slot->state == Slot::kPending) {
-    (void)hipStreamSynchronize(stream);  // an earlier kernel of the call may read the slot
+    lock.unlock();
+    (void)hipStreamSynchronize(stream);  // an earlier kernel of the failed call may read the slot
+    lock.lock();
     slot->state = Slot::kFree;
   }
   return rc;
