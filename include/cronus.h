@@ -133,7 +133,10 @@ int cronus_kv_append(const cronus_kv_cache* cache, const void* k_src, const void
  *                  must not be shared by calls that can overlap on the device
  * The work list is built on the host during the call and read by the kernels from
  * pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
- * demand, never freed; the ninth call in flight waits on the host for the first).  The main
+ * demand, never freed; the ninth call in flight waits on the host for one of them).  A call
+ * captured into a HIP graph keeps its buffer for good, since replays read it: later calls use
+ * the others, and fail with CRONUS_ERR_HIP once eight calls have been captured
+ * (cronus_attn_mixed_static keeps none).  The main
  * kernel's work-groups stay resident and take their items from work queues whose heads (a
  * few integers per call in flight) live in a small static device array of the library; every
  * launch leaves its set of heads zero for the next one.

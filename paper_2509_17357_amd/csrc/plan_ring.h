@@ -33,7 +33,6 @@ struct PlanRing {
 
   // A slot that no kernel reads any more, the one after the last taken if that is free; nullptr: none yet.
   Slot* take() {
-    if (slots[next].state == Slot::kLost) return nullptr;
     for (int i = 0; i < kSlots; ++i) {
       Slot* s = &slots[(next + i) % kSlots];
       if (s->state == Slot::kLost || (s->state == Slot::kPending && !s->reported())) continue;
@@ -44,10 +43,9 @@ struct PlanRing {
     }
     return nullptr;
   }
-  // Whether the next call can get a slot at all; the call after one that cannot is the next slot's.
-  bool usable() {
-    if (slots[next].state != Slot::kLost) return true;
-    next = (next + 1) % kSlots;
+  bool usable() const {
+    for (const Slot& s : slots)
+      if (s.state != Slot::kLost) return true;
     return false;
   }
   // The work on `stream` is over, or failed: its calls that have not reported never will.

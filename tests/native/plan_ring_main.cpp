@@ -63,6 +63,21 @@ static int lock_is_free() {
   return 0;
 }
 
+// a stream whose work is over: its calls that have not reported are given up, others' are kept
+static int ended_calls() {
+  for (int i = 0; i < kSlots; ++i) enqueue(ring.take(), i < 6 ? (const void*)&stream_a : &stream_b);
+  std::unique_lock<std::timed_mutex> lock(mu);
+  int n = 0;
+  Slot* s = wait_for_slot(ring, lock, &stream_a, milliseconds(2), [&] {
+    if (++n == 2) report(6);
+    return n == 1 ? StreamIs::kDone : StreamIs::kBusy;
+  });
+  CHECK(index_of(s) == 6 && lock.owns_lock());
+  for (int i = 0; i < 6; ++i) CHECK(ring.slots[i].state == Slot::kLost);
+  CHECK(ring.slots[7].state == Slot::kPending);
+  return 0;
+}
+
 // a failed stream: the call fails, without waiting again the next time
 static int failed_stream() {
   for (int i = 0; i < kSlots; ++i) enqueue(ring.take(), &stream_a);
@@ -77,7 +92,7 @@ static int failed_stream() {
 
 int main(int argc, char** argv) {
   const struct { const char* name; int (*run)(); } cases[] = {
-      {"order", order}, {"lock_is_free", lock_is_free}, {"failed_stream", failed_stream}};
+      {"order", order}, {"lock_is_free", lock_is_free}, {"ended_calls", ended_calls}, {"failed_stream", failed_stream}};
   for (const auto& c : cases)
     if (argc > 1 && !std::strcmp(argv[1], c.name)) return c.run();
   return 2;

@@ -22,7 +22,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["order", "lock_is_free", "failed_stream"])
+@pytest.mark.parametrize("case", ["order", "lock_is_free", "ended_calls", "failed_stream"])
 def test_ring(program, case):
     env = dict(os.environ)
     env.pop("LD_PRELOAD", None)  # the sanitizer runtime must come first in the library list
