@@ -2,8 +2,10 @@
 uploads: for every batch it accepts, each reference must expand to the record of the ordinary
 list, bit for bit (under AddressSanitizer and UndefinedBehaviorSanitizer).  Batches: decodes
 unsplit and split, chunks with narrow tails, tiles cut into spans, half tiles, more than 32
-heads per KV head, one KV head, more references than 16 bits hold, empty chunks, and a launch
-that runs out of merge groups (which must be refused, not mangled)."""
+heads per KV head, one KV head, more references than 16 bits hold, empty chunks, a launch with
+more rows to cut than merge groups; and lists that the compact form cannot express, which must
+be refused, not mangled: more than 255 head groups, a row whose first partial slot is beyond 16
+bits, and merge groups that run out between the KV heads of a tile."""
 import os
 import shutil
 import subprocess
@@ -27,6 +29,9 @@ def _cases():
         ("many tiles", 32, 8, 128, 304, [(0, 7000), (100, 9000)]),
         ("many sequences", 4, 2, 64, 256, [(int(p), int(c)) for p, c in zip(rng.integers(0, 900, 9000), rng.integers(0, 3, 9000))]),
         ("no merge groups left", 8, 8, 64, 4096, [(int(p), 1) for p in rng.integers(5000, 9000, 600)]),
+        ("refused: 257 head groups", 8224, 1, 64, 256, [(300, 1), (40, 3)]),
+        ("refused: partial slots beyond 16 bits", 32, 8, 128, 256, [(400000, 1)] * 100),
+        ("refused: groups end between KV heads", 3, 3, 64, 8400, [(20000, 256)] * 1400),
     ]
     for i in range(40):
         n = int(rng.integers(1, 60))
@@ -60,6 +65,8 @@ def test_every_accepted_list_expands_to_the_records(tmp_path):
         assert not accepted or nbytes <= 64 * items, name
     by_name = {c[0]: rep for c, rep in zip(cases, replies)}
     for name in ("decodes", "split decodes", "one decode", "tile spans and tails", "half tiles", "two head groups",
-                 "many tiles", "many sequences"):
+                 "many tiles", "many sequences", "no merge groups left"):
         assert by_name[name][0] == 1, name
+    for name in by_name:
+        assert not (name.startswith("refused") and by_name[name][0]), name
     assert by_name["decodes"][2] <= 3840  # one launch's arguments
