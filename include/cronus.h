@@ -31,7 +31,7 @@
  *     and the outputs of that call are then undefined.
  *   - Device-side facts (CU count, kernel set-up, plan buffers) are kept per device and
  *     looked up for the device that is current in the calling thread; calls are
- *     serialised by one lock.
+ *     serialised by one lock (not held while a call waits for a plan buffer).
  *   - Block ids in block tables are NOT checked on the device: an id outside
  *     [0, num_blocks) or two rows mapped to one slot in a single call is undefined
  *     behaviour.  Table entries past ceil(len/16) are never read and may hold
@@ -47,7 +47,9 @@
  *   V pool: [num_blocks][Hkv][2][D][8] E
  *       element (b, g, t, d) at (((b*Hkv + g)*2 + t/8)*D + d)*8 + t%8
  *       (a chunk = 8 consecutive tokens of one d)
- *   One (block, head) is 16*D elements in either pool.
+ *   One (block, head) is 16*D elements in either pool.  The pools start at a multiple of
+ *   16 bytes (blocks are moved in whole 16-byte pieces); q and out may lie at any address
+ *   of a bf16 element.
  * fp8 pools: real value = code_value * scale[g], one fp32 scale per KV head for K
  *   and one for V (OCP e4m3: no infinities, max 448).
  */

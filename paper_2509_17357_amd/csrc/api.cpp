@@ -347,6 +347,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 504; }  // 0.5.4: resident work-groups with work queues; plan items carry their queue; MFMA probe
+int cronus_version(void) { return 505; }  // 0.5.5: key spans merged by the main kernel; chained wide tiles; compact static list
 
 }  // extern "C"

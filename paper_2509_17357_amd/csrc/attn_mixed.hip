@@ -199,20 +199,6 @@ __device__ __forceinline__ void softmax_tile(f32x16& s, bool need_mask, int sub_
 constexpr float kTileSumLimit = 16.0f * 256.0f;
 static_assert(kLazyLog2 == 8.0f, "kTileSumLimit = 16 * 2^kLazyLog2");
 
-// Store one lane's share of a finished row: dims 32*db + 16*j + 8*half + 0..7.
-template <int NDB>
-__device__ __forceinline__ void store_row_bf16(unsigned short* row_ptr, const f32x16 (&o)[NDB], float mul, int half) {
-#pragma unroll
-  for (int db = 0; db < NDB; ++db)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      u32x4 w;
-#pragma unroll
-      for (int x = 0; x < 4; ++x) w[x] = pack_bf16(o[db][8 * j + 2 * x] * mul, o[db][8 * j + 2 * x + 1] * mul);
-      *reinterpret_cast<u32x4*>(row_ptr + 32 * db + 16 * j + 8 * half) = w;
-    }
-}
-
 // Partial results of key spans.  A slot holds 32 rows: O (32 x D fp32; a wide tile's wave
 // writes it in the order of its registers, a narrow item row by row), then (m in log2 units,
 // l) of every row.  Every XCD has its own L2, so the slots are written and read with agent
@@ -1078,8 +1064,7 @@ template <int D, bool FP8>
 __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& it, unsigned char* smem) {
   constexpr int NSTEP = D / 16, NDB = D / 32;
   constexpr int ESZ = FP8 ? 1 : 2;
-  constexpr int NACC = NDB * 16;
-  constexpr int WAVE_LDS = 2 * NSTEP * 1024 + (FP8 ? 512 : 0);  // per-wave LDS: K planes then V planes (= NACC * 256); fp8: two sets of block images
+  constexpr int WAVE_LDS = 2 * NSTEP * 1024 + (FP8 ? 512 : 0);  // per-wave LDS: K planes then V planes; fp8: two sets of block images
 
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers

@@ -170,6 +170,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
 void write_plan(const Plan* plan, void* host_buf);
 // The same list in compact form ([CompactUnit x n_units | references], *bytes of buf used, a
 // multiple of 16), when it can be expressed (it holds every record) and fits in `capacity`.
+// Checking every record costs the host less than the launches it saves (host time of a static
+// call, records / compact: 512 items 66 / 26 us, 1024 110 / 49, 2800 246 / 119).
 bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c, void* buf, size_t capacity, size_t* bytes);
 
 struct AttnLaunch {

@@ -153,7 +153,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   //    run in rounds over the CUs; the CUs that the last round leaves free take narrow items
   //    meanwhile, the narrow items left after that follow in rounds of their own.  A wide item
   //    takes 8 us + 23.7 ns per key at 256 rows (three quarters of that per key at half
-  //    height), a narrow span 6 us + 12 ns per key, the merge 13 us + 3 ns per partial slot.
+  //    height), a narrow span 6 us + 12 ns per key, a launch with cut tiles 13 us + 3 ns per
+  //    partial slot.
   //  * decode-rich: the launch cannot end before the items' times summed over the CUs, before
   //    the wide items alone have run in rounds, or before the narrow items' K/V has streamed at
   //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, so the
@@ -162,10 +163,14 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   //    launch cannot end before the longest of them, 10 us + 25.5 ns per key from its start.
   //    Next to streaming CUs a wide item takes 10 us + 16 ns per key (the clock is higher than
   //    under a chip-wide MFMA load), a narrow span 8 us + 6.7 ns per key, and a partial slot
-  //    costs 21 ns (its traffic competes with the decodes'), the merge launch 4 us.
+  //    costs 21 ns (its traffic competes with the decodes'), a launch with cut tiles 4 us.
+  // The 13 us and 4 us were measured with the merge as a launch of its own behind the main
+  // kernel; the main kernel merges now, and the model has not been fitted to that, so it leans
+  // against cutting.  The three quarters are counted over the launch here and per queue below:
+  // a queue that was dealt more than its share of the wide items interleaves all the same.
   if (wide_cost_total > 0 && wide_tiles <= 2LL * std::max(n_cus, 1)) {
     const int cus = std::max(n_cus, 1);
-    struct Costs { double wide_us0, wide_us_key, narrow_us0, narrow_us_key, slot_us, merge_us0; };
+    struct Costs { double wide_us0, wide_us_key, narrow_us0, narrow_us_key, slot_us, cut_us0; };
     const Costs chunk_dominated{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0}, decode_rich{10.0, 0.016, 8.0, 0.0067, 0.0206, 4.0},
         at_once{10.0, 0.0255, 0.0, 0.0, 0.0, 0.0};
     const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77;
@@ -249,7 +254,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         else if (ratio <= 10.0) us = std::max(floor_us, last_wide_start * floor_us + w.longest_us);
         else us = std::max(floor_us, w.longest_us);
       }
-      us += c.slot_us * (double)w.slots + (w.slots ? c.merge_us0 : 0.0);
+      us += c.slot_us * (double)w.slots + (w.slots ? c.cut_us0 : 0.0);
       if (best_piece == 0 || us < best_us) {
         best_us = us;
         best_piece = piece;
