@@ -47,9 +47,9 @@ BOUND = {"tiny": "hbm", "llama3_8b": "hbm", "prefill_heavy": "mfma", "decode_hea
 # 2.000, WRITE_SIZE x 1.000).  These are STATIC figures copied from the summary named below, taken
 # with the library version named below; with any other library version the line carries null.
 TRAFFIC_SOURCE = "profiles/attn_mixed_kernel_benchmark_batches_rocprofv3.md"
-TRAFFIC_LIB_VERSION = 504
-MEASURED_TRAFFIC_BYTES = {"llama3_8b": 624168265, "prefill_heavy": 612655156, "decode_heavy": 4868695611,
-                          "llama_70b_fp8": 4032754278, "paper_iteration_16k": 273880466}
+TRAFFIC_LIB_VERSION = 505
+MEASURED_TRAFFIC_BYTES = {"llama3_8b": 624381617, "prefill_heavy": 609010131, "decode_heavy": 4877200557,
+                          "llama_70b_fp8": 4021937151, "paper_iteration_16k": 303146550}
 
 
 def make_batch(name, trial=0):
