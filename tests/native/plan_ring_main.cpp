@@ -1,6 +1,7 @@
 // Host-only driver for the ring of plan buffers (plan_ring.h): runs the case named by the
 // argument and exits with 0 if the ring did what it has to.  "The device" is this program: a
 // call reports by storing its number in its slot.
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -47,12 +48,12 @@ static int order() {
 static int lock_is_free() {
   for (int i = 0; i < kSlots; ++i) enqueue(ring.take(), &stream_a);
   Slot* got = nullptr;
-  bool asked = false;
+  std::atomic<bool> asked{false};
   std::thread waiter([&] {
     std::unique_lock<std::timed_mutex> lock(mu);
     got = wait_for_slot(ring, lock, &stream_b, milliseconds(5), [&] { asked = true; return StreamIs::kBusy; });
   });
-  for (int n = 0; n < 20; ++n) {
+  for (int n = 0; n < 20 || (!asked && n < 4000); ++n) {
     std::this_thread::sleep_for(milliseconds(2));
     CHECK(mu.try_lock_for(milliseconds(500)));
     mu.unlock();
