@@ -18,12 +18,16 @@
 // Items that cover a span only leave (O, m, l) partial results; the wave whose result of a
 // row group arrives last combines them (arrive_last below): there is no merge launch.
 //
-// Both compute S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, so a
-// lane owns one query row (column of S^T): its softmax statistics are lane-local
-// except for one exchange with lane^32.  The row order of the K operand is permuted
-// (perm32) so that the accumulators a lane holds after S^T are, in order, exactly
-// the 8-key chunks the P^T operand needs; the same permutation on the V^T operand
-// rows makes each lane own 8 consecutive output dims.
+// Both compute S^T = K Q^T and O^T = V^T P^T, so that a query row is a column of S^T and
+// belongs to the lanes of one column.  Wide items use v_mfma_f32_16x16x32_bf16 (a lane shares
+// two rows with lane^16, lane^32 and lane^48), narrow items v_mfma_f32_32x32x16_bf16 (a lane
+// shares one row with lane^32).  The row order of the K operand is permuted so that the
+// accumulators a lane holds after S^T are, in order, exactly the 8-key chunks the P^T operand
+// needs: P never leaves registers.
+// Why 16x16x32 for the wide items: they are bound by the clock that the power limit leaves, and
+// on random operands the chip sustains 2100 TFLOP/s of 16x16x32 (A held for two products, as
+// here) against 1890 of 32x32x16; it takes 10.5 of 16 issue cycles where the larger shape takes
+// 16 of 32, so it only pays with the softmax spread between the products (fast_step).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -60,6 +64,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLazyLog2 = 8.0f;  // slack of the running reference of the online softmax, in bits
+constexpr float kBiasLog2 = 7.0f;  // wide tiles: a row's largest score has the numerator 2^-kBiasLog2 when its reference is fresh
 constexpr float kNeg = -1.0e30f;  // initial running maximum: finite, so that differences of maxima stay finite
 
 struct AttnParams {
@@ -89,7 +94,7 @@ struct AttnParams {
   int q_len[kQueues];
 };
 
-// S^T row r of a 32-row MFMA tile holds key perm32(r) of the 32-key sub-tile
+// Narrow items: S^T row r of a 32-row MFMA tile holds key perm32(r) of the 32-key sub-tile
 // (bits 2 and 3 swapped), see the file comment.
 __device__ __forceinline__ int perm32(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
 
@@ -101,6 +106,17 @@ __device__ __forceinline__ float pair_max(float x) {
 __device__ __forceinline__ float pair_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Combine a value with those held by lane^16, lane^32 and lane^48 (the lanes of one row of a
+// wide tile's wave).
+__device__ __forceinline__ float quad_max(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -195,9 +211,49 @@ __device__ __forceinline__ void softmax_tile(f32x16& s, bool need_mask, int sub_
   softmax_max_part<NDB>(s, need_mask, sub_base, half, limit, c, m, l, o);
   l += softmax_exp_part(s, c, m, p);
 }
-// A lane's 16 numerators are each at most 2^kLazyLog2 when its reference is fresh enough.
-constexpr float kTileSumLimit = 16.0f * 256.0f;
-static_assert(kLazyLog2 == 8.0f, "kTileSumLimit = 16 * 2^kLazyLog2");
+
+// A wave of a wide tile, whose S^T sub-tile of 32 keys x 32 rows is four 16x16
+// accumulators: s[kt][qt] register i = row 16 qt + lane % 16, key sub_base + 8 g + 4 kt + i with
+// g = lane / 16.  A lane's eight keys of a row are consecutive, as the P^T operand needs them.
+// o[dt][qt] register i = dim 16 dt + 4 g + i of row 16 qt + lane % 16.
+// The reference mc of a row (log2 units) is chosen kBiasLog2 bits above its largest score, so a
+// score that outgrows the reference's by kLazyLog2 bits has a numerator of 2 and more: one bit of
+// the packed numerators tells, and until then O and l need no rescaling.
+//
+// Largest of a lane's eight scores of a row.
+__device__ __forceinline__ float wide_lane_max(const f32x4 (&s)[2][2], int qt) {
+  float mx = s[0][qt][0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) mx = fmaxf(mx, s[i >> 2][qt][i & 3]);
+  return mx;
+}
+// Some row's scores outgrew its reference: every row takes its true maximum (and kBias bits),
+// O and l are rescaled.
+template <int NDT>
+__device__ __forceinline__ void wide_rescale(const f32x4 (&s)[2][2], float c, float (&mc)[2], f32x4 (&l)[2], f32x4 (&o)[NDT][2]) {
+#pragma unroll
+  for (int qt = 0; qt < 2; ++qt) {
+    const float mc_new = fmaxf(mc[qt], __builtin_fmaf(quad_max(wide_lane_max(s, qt)), c, kBiasLog2));
+    const float alpha = __builtin_amdgcn_exp2f(mc[qt] - mc_new);
+    l[qt] *= alpha;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt) o[dt][qt] *= alpha;
+    mc[qt] = mc_new;
+  }
+}
+// The numerators of scores 2 x and 2 x + 1 (keys) of the lane's row qt, packed.
+__device__ __forceinline__ unsigned wide_exp_pair(const f32x4 (&s)[2][2], int qt, int x, float c, float mc) {
+  return pack_bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(s[x >> 1][qt][2 * (x & 1)], c, -mc)),
+                   __builtin_amdgcn_exp2f(__builtin_fmaf(s[x >> 1][qt][2 * (x & 1) + 1], c, -mc)));
+}
+// The compiler shall not move what follows a rare branch into both of its arms: it would give
+// O a second set of registers in one of them.
+template <int NDT>
+__device__ __forceinline__ void wide_join(float (&mc)[2], u32x4 (&p)[2], f32x4 (&l)[2], f32x4 (&o)[NDT][2]) {
+  asm volatile("" : "+v"(mc[0]), "+v"(mc[1]), "+v"(p[0]), "+v"(p[1]), "+v"(l[0]), "+v"(l[1]));
+#pragma unroll
+  for (int x = 0; x < 2 * NDT; ++x) asm volatile("" : "+v"(o[x >> 1][x & 1]));
+}
 
 // Partial results of key spans.  A slot holds 32 rows: O (32 x D fp32; a wide tile's wave
 // writes it in the order of its registers, a narrow item row by row), then (m in log2 units,
@@ -252,50 +308,65 @@ __device__ __forceinline__ float merge_max(const float* ml, size_t step, int n_s
 // and, as the last wave of the row group to arrive, combine the spans in order:
 // O = sum_s O_s 2^(m_s - M), l = sum_s l_s 2^(m_s - M), M = max_s m_s.  Returns whether o
 // and lt now hold the finished rows.
-template <int NDB, int D>
+template <int NDT, int D>
 __device__ __forceinline__ bool merge_wide_rows(const AttnParams& p, const WorkItem& it, int wave, int lane,
-                                                f32x16 (&o)[NDB], float m_log2, float& lt) {
+                                                f32x4 (&o)[NDT][2], const float (&m_log2)[2], float (&lt)[2]) {
   constexpr size_t kSlot = (size_t)kNarrowRows * (D + 2);
-  const int half = lane >> 5, c32 = lane & 31;
+  const int c16 = lane & 15;
   float* ps = p.partials + (size_t)(it.partial + wave) * kSlot;
 #pragma unroll
-  for (int db = 0; db < NDB; ++db)
+  for (int k = 0; k < NDT * 4; ++k) {
+    const f32x4& x = o[k >> 2][(k >> 1) & 1];
+    put_pair(ps + (k * 64 + lane) * 2, x[2 * (k & 1)], x[2 * (k & 1) + 1]);
+  }
+  if (lane < 16) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) put_pair(ps + ((db * 8 + i) * 64 + lane) * 2, o[db][2 * i], o[db][2 * i + 1]);
-  if (half == 0) put_pair(ps + kNarrowRows * D + 2 * c32, m_log2, lt);
+    for (int qt = 0; qt < 2; ++qt) put_pair(ps + kNarrowRows * D + 2 * (16 * qt + c16), m_log2[qt], lt[qt]);
+  }
   const int n_split = merge_splits(it);
   if (!arrive_last(merge_counter(p, it, wave), n_split, lane)) return false;
   const float* base = p.partials + (size_t)(it.first_partial + wave) * kSlot;
   const size_t step = kSlot * kWaves;
-  const float* ml = base + kNarrowRows * D + 2 * c32;
-  const float mt = merge_max(ml, step, n_split);
-  lt = 0.f;
+  const float* ml = base + kNarrowRows * D + 2 * c16;
+  const float mt[2] = {merge_max(ml, step, n_split), merge_max(ml + 32, step, n_split)};
+  lt[0] = lt[1] = 0.f;
 #pragma unroll
-  for (int db = 0; db < NDB; ++db)
+  for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+    for (int i = 0; i < 4; ++i) o[dt][0][i] = o[dt][1][i] = 0.f;
   for (int s = 0; s < n_split; ++s) {
     const float* sp = base + s * step + 2 * lane;
-    f32x2 v[NDB * 8];
-    const f32x2 st = get_pair(ml + s * step);
+    f32x2 v[NDT * 4];
+    const f32x2 st[2] = {get_pair(ml + s * step), get_pair(ml + 32 + s * step)};
 #pragma unroll
-    for (int k = 0; k < NDB * 8; ++k) v[k] = get_pair(sp + k * 128);
-    const float w = __builtin_amdgcn_exp2f(st[0] - mt);
-    lt += st[1] * w;
+    for (int k = 0; k < NDT * 4; ++k) v[k] = get_pair(sp + k * 128);
+    float w[2];
 #pragma unroll
-    for (int k = 0; k < NDB * 8; ++k) {
-      o[k / 8][2 * (k & 7)] += v[k][0] * w;
-      o[k / 8][2 * (k & 7) + 1] += v[k][1] * w;
+    for (int qt = 0; qt < 2; ++qt) {
+      w[qt] = __builtin_amdgcn_exp2f(st[qt][0] - mt[qt]);
+      lt[qt] += st[qt][1] * w[qt];
+    }
+#pragma unroll
+    for (int k = 0; k < NDT * 4; ++k) {
+      const int qt = (k >> 1) & 1;
+      f32x4& x = o[k >> 2][qt];
+      x[2 * (k & 1)] += v[k][0] * w[qt];
+      x[2 * (k & 1) + 1] += v[k][1] * w[qt];
     }
   }
   return true;
 }
 
 // ------------------------------------------------------------------ work queues
+// K blocks of a wide tile's stage are this many bytes further apart than their size: a row of
+// the K operand's 16 comes from one of two blocks, four slots (64 bytes) at a time, and both
+// blocks' slots would otherwise lie in the same half of the banks.
+constexpr int kKPad = 64;
 template <int D, bool FP8>
 constexpr int attn_lds_bytes() {
   constexpr int tile = 2 * 4 * 16 * D * 2;          // a K and V tile of 64 keys, bf16
-  constexpr int wide_lds = FP8 ? 3 * tile + 3 * tile / 2 : 4 * tile;  // stages (fp8: three, and three tiles of codes)
+  constexpr int stage = tile + 4 * kKPad;
+  constexpr int wide_lds = FP8 ? 3 * stage + 3 * tile / 2 : 4 * stage;  // stages (fp8: three, and three tiles of codes)
   constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * kNarrowRows * 4;
   constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
   static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
@@ -405,8 +476,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // Copy 1 KiB, global -> LDS, by one wave (lane i moves bytes [16 i, 16 i + 16)): g and dst
 // are the wave's bases (no lane term).  Four 4-byte-per-lane instructions measured the same.
-__device__ __forceinline__ void dma_1k(const unsigned char* g, lds_byte* dst, int lane) {
-  __builtin_amdgcn_global_load_lds(g + lane * 16, dst, 16, 0, 0);
+// lane16 = 16 x lane is opaque here, so that the instruction takes the base from scalar and a
+// 32-bit offset from one vector register (the wide loops have none to spare).
+__device__ __forceinline__ void dma_1k(const unsigned char* g, lds_byte* dst, unsigned& lane16) {
+  asm volatile("" : "+v"(lane16));
+  typedef const __attribute__((address_space(1))) unsigned char global_byte;
+  __builtin_amdgcn_global_load_lds((global_byte*)g + lane16, dst, 16, 0, 0);
 }
 
 // LDS reads of data that arrived by global_load_lds are written as asm, so that the
@@ -496,10 +571,11 @@ struct RowTile {
   static constexpr int RPI = 64 / CPR;     // rows per instruction
   static constexpr int NINS = 32 / RPI;    // instructions for 32 rows
   static __device__ __forceinline__ int swz(int row) { return (D == 128 ? row : row >> 1) & (CPR - 1); }
-  // LDS offset of chunk `half` of a row; that of chunk 2 s + half is this value ^ 32 s (the
-  // wave's rows start at a multiple of a row's size).
-  static __device__ __forceinline__ unsigned row_chunk(int row, int half) {
-    return (unsigned)(row * (2 * D) + ((half ^ swz(row)) * 16));
+  // LDS offset of chunk ch < 4 of a row; that of chunk 2 n + ch (4 n + ch) is this value ^ 32 n
+  // (^ 64 n) where the bits do not overlap (the wave's rows start at a multiple of a row's size).
+  // Row r + 16 is 16 rows further with the same swizzle.
+  static __device__ __forceinline__ unsigned row_chunk(int row, int ch) {
+    return (unsigned)(row * (2 * D) + ((ch ^ swz(row)) * 16));
   }
   // Byte offset of the chunk that lane `lane` moves in instruction n, relative to the tile's
   // first token: row (clamped to the tile) -> token and head.  The planner makes wide tiles only
@@ -515,6 +591,10 @@ struct RowTile {
 template <int OFF>
 __device__ __forceinline__ void lds_write_b128(unsigned addr, u32x4 v) {
   asm volatile("ds_write_b128 %0, %1 offset:%2" ::"v"(addr), "v"(v), "i"(OFF) : "memory");
+}
+template <int OFF>
+__device__ __forceinline__ void lds_write_b64(unsigned addr, u32x2 v) {
+  asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "i"(OFF) : "memory");
 }
 
 // Schedule per wave (n = number of 32-key sub-tiles, S(u) = K(u) Q^T, P(u) = softmax
@@ -550,23 +630,26 @@ enum { kPool, kCopy, kCodes };
 template <int D, int MODE>
 __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsigned char* smem) {
   constexpr bool FP8 = MODE != kPool, CODES = MODE == kCodes;
-  constexpr int NSTEP = D / 16, NDB = D / 32;
+  constexpr int NSTEP = D / 16, NDT = D / 16;  // K (and V) operands of a 32-key sub-tile
   constexpr int BLK_LDS = 16 * D * 2;     // bytes of one (block, head)
-  constexpr int KT_BYTES = 4 * BLK_LDS;   // K (or V) tile: 64 keys
-  constexpr int STAGE = 2 * KT_BYTES;
+  constexpr int KBLK = BLK_LDS + kKPad;   // K blocks of a stage: see kKPad
+  constexpr int KT_BYTES = 4 * KBLK;      // K tile: 64 keys; V behind it
+  constexpr int STAGE = KT_BYTES + 4 * BLK_LDS;
   constexpr int kStages = CODES ? 3 : 4, kAhead = 3;
   // CODES: a ring of kRaw tiles of codes behind the stages; a wave converts what it fetched
-  constexpr int kRaw = 3, RAW = kStages * STAGE, RAW_TILE = STAGE / 2;
+  constexpr int kRaw = 3, RAW = kStages * STAGE, RAW_TILE = 4 * BLK_LDS;
   constexpr int kLead = 6;                // tiles of an item that are left when the next item is asked for
   constexpr int UPW = D / 64;             // 1-KiB units of K (and of V) each wave fetches per tile
   constexpr int UPB = BLK_LDS / 1024;     // units per block
   constexpr int NI = CODES ? D / 64 : 2 * UPW;  // DMA instructions per wave per tile
   using Rows = RowTile<D>;
-  static_assert(Rows::NINS == NSTEP && 2 * STAGE == kWaves * 32 * D * 2, "Q of a tile fills two stages");
+  static_assert(Rows::NINS == NSTEP && 2 * STAGE >= kWaves * 32 * D * 2, "Q of a tile fits in two stages");
+  static_assert(STAGE % (2 * D) == 0, "swizzled rows start at a multiple of their size");
 
   int tid = threadIdx.x;
   asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
   int lane = tid & 63;
+  unsigned lane16 = 16u * (unsigned)lane;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int row_base = wave * 32;
   const unsigned char* const k_src = MODE == kCopy ? p.stage_k : p.k_pool;
@@ -592,14 +675,14 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     const long long b = __builtin_amdgcn_readlane(bt, j & 63);
     if constexpr (CODES) {
       dma_1k((wave < 4 ? k_src : v_src) + (b * p.n_kv_heads + kv_head) * (BLK_LDS / 2) + q * 1024,
-             lds0 + RAW + (j % kRaw) * RAW_TILE + (wave * NI + q) * 1024, lane);
+             lds0 + RAW + (j % kRaw) * RAW_TILE + (wave * NI + q) * 1024, lane16);
       return;
     }
     const long long goff = (b * p.n_kv_heads + kv_head) * head_stride + part_w * 1024;
-    lds_byte* dst = lds0 + (j % kStages) * STAGE + blk_w * BLK_LDS + part_w * 1024;
+    lds_byte* dst = lds0 + (j % kStages) * STAGE + part_w * 1024;
     const int x = q >> 1;
-    if (q & 1) dma_1k(v_src + goff + x * 1024, dst + KT_BYTES + x * 1024, lane);
-    else dma_1k(k_src + goff + x * 1024, dst + x * 1024, lane);
+    if (q & 1) dma_1k(v_src + goff + x * 1024, dst + KT_BYTES + blk_w * BLK_LDS + x * 1024, lane16);
+    else dma_1k(k_src + goff + x * 1024, dst + blk_w * KBLK + x * 1024, lane16);
   };
   auto issue_tile = [&](int j, int bt, int kv_head) {
 #pragma unroll
@@ -614,7 +697,7 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
                  : "=&v"(r)
                  : "v"(lds_base + RAW + (j % kRaw) * RAW_TILE + (wave * NI + q) * 1024 + lane * 16)
                  : "memory");
-    const unsigned a = lds_base + (j % kStages) * STAGE + (wave >> 2) * KT_BYTES + blk_w * BLK_LDS + q * 2048 + lane * 32;
+    const unsigned a = lds_base + (j % kStages) * STAGE + (wave < 4 ? blk_w * KBLK : KT_BYTES + blk_w * BLK_LDS) + q * 2048 + lane * 32;
     lds_write_b128<0>(a, fp8x8_to_bf16x8(u32x2{r[0], r[1]}));
     lds_write_b128<16>(a, fp8x8_to_bf16x8(u32x2{r[2], r[3]}));
   };
@@ -672,7 +755,7 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
 
   for (;;) {
   asm volatile("" : "+v"(lane));  // lane terms are recomputed per item
-  const int half = lane >> 5, c32 = lane & 31, pr = perm32(c32);
+  const int g = lane >> 4, c16 = lane & 15;
   const WorkItem it = current();
   const int kv_head = it.kv_head;
   const int gi_n = it.n_heads;
@@ -688,15 +771,17 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
   const int wave_min_limit = __builtin_amdgcn_readfirstlane(pos0 + token_of(min(row_base, rows_valid - 1)));
   const int wave_max_limit =
       wave_has_rows ? __builtin_amdgcn_readfirstlane(pos0 + token_of(min(row_base + 31, rows_valid - 1))) : -1;
-  const int limit = pos0 + token_of(min(row_base + c32, rows_valid - 1));
+  const int limit[2] = {pos0 + token_of(min(row_base + c16, rows_valid - 1)),
+                        pos0 + token_of(min(row_base + 16 + c16, rows_valid - 1))};
   const int n_sub = (it.kv_end - it.kv_begin + 31) >> 5;
   const int n_tiles = tiles_of(it);
-  f32x16 o[NDB];
-  float m = kNeg, l = 0.f;
+  f32x4 o[NDT][2];
+  float mc[2] = {kNeg, kNeg};  // running reference of rows lane % 16 and lane % 16 + 16, log2 units
+  f32x4 l[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};  // row sums, the same value four times
 #pragma unroll
-  for (int db = 0; db < NDB; ++db)
+  for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) o[db][i] = 0.f;
+    for (int i = 0; i < 4; ++i) o[dt][0][i] = o[dt][1][i] = 0.f;
 
   // ---- the next item, step by step: wave 0 takes a ticket, fetches the record and posts it;
   // then every wave requests its table entries
@@ -718,31 +803,37 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     known = true;
   };
 
-  // ---- LDS operand reads (byte addresses)
-  const unsigned k_lane = lds_base + (pr >> 4) * BLK_LDS + (half * 16 + (pr & 15)) * 16;
-  const unsigned v_lane = lds_base + KT_BYTES + (half * D + pr) * 16;
+  // ---- LDS operand reads (byte addresses).  K operand (s, kt), read as number 2 s + kt: dims
+  // 32 s + 8 g .. of key 8 (c16 / 4) + 4 kt + c16 % 4.  V operand dt: dim 16 dt + c16 of keys 8 g ..
+  const unsigned k_lane = lds_base + (c16 >> 3) * KBLK + (g * 16 + (c16 & 4) * 2 + (c16 & 3)) * 16;
+  const unsigned v_lane = lds_base + KT_BYTES + (g * D + c16) * 16;
   u32x4 ka[NSTEP], va[NSTEP];
   auto read_k = [&](int u) {
-    const unsigned a = k_lane + ((u >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
-    if constexpr (NSTEP == 8) lds_read8<0, 512, 1024, 1536, 2048, 2560, 3072, 3584>(ka, a);
-    else lds_read4<0, 512, 1024, 1536>(ka[0], ka[1], ka[2], ka[3], a);
+    const unsigned a = k_lane + ((u >> 1) % kStages) * STAGE + (u & 1) * 2 * KBLK;
+    if constexpr (NSTEP == 8) lds_read8<0, 64, 1024, 1088, 2048, 2112, 3072, 3136>(ka, a);
+    else lds_read4<0, 64, 1024, 1088>(ka[0], ka[1], ka[2], ka[3], a);
   };
   auto read_v = [&](int u) {
     const unsigned a = v_lane + ((u >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
-    if constexpr (NSTEP == 8)
-      lds_read8<0, 512, 1024, 1536, BLK_LDS, BLK_LDS + 512, BLK_LDS + 1024, BLK_LDS + 1536>(va, a);
-    else lds_read4<0, 512, BLK_LDS, BLK_LDS + 512>(va[0], va[1], va[2], va[3], a);
+    if constexpr (NSTEP == 8) lds_read8<0, 256, 512, 768, 1024, 1280, 1536, 1792>(va, a);
+    else lds_read4<0, 256, 512, 768>(va[0], va[1], va[2], va[3], a);
   };
   auto active = [&](int u) { return 32 * u <= wave_max_limit; };
 
-  u32x4 pp[2];
-  bf16x8 qreg[NSTEP];
-  auto qk = [&](f32x16& s) {
+  u32x4 pp[2], pq[2];  // P^T operands [row tile] of even and odd sub-tiles
+  bf16x8 qreg[2][NSTEP / 2];
+  auto mfma = [](u32x4 a, bf16x8 b, f32x4 acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(a), b, acc, 0, 0, 0);
+  };
+  u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+  asm volatile("" : "+v"(ones));
+  auto qk = [&](f32x4 (&s)[2][2]) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    for (int x = 0; x < 4; ++x) s[x >> 1][x & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st)
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[st]), qreg[st], s, 0, 0, 0);
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) s[st & 1][qt] = mfma(ka[st], qreg[qt][st >> 1], s[st & 1][qt]);
   };
 
   // ---- prologue: Q and the first tiles are in flight; tile 0 landed everywhere and Q in
@@ -753,15 +844,15 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
   else wait_vmcnt<0>();
   if constexpr (CODES) convert_tile(0);
   {
-    const unsigned a = lds_base + own_off + Rows::row_chunk(c32, half);
+    const unsigned a = lds_base + own_off + Rows::row_chunk(c16, g);
     u32x4 q[NSTEP];
     static_for<0, NSTEP>([&](auto I) {
-      constexpr int st = decltype(I)::value;
-      lds_issue1<0>(q[st], a ^ (32 * st));
+      constexpr int x = decltype(I)::value;
+      lds_issue1<(x & 1) * 16 * 2 * D>(q[x], a ^ (64 * (x >> 1)));
     });
     lds_land<0>(q);
 #pragma unroll
-    for (int st = 0; st < NSTEP; ++st) qreg[st] = as_bf16x8(q[st]);
+    for (int x = 0; x < NSTEP; ++x) qreg[x & 1][x >> 1] = as_bf16x8(q[x]);
   }
   __builtin_amdgcn_s_barrier();
   if (wave == 0)
@@ -779,10 +870,13 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     }
     if (n_tiles > 4) issue_tile(4, bt_reg, kv_head);
   }
-  f32x16 s_even, s_odd;  // S(u) of even / odd sub-tiles
+  f32x4 s_even[2][2], s_odd[2][2];  // S(u) of even / odd sub-tiles, [key tile][row tile]
   // written only where this wave sees a sub-tile: without a definition here the registers
   // would count as live from the item before
-  asm volatile("" : "=v"(s_even), "=v"(s_odd), "=v"(pp[0]), "=v"(pp[1]));
+  asm volatile("" : "=v"(pp[1]), "=v"(pq[0]), "=v"(pq[1]));
+  pp[0] = u32x4{0x7f807f80u, 0x7f807f80u, 0x7f807f80u, 0x7f807f80u};  // the first sub-tile's reference is not there yet
+#pragma unroll
+  for (int x = 0; x < 4; ++x) asm volatile("" : "=v"(s_even[x >> 1][x & 1]), "=v"(s_odd[x >> 1][x & 1]));
   read_k(0);
   if (active(0)) qk(s_even);
   if (n_sub > 1) read_k(1);
@@ -824,11 +918,24 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     }
   };
   // one sub-tile: s_cur = S(u) is consumed, s_nxt receives S(u+1)
-  auto step = [&](int u, f32x16& s_cur, f32x16& s_nxt, bool opens_tile) {
+  auto step = [&](int u, f32x4 (&s_cur)[2][2], f32x4 (&s_nxt)[2][2], bool opens_tile) {
     const int sub_base = 32 * u;
     const bool act = active(u);
     if (u + 1 < n_sub && active(u + 1)) qk(s_nxt);    // S(u+1): MFMA work that overlaps the softmax below
-    if (act) softmax_tile<NDB>(s_cur, sub_base + 31 > wave_min_limit, sub_base, half, limit, c, m, l, o, pp);
+    if (act) {
+      if (sub_base + 31 > wave_min_limit) {  // causal mask
+#pragma unroll
+        for (int qt = 0; qt < 2; ++qt)
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (sub_base + 8 * g + i > limit[qt]) s_cur[i >> 2][qt][i & 3] = -__builtin_inff();  // weight exactly 0
+      }
+      const float over = fmaxf(__builtin_fmaf(wide_lane_max(s_cur, 0), c, -mc[0]), __builtin_fmaf(wide_lane_max(s_cur, 1), c, -mc[1]));
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(over > kLazyLog2 - kBiasLog2) != 0, 0)) wide_rescale<NDT>(s_cur, c, mc, l, o);
+      wide_join<NDT>(mc, pp, l, o);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) pp[x >> 2][x & 3] = wide_exp_pair(s_cur, x >> 2, x & 3, c, mc[x >> 2]);
+    }
     read_v(u);
     if (u + 2 < n_sub) {
       if (opens_tile) {
@@ -839,69 +946,111 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     if (act) {
       if (sub_base + 32 > kv_len) {  // slots past the sequence's length hold anything
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int db = 0; db < NDB; ++db)
-            va[t * NDB + db] = zero_tail(va[t * NDB + db], sub_base + 16 * t + 8 * half, kv_len);
+        for (int dt = 0; dt < NDT; ++dt) va[dt] = zero_tail(va[dt], sub_base + 8 * g, kv_len);
       }
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+      for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
-          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[t * NDB + db]), as_bf16x8(pp[t]), o[db], 0, 0, 0);
+        for (int qt = 0; qt < 2; ++qt) o[dt][qt] = mfma(va[dt], as_bf16x8(pp[qt]), o[dt][qt]);
+#pragma unroll
+      for (int qt = 0; qt < 2; ++qt) l[qt] = mfma(ones, as_bf16x8(pp[qt]), l[qt]);
     }
   };
   // Steady state: sub-tiles that this wave sees whole (no causal mask, no tail) and that
-  // are followed by two more.  No conditionals besides the once-per-tile hand-over.  The
-  // instruction order is fixed by hand (a scheduling barrier closes every MFMA slot; the
-  // compiler's own interleaving hints left the S(u+1) chain in one clump): each of the
-  // NSTEP slots of the first block holds one LDS read of V(u), the MFMA of the S(u+1)
-  // chain and the numerators of S(u) that go with it; each slot of the second block one
-  // LDS read of K(u+2) and one O product.  An operand is thus requested NSTEP MFMA slots
-  // before its use, and LDS sees single reads, not bursts of eight per wave.
+  // are followed by two more.  No conditionals besides the once-per-tile hand-over and the rescaling.
+  // The instruction order is fixed by hand (scheduling barriers), because issue slots bound it: per
+  // wave and step 34 MFMAs take 10.5 cycles each beside VALU work, a numerator 8.6 (exp) + 6.3 (FMA,
+  // half a pack), an MFMA gap hides about two plain VALU instructions.  So
+  // the numerators are spread over both blocks: those of row tile 1 of S(u) go between the MFMAs
+  // of S(u+1), those of row tile 0 of S(u+1) between the O products of u; the row sums are MFMAs
+  // too (A = ones, 2 x 16 cycles a step, where v_dot2c_f32_bf16 costs 16 + 4 cycles each time that it
+  // follows an MFMA, 8 times a step); and the numerators themselves tell whether a reference is stale.
+  // Each slot issues one LDS read, NSTEP - 1 slots before its use, and lands the next operand between its
+  // two MFMAs.  The wave runs at priority 1 in the first block: the two waves of a SIMD then tend
+  // to be in different blocks.
+  // Measured (main kernel, us; large chunks behind prefixes / one chunk behind 16 k / fp8 chunks behind 28 k):
+  // 32x32x16, numerators in the first block 782 / 148 / 6596; 16x16x32 in the same order 794 / 159 / 6586;
+  // this order 719 / 138.4 / 5993; with the priority 1-2.5 % less again.
   // fetch: the tile after next exists and is fetched here; otherwise open_tile decides.
-  auto fast_step = [&](int u, f32x16& s_cur, f32x16& s_nxt, bool opens_tile, bool fetch) {
+  auto fast_step = [&](int u, f32x4 (&s_cur)[2][2], f32x4 (&s_nxt)[2][2], auto even, bool fetch) {
+    constexpr bool opens_tile = decltype(even)::value;  // u is even
     const int jn = (u >> 1) + (CODES ? kAhead + 2 : kAhead);  // the tile to fetch
-    const unsigned av = v_lane + ((u >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
-    const unsigned ak = k_lane + (((u + 2) >> 1) % kStages) * STAGE + (u & 1) * 2 * BLK_LDS;
-    // On entry the NSTEP reads of K(u+1) are in flight or landed and nothing else is.
-    // Every MFMA slot issues one read and lands the operand it uses, which was issued
-    // NSTEP reads earlier: after the slot's own issue NSTEP + 1 reads can be outstanding,
-    // and waiting for all but NSTEP of them lands exactly the oldest.
-    // Optimistic numerators: against the reference as it is; the row maxima are looked at
-    // only if some lane's sum shows that a score outgrew the reference (or it is the first
-    // sub-tile, whose reference is kNeg and whose numerators overflow).
-    float tile_sum = 0.f;
+    constexpr int VO = opens_tile ? 0 : 2 * BLK_LDS, KO = opens_tile ? 0 : 2 * KBLK;
+    const unsigned av = v_lane + ((u >> 1) % kStages) * STAGE;
+    const unsigned ak = k_lane + (((u + 2) >> 1) % kStages) * STAGE;
+    // On entry the first K(u+1) operand has landed, the NSTEP - 1 others are in flight or landed
+    // and nothing else is.  After a slot's own issue NSTEP reads can be outstanding, and waiting
+    // for all but NSTEP - 1 of them lands exactly the oldest, the next slot's operand.
+    // p0: P(u), of which the step before made row tile 0 (the first step of an item finds
+    // infinities there, which send it to the rescaling); pn: P(u+1).
+    u32x4 (&p0)[2] = opens_tile ? pp : pq, (&pn)[2] = opens_tile ? pq : pp;
+    // numerator pairs of row tile qt of s between the MFMAs: what goes into gap `gap` of a block
+    float f0, f1, e0, e1;
+    auto piece = [&](auto GAP, auto QT, auto PER, const f32x4 (&s)[2][2], u32x4 (&p)[2]) {
+      constexpr int gap = decltype(GAP)::value, qt = decltype(QT)::value, per = decltype(PER)::value, x = gap / per, ph = gap % per;
+      auto score = [&](int e) { return __builtin_fmaf(s[(x & 3) >> 1][qt][2 * (x & 1) + e], c, -mc[qt]); };
+      if constexpr (per == 2) {
+        if constexpr (ph == 0 && x < 4) {
+          f0 = score(0);
+          f1 = score(1);
+          e0 = __builtin_amdgcn_exp2f(f0);
+        }
+        if constexpr (ph == 1 && x < 4) p[qt][x] = pack_bf16(e0, __builtin_amdgcn_exp2f(f1));
+      } else if constexpr (per == 3) {
+        if constexpr (ph == 0 && x > 0 && x < 5) p[qt][x - 1] = pack_bf16(e0, e1);
+        if constexpr (x < 4) {
+          if constexpr (ph == 0) {
+            f0 = score(0);
+            f1 = score(1);
+          }
+          if constexpr (ph == 1) e0 = __builtin_amdgcn_exp2f(f0);
+          if constexpr (ph == 2) e1 = __builtin_amdgcn_exp2f(f1);
+        }
+      } else {
+        if constexpr (ph == 0) f0 = score(0);
+        if constexpr (ph == 1) {
+          e0 = __builtin_amdgcn_exp2f(f0);
+          f1 = score(1);
+        }
+        if constexpr (ph == 2) e1 = __builtin_amdgcn_exp2f(f1);
+        if constexpr (ph == 3) p[qt][x] = pack_bf16(e0, e1);
+      }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    unsigned bits;
     {
-      const float mc = m * c;
-      const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3f803f80u);
-      constexpr int PPM = 8 / NSTEP;  // numerator pairs per MFMA
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s_nxt[i] = 0.f;
+      for (int x = 0; x < 4; ++x) s_nxt[x >> 1][x & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      __builtin_amdgcn_s_setprio(1);
       __builtin_amdgcn_sched_barrier(0);
       static_for<0, NSTEP>([&](auto I) {
         constexpr int st = decltype(I)::value;
-        lds_issue1<(st / NDB) * BLK_LDS + (st % NDB) * 512>(va[st], av);
-        lds_land1<NSTEP>(ka[st]);
-        s_nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[st]), qreg[st], s_nxt, 0, 0, 0);
-#pragma unroll
-        for (int x = 0; x < PPM; ++x) {
-          const int pr = st * PPM + x;
-          const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[2 * pr], c, -mc));
-          const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[2 * pr + 1], c, -mc));
-          const f32x2 e = {e0, e1};
-          const bf16x2_t pk = __builtin_convertvector(e, bf16x2_t);
-          pp[pr >> 2][pr & 3] = __builtin_bit_cast(unsigned int, pk);
-          tile_sum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, tile_sum, false);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        lds_issue1<VO + st * 256>(va[st], av);
+        static_for<0, 2>([&](auto J) {
+          constexpr int qt = decltype(J)::value, gap = 2 * st + qt;
+          s_nxt[st & 1][qt] = mfma(ka[st], qreg[qt][st >> 1], s_nxt[st & 1][qt]);
+          __builtin_amdgcn_sched_barrier(0);
+          piece(std::integral_constant<int, gap>{}, I1{}, std::integral_constant<int, NSTEP == 8 ? 3 : 2>{}, s_cur, p0);
+          if constexpr (gap == 1) bits = p0[0][0] | p0[0][1] | p0[0][2];
+          if constexpr (gap == 2 * NSTEP - 6) bits = bits | p0[0][3] | p0[1][0];
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (qt == 0) {
+            if constexpr (st + 1 < NSTEP) lds_land1<NSTEP - 1>(ka[st + 1]);
+            else lds_land1<NSTEP - 1>(va[0]);
+          }
+        });
       });
+      __builtin_amdgcn_s_setprio(0);
+      bits = bits | p0[1][1] | p0[1][2];
     }
-    if (__builtin_amdgcn_ballot_w64(!(tile_sum <= kTileSumLimit)) != 0) {
-      softmax_max_part<NDB, true>(s_cur, false, 32 * u, half, limit, c, m, l, o);
-      tile_sum = softmax_exp_part(s_cur, c, m, pp);
+    // bit 14 of a numerator: it is 2 or more (or no number)
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(((bits | p0[1][3]) & 0x40004000u) != 0) != 0, 0)) {
+      wide_rescale<NDT>(s_cur, c, mc, l, o);
+#pragma unroll
+      for (int x = 0; x < 8; ++x) p0[x >> 2][x & 3] = wide_exp_pair(s_cur, x >> 2, x & 3, c, mc[x >> 2]);
     }
-    l += tile_sum;
+    wide_join<NDT>(mc, p0, l, o);
     if (!fetch) {
       if (opens_tile) open_tile((u >> 1) + 1);
     } else if (opens_tile) {
@@ -930,10 +1079,23 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     __builtin_amdgcn_sched_barrier(0);
     static_for<0, NSTEP>([&](auto I) {
       constexpr int i = decltype(I)::value;
-      lds_issue1<i * 512>(ka[i], ak);
-      lds_land1<NSTEP>(va[i]);
-      o[i % NDB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va[i]), as_bf16x8(pp[i / NDB]), o[i % NDB], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
+      lds_issue1<KO + (i >> 1) * 1024 + (i & 1) * 64>(ka[i], ak);
+      static_for<0, 2>([&](auto J) {
+        constexpr int qt = decltype(J)::value;
+        o[i][qt] = mfma(va[i], as_bf16x8(p0[qt]), o[i][qt]);
+        __builtin_amdgcn_sched_barrier(0);
+        piece(std::integral_constant<int, 2 * i + qt>{}, I0{}, std::integral_constant<int, NSTEP == 8 ? 4 : 2>{}, s_nxt, pn);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (qt == 0) {
+          if constexpr (i + 1 < NSTEP) lds_land1<NSTEP - 1>(va[i + 1]);
+          else lds_land1<NSTEP - 1>(ka[0]);
+        }
+      });
+      constexpr int first = NSTEP / 4, second = NSTEP / 2 + 1;
+      if constexpr (i == first || i == second) {
+        l[i == second] = mfma(ones, as_bf16x8(p0[i == second]), l[i == second]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     });
   };
   // sub-tile u is "whole" for this wave when u + 1 is too: 32 (u + 1) + 31 <= wave_min_limit
@@ -941,17 +1103,18 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
   n_fast = max(n_fast, 0) & ~1;
   const int n_fetch = min(n_fast, max(2 * (n_tiles - kLead), 0));
   int u = 0;
+  if (n_fast > 0) lds_land1<NSTEP - 1>(ka[0]);
   for (; u < n_fetch; u += 2) {
-    fast_step(u, s_even, s_odd, true, true);
-    fast_step(u + 1, s_odd, s_even, false, true);
+    fast_step(u, s_even, s_odd, std::true_type{}, true);
+    fast_step(u + 1, s_odd, s_even, std::false_type{}, true);
   }
   if (wave == 0 && feed.left >= 2 * (int)(gridDim.x / kQueues)) {
     early = true;
     head = request_item(p, feed, lane);
   }
   for (; u < n_fast; u += 2) {
-    fast_step(u, s_even, s_odd, true, false);
-    fast_step(u + 1, s_odd, s_even, false, false);
+    fast_step(u, s_even, s_odd, std::true_type{}, false);
+    fast_step(u + 1, s_odd, s_even, std::false_type{}, false);
   }
   lds_land<0>(ka);  // the steps below expect K(u+1) in registers
   for (; u < n_sub; u += 2) {
@@ -986,23 +1149,26 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
   asm volatile("" : "+v"(lane));
   const WorkItem fin = current();
   const int fin_rows = fin.n_tok * fin.n_heads;
-  float lt = pair_sum(l);
+  float lt[2] = {l[0][0], l[1][0]};
   const bool finished =
-      fin.partial < 0 || (row_base < fin_rows && merge_wide_rows<NDB, D>(p, fin, wave, lane, o, m * c, lt));
+      fin.partial < 0 || (row_base < fin_rows && merge_wide_rows<NDT, D>(p, fin, wave, lane, o, mc, lt));
   u32x4 w[NSTEP];
 #pragma unroll
   for (int n = 0; n < NSTEP; ++n) asm volatile("" : "=v"(w[n]));  // as for s_even
   if (finished) {
-    float mul = 1.0f / lt;
-    if constexpr (FP8) mul = p.v_scale[fin.kv_head] / lt;
-    const unsigned a = lds_base + own_off + Rows::row_chunk(lane & 31, lane >> 5);
-    static_for<0, NSTEP>([&](auto I) {
-      constexpr int ch = decltype(I)::value;  // dims 16 ch + 8 half + 0..7
-      u32x4 x;
-#pragma unroll
-      for (int y = 0; y < 4; ++y)
-        x[y] = pack_bf16(o[ch / 2][8 * (ch & 1) + 2 * y] * mul, o[ch / 2][8 * (ch & 1) + 2 * y + 1] * mul);
-      lds_write_b128<0>(a ^ (32 * ch), x);
+    const float vs = FP8 ? p.v_scale[fin.kv_head] : 1.0f;
+    const int lg = lane >> 4;
+    // dims 16 dt + 4 lg .. + 3 of rows lane % 16 and lane % 16 + 16: half a chunk each
+    const unsigned a = lds_base + own_off + Rows::row_chunk(lane & 15, lg >> 1) + (lg & 1) * 8;
+    const float mul[2] = {vs / lt[0], vs / lt[1]};
+    static_for<0, NDT>([&](auto I) {
+      constexpr int dt = decltype(I)::value;
+      static_for<0, 2>([&](auto J) {
+        constexpr int qt = decltype(J)::value;
+        const f32x4& x = o[dt][qt];
+        lds_write_b64<qt * 16 * 2 * D>(a ^ (32 * dt), u32x2{pack_bf16(x[0] * mul[qt], x[1] * mul[qt]),
+                                                            pack_bf16(x[2] * mul[qt], x[3] * mul[qt])});
+      });
       __builtin_amdgcn_sched_barrier(0);
     });
     lds_read_planes<NSTEP>(w, lds_base + own_off + lane * 16);
