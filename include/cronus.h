@@ -111,6 +111,24 @@ int cronus_kv_append(const cronus_kv_cache* cache, const void* k_src, const void
                      int32_t n_tokens, void* hip_stream);
 
 /*
+ * cronus_kv_append_pair - two sets of rows of the same sequences in one launch: what two
+ * calls of cronus_kv_append write (an iteration's transferred prefixes and its new rows).
+ * The two sets must address different slots.  A set of n_tokens = 0 is left out.
+ * Errors: as cronus_kv_append; nothing is launched when either set is refused.
+ */
+typedef struct cronus_kv_rows {
+  const void* k_src;        /* as the arguments of cronus_kv_append of these names */
+  const void* v_src;
+  const int32_t* cu_tokens;
+  const int32_t* start_pos;
+  int32_t n_tokens;
+} cronus_kv_rows;
+
+int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* first,
+                          const cronus_kv_rows* second, const int32_t* block_tables,
+                          int32_t max_blocks_per_seq, int32_t n_seqs, void* hip_stream);
+
+/*
  * cronus_attn_mixed - attention of one mixed iteration (section 4.4; section 2 for
  * decode as one token against the whole cache).  Sequence s contributes
  * chunk_lens[s] query rows (1 = a decode, 0 = skipped) at logical positions

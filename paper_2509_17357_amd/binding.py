@@ -23,7 +23,7 @@ CRONUS_ERR_HIP = 4
 CRONUS_KV_BF16 = 0
 CRONUS_KV_FP8_E4M3 = 1
 
-EXPORTS = ("cronus_kv_append", "cronus_kv_gather", "cronus_attn_mixed", "cronus_attn_mixed_static",
+EXPORTS = ("cronus_kv_append", "cronus_kv_append_pair", "cronus_kv_gather", "cronus_attn_mixed", "cronus_attn_mixed_static",
            "cronus_attn_mixed_workspace_bytes",
            "cronus_attn_mixed_plan_stats", "cronus_attn_mixed_plan_items", "cronus_balancer_split",
            "cronus_profile_events", "cronus_probe_mfma", "cronus_probe_mfma_sink_floats", "cronus_status_string",
@@ -43,6 +43,11 @@ class cronus_balancer_model(ctypes.Structure):
     _fields_ = [("k_p", ctypes.c_double), ("b_p", ctypes.c_double),
                 ("k_ctxp", ctypes.c_double), ("k_ctxd", ctypes.c_double), ("b_c", ctypes.c_double),
                 ("block_size", ctypes.c_int32), ("batch_tokens", ctypes.c_int32), ("n_candidates", ctypes.c_int32)]
+
+
+class cronus_kv_rows(ctypes.Structure):
+    _fields_ = [("k_src", ctypes.c_void_p), ("v_src", ctypes.c_void_p), ("cu_tokens", ctypes.c_void_p),
+                ("start_pos", ctypes.c_void_p), ("n_tokens", ctypes.c_int32)]
 
 
 class CronusError(RuntimeError):
@@ -66,6 +71,9 @@ def lib() -> ctypes.CDLL:
         cp = ctypes.POINTER(cronus_kv_cache)
         L.cronus_kv_append.argtypes = [cp, vp, vp, vp, vp, vp, i32, i32, i32, vp]
         L.cronus_kv_append.restype = ctypes.c_int
+        rp = ctypes.POINTER(cronus_kv_rows)
+        L.cronus_kv_append_pair.argtypes = [cp, rp, rp, vp, i32, i32, vp]
+        L.cronus_kv_append_pair.restype = ctypes.c_int
         L.cronus_kv_gather.argtypes = [cp, vp, vp, vp, vp, vp, i32, i32, i32, vp]
         L.cronus_kv_gather.restype = ctypes.c_int
         i64, f64p = ctypes.c_int64, ctypes.POINTER(ctypes.c_double)
@@ -180,6 +188,17 @@ def cronus_kv_append(cache: cronus_kv_cache, k_src, v_src, cu_tokens, start_pos,
                                 stream)
     if check and rc != CRONUS_OK:
         raise CronusError(rc, "cronus_kv_append")
+    return rc
+
+
+def cronus_kv_append_pair(cache: cronus_kv_cache, first, second, block_tables, max_blocks_per_seq: int, n_seqs: int,
+                          stream: int = 0, check=True) -> int:
+    """first, second: (k_src, v_src, cu_tokens, start_pos, n_tokens) each, device tensors (or addresses)."""
+    a, b = (cronus_kv_rows(_ptr(r[0]), _ptr(r[1]), _ptr(r[2]), _ptr(r[3]), int(r[4])) for r in (first, second))
+    rc = lib().cronus_kv_append_pair(ctypes.byref(cache), ctypes.byref(a), ctypes.byref(b), _ptr(block_tables),
+                                     int(max_blocks_per_seq), int(n_seqs), stream)
+    if check and rc != CRONUS_OK:
+        raise CronusError(rc, "cronus_kv_append_pair")
     return rc
 
 

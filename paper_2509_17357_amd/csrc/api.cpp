@@ -143,8 +143,23 @@ int cronus_kv_append(const cronus_kv_cache* cache, const void* k_src, const void
   if (n_seqs < 0 || n_tokens < 0 || max_blocks_per_seq <= 0) return CRONUS_ERR_INVALID_ARG;
   if (n_tokens == 0 || n_seqs == 0) return CRONUS_OK;
   if (!k_src || !v_src || !cu_tokens || !start_pos || !block_tables) return CRONUS_ERR_INVALID_ARG;
-  return launch_kv_append(cache, k_src, v_src, cu_tokens, start_pos, block_tables, max_blocks_per_seq, n_seqs,
-                          n_tokens, hip_stream);
+  const cronus_kv_rows rows{k_src, v_src, cu_tokens, start_pos, n_tokens};
+  return launch_kv_append(cache, &rows, nullptr, block_tables, max_blocks_per_seq, n_seqs, hip_stream);
+}
+
+int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
+                          const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* hip_stream) {
+  if (int rc = check_cache(cache)) return rc;
+  if (!first || !second || n_seqs < 0 || max_blocks_per_seq <= 0) return CRONUS_ERR_INVALID_ARG;
+  for (const cronus_kv_rows* r : {first, second}) {
+    if (r->n_tokens < 0) return CRONUS_ERR_INVALID_ARG;
+    if (r->n_tokens > 0 && n_seqs > 0 && (!r->k_src || !r->v_src || !r->cu_tokens || !r->start_pos || !block_tables))
+      return CRONUS_ERR_INVALID_ARG;
+  }
+  if (first->n_tokens == 0) std::swap(first, second);
+  if (first->n_tokens == 0 || n_seqs == 0) return CRONUS_OK;
+  return launch_kv_append(cache, first, second->n_tokens > 0 ? second : nullptr, block_tables, max_blocks_per_seq, n_seqs,
+                          hip_stream);
 }
 
 int cronus_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, const int32_t* cu_tokens,

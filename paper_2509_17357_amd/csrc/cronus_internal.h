@@ -216,9 +216,9 @@ int static_scratch_upload(void* dst, const void* host_src, size_t bytes, void* s
 // that does not fit in the arguments of one launch goes through `staging` (device, 16-byte
 // aligned, `bytes` bytes).
 int static_scratch_expand(void* items, void* staging, const CompactPlan& c, const void* host_src, size_t bytes, void* stream);
-int launch_kv_append(const cronus_kv_cache* cache, const void* k_src, const void* v_src,
-                     const int32_t* cu_tokens, const int32_t* start_pos, const int32_t* block_tables,
-                     int32_t max_blocks_per_seq, int32_t n_seqs, int32_t n_tokens, void* stream);
+// second may be null
+int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
+                     const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* stream);
 int launch_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, const int32_t* cu_tokens,
                      const int32_t* start_pos, const int32_t* block_tables, int32_t max_blocks_per_seq,
                      int32_t n_seqs, int32_t n_tokens, void* stream);

@@ -32,25 +32,37 @@ __device__ __forceinline__ unsigned int quant_e4m3(float x, float scale) {
   return (unsigned int)__builtin_amdgcn_cvt_pk_fp8_f32(y, y, 0, false) & 0xffu;
 }
 
-// Work-group g of the grid's x dimension serves sequence s = the last one with
+// One set of rows to place.  A launch takes up to two (an iteration places transferred prefixes
+// and new rows: two launches of 5 and 4 us next to a few decodes, one of 5.5), the work-groups of the
+// second behind those of the first; the two sets address different slots, so no order is needed.
+struct AppendRows {
+  const unsigned short* k;
+  const unsigned short* v;
+  const int* cu_tokens;
+  const int* start_pos;
+};
+
+// Work-group g of a set's part of the grid's x dimension serves sequence s = the last one with
 // first_group(s) <= g, where first_group(s) = cu_tokens[s] / 16 + 2 s, and within it the
 // j-th cache block the rows touch, j = g - first_group(s).  A sequence with n rows
 // touches at most n / 16 + 2 blocks, which is what this numbering reserves; work-groups
-// past the last touched block have nothing to do.  Host side: grid.x = n_tokens/16 + 2 n_seqs + 1.
+// past the last touched block have nothing to do.  Host side: n_tokens/16 + 2 n_seqs + 1 work-groups a set.
 template <bool FP8>
 __global__ __launch_bounds__(256) void kv_append_kernel(
-    const unsigned short* __restrict__ k_src, const unsigned short* __restrict__ v_src,
-    void* __restrict__ k_pool, void* __restrict__ v_pool, const float* __restrict__ k_scale,
-    const float* __restrict__ v_scale, const int* __restrict__ cu_tokens,
-    const int* __restrict__ start_pos, const int* __restrict__ block_tables, int max_blocks,
-    int n_seqs, int n_kv_heads, int head_dim) {
+    AppendRows first, AppendRows second, int first_groups, void* __restrict__ k_pool, void* __restrict__ v_pool,
+    const float* __restrict__ k_scale, const float* __restrict__ v_scale, const int* __restrict__ block_tables,
+    int max_blocks, int n_seqs, int n_kv_heads, int head_dim) {
   __shared__ unsigned short vt[256][8 + 2];  // [thread = dc*16 + slot][8 d values], padded rows
-  const int g = blockIdx.x, head = blockIdx.y;
+  const bool in_first = (int)blockIdx.x < first_groups;
+  const AppendRows rows = in_first ? first : second;
+  const unsigned short* __restrict__ k_src = rows.k;
+  const unsigned short* __restrict__ v_src = rows.v;
+  const int g = (int)blockIdx.x - (in_first ? 0 : first_groups), head = blockIdx.y;
   const int t = threadIdx.x;
   const int slot = t & 15, dc = t >> 4;
   const int n_dc = head_dim >> 3;
 
-  const SeqRows sr = find_sequence(cu_tokens, start_pos, n_seqs, g);
+  const SeqRows sr = find_sequence(rows.cu_tokens, rows.start_pos, n_seqs, g);
   const int s = sr.seq, row0 = sr.row0, n_rows = sr.n_rows, start = sr.start;
   const int j = g - ((row0 >> 4) + 2 * s);
   const int bi = (start >> 4) + j;                  // logical block of the sequence
@@ -137,24 +149,21 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
 
 }  // namespace
 
-int launch_kv_append(const cronus_kv_cache* cache, const void* k_src, const void* v_src,
-                     const int32_t* cu_tokens, const int32_t* start_pos, const int32_t* block_tables,
-                     int32_t max_blocks_per_seq, int32_t n_seqs, int32_t n_tokens, void* stream) {
-  const long long groups = (long long)n_tokens / 16 + 2LL * n_seqs + 1;
+int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
+                     const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* stream) {
+  auto groups_of = [&](const cronus_kv_rows* r) { return r ? (long long)r->n_tokens / 16 + 2LL * n_seqs + 1 : 0; };
+  const long long groups = groups_of(first) + groups_of(second);
   if (groups > 0x7fffffffLL || cache->num_kv_heads > 65535) return CRONUS_ERR_INVALID_ARG;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  auto ks = static_cast<const unsigned short*>(k_src);
-  auto vs = static_cast<const unsigned short*>(v_src);
+  auto rows_of = [](const cronus_kv_rows* r) {
+    return r ? AppendRows{static_cast<const unsigned short*>(r->k_src), static_cast<const unsigned short*>(r->v_src),
+                          r->cu_tokens, r->start_pos}
+             : AppendRows{};
+  };
   const dim3 grid((unsigned)groups, (unsigned)cache->num_kv_heads);
-  if (cache->kv_dtype == CRONUS_KV_FP8_E4M3) {
-    hipLaunchKernelGGL(kv_append_kernel<true>, grid, dim3(256), 0, s, ks, vs, cache->k_cache, cache->v_cache,
-                       cache->k_scale, cache->v_scale, cu_tokens, start_pos, block_tables, max_blocks_per_seq,
-                       n_seqs, cache->num_kv_heads, cache->head_dim);
-  } else {
-    hipLaunchKernelGGL(kv_append_kernel<false>, grid, dim3(256), 0, s, ks, vs, cache->k_cache, cache->v_cache,
-                       cache->k_scale, cache->v_scale, cu_tokens, start_pos, block_tables, max_blocks_per_seq,
-                       n_seqs, cache->num_kv_heads, cache->head_dim);
-  }
+  auto kernel = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? kv_append_kernel<true> : kv_append_kernel<false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, static_cast<hipStream_t>(stream), rows_of(first), rows_of(second),
+                     (int)groups_of(first), cache->k_cache, cache->v_cache, cache->k_scale, cache->v_scale, block_tables,
+                     max_blocks_per_seq, n_seqs, cache->num_kv_heads, cache->head_dim);
   return hipGetLastError() == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
 }
 

@@ -4,7 +4,8 @@ every computation through the C ABI (binding.py).  No oracle, no fallback.
 The hot path of one iteration (Cronus section 4.2 and 4.4) is, in order:
   1. ingest_prefix  - cronus_kv_append of the transferred prefix KV of the continuation
                       chunks (start_pos = 0)
-  2. append_new     - cronus_kv_append of this iteration's K/V rows (start_pos = prefix)
+  2. append_new     - cronus_kv_append of this iteration's K/V rows (start_pos = prefix); a step does
+                      1 and 2 in one launch (place_rows, cronus_kv_append_pair)
   3. attention      - cronus_attn_mixed over chunks and decodes
 The contexts of the decode requests were cached by earlier iterations; here they are
 placed by setup_decode_context(), which is set-up, not part of the iteration.
@@ -144,6 +145,14 @@ class DeviceIteration:
         return B.cronus_kv_append(self.cache, self.new_k, self.new_v, self.cu_new, self.prefix_pos,
                                   self.block_tables, b.max_blocks, b.n_seqs, self.n_new_tokens, self._stream())
 
+    def place_rows(self):
+        """ingest_prefix and append_new in one launch (the rows go to different slots)."""
+        b = self.batch
+        return B.cronus_kv_append_pair(self.cache,
+                                       (self.prefix_k, self.prefix_v, self.cu_prefix, self.zero_pos, self.n_prefix_tokens),
+                                       (self.new_k, self.new_v, self.cu_new, self.prefix_pos, self.n_new_tokens),
+                                       self.block_tables, b.max_blocks, b.n_seqs, self._stream())
+
     def ensure_workspace(self):
         """Workspace for this batch's lengths (sized once: the lengths of a batch do not change)."""
         if self.workspace is None:
@@ -162,6 +171,5 @@ class DeviceIteration:
 
     def step(self):
         """One pass of the whole hot path (after setup_decode_context())."""
-        self.ingest_prefix()
-        self.append_new()
+        self.place_rows()
         self.attention()
