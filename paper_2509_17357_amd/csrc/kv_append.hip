@@ -25,11 +25,41 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf16_bits_to_float(unsigned int b) { return __uint_as_float(b << 16); }
 
-// e4m3_rne(clamp(x / scale, -448, 448)); the division is one IEEE fp32 division.
-__device__ __forceinline__ unsigned int quant_e4m3(float x, float scale) {
-  float y = x / scale;
-  y = fminf(fmaxf(y, -448.0f), 448.0f);
-  return (unsigned int)__builtin_amdgcn_cvt_pk_fp8_f32(y, y, 0, false) & 0xffu;
+// Eight codes e4m3_rne(clamp(x / scale, -448, 448)); the quotients are those of one IEEE fp32
+// division each.  With r = RN(1 / scale) and q = RN(x r), RN(q - RN(q scale - x) r) is the correctly
+// rounded quotient (Markstein's theorem) as long as nothing in it under- or overflows: for scales of
+// 2^-64 .. 2^64 that concerns quotients below 2^-11, whose code is a zero either way, and above
+// 1024, where q is clamped first (the correction then only has to be positive or infinite).
+// The residual's sign is such that -0 stays -0.  Other scales divide.  The kernel was bound by
+// these instructions: 11 an element with the division, one conversion per code and a packing of bytes; 5.5 now.
+struct Quantiser {
+  float scale, r;
+  bool exact;
+};
+__device__ __forceinline__ Quantiser make_quantiser(float scale) {
+  return Quantiser{scale, 1.0f / scale, fabsf(scale) >= 0x1p-64f && fabsf(scale) <= 0x1p64f};
+}
+__device__ __forceinline__ u32x2 quant_e4m3_x8(const float (&x)[8], const Quantiser& z) {
+  float y[8];
+  if (z.exact) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float q = __builtin_amdgcn_fmed3f(x[e] * z.r, -1024.0f, 1024.0f);
+      y[e] = __builtin_fmaf(-__builtin_fmaf(q, z.scale, -x[e]), z.r, q);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) y[e] = x[e] / z.scale;
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) y[e] = fminf(fmaxf(y[e], -448.0f), 448.0f);
+  u32x2 c;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[4 * h], y[4 * h + 1], 0, false);
+    c[h] = (unsigned int)__builtin_amdgcn_cvt_pk_fp8_f32(y[4 * h + 2], y[4 * h + 3], lo, true);
+  }
+  return c;
 }
 
 // One set of rows to place.  A launch takes up to two (an iteration places transferred prefixes
@@ -85,17 +115,10 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
     if constexpr (!FP8) {
       *reinterpret_cast<u32x4*>(static_cast<unsigned short*>(k_pool) + k_off) = kk;
     } else {
-      const float ks = k_scale[head];
-      unsigned int c[8];
+      float x[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const unsigned int w = kk[e >> 1];
-        c[e] = quant_e4m3(bf16_bits_to_float((e & 1) ? (w >> 16) : (w & 0xffffu)), ks);
-      }
-      u32x2 packed;
-      packed[0] = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-      packed[1] = c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24);
-      *reinterpret_cast<u32x2*>(static_cast<unsigned char*>(k_pool) + k_off) = packed;
+      for (int e = 0; e < 8; ++e) x[e] = __uint_as_float((e & 1) ? (kk[e >> 1] & 0xffff0000u) : (kk[e >> 1] << 16));
+      *reinterpret_cast<u32x2*>(static_cast<unsigned char*>(k_pool) + k_off) = quant_e4m3_x8(x, make_quantiser(k_scale[head]));
     }
   }
   // ---- V: through LDS; thread (dc, kc, jj) then owns the chunk of d = 8 dc + jj, slots 8 kc .. 8 kc + 7
@@ -127,20 +150,17 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
             if (8 * kc + e >= c_lo && 8 * kc + e < c_hi) vp[e] = (unsigned short)el[e];
         }
       } else {
-        const float vs = v_scale[head];
-        unsigned int c[8];
+        float x[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) c[e] = quant_e4m3(bf16_bits_to_float(el[e]), vs);
+        for (int e = 0; e < 8; ++e) x[e] = bf16_bits_to_float(el[e]);
+        const u32x2 packed = quant_e4m3_x8(x, make_quantiser(v_scale[head]));
         unsigned char* vp = static_cast<unsigned char*>(v_pool) + v_off;
         if (c_hi - c_lo == 8) {
-          u32x2 packed;
-          packed[0] = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
-          packed[1] = c[4] | (c[5] << 8) | (c[6] << 16) | (c[7] << 24);
           *reinterpret_cast<u32x2*>(vp) = packed;
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            if (8 * kc + e >= c_lo && 8 * kc + e < c_hi) vp[e] = (unsigned char)c[e];
+            if (8 * kc + e >= c_lo && 8 * kc + e < c_hi) vp[e] = (unsigned char)(packed[e >> 2] >> (8 * (e & 3)));
         }
       }
     }
