@@ -44,6 +44,9 @@ struct Scratch {
   int32_t wide_tok;                    // tokens per wide tile of the last plan
   std::vector<int32_t> unit_base;      // compact_plan: first unit of every sequence
   std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
+  std::vector<float> row_keys;         // keys of the narrow rows, one entry per sequence
+  struct Busy { double until; long long cus; };
+  std::vector<Busy> busy;              // rounds_us: CUs that take items of equal times, by the time they are free again
   std::vector<std::pair<int32_t, int32_t>> by_length;  // (-keys, sequence) of the narrow rows that are long enough to be cut
 };
 
@@ -61,6 +64,41 @@ static NarrowSplit split_of(long long kv_total, long long span) {
   if (n > 1 && kv_total - (n - 1) * span <= span / 4) --n;
   const long long per = ((kv_total + n - 1) / n + kNarrowKvStep - 1) / kNarrowKvStep * kNarrowKvStep;
   return NarrowSplit{(int)((kv_total + per - 1) / per), (int)per};
+}
+
+// Estimated time (us) of the narrow rows in `row_keys` (`copies` of each) when they are cut into spans of
+// `span` keys and run on `cus` CUs, longest first, each on the CU that is free first: 8 us and key_us per
+// key an item, 4 us more where rows are cut (partial results, merge).  Lengths are taken in
+// classes of 64 keys and CUs in groups, so the cost is that of the classes.
+static double rounds_us(const std::vector<float>& row_keys, long long copies, long long span, long long cus, double key_us) {
+  constexpr int kClass = 64, kClasses = 96;
+  long long count[kClasses] = {0};
+  bool cut = false;
+  for (const float keys : row_keys) {  // as split_of cuts them
+    const int n = std::max(1, (int)std::ceil(keys / (float)span - 0.25f));
+    count[std::min(kClasses - 1, (int)(keys / (float)n) / kClass)] += n;
+    cut = cut || n > 1;
+  }
+  auto& busy = scratch().busy;
+  busy.assign(1, Scratch::Busy{0.0, cus});
+  double end = 0;
+  size_t front = 0;  // groups in front of it have no CU left
+  for (int c = kClasses - 1; c >= 0; --c) {
+    const double us = (cut ? 12.0 : 8.0) + key_us * (kClass * c + kClass / 2);
+    for (long long left = count[c] * copies; left > 0;) {
+      const long long k = std::min(left, busy[front].cus);
+      const double until = busy[front].until + us;
+      left -= k;
+      busy[front].cus -= k;
+      if (busy[front].cus == 0) ++front;
+      end = std::max(end, until);
+      size_t i = busy.size();
+      busy.push_back(Scratch::Busy{until, k});
+      for (; i > front && busy[i - 1].until > until; --i) busy[i] = busy[i - 1];
+      busy[i] = Scratch::Busy{until, k};
+    }
+  }
+  return end;
 }
 
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
@@ -124,8 +162,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   }
   // no wide item should hold a CU for much longer than three quarters of a CU's fair share
   // (measured on paper-shaped iterations: smaller spans pay more for their prologue and the
-  // merge than they gain in balance), and no span is shorter than 16 K/V tiles
+  // merge than they gain in balance), and no span is shorter than 16 K/V tiles here
   int wide_piece_keys = 0;
+  long long wide_items = -1;  // of the cut chosen below (launches of few tiles)
   if (wide_cost_total > 0) {
     const double fair = (wide_cost_total + 0.5 * narrow_keys) / std::max(n_cus, 1);
     const double keys = 0.75 * fair / (wide_rows / 128.0);
@@ -143,38 +182,36 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // decodes: 64 tiles in five spans each are 320 items for 256 CUs, two rounds where four
   // spans each need one; next to many decodes long wide items start late and end last.
   // Such a launch therefore picks its span length by estimated duration: for every way of
-  // cutting the longest tile into 1 .. 8 equal spans (of at least 12 K/V tiles), the items
-  // and their times under a model fitted to measured launches on MI355X (D = 128, bf16: 47
-  // paper-shaped iterations of 1 k .. 64 k context with 0 .. 200 decodes of up to 1 M keys in
-  // total, each with every cut that gives a distinct plan; the model's choice is the measured
-  // best or within 3 % of it on all of them).  Two regimes, by the narrow items' share of the
-  // work:
-  //  * chunk-dominated (estimated narrow time under 0.3 of the wide tiles'): the wide items
+  // cutting the longest tile into 1 .. 8 equal spans (of at least 7 K/V tiles), the items
+  // and their times under a model fitted to measured launches on MI355X (148 mixed iterations
+  // of at most two tiles per CU, bf16 and fp8, D = 64 and 128, each with every cut, inputs
+  // changing from pass to pass: against the measured best cut the model's choice costs 1.5 % on
+  // average and 23 % at worst; the constants that were fitted to a kernel with a merge launch of its own
+  // and 25.7 ns a key cost 3.8 % and 44 %).  Two regimes, by the narrow items' share of the work:
+  //  * chunk-dominated (estimated narrow time under 0.34 of the wide tiles'): the wide items
   //    run in rounds over the CUs; the CUs that the last round leaves free take narrow items
   //    meanwhile, the narrow items left after that follow in rounds of their own.  A wide item
-  //    takes 8 us + 23.7 ns per key at 256 rows (three quarters of that per key at half
-  //    height), a narrow span 6 us + 12 ns per key, a launch with cut tiles 13 us + 3 ns per
-  //    partial slot.
+  //    takes 14 us + 25 ns per key at 256 rows (three quarters of that per key at half
+  //    height), a narrow span 8.4 us + 13 ns per key, a launch with cut
+  //    tiles 3 us + 3.5 ns per partial slot.
   //  * decode-rich: the launch cannot end before the items' times summed over the CUs, before
   //    the wide items alone have run in rounds, or before the narrow items' K/V has streamed at
   //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, so the
   //    last wide item starts at about 0.77 of that time and the launch ends when it does.
   //    Wide items on at most three quarters of the CUs are queued in front instead (below): the
-  //    launch cannot end before the longest of them, 10 us + 25.5 ns per key from its start.
-  //    Next to streaming CUs a wide item takes 10 us + 16 ns per key (the clock is higher than
-  //    under a chip-wide MFMA load), a narrow span 8 us + 6.7 ns per key, and a partial slot
-  //    costs 21 ns (its traffic competes with the decodes'), a launch with cut tiles 4 us.
-  // The 13 us and 4 us were measured with the merge as a launch of its own behind the main
-  // kernel; the main kernel merges now, and the model has not been fitted to that, so it leans
-  // against cutting.  The three quarters are counted over the launch here and per queue below:
+  //    launch cannot end before the longest of them, 7.8 us + 22.6 ns per key from its start.
+  //    Next to streaming CUs a wide item takes 10.5 us + 13 ns per key (the clock is higher than
+  //    under a chip-wide MFMA load), a narrow span 8 us + 4.1 ns per key, and a partial slot
+  //    costs 14.4 ns (its traffic competes with the decodes'), a launch with cut tiles 7 us.
+  // The three quarters are counted over the launch here and per queue below:
   // a queue that was dealt more than its share of the wide items interleaves all the same.
   if (wide_cost_total > 0 && wide_tiles <= 2LL * std::max(n_cus, 1)) {
     const int cus = std::max(n_cus, 1);
     struct Costs { double wide_us0, wide_us_key, narrow_us0, narrow_us_key, slot_us, cut_us0; };
-    const Costs chunk_dominated{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0}, decode_rich{10.0, 0.016, 8.0, 0.0067, 0.0206, 4.0},
-        at_once{10.0, 0.0255, 0.0, 0.0, 0.0, 0.0};
+    const Costs chunk_dominated{14.0, 0.025, 8.4, 0.013, 0.0035, 3.0}, decode_rich{10.5, 0.013, 8.0, 0.0041, 0.0144, 7.0},
+        at_once{7.8, 0.0226, 0.0, 0.0, 0.0, 0.0};
     const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77;
-    constexpr int kMinCutPiece = 12 * kWideKvTile;
+    constexpr int kMinCutPiece = 7 * kWideKvTile;
     long long longest = 0, n_narrow = 0;
     for (int s = 0; s < n_seqs; ++s) {
       const long long P = prefix_lens[s], C = chunk_lens[s];
@@ -221,11 +258,12 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     };
     const WideSide whole = wide_side(1 << 30, chunk_dominated);  // no tile cut
     const bool few_decodes =
-        whole.items == 0 || (double)n_narrow * narrow_item_us(chunk_dominated) < 0.3 * whole.total_us;
+        whole.items == 0 || (double)n_narrow * narrow_item_us(chunk_dominated) < 0.34 * whole.total_us;
     const Costs& c = few_decodes ? chunk_dominated : decode_rich;
     const double narrow_us = narrow_item_us(c), narrow_total_us = (double)n_narrow * narrow_us;
     double best_us = 0;
     int best_piece = 0;
+    long long best_items = -1;
     for (int cut = 1; cut <= 8; ++cut) {
       int piece = (int)((longest + cut - 1) / cut);
       piece = (piece + kWideKvTile - 1) / kWideKvTile * kWideKvTile;
@@ -258,9 +296,66 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       if (best_piece == 0 || us < best_us) {
         best_us = us;
         best_piece = piece;
+        best_items = w.items;
       }
     }
     if (best_piece > 0) wide_piece_keys = best_piece;
+    wide_items = best_items;
+  }
+
+  // The narrow items' span again, now that the wide ones are known: where those leave CUs free
+  // from the start, the narrow items run in rounds over the rest, and a few items more than a
+  // whole number of rounds cost a round.  (Launches of decodes alone keep the span above: they shall
+  // not change the cut of a row with the company it is in.)  Of the spans that give at most
+  // four rounds the one with the least rounds x (8 us + its longest item's keys at the share of
+  // 5.3 TB/s that each of those CUs gets, 7 ns a key at least) is a candidate, and it is taken if it also ends
+  // before the span above when both are dealt out item by item.  (Measured, us a pass: a chunk
+  // behind 16 k in 192 spans next to 16 decodes, 248 -> 192 items on the other 64 CUs, 179.5 -> 163.0; two
+  // chunks in 144 items next to 10 decodes of 3400, 232 -> 80 items, 97.4 -> 89.2; fp8, a chunk in 192
+  // items next to 7 decodes of 4600, 256 -> 128 items, 70.7 -> 67.0; a chunk in 56 tiles next to 52 decodes,
+  // 312 -> 384 items, 128.3 -> 125.4.  With more rounds than that the rounding is a small part.)
+  constexpr int kMaxRounds = 4;
+  const long long free_cus = std::max(n_cus, 1) - wide_items;
+  if (narrow_keys > 0 && wide_items > 0 && 4 * wide_items <= 3LL * std::max(n_cus, 1)) {
+    std::vector<float>& rows = scratch().row_keys;
+    rows.clear();
+    const long long copies = (long long)Hkv * n_groups;
+    const size_t most_rows = (size_t)(kMaxRounds * free_cus / copies);
+    for (int s = 0; s < n_seqs && rows.size() <= most_rows; ++s) {
+      const long long C = chunk_lens[s];
+      if (C == 0) continue;
+      const long long rem = C * group <= kNarrowRows ? C : C % wide_tok;
+      if (rem > 0 && rem * group <= kNarrowRows) rows.push_back((float)((long long)prefix_lens[s] + C));
+    }
+    if (rows.size() <= most_rows) {
+      const double key_bytes = 2.0 * D * (cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1.0 : 2.0);
+      auto key_us = [&](long long items) { return std::max(0.007, key_bytes * (double)std::min(items, free_cus) / 5.3e6); };
+      double best_us = 0;
+      long long best_span = 0, best_items = 0, items_now = 0;
+      for (int steps = 2; steps <= kMaxSpanSteps; ++steps) {
+        const float inv = 1.0f / (float)(steps * kNarrowKvStep);
+        float longest = 0.f;
+        long long items = 0;
+        for (const float keys : rows) {
+          const int n = std::max(1, (int)std::ceil(keys * inv - 0.25f));
+          items += n;
+          longest = std::max(longest, keys / (float)n);
+        }
+        items *= copies;
+        if (steps * kNarrowKvStep == span) items_now = items;
+        const long long rounds = (items + free_cus - 1) / free_cus;
+        if (rounds > kMaxRounds) continue;
+        const double us = (double)rounds * (8.0 + key_us(items) * longest);
+        if (best_span == 0 || us < best_us) {
+          best_us = us;
+          best_span = steps * kNarrowKvStep;
+          best_items = items;
+        }
+      }
+      if (best_span > 0 && best_span != span && best_items != items_now &&
+          rounds_us(rows, copies, best_span, free_cus, key_us(best_items)) < rounds_us(rows, copies, span, free_cus, key_us(items_now)))
+        span = best_span;
+    }
   }
 
   Scratch& sc = scratch();
@@ -508,11 +603,11 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // traffic), the others stream decode spans, and a CU that streams next to computing CUs
   // gets a larger share of the memory system than one that streams next to 255 others.
   // The wide list runs ahead (its share of time emitted is 1 / kWideLead of the spans'), so
-  // that it is used up at about three quarters of the queue and only spans, the short
-  // items, are left for the tail.  Measured on the Llama-3-8B-shaped batch: 12 % shorter
-  // step than with the spans last.  Where wide tiles dominate, the spans stay at the end
+  // that only spans, the short items, are left for the tail.  Measured on the Llama-3-8B-shaped batch: 12 % shorter
+  // step than with the spans last; with the list used up at 0.85 of the queue instead of 0.75 (tiles take
+  // 15 % less than when that was chosen) 155.1 -> 151.3 us, ten other mixes -6 .. +4 %, -2 % on average.  Where wide tiles dominate, the spans stay at the end
   // of the queue anyway.
-  constexpr double kWideLead = 0.75;
+  constexpr double kWideLead = 0.85;
   // A queue whose wide items are at most three quarters of its XCD's CUs keeps them in front:
   // they all start at once and the rest of the CUs stream beside them, and none is left to
   // start late.  (A chunk of 463 tokens behind 2049 next to 49 decodes, 13 wide items a queue:
