@@ -168,9 +168,12 @@ _I32 = np.dtype(np.int32)
 
 def _lens(a):
     """A host int32 array and its address, for the calls of the hot path.  (`_host_i32` builds a
-    typed pointer: 4.7 us an array; this is 0.6 us, and a small iteration is bound by the host.)"""
+    typed pointer: 4.7 us an array; the array interface is 1.4 us, the buffer 0.6, and a small iteration is
+    bound by the host.)"""
     if type(a) is not np.ndarray or a.dtype != _I32 or not a.flags.c_contiguous:
         a = np.ascontiguousarray(a, dtype=np.int32)
+    if a.size and a.flags.writeable:
+        return a, ctypes.addressof(ctypes.c_char.from_buffer(a))
     return a, a.__array_interface__["data"][0]
 
 
@@ -194,7 +197,10 @@ def cronus_kv_append(cache: cronus_kv_cache, k_src, v_src, cu_tokens, start_pos,
 def cronus_kv_append_pair(cache: cronus_kv_cache, first, second, block_tables, max_blocks_per_seq: int, n_seqs: int,
                           stream: int = 0, check=True) -> int:
     """first, second: (k_src, v_src, cu_tokens, start_pos, n_tokens) each, device tensors (or addresses)."""
-    a, b = (cronus_kv_rows(_ptr(r[0]), _ptr(r[1]), _ptr(r[2]), _ptr(r[3]), int(r[4])) for r in (first, second))
+    k, v, cu, pos, n = first
+    a = cronus_kv_rows(_ptr(k), _ptr(v), _ptr(cu), _ptr(pos), int(n))
+    k, v, cu, pos, n = second
+    b = cronus_kv_rows(_ptr(k), _ptr(v), _ptr(cu), _ptr(pos), int(n))
     rc = lib().cronus_kv_append_pair(ctypes.byref(cache), ctypes.byref(a), ctypes.byref(b), _ptr(block_tables),
                                      int(max_blocks_per_seq), int(n_seqs), stream)
     if check and rc != CRONUS_OK:

@@ -145,13 +145,14 @@ class DeviceIteration:
         return B.cronus_kv_append(self.cache, self.new_k, self.new_v, self.cu_new, self.prefix_pos,
                                   self.block_tables, b.max_blocks, b.n_seqs, self.n_new_tokens, self._stream())
 
-    def place_rows(self):
+    def place_rows(self, stream=None):
         """ingest_prefix and append_new in one launch (the rows go to different slots)."""
         b = self.batch
         return B.cronus_kv_append_pair(self.cache,
                                        (self.prefix_k, self.prefix_v, self.cu_prefix, self.zero_pos, self.n_prefix_tokens),
                                        (self.new_k, self.new_v, self.cu_new, self.prefix_pos, self.n_new_tokens),
-                                       self.block_tables, b.max_blocks, b.n_seqs, self._stream())
+                                       self.block_tables, b.max_blocks, b.n_seqs,
+                                       self._stream() if stream is None else stream)
 
     def ensure_workspace(self):
         """Workspace for this batch's lengths (sized once: the lengths of a batch do not change)."""
@@ -163,13 +164,15 @@ class DeviceIteration:
             self.workspace_bytes = need
         return self.workspace_bytes
 
-    def attention(self):
+    def attention(self, stream=None):
         b = self.batch
         self.ensure_workspace()
         return B.cronus_attn_mixed(self.cache, self.q, self.out, b.prefix_lens, b.chunk_lens, self.block_tables,
-                                   b.max_blocks, self.sm_scale, self.workspace, self.workspace_bytes, self._stream())
+                                   b.max_blocks, self.sm_scale, self.workspace, self.workspace_bytes,
+                                   self._stream() if stream is None else stream)
 
     def step(self):
         """One pass of the whole hot path (after setup_decode_context())."""
-        self.place_rows()
-        self.attention()
+        stream = self._stream()  # looked up once: 1.9 us each time
+        self.place_rows(stream)
+        self.attention(stream)
