@@ -1524,9 +1524,8 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
         const int row = e / U, u = e % U;
         const float* ml = base + kNarrowRows * D + 2 * row;
         const float* op = base + row * D + 4 * u;
-        const float mx = merge_max(ml, kSlot, n_split);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        float lsum = 0.f;
+        float lsum = 0.f, mx = kNeg * 4.f;
         for (int s0 = 0; s0 < n_split; s0 += 4) {  // twelve loads in flight
           f32x2 st[4], lo[4], hi[4];
 #pragma unroll
@@ -1535,6 +1534,13 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
             st[k] = get_pair(ml + off);
             lo[k] = get_pair(op + off);
             hi[k] = get_pair(op + off + 2);
+          }
+          // The references of up to four spans come in the round trip of their results (two before:
+          // one decode of 2.4 k keys 14.30 -> 14.02 us a pass, eight of 1.3 k 19.77 -> 19.47).
+          if (s0 == 0) {
+            mx = n_split > 4 ? merge_max(ml, kSlot, n_split) : mx;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) mx = fmaxf(mx, st[k][0]);
           }
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
