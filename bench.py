@@ -2,8 +2,8 @@
 """Benchmark of the mixed-iteration attention hot path on one MI355X.
 
 A step is one pass of the whole path over one synthetic batch: ingest of the
-transferred prefixes of the continuation chunks (cronus_kv_append), append of the
-iteration's new K/V rows (cronus_kv_append), and the mixed attention
+transferred prefixes of the continuation chunks and append of the iteration's new K/V
+rows (one launch: cronus_kv_append_pair), and the mixed attention
 (cronus_attn_mixed: work decomposition, chunk tiles, decode spans and their merge).  Inputs are
 resident in HBM before the timed region.  Prints ONE JSON line.
 
@@ -47,9 +47,9 @@ BOUND = {"tiny": "hbm", "llama3_8b": "hbm", "prefill_heavy": "mfma", "decode_hea
 # 2.000, WRITE_SIZE x 1.000).  These are STATIC figures copied from the summary named below, taken
 # with the library version named below; with any other library version the line carries null.
 TRAFFIC_SOURCE = "profiles/attn_mixed_kernel_benchmark_batches_rocprofv3.md"
-TRAFFIC_LIB_VERSION = 505
-MEASURED_TRAFFIC_BYTES = {"llama3_8b": 624381617, "prefill_heavy": 609010131, "decode_heavy": 4877200557,
-                          "llama_70b_fp8": 4021937151, "paper_iteration_16k": 303146550}
+TRAFFIC_LIB_VERSION = 506
+MEASURED_TRAFFIC_BYTES = {"llama3_8b": 628098882, "prefill_heavy": 610301431, "decode_heavy": 4877225303,
+                          "llama_70b_fp8": 4022321890, "paper_iteration_16k": 301262510}
 
 
 def make_batch(name, trial=0):

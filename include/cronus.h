@@ -307,7 +307,7 @@ void cronus_profile_events(void* main_start, void* main_stop, void* first_start,
 
 /*
  * cronus_probe_mfma - measurement aid, not part of the attention path: the rate of
- * v_mfma_f32_32x32x16_bf16 (the instruction of both products of cronus_attn_mixed) that the
+ * v_mfma_f32_32x32x16_bf16 (cronus_attn_mixed: decode spans; chunk tiles use 16x16x32) that the
  * current GPU sustains when every CU issues nothing else.  Enqueues one kernel on hip_stream:
  * one work-group of 8 wavefronts per CU, each wavefront issuing iters x 32 independent MFMAs
  * on operand registers that hold small integer bit patterns (random_operands = 0) or random

@@ -362,6 +362,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 505; }  // 0.5.5: key spans merged by the main kernel; chained wide tiles; compact static list
+int cronus_version(void) { return 506; }  // 0.5.6: wide tiles on 16x16x32 MFMAs; prefixes and new rows placed by one launch
 
 }  // extern "C"

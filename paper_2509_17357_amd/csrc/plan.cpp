@@ -617,7 +617,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   const size_t wide_at_once = (size_t)(3 * std::max(n_cus, 1) / (4 * kXcds));
   for (auto& q : sc.queue) {
     // microseconds per item, fitted to per-work-group timestamps of the Llama-3-8B-shaped
-    // batch on MI355X (D = 128, bf16; only the ratio of the two kinds matters here)
+    // batch on MI355X (D = 128, bf16; only the ratio of the two kinds matters here: wide tiles take
+    // 15 % less since, which the choice of kWideLead was measured with)
     auto time_of = [&](int32_t ref) {
       if (ref >= 0) {
         const WorkItem& w = sc.wide[(size_t)ref];
