@@ -181,6 +181,8 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * per-thread arrays (ordinary heap memory, grown to the largest batch the thread has planned).
  *   - CRONUS_ERR_WORKSPACE, nothing enqueued: the batch's plan image plus partial results
  *     exceed the array (about 4000 partial slots at head_dim 128; every benchmark batch fits).
+ *     Chunk tiles are cut into fewer key spans first; such a call's results can differ from
+ *     cronus_attn_mixed's in the last bf16 bit.
  *   - fp8 cache: no bf16 copy is made (it would not fit); chunks of many tiles convert codes on
  *     the fly, so results can differ from cronus_attn_mixed's in the last bf16 bit.
  *   - Every call on a GPU uses that GPU's one array, which keeps the previous call's contents

@@ -312,8 +312,13 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
     return rc;
   if (plan.n_items > 0x7fffffffLL) return CRONUS_ERR_INVALID_ARG;
   // scratch layout: [plan image | partial results]; both sizes are multiples of 256
-  if (plan.image_bytes > kStaticScratchBytes || plan.total_bytes > kStaticScratchBytes - plan.image_bytes)
-    return CRONUS_ERR_WORKSPACE;
+  auto fits = [&] { return plan.image_bytes <= kStaticScratchBytes && plan.total_bytes <= kStaticScratchBytes - plan.image_bytes; };
+  // the fastest cut of the wide tiles may not fit where a coarser one does
+  if (!fits()) {
+    if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, device_cus(), &plan, false, kStaticScratchBytes))
+      return rc;
+  }
+  if (!fits()) return CRONUS_ERR_WORKSPACE;
 
   std::lock_guard<std::mutex> lock(g_mu);
   int dev = 0;

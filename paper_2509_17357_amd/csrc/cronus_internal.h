@@ -164,9 +164,11 @@ int wide_rows_for(int head_dim, int kv_dtype);
 // in a per-thread scratch).  write_plan() then copies that list into host_buf, which must
 // hold plan->image_bytes bytes; it must follow build_plan() on the same thread.
 // allow_stage = false: an fp8 cache gets no bf16 copy (every chunk tile converts codes on
-// the fly), so the workspace holds partial results only.
+// the fly), so the workspace holds partial results only.  scratch_limit > 0: the wide tiles of a
+// launch that picks its span length get no cut whose list and partial results exceed that many bytes.
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
-               int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage = true);
+               int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage = true,
+               size_t scratch_limit = 0);
 void write_plan(const Plan* plan, void* host_buf);
 // The same list in compact form ([CompactUnit x n_units | references], *bytes of buf used, a
 // multiple of 16), when it can be expressed (it holds every record) and fits in `capacity`.

@@ -102,7 +102,8 @@ static double rounds_us(const std::vector<float>& row_keys, long long copies, lo
 }
 
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
-               int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage) {
+               int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage,
+               size_t scratch_limit) {
   const int D = cache->head_dim, Hq = cache->num_q_heads, Hkv = cache->num_kv_heads;
   const int G = Hq / Hkv;
   const int group = std::min(G, kNarrowRows);          // q heads handled together by one item
@@ -212,7 +213,12 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         at_once{7.8, 0.0226, 0.0, 0.0, 0.0, 0.0};
     const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77;
     constexpr int kMinCutPiece = 7 * kWideKvTile;
-    long long longest = 0, n_narrow = 0;
+    long long longest = 0, n_narrow = 0, narrow_slots = 0;
+    auto count_narrow = [&](long long keys, long long copies) {
+      const long long n = std::max<long long>(1, (keys + span - 1) / span) * copies;
+      n_narrow += n;
+      if (n > copies) narrow_slots += n;
+    };
     for (int s = 0; s < n_seqs; ++s) {
       const long long P = prefix_lens[s], C = chunk_lens[s];
       if (C <= 0) continue;
@@ -220,9 +226,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       if (C * group > kNarrowRows) {
         longest = std::max(longest, P + C);
         const long long rem = C % wide_tok;
-        if (rem && rem * group <= kNarrowRows) n_narrow += std::max<long long>(1, (P + C + span - 1) / span) * copies;
+        if (rem && rem * group <= kNarrowRows) count_narrow(P + C, copies);
       } else {
-        n_narrow += std::max<long long>(1, (P + C + span - 1) / span) * copies;
+        count_narrow(P + C, copies);
       }
     }
     const double kv_elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1.0 : 2.0;
@@ -270,6 +276,12 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       if (cut > 1 && piece < kMinCutPiece) break;
       const WideSide w = wide_side(piece, c);
       if (w.items == 0) break;
+      // (a merge record belongs to at least two slots; the estimate never counts fewer spans than are cut)
+      if (scratch_limit > 0 && cut > 1 &&
+          (size_t)(w.items + n_narrow) * sizeof(WorkItem) +
+                  (size_t)(w.slots + narrow_slots) * (sizeof(float) * partial_floats(D) + sizeof(MergeItem)) + 1024 >
+              scratch_limit)
+        continue;
       const long long rounds = (w.items + cus - 1) / cus;
       const double mean_us = w.total_us / (double)w.items;
       const double wide_alone_us = (double)(rounds - 1) * mean_us + w.longest_us;
