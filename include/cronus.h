@@ -150,7 +150,10 @@ int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* fi
  *                  cached tokens (4 x Hkv x D bytes per cached or
  *                  new token of such a sequence, 1 GiB at most: sequences beyond that
  *                  are computed from the codes); contents are undefined afterwards;
- *                  must not be shared by calls that can overlap on the device
+ *                  must not be shared by calls that can overlap on the device.  A smaller
+ *                  one is accepted where it holds what versions up to 505 needed for these
+ *                  lengths: chunk tiles are then cut into fewer key spans, and results can
+ *                  differ in the last bf16 bit
  * The work list is built on the host during the call and read by the kernels from
  * pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
  * demand, never freed; the ninth call in flight waits on the host for one of them).  A call
@@ -198,7 +201,9 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
                              int32_t n_seqs, float sm_scale, void* hip_stream);
 
 /* Bytes of workspace cronus_attn_mixed needs for these lengths (host arrays); 0 on
- * invalid arguments.  Depends only on the shapes and lengths, not on cache contents. */
+ * invalid arguments.  Depends only on the shapes and lengths, not on cache contents.  Not
+ * monotonic: a smaller batch can need more (fewer tiles are cut into more key spans), so the
+ * need is asked for each batch's lengths. */
 size_t cronus_attn_mixed_workspace_bytes(const cronus_kv_cache* cache, const int32_t* prefix_lens,
                                          const int32_t* chunk_lens, int32_t n_seqs);
 

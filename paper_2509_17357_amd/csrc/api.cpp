@@ -266,6 +266,10 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, co
   const int n_cus = device_cus();
   if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, n_cus, &plan)) return rc;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return CRONUS_ERR_WORKSPACE;
+  // a workspace that served these lengths before the tiles were cut finer still does
+  if (workspace_bytes < plan.total_bytes) {
+    if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, n_cus, &plan, true, 0, true)) return rc;
+  }
   if (workspace_bytes < plan.total_bytes) return CRONUS_ERR_WORKSPACE;
   if (plan.n_items > 0x7fffffffLL) return CRONUS_ERR_INVALID_ARG;
 

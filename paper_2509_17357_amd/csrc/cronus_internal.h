@@ -166,9 +166,10 @@ int wide_rows_for(int head_dim, int kv_dtype);
 // allow_stage = false: an fp8 cache gets no bf16 copy (every chunk tile converts codes on
 // the fly), so the workspace holds partial results only.  scratch_limit > 0: the wide tiles of a
 // launch that picks its span length get no cut whose list and partial results exceed that many bytes.
+// lean: the cut that library versions up to 505 chose, for a workspace that is too small for the faster one.
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
                int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage = true,
-               size_t scratch_limit = 0);
+               size_t scratch_limit = 0, bool lean = false);
 void write_plan(const Plan* plan, void* host_buf);
 // The same list in compact form ([CompactUnit x n_units | references], *bytes of buf used, a
 // multiple of 16), when it can be expressed (it holds every record) and fits in `capacity`.

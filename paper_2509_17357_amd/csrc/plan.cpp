@@ -103,7 +103,7 @@ static double rounds_us(const std::vector<float>& row_keys, long long copies, lo
 
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
                int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage,
-               size_t scratch_limit) {
+               size_t scratch_limit, bool lean) {
   const int D = cache->head_dim, Hq = cache->num_q_heads, Hkv = cache->num_kv_heads;
   const int G = Hq / Hkv;
   const int group = std::min(G, kNarrowRows);          // q heads handled together by one item
@@ -206,13 +206,16 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   //    costs 14.4 ns (its traffic competes with the decodes'), a launch with cut tiles 7 us.
   // The three quarters are counted over the launch here and per queue below:
   // a queue that was dealt more than its share of the wide items interleaves all the same.
+  // A lean plan prices cutting as library versions up to 505 did (a merge launch of its own, no span of
+  // less than 12 K/V tiles): where that gives fewer partial slots, it fits a workspace sized by those.
   if (wide_cost_total > 0 && wide_tiles <= 2LL * std::max(n_cus, 1)) {
     const int cus = std::max(n_cus, 1);
     struct Costs { double wide_us0, wide_us_key, narrow_us0, narrow_us_key, slot_us, cut_us0; };
-    const Costs chunk_dominated{14.0, 0.025, 8.4, 0.013, 0.0035, 3.0}, decode_rich{10.5, 0.013, 8.0, 0.0041, 0.0144, 7.0},
-        at_once{7.8, 0.0226, 0.0, 0.0, 0.0, 0.0};
-    const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77;
-    constexpr int kMinCutPiece = 7 * kWideKvTile;
+    const Costs chunk_dominated = lean ? Costs{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0} : Costs{14.0, 0.025, 8.4, 0.013, 0.0035, 3.0},
+                decode_rich = lean ? Costs{10.0, 0.016, 8.0, 0.0067, 0.0206, 4.0} : Costs{10.5, 0.013, 8.0, 0.0041, 0.0144, 7.0},
+                at_once = lean ? Costs{10.0, 0.0255, 0.0, 0.0, 0.0, 0.0} : Costs{7.8, 0.0226, 0.0, 0.0, 0.0, 0.0};
+    const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77, few_decodes_share = lean ? 0.3 : 0.34;
+    const int min_cut_piece = (lean ? 12 : 7) * kWideKvTile;
     long long longest = 0, n_narrow = 0, narrow_slots = 0;
     auto count_narrow = [&](long long keys, long long copies) {
       const long long n = std::max<long long>(1, (keys + span - 1) / span) * copies;
@@ -264,7 +267,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     };
     const WideSide whole = wide_side(1 << 30, chunk_dominated);  // no tile cut
     const bool few_decodes =
-        whole.items == 0 || (double)n_narrow * narrow_item_us(chunk_dominated) < 0.34 * whole.total_us;
+        whole.items == 0 || (double)n_narrow * narrow_item_us(chunk_dominated) < few_decodes_share * whole.total_us;
     const Costs& c = few_decodes ? chunk_dominated : decode_rich;
     const double narrow_us = narrow_item_us(c), narrow_total_us = (double)n_narrow * narrow_us;
     double best_us = 0;
@@ -273,7 +276,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     for (int cut = 1; cut <= 8; ++cut) {
       int piece = (int)((longest + cut - 1) / cut);
       piece = (piece + kWideKvTile - 1) / kWideKvTile * kWideKvTile;
-      if (cut > 1 && piece < kMinCutPiece) break;
+      if (cut > 1 && piece < min_cut_piece) break;
       const WideSide w = wide_side(piece, c);
       if (w.items == 0) break;
       // (a merge record belongs to at least two slots; the estimate never counts fewer spans than are cut)
@@ -328,7 +331,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // 312 -> 384 items, 128.3 -> 125.4.  With more rounds than that the rounding is a small part.)
   constexpr int kMaxRounds = 4;
   const long long free_cus = std::max(n_cus, 1) - wide_items;
-  if (narrow_keys > 0 && wide_items > 0 && 4 * wide_items <= 3LL * std::max(n_cus, 1)) {
+  if (!lean && narrow_keys > 0 && wide_items > 0 && 4 * wide_items <= 3LL * std::max(n_cus, 1)) {
     std::vector<float>& rows = scratch().row_keys;
     rows.clear();
     const long long copies = (long long)Hkv * n_groups;
