@@ -46,7 +46,9 @@ struct Scratch {
   std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
   std::vector<float> row_keys;         // keys of the narrow rows, one entry per sequence
   struct Busy { double until; long long cus; };
-  std::vector<Busy> busy;              // rounds_us: CUs that take items of equal times, by the time they are free again
+  std::vector<Busy> busy;              // list_us: CUs by the time they are free again, a heap
+  struct Load { double us; long long items; };
+  std::vector<Load> loads;             // items of equal estimated times
   std::vector<std::pair<int32_t, int32_t>> by_length;  // (-keys, sequence) of the narrow rows that are long enough to be cut
 };
 
@@ -66,10 +68,40 @@ static NarrowSplit split_of(long long kv_total, long long span) {
   return NarrowSplit{(int)((kv_total + per - 1) / per), (int)per};
 }
 
+// End (us) of the items in `loads`, dealt in their order to `cus` CUs, each to the CU that is free first.
+static double list_us(const std::vector<Scratch::Load>& loads, long long cus) {
+  auto& busy = scratch().busy;
+  auto later = [](const Scratch::Busy& a, const Scratch::Busy& b) { return a.until > b.until; };
+  busy.assign(1, Scratch::Busy{0.0, cus});
+  double end = 0;
+  for (size_t i = 0; i < loads.size();) {
+    const Scratch::Load& l = loads[i];
+    long long left = 0;
+    for (; i < loads.size() && loads[i].us == l.us; ++i) left += loads[i].items;
+    while (left > 0) {
+      std::pop_heap(busy.begin(), busy.end(), later);
+      Scratch::Busy& first = busy.back();
+      const long long k = std::min(left, first.cus);
+      const double until = first.until + l.us;
+      left -= k;
+      first.cus -= k;
+      if (first.cus == 0) {
+        first = Scratch::Busy{until, k};
+      } else {
+        std::push_heap(busy.begin(), busy.end(), later);
+        busy.push_back(Scratch::Busy{until, k});
+      }
+      std::push_heap(busy.begin(), busy.end(), later);
+      end = std::max(end, until);
+    }
+  }
+  return end;
+}
+
 // Estimated time (us) of the narrow rows in `row_keys` (`copies` of each) when they are cut into spans of
-// `span` keys and run on `cus` CUs, longest first, each on the CU that is free first: 8 us and key_us per
-// key an item, 4 us more where rows are cut (partial results, merge).  Lengths are taken in
-// classes of 64 keys and CUs in groups, so the cost is that of the classes.
+// `span` keys and run on `cus` CUs, longest first: 8 us and key_us per key an item, 4 us more for each item of a
+// launch that cuts any row (partial results, merge).  Lengths are taken in classes of 64 keys, so the cost is
+// that of the classes.
 static double rounds_us(const std::vector<float>& row_keys, long long copies, long long span, long long cus, double key_us) {
   constexpr int kClass = 64, kClasses = 96;
   long long count[kClasses] = {0};
@@ -79,26 +111,11 @@ static double rounds_us(const std::vector<float>& row_keys, long long copies, lo
     count[std::min(kClasses - 1, (int)(keys / (float)n) / kClass)] += n;
     cut = cut || n > 1;
   }
-  auto& busy = scratch().busy;
-  busy.assign(1, Scratch::Busy{0.0, cus});
-  double end = 0;
-  size_t front = 0;  // groups in front of it have no CU left
-  for (int c = kClasses - 1; c >= 0; --c) {
-    const double us = (cut ? 12.0 : 8.0) + key_us * (kClass * c + kClass / 2);
-    for (long long left = count[c] * copies; left > 0;) {
-      const long long k = std::min(left, busy[front].cus);
-      const double until = busy[front].until + us;
-      left -= k;
-      busy[front].cus -= k;
-      if (busy[front].cus == 0) ++front;
-      end = std::max(end, until);
-      size_t i = busy.size();
-      busy.push_back(Scratch::Busy{until, k});
-      for (; i > front && busy[i - 1].until > until; --i) busy[i] = busy[i - 1];
-      busy[i] = Scratch::Busy{until, k};
-    }
-  }
-  return end;
+  auto& loads = scratch().loads;
+  loads.clear();
+  for (int c = kClasses - 1; c >= 0; --c)
+    if (count[c] > 0) loads.push_back(Scratch::Load{(cut ? 12.0 : 8.0) + key_us * (kClass * c + kClass / 2), count[c] * copies});
+  return list_us(loads, cus);
 }
 
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
@@ -183,18 +200,22 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // decodes: 64 tiles in five spans each are 320 items for 256 CUs, two rounds where four
   // spans each need one; next to many decodes long wide items start late and end last.
   // Such a launch therefore picks its span length by estimated duration: for every way of
-  // cutting the longest tile into 1 .. 8 equal spans (of at least 7 K/V tiles), the items
-  // and their times under a model fitted to measured launches on MI355X (148 mixed iterations
-  // of at most two tiles per CU, bf16 and fp8, D = 64 and 128, each with every cut, inputs
-  // changing from pass to pass: against the measured best cut the model's choice costs 1.5 % on
-  // average and 23 % at worst; the constants that were fitted to a kernel with a merge launch of its own
-  // and 25.7 ns a key cost 3.8 % and 44 %).  Two regimes, by the narrow items' share of the work:
+  // cutting the longest tile into 1 .. 8 equal spans (of at least 8 K/V tiles), the items
+  // and their times under a model fitted to measured launches on MI355X (489 iterations of at most
+  // two tiles per CU: whole prompts, chunks behind prefixes, with and without decodes, bf16 and fp8,
+  // D = 64 and 128, G = 4, 5, 7 and 8, each with every cut: against the measured best cut the model's choice costs
+  // 1.6 % on average and 25 % at worst).  Two regimes, by the narrow items' share of the work:
   //  * chunk-dominated (estimated narrow time under 0.34 of the wide tiles'): the wide items
   //    run in rounds over the CUs; the CUs that the last round leaves free take narrow items
-  //    meanwhile, the narrow items left after that follow in rounds of their own.  A wide item
-  //    takes 14 us + 25 ns per key at 256 rows (three quarters of that per key at half
+  //    meanwhile, the narrow items left after that follow in rounds of their own.  More than one round
+  //    of wide items takes 0.3 of (all rounds but one at the mean time, and the longest item) and 0.7 of what
+  //    dealing them longest first takes: tiles of one length need whole rounds, those of a whole
+  //    prompt (36, 72 .. 1200 keys) do not.  With whole rounds alone, and 14 us an item, one prompt of 1228 tokens, G = 8, was cut
+  //    into 384 items instead of 312, 51.6 us instead of 40.0; over the 489 iterations that cost 2.8 % on
+  //    average, 34 % at worst against the cut of version 505.  A wide item takes 23 us + 25 ns
+  //    per key at 256 rows (three quarters of that per key at half
   //    height), a narrow span 8.4 us + 13 ns per key, a launch with cut
-  //    tiles 3 us + 3.5 ns per partial slot.
+  //    tiles 3 us + 2.4 ns per partial slot.
   //  * decode-rich: the launch cannot end before the items' times summed over the CUs, before
   //    the wide items alone have run in rounds, or before the narrow items' K/V has streamed at
   //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, so the
@@ -211,11 +232,11 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   if (wide_cost_total > 0 && wide_tiles <= 2LL * std::max(n_cus, 1)) {
     const int cus = std::max(n_cus, 1);
     struct Costs { double wide_us0, wide_us_key, narrow_us0, narrow_us_key, slot_us, cut_us0; };
-    const Costs chunk_dominated = lean ? Costs{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0} : Costs{14.0, 0.025, 8.4, 0.013, 0.0035, 3.0},
+    const Costs chunk_dominated = lean ? Costs{8.0, 0.0237, 6.0, 0.012, 0.003, 13.0} : Costs{23.0, 0.025, 8.4, 0.013, 0.0024, 3.0},
                 decode_rich = lean ? Costs{10.0, 0.016, 8.0, 0.0067, 0.0206, 4.0} : Costs{10.5, 0.013, 8.0, 0.0041, 0.0144, 7.0},
                 at_once = lean ? Costs{10.0, 0.0255, 0.0, 0.0, 0.0, 0.0} : Costs{7.8, 0.0226, 0.0, 0.0, 0.0, 0.0};
-    const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77, few_decodes_share = lean ? 0.3 : 0.34;
-    const int min_cut_piece = (lean ? 12 : 7) * kWideKvTile;
+    const double hbm_bytes_per_us = 5.24e6, last_wide_start = 0.77, few_decodes_share = lean ? 0.3 : 0.34, whole_rounds = 0.3;
+    const int min_cut_piece = (lean ? 12 : 8) * kWideKvTile;
     long long longest = 0, n_narrow = 0, narrow_slots = 0;
     auto count_narrow = [&](long long keys, long long copies) {
       const long long n = std::max<long long>(1, (keys + span - 1) / span) * copies;
@@ -237,9 +258,11 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     const double kv_elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1.0 : 2.0;
     const double hbm_us = (double)narrow_keys * 2.0 * D * kv_elem_bytes / hbm_bytes_per_us;  // K and V of every narrow key
     // items, summed and longest time of the wide items, and partial slots for a span length
+    auto& loads = scratch().loads;  // the items themselves
     struct WideSide { long long items, slots; double total_us, longest_us, longest_keys; };
     auto wide_side = [&](int piece, const Costs& c) {
       WideSide w{0, 0, 0.0, 0.0, 0.0};
+      loads.clear();
       for (int s = 0; s < n_seqs; ++s) {
         const long long P = prefix_lens[s], C = chunk_lens[s];
         if (C * group <= kNarrowRows) continue;
@@ -253,6 +276,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
           const double height = nt * group * 2 <= wide_rows ? 0.75 : 1.0;
           const double us = c.wide_us0 + c.wide_us_key * height * (double)per;
           const long long copies = (long long)Hkv * n_groups;
+          loads.push_back(Scratch::Load{us, n_split * copies});
           w.items += n_split * copies;
           w.total_us += us * (double)(n_split * copies);
           w.longest_us = std::max(w.longest_us, us);
@@ -287,7 +311,6 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         continue;
       const long long rounds = (w.items + cus - 1) / cus;
       const double mean_us = w.total_us / (double)w.items;
-      const double wide_alone_us = (double)(rounds - 1) * mean_us + w.longest_us;
       // narrow items that the CUs left free by the last round of wide items take meanwhile
       auto trailing_us = [&]() {
         if (n_narrow == 0) return 0.0;
@@ -296,18 +319,30 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         const long long left = std::max<long long>(0, n_narrow - absorbed);
         return (double)((left + cus - 1) / cus) * narrow_us;
       };
+      auto launch_us = [&](double wide_alone_us) {
+        double us;
+        if (few_decodes) {
+          us = wide_alone_us + trailing_us();
+        } else {
+          const double floor_us = std::max(std::max((w.total_us + narrow_total_us) / cus, hbm_us), wide_alone_us);
+          const double ratio = narrow_total_us / w.total_us;
+          if (ratio < 0.3) us = wide_alone_us + trailing_us();
+          else if (4 * w.items <= 3 * cus) us = std::max(floor_us, at_once.wide_us0 + at_once.wide_us_key * w.longest_keys);
+          else if (ratio <= 10.0) us = std::max(floor_us, last_wide_start * floor_us + w.longest_us);
+          else us = std::max(floor_us, w.longest_us);
+        }
+        return us + c.slot_us * (double)w.slots + (w.slots ? c.cut_us0 : 0.0);
+      };
+      const double in_rounds_us = (double)(rounds - 1) * mean_us + w.longest_us;
       double us;
-      if (few_decodes) {
-        us = wide_alone_us + trailing_us();
+      if (rounds > 1 && !lean) {
+        auto wide_alone_us = [&](double dealt_us) { return whole_rounds * in_rounds_us + (1.0 - whole_rounds) * dealt_us; };
+        if (best_piece > 0 && launch_us(wide_alone_us(std::max(w.total_us / cus, w.longest_us))) >= best_us) continue;
+        std::sort(loads.begin(), loads.end(), [](const Scratch::Load& a, const Scratch::Load& b) { return a.us > b.us; });
+        us = launch_us(wide_alone_us(list_us(loads, cus)));
       } else {
-        const double floor_us = std::max(std::max((w.total_us + narrow_total_us) / cus, hbm_us), wide_alone_us);
-        const double ratio = narrow_total_us / w.total_us;
-        if (ratio < 0.3) us = wide_alone_us + trailing_us();
-        else if (4 * w.items <= 3 * cus) us = std::max(floor_us, at_once.wide_us0 + at_once.wide_us_key * w.longest_keys);
-        else if (ratio <= 10.0) us = std::max(floor_us, last_wide_start * floor_us + w.longest_us);
-        else us = std::max(floor_us, w.longest_us);
+        us = launch_us(in_rounds_us);
       }
-      us += c.slot_us * (double)w.slots + (w.slots ? c.cut_us0 : 0.0);
       if (best_piece == 0 || us < best_us) {
         best_us = us;
         best_piece = piece;

@@ -12,8 +12,8 @@ import parity_util as U
 
 pytestmark = pytest.mark.gpu
 
-CASES = [((32, 8, 128, "bf16"), [0], [1200], 256), ((32, 8, 128, "fp8"), [1000], [300], 256),
-         ((28, 4, 128, "bf16"), [1000, 2500], [300, 1], 332800), ((64, 8, 128, "fp8"), [1500, 2500], [100, 1], 7454720)]
+CASES = [((32, 8, 128, "bf16"), [0], [1200], 256), ((32, 8, 128, "fp8"), [1100], [400], 256),
+         ((28, 4, 128, "bf16"), [1800, 2500], [300, 1], 9917440), ((64, 8, 128, "fp8"), [1500, 2500], [100, 1], 7454720)]
 GUARD = 1 << 20
 
 

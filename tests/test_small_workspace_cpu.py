@@ -8,8 +8,8 @@ from paper_2509_17357_amd import binding as B
 
 BF16, FP8 = B.CRONUS_KV_BF16, B.CRONUS_KV_FP8_E4M3
 # (heads, cache, prefixes, chunks, bytes up to version 505); the last two need no more now
-CASES = [((32, 8, 128), BF16, [0], [1200], 256), ((32, 8, 128), FP8, [1000], [300], 256),
-         ((28, 4, 128), BF16, [1000, 2500], [300, 1], 332800), ((8, 2, 64), BF16, [900, 4000], [700, 1], 135168),
+CASES = [((32, 8, 128), BF16, [0], [1200], 256), ((32, 8, 128), FP8, [1100], [400], 256),
+         ((28, 4, 128), BF16, [1800, 2500], [300, 1], 9917440), ((8, 2, 64), BF16, [900, 4000], [700, 1], 135168),
          ((64, 8, 128), FP8, [1500, 2500], [100, 1], 7454720), ((32, 8, 128), BF16, [2500, 2500, 7000], [200, 1, 1], 12912640),
          ((32, 8, 128), BF16, [0], [700], 256), ((64, 8, 128), FP8, [4000, 2500, 700], [200, 1, 90], 23029760)]
 
