@@ -27,7 +27,8 @@ def call(shape, P, C):
                                                  ([5000] * 50, False, True), ([40000] * 128, True, False)])
 def test_tiles_are_cut_coarser_before_a_batch_is_refused(decodes, over, fits):
     shape = W.HeadShape(64, 8, 128)
-    P, C = [1700, 3900, 3800] + decodes, [767, 852, 166] + [1] * len(decodes)
+    # (tiles of nearly one length, which the planner cuts)
+    P, C = [6948, 3291, 3262] + decodes, [1128, 564, 125] + [1] * len(decodes)
     _, stats = plan_for(shape, P, C)
     assert (stats["partials"] * SLOT_BYTES > 64 << 20) == over  # the fastest cut
     assert (call(shape, P, C) != B.CRONUS_ERR_WORKSPACE) == fits
