@@ -182,7 +182,15 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // (measured on paper-shaped iterations: smaller spans pay more for their prologue and the
   // merge than they gain in balance), and no span is shorter than 16 K/V tiles here
   int wide_piece_keys = 0;
-  long long wide_items = -1;  // of the cut chosen below (launches of few tiles)
+  long long wide_items = -1, wide_slots = 0;  // of the cut chosen below (launches of few tiles)
+  // With a limit: that many items and partial slots would exceed it.  (A merge record belongs to at
+  // least two slots.  The narrow rows' shares are those of the span that they are counted with: a span that
+  // is chosen anew below is counted anew.)
+  auto too_large = [&](long long items, long long slots) {
+    return scratch_limit > 0 && (size_t)items * sizeof(WorkItem) +
+                                        (size_t)slots * (sizeof(float) * partial_floats(D) + sizeof(MergeItem)) + 1024 >
+                                    scratch_limit;
+  };
   if (wide_cost_total > 0) {
     const double fair = (wide_cost_total + 0.5 * narrow_keys) / std::max(n_cus, 1);
     const double keys = 0.75 * fair / (wide_rows / 128.0);
@@ -303,12 +311,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       if (cut > 1 && piece < min_cut_piece) break;
       const WideSide w = wide_side(piece, c);
       if (w.items == 0) break;
-      // (a merge record belongs to at least two slots; the estimate never counts fewer spans than are cut)
-      if (scratch_limit > 0 && cut > 1 &&
-          (size_t)(w.items + n_narrow) * sizeof(WorkItem) +
-                  (size_t)(w.slots + narrow_slots) * (sizeof(float) * partial_floats(D) + sizeof(MergeItem)) + 1024 >
-              scratch_limit)
-        continue;
+      if (cut > 1 && too_large(w.items + n_narrow, w.slots + narrow_slots)) continue;
       const long long rounds = (w.items + cus - 1) / cus;
       const double mean_us = w.total_us / (double)w.items;
       // narrow items that the CUs left free by the last round of wide items take meanwhile
@@ -347,6 +350,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         best_us = us;
         best_piece = piece;
         best_items = w.items;
+        wide_slots = w.slots;
       }
     }
     if (best_piece > 0) wide_piece_keys = best_piece;
@@ -385,16 +389,17 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       for (int steps = 2; steps <= kMaxSpanSteps; ++steps) {
         const float inv = 1.0f / (float)(steps * kNarrowKvStep);
         float longest = 0.f;
-        long long items = 0;
+        long long items = 0, slots = 0;
         for (const float keys : rows) {
           const int n = std::max(1, (int)std::ceil(keys * inv - 0.25f));
           items += n;
+          if (n > 1) slots += n;
           longest = std::max(longest, keys / (float)n);
         }
         items *= copies;
         if (steps * kNarrowKvStep == span) items_now = items;
         const long long rounds = (items + free_cus - 1) / free_cus;
-        if (rounds > kMaxRounds) continue;
+        if (rounds > kMaxRounds || too_large(wide_items + items, wide_slots + slots * copies)) continue;
         const double us = (double)rounds * (8.0 + key_us(items) * longest);
         if (best_span == 0 || us < best_us) {
           best_us = us;

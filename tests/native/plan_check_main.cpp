@@ -9,6 +9,7 @@
 //     -> "plan <rc> <n_items> <n_wide> <n_partials> <n_merge> <n_merge_rows> <n_stage_blocks>
 //              <total_bytes> <image_bytes>", then n_items lines "i" with the 11 item fields,
 //        then n_merge lines "m" with the 12 merge fields
+//   limited <bytes> ... , lean ...   (as plan, with that scratch limit / as a lean plan)
 //   split <l_in> <n_d> <l_ctxd> <n_free> <k_p> <b_p> <k_ctxp> <k_ctxd> <b_c> <n_size> <B> <n_cand>
 //     -> "split <rc> <l_p> <t_prefill> <t_chunked>"
 #include <cinttypes>
@@ -27,8 +28,10 @@ int wide_rows_for(int, int) { return kWaves * 32; }  // the kernels' tile height
 int main() {
   std::string word;
   while (std::cin >> word) {
-    if (word == "plan") {
+    if (word == "plan" || word == "limited" || word == "lean") {
       int hq, hkv, d, fp8, n_cus, allow_stage, n;
+      size_t limit = 0;
+      if (word == "limited") std::cin >> limit;
       std::cin >> hq >> hkv >> d >> fp8 >> n_cus >> allow_stage >> n;
       std::vector<int32_t> P((size_t)n), C((size_t)n);
       for (int i = 0; i < n; ++i) std::cin >> P[(size_t)i] >> C[(size_t)i];
@@ -40,7 +43,8 @@ int main() {
       c.block_size = 16;
       c.kv_dtype = fp8 ? CRONUS_KV_FP8_E4M3 : CRONUS_KV_BF16;
       cronus::Plan plan;
-      const int rc = cronus::build_plan(&c, P.data(), C.data(), n, 0x7fffffff / 16, n_cus, &plan, allow_stage != 0);
+      const int rc = cronus::build_plan(&c, P.data(), C.data(), n, 0x7fffffff / 16, n_cus, &plan, allow_stage != 0, limit,
+                                        word == "lean");
       std::printf("plan %d %" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 " %zu %zu\n", rc,
                   rc ? 0 : plan.n_items, plan.n_wide, plan.n_partials, plan.n_merge, plan.n_merge_rows,
                   plan.n_stage_blocks, plan.total_bytes, plan.image_bytes);
