@@ -226,8 +226,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   //    tiles 3 us + 2.4 ns per partial slot.
   //  * decode-rich: the launch cannot end before the items' times summed over the CUs, before
   //    the wide items alone have run in rounds, or before the narrow items' K/V has streamed at
-  //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, so the
-  //    last wide item starts at about 0.77 of that time and the launch ends when it does.
+  //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, and the
+  //    launch ends 0.77 of that time and the longest wide item after its start (0.77 is fitted like
+  //    the other constants: the wide list is used up later, see kWideLead).
   //    Wide items on at most three quarters of the CUs are queued in front instead (below): the
   //    launch cannot end before the longest of them, 7.8 us + 22.6 ns per key from its start.
   //    Next to streaming CUs a wide item takes 10.5 us + 13 ns per key (the clock is higher than
@@ -359,8 +360,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
 
   // The narrow items' span again, now that the wide ones are known: where those leave CUs free
   // from the start, the narrow items run in rounds over the rest, and a few items more than a
-  // whole number of rounds cost a round.  (Launches of decodes alone keep the span above: they shall
-  // not change the cut of a row with the company it is in.)  Of the spans that give at most
+  // whole number of rounds cost a round.  (Launches of decodes alone keep the one rule above, keys over
+  // CUs, which tests/test_plan_spans_cpu.py states.)  Of the spans that give at most
   // four rounds the one with the least rounds x (8 us + its longest item's keys at the share of
   // 5.3 TB/s that each of those CUs gets, 7 ns a key at least) is a candidate, and it is taken if it also ends
   // before the span above when both are dealt out item by item.  (Measured, us a pass: a chunk

@@ -1,7 +1,7 @@
 """Key spans of decodes: one length for the whole launch, the narrow items' keys over the CUs in
 whole steps of 256, from 512 to 4096; a row's keys in equal spans of at most that length and a
 quarter of it, in whole steps.  The cut decides the bits of a result (the running reference and
-the order of the sums), so a decode-only iteration must not choose another one by itself."""
+the order of the sums): a decode-only iteration takes this one rule and no other."""
 import numpy as np
 import pytest
 
