@@ -25,10 +25,15 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float bf16_bits_to_float(unsigned int b) { return __uint_as_float(b << 16); }
 
-// Eight codes e4m3_rne(clamp(x / scale, -448, 448)); the quotients are those of one IEEE fp32
-// division each.  With r = RN(1 / scale) and q = RN(x r), RN(q - RN(q scale - x) r) is the correctly
-// rounded quotient (Markstein's theorem) as long as nothing in it under- or overflows: for scales of
-// 2^-64 .. 2^64 that concerns quotients below 2^-11, whose code is a zero either way, and above
+// Eight codes e4m3_rne(clamp(x / scale, -448, 448)), those of one IEEE fp32 division each.  With
+// r = RN(1 / scale), q = RN(x r) and d = RN(q scale - x), the quotient here is RN(q - d r) (the residual step
+// of Markstein's method).  q can be 1.5 ulp from x / scale where his theorem asks for 1, so the quotient is not
+// claimed to be correctly rounded; but q - d r is within 2^-22 ulp of x / scale, so it differs from the division only next to
+// the midpoint of two fp32 numbers, and the code only if one of them is a boundary between two codes, B 2^n with
+// 16 <= B < 32.  That asks for x = (B + 2^-20) 2^n scale (or B - 2^-20) but for a relative 2^-45, with scale =
+// (k / 8 + j 2^-23) 2^m, 8 <= k < 16 and a small j: the bits of x below its 8-bit significand vanish
+// only if B j = -k (or k), and 16 <= B > k has no such j.  Under- and overflow: for scales of
+// 2^-64 .. 2^64 they concern quotients below 2^-11, whose code is a zero either way, and above
 // 1024, where q is clamped first (the correction then only has to be positive or infinite).
 // The residual's sign is such that -0 stays -0.  Other scales divide.  The kernel was bound by
 // these instructions: 11 an element with the division, one conversion per code and a packing of bytes; 5.5 now.
