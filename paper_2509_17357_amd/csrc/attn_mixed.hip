@@ -108,15 +108,11 @@ __device__ __forceinline__ float pair_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Combine a value with those held by lane^16, lane^32 and lane^48 (the lanes of one row of a
+// Maximum of a value and those held by lane^16, lane^32 and lane^48 (the lanes of one row of a
 // wide tile's wave).
 __device__ __forceinline__ float quad_max(float x) {
   auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
-}
-__device__ __forceinline__ float quad_sum(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -155,7 +151,7 @@ __device__ __forceinline__ u32x4 zero_tail(u32x4 v, int kv0, int kv_len) {
 // First part: causal mask, running reference m (rescales O and l when some row's maximum
 // outgrew it by more than kLazyLog2 bits).  Second part: numerators, their row sum, and
 // the bf16 P^T operands.
-template <int NDB, bool FORCE = false>
+template <int NDB>
 __device__ __forceinline__ void softmax_max_part(f32x16& s, bool need_mask, int sub_base, int half, int limit,
                                                  float c, float& m, float& l, f32x16 (&o)[NDB]) {
   if (need_mask) {
@@ -173,7 +169,7 @@ __device__ __forceinline__ void softmax_max_part(f32x16& s, bool need_mask, int 
   // 2^kLazyLog2 keep their relative precision in bf16 and their sums stay far from the
   // fp32 range, so O and l are rescaled only when some row's maximum outgrew its
   // reference by more than that (wave-uniform branch; every row then takes its true maximum).
-  if (FORCE || __builtin_amdgcn_ballot_w64((mx - m) * c > kLazyLog2) != 0) {
+  if (__builtin_amdgcn_ballot_w64((mx - m) * c > kLazyLog2) != 0) {
     const float m_new = fmaxf(m, mx);
     const float alpha = __builtin_amdgcn_exp2f((m - m_new) * c);
     l *= alpha;
