@@ -96,6 +96,13 @@ def threshold_cases():
             ([511 + x], [1]), ([255 + x], [1]),  # span granularity
             ([2 ** 20 + x], [1]),                # a million keys
         ]
+    for x in (-1, 0, 1):
+        cases += [
+            ([1024 + 64 * x - 300], [300]),              # two spans of the least length (8 K/V tiles)
+            ([1500] + [900] * 20, [1536 + 64 * x] + [1] * 20),   # G = 4: 192 tiles, three quarters of 256 CUs, +- 8
+            ([16384] + [2000] * (32 + x), [496] + [1] * (32 + x)),   # rows that make four rounds on the 64 CUs beside 192 spans
+            ([4096] + [3000] * (6 + x), [300] + [1] * (6 + x)),
+        ]
     cases += [([0] * 32, [64 * 16] * 32), ([0] * 31, [64 * 16] * 31),   # 16 tiles per CU at 256 CUs
               ([200000, 200000, 100], [1024, 1024, 1024])]              # fp8 copy: the second sequence would pass the 1 GiB cap at Hkv = 8
     return cases
