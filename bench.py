@@ -175,27 +175,30 @@ def time_workload(name, steps, warmup, trial=0):
 
 
 def time_mfma_probe(iters=4000, reps=5):
-    """What rate of v_mfma_f32_32x32x16_bf16 this GPU sustains when every CU issues nothing else
-    (cronus_probe_mfma): with operand registers that hold small constants, and with random bf16
+    """What rate of v_mfma_f32_16x16x32_bf16 (chunk tiles) and v_mfma_f32_32x32x16_bf16 (decode spans) this
+    GPU sustains when every CU issues nothing else: with operand registers that hold small constants, and with random bf16
     values.  Context for the MFMA roofline fractions: the published peak assumes the nominal
     clock, which the GPU does not hold under a chip-wide MFMA load on real data."""
     import torch
     from paper_2509_17357_amd import binding as B
     sink = torch.empty(B.cronus_probe_mfma_sink_floats(), dtype=torch.float32, device="cuda:0")
     stream = torch.cuda.current_stream().cuda_stream
-    out = {"instruction": "v_mfma_f32_32x32x16_bf16", "wavefronts_per_cu": 8, "mfma_per_wavefront": 32 * iters}
-    for name, rnd in (("constant_operands", False), ("random_operands", True)):
-        for _ in range(3):
-            flops = B.cronus_probe_mfma(rnd, iters, sink, stream=stream)
-        torch.cuda.synchronize()
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        e0.record()
-        for _ in range(reps):
-            B.cronus_probe_mfma(rnd, iters, sink, stream=stream)
-        e1.record()
-        torch.cuda.synchronize()
-        ms = e0.elapsed_time(e1) / reps
-        out[name] = {"ms": ms, "tflops": flops / 1e12 / (ms * 1e-3), "frac_of_peak": flops / 1e12 / (ms * 1e-3) / PEAK_BF16_TFLOPS}
+    out = {"wavefronts_per_cu": 8}
+    for instruction, probe, n in (("v_mfma_f32_16x16x32_bf16", B.cronus_probe_mfma_16x16x32, 2 * iters),
+                                  ("v_mfma_f32_32x32x16_bf16", B.cronus_probe_mfma, iters)):
+        res = out[instruction] = {"mfma_per_wavefront": 32 * n}
+        for name, rnd in (("constant_operands", False), ("random_operands", True)):
+            for _ in range(3):
+                flops = probe(rnd, n, sink, stream=stream)
+            torch.cuda.synchronize()
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(reps):
+                probe(rnd, n, sink, stream=stream)
+            e1.record()
+            torch.cuda.synchronize()
+            ms = e0.elapsed_time(e1) / reps
+            res[name] = {"ms": ms, "tflops": flops / 1e12 / (ms * 1e-3), "frac_of_peak": flops / 1e12 / (ms * 1e-3) / PEAK_BF16_TFLOPS}
     return out
 
 
@@ -349,11 +352,13 @@ def main():
             del b
         scatter_gather = time_scatter_gather()
     if mfma_probe is not None:
-        # context, not the roofline: the fraction of what plain MFMA issue sustains on this GPU, on random data
+        # context, not the roofline: the fraction of what plain issue of the chunk tiles' MFMA sustains on this GPU, on
+        # random data
+        rate = mfma_probe["v_mfma_f32_16x16x32_bf16"]["random_operands"]["tflops"]
         for res in [main_res, *others.values()]:
             if res["roofline"]["bound"] == "mfma":
-                res["roofline"]["mfma_probe_tflops"] = mfma_probe["random_operands"]["tflops"]
-                res["roofline"]["frac_of_mfma_probe"] = res["roofline"]["achieved"] / mfma_probe["random_operands"]["tflops"]
+                res["roofline"]["mfma_probe_tflops"] = rate
+                res["roofline"]["frac_of_mfma_probe"] = res["roofline"]["achieved"] / rate
     sh = batch.shape
     line = {
         "metric": "mixed-batch attention tokens/s; TFLOP/s and HBM GB/s as % of MI355X peak",
@@ -372,7 +377,7 @@ def main():
         "config": {"workload": args.workload, "q_heads": sh.n_q_heads, "kv_heads": sh.n_kv_heads,
                    "head_dim": sh.head_dim, "kv_dtype": sh.kv_dtype, "block_size": 16,
                    "n_seqs": batch.n_seqs, "q_tokens": batch.total_q, "kv_tokens": int(batch.kv_lens.sum()),
-                   "step": "kv_append(prefix of chunks) + kv_append(new tokens) + attn_mixed"},
+                   "step": "kv_append_pair(prefix of chunks, new tokens) + attn_mixed"},
         "detail": main_res,
         "roofline": main_res["roofline"],
         "other_workloads": others,

@@ -329,6 +329,11 @@ void cronus_profile_events(void* main_start, void* main_stop, void* first_start,
 int cronus_probe_mfma(int random_operands, int iters, float* sink, size_t sink_floats, void* hip_stream,
                       double* flops_host);
 
+/* The same for v_mfma_f32_16x16x32_bf16 (cronus_attn_mixed: chunk tiles), each A operand held for two
+ * products; 2 x 16 x 16 x 32 operations per MFMA. */
+int cronus_probe_mfma_16x16x32(int random_operands, int iters, float* sink, size_t sink_floats, void* hip_stream,
+                               double* flops_host);
+
 /* Floats the sink of cronus_probe_mfma must hold on the current device (CUs x 512). */
 size_t cronus_probe_mfma_sink_floats(void);
 

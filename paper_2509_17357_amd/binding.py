@@ -26,7 +26,7 @@ CRONUS_KV_FP8_E4M3 = 1
 EXPORTS = ("cronus_kv_append", "cronus_kv_append_pair", "cronus_kv_gather", "cronus_attn_mixed", "cronus_attn_mixed_static",
            "cronus_attn_mixed_workspace_bytes",
            "cronus_attn_mixed_plan_stats", "cronus_attn_mixed_plan_items", "cronus_balancer_split",
-           "cronus_profile_events", "cronus_probe_mfma", "cronus_probe_mfma_sink_floats", "cronus_status_string",
+           "cronus_profile_events", "cronus_probe_mfma", "cronus_probe_mfma_16x16x32", "cronus_probe_mfma_sink_floats", "cronus_status_string",
            "cronus_version")
 
 
@@ -92,8 +92,9 @@ def lib() -> ctypes.CDLL:
         L.cronus_attn_mixed_plan_items.restype = ctypes.c_int64
         L.cronus_profile_events.argtypes = [vp, vp, vp, vp]
         L.cronus_profile_events.restype = None
-        L.cronus_probe_mfma.argtypes = [ctypes.c_int, ctypes.c_int, vp, ctypes.c_size_t, vp, ctypes.POINTER(ctypes.c_double)]
-        L.cronus_probe_mfma.restype = ctypes.c_int
+        for probe in (L.cronus_probe_mfma, L.cronus_probe_mfma_16x16x32):
+            probe.argtypes = [ctypes.c_int, ctypes.c_int, vp, ctypes.c_size_t, vp, ctypes.POINTER(ctypes.c_double)]
+            probe.restype = ctypes.c_int
         L.cronus_probe_mfma_sink_floats.argtypes = []
         L.cronus_probe_mfma_sink_floats.restype = ctypes.c_size_t
         L.cronus_status_string.argtypes = [ctypes.c_int]
@@ -219,19 +220,28 @@ def cronus_kv_gather(cache: cronus_kv_cache, k_dst, v_dst, cu_tokens, start_pos,
     return rc
 
 
-def cronus_probe_mfma(random_operands: bool, iters: int, sink, sink_floats=None, stream: int = 0, check=True):
-    """Enqueues the MFMA rate probe; returns the floating-point operations of the launch.
-    sink: device float32 tensor (or address + sink_floats) of at least cronus_probe_mfma_sink_floats() elements."""
+def _probe_mfma(name, random_operands, iters, sink, sink_floats, stream, check):
     flops = ctypes.c_double(0.0)
     if sink_floats is None:
         sink_floats = sink.numel() if hasattr(sink, "numel") else 0
-    rc = lib().cronus_probe_mfma(int(bool(random_operands)), int(iters), _ptr(sink), int(sink_floats),
-                                 ctypes.c_void_p(stream), ctypes.byref(flops))
+    rc = getattr(lib(), name)(int(bool(random_operands)), int(iters), _ptr(sink), int(sink_floats),
+                              ctypes.c_void_p(stream), ctypes.byref(flops))
     if rc != CRONUS_OK:
         if check:
-            raise CronusError(rc, "cronus_probe_mfma")
+            raise CronusError(rc, name)
         return rc
     return flops.value
+
+
+def cronus_probe_mfma(random_operands: bool, iters: int, sink, sink_floats=None, stream: int = 0, check=True):
+    """Enqueues the MFMA rate probe; returns the floating-point operations of the launch.
+    sink: device float32 tensor (or address + sink_floats) of at least cronus_probe_mfma_sink_floats() elements."""
+    return _probe_mfma("cronus_probe_mfma", random_operands, iters, sink, sink_floats, stream, check)
+
+
+def cronus_probe_mfma_16x16x32(random_operands: bool, iters: int, sink, sink_floats=None, stream: int = 0, check=True):
+    """The same for the instruction of the chunk tiles."""
+    return _probe_mfma("cronus_probe_mfma_16x16x32", random_operands, iters, sink, sink_floats, stream, check)
 
 
 def cronus_probe_mfma_sink_floats() -> int:

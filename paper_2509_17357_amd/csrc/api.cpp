@@ -175,12 +175,22 @@ int cronus_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, con
 
 size_t cronus_probe_mfma_sink_floats(void) { return (size_t)mfma_probe_sink_floats(device_cus()); }
 
-int cronus_probe_mfma(int random_operands, int iters, float* sink, size_t sink_floats, void* hip_stream,
+static int probe_mfma(bool small_shape, int random_operands, int iters, float* sink, size_t sink_floats, void* hip_stream,
                       double* flops_host) {
   if (iters < 1 || iters > (1 << 20) || !sink || !flops_host) return CRONUS_ERR_INVALID_ARG;
   const int n_cus = device_cus();
   if (sink_floats < (size_t)mfma_probe_sink_floats(n_cus)) return CRONUS_ERR_WORKSPACE;
-  return launch_mfma_probe(random_operands, iters, n_cus, sink, hip_stream, flops_host);
+  return launch_mfma_probe(small_shape, random_operands, iters, n_cus, sink, hip_stream, flops_host);
+}
+
+int cronus_probe_mfma(int random_operands, int iters, float* sink, size_t sink_floats, void* hip_stream,
+                      double* flops_host) {
+  return probe_mfma(false, random_operands, iters, sink, sink_floats, hip_stream, flops_host);
+}
+
+int cronus_probe_mfma_16x16x32(int random_operands, int iters, float* sink, size_t sink_floats, void* hip_stream,
+                               double* flops_host) {
+  return probe_mfma(true, random_operands, iters, sink, sink_floats, hip_stream, flops_host);
 }
 
 size_t cronus_attn_mixed_workspace_bytes(const cronus_kv_cache* cache, const int32_t* prefix_lens,

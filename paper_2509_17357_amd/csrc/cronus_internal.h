@@ -227,7 +227,7 @@ int launch_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, con
                      int32_t n_seqs, int32_t n_tokens, void* stream);
 
 // mfma_probe.hip (measurement aid)
-int launch_mfma_probe(int random_operands, int iters, int n_cus, float* sink, void* stream, double* flops);
+int launch_mfma_probe(bool small_shape, int random_operands, int iters, int n_cus, float* sink, void* stream, double* flops);
 int mfma_probe_sink_floats(int n_cus);
 
 }  // namespace cronus

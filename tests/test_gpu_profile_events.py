@@ -85,3 +85,20 @@ def test_mfma_probe_runs_and_reports_its_work():
         torch.cuda.synchronize()
         tflops = flops * 10 / 1e12 / (e0.elapsed_time(e1) * 1e-3)
         assert 200.0 < tflops < 2600.0, tflops
+
+
+def test_mfma_probe_of_the_chunk_tiles_instruction():
+    """The same for v_mfma_f32_16x16x32_bf16."""
+    need = B.cronus_probe_mfma_sink_floats()
+    n_cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sink = torch.empty((need,), dtype=torch.float32, device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    for rnd in (False, True):
+        sink.fill_(float("nan"))
+        flops = B.cronus_probe_mfma_16x16x32(rnd, 200, sink, stream=stream)
+        assert flops == 2.0 * 16 * 16 * 32 * 32 * 200 * 8 * n_cus
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(sink).all())
+        assert bool((sink != 0).any()) == rnd
+    assert B.cronus_probe_mfma_16x16x32(True, 0, sink, check=False) == B.CRONUS_ERR_INVALID_ARG
+    assert B.cronus_probe_mfma_16x16x32(True, 10, sink, need - 1, check=False) == B.CRONUS_ERR_WORKSPACE
