@@ -226,9 +226,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   //    tiles 3 us + 2.4 ns per partial slot.
   //  * decode-rich: the launch cannot end before the items' times summed over the CUs, before
   //    the wide items alone have run in rounds, or before the narrow items' K/V has streamed at
-  //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead, and the
+  //    5.2 TB/s; the queues alternate the two kinds with the wide list running ahead (kWideLead), and the
   //    launch ends 0.77 of that time and the longest wide item after its start (0.77 is fitted like
-  //    the other constants: the wide list is used up later, see kWideLead).
+  //    the other constants).
   //    Wide items on at most three quarters of the CUs are queued in front instead (below): the
   //    launch cannot end before the longest of them, 7.8 us + 22.6 ns per key from its start.
   //    Next to streaming CUs a wide item takes 10.5 us + 13 ns per key (the clock is higher than
@@ -658,12 +658,12 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // kind keeping its order: while some CUs of the XCD compute wide tiles (little HBM
   // traffic), the others stream decode spans, and a CU that streams next to computing CUs
   // gets a larger share of the memory system than one that streams next to 255 others.
-  // The wide list runs ahead (its share of time emitted is 1 / kWideLead of the spans'), so
-  // that only spans, the short items, are left for the tail.  Measured on the Llama-3-8B-shaped batch: 12 % shorter
-  // step than with the spans last; with the list used up at 0.85 of the queue instead of 0.75 (tiles take
-  // 15 % less than when that was chosen) 155.1 -> 151.3 us, ten other mixes -6 .. +4 %, -2 % on average.  Where wide tiles dominate, the spans stay at the end
-  // of the queue anyway.
-  constexpr double kWideLead = 0.85;
+  // The wide list runs ahead (its share of time emitted is 1 / kWideLead of the spans'), so that it is used up
+  // before the queue's last quarter and only spans, the short items, are left for the tail.  Measured on the
+  // Llama-3-8B-shaped batch: 12 % shorter step than with the spans last.  (Lead 0.85: that batch 151.7 -> 150.4 us a step, but
+  // 108 mixes take 0.5 % more attention time on average, 22 of them more than 2 % and 9 % at most, 5 less by as much.)  Where
+  // wide tiles dominate, the spans stay at the end of the queue anyway.
+  constexpr double kWideLead = 0.75;
   // A queue whose wide items are at most three quarters of its XCD's CUs keeps them in front:
   // they all start at once and the rest of the CUs stream beside them, and none is left to
   // start late.  (A chunk of 463 tokens behind 2049 next to 49 decodes, 13 wide items a queue:
@@ -674,7 +674,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   for (auto& q : sc.queue) {
     // microseconds per item, fitted to per-work-group timestamps of the Llama-3-8B-shaped
     // batch on MI355X (D = 128, bf16; only the ratio of the two kinds matters here: wide tiles take
-    // 15 % less since, which the choice of kWideLead was measured with)
+    // 15 % less since, which kWideLead was measured with)
     auto time_of = [&](int32_t ref) {
       if (ref >= 0) {
         const WorkItem& w = sc.wide[(size_t)ref];
