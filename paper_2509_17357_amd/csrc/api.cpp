@@ -381,6 +381,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 506; }  // 0.5.6: wide tiles on 16x16x32 MFMAs; prefixes and new rows placed by one launch
+int cronus_version(void) { return 507; }  // 0.5.7: smaller workspaces accepted again; whole prompts uncut; first reference before the steady loop
 
 }  // extern "C"
