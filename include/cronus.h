@@ -154,9 +154,10 @@ int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* fi
  *                  one is accepted where it holds what versions up to 505 needed for these
  *                  lengths: chunk tiles are then cut into fewer key spans, and results can
  *                  differ in the last bf16 bit
- * The work list is built on the host during the call and read by the kernels from
- * pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
- * demand, never freed; the ninth call in flight waits on the host for one of them).  A call
+ * The work list is built on the host during the call.  A list of at most 3.75 KiB in compact form
+ * (80 decodes of 8 KV heads, uncut) travels in the main kernel's arguments; a longer one is read by
+ * the kernels from pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
+ * demand, never freed; the ninth call in flight waits on the host for one of them, either way).  A call
  * captured into a HIP graph keeps its buffer for good, since replays read it: later calls use
  * the others, and fail with CRONUS_ERR_HIP once eight calls have been captured
  * (cronus_attn_mixed_static keeps none).  The main
@@ -177,9 +178,10 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * without the workspace, same kernels, same results; the call allocates no device or pinned
  * memory and calls no allocating HIP routine.  The plan image and the partial results live in
  * a static device array inside the library (64 MiB, CRONUS_STATIC_SCRATCH_BYTES; every GPU
- * that the library runs on holds its own copy until the process ends); the work list reaches
- * it as kernel arguments on `hip_stream`, in a compact form that one launch expands (64 decodes
- * of 8 KV heads: 3 KiB, that launch alone; more: one upload launch per 3.75 KiB before it).  The first call on a device looks up that device's address of the array and
+ * that the library runs on holds its own copy until the process ends); the work list travels
+ * as kernel arguments on `hip_stream`: a compact list of at most 3.75 KiB (64 decodes of 8 KV heads: 3 KiB)
+ * in the main kernel's own, a longer one by one upload launch per 3.75 KiB and one that builds its
+ * records.  The first call on a device looks up that device's address of the array and
  * sets the kernels' attributes (no allocation either).  On the host the planner keeps its
  * per-thread arrays (ordinary heap memory, grown to the largest batch the thread has planned).
  *   - CRONUS_ERR_WORKSPACE, nothing enqueued: the batch's plan image plus partial results

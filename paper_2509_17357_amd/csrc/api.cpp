@@ -292,10 +292,17 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, co
   if (!slot) return CRONUS_ERR_HIP;
   unsigned char* const host = static_cast<unsigned char*>(slot->host);
   unsigned char* const dev_mem = static_cast<unsigned char*>(slot->dev);
-  write_plan(&plan, host + kSlotHeader);
+  // a short list travels in the launch's arguments, which the device reads sooner than host memory
+  alignas(16) unsigned char list[kListBytes];
+  CompactPlan compact{};
+  size_t list_bytes = 0;
+  const bool listed = plan.n_stage_seqs == 0 && compact_plan(cache, &plan, &compact, list, sizeof(list), &list_bytes) &&
+                      compact.ref_bytes == 2;
+  if (!listed) write_plan(&plan, host + kSlotHeader);
   // the set of queue heads that belongs to this plan buffer: free again when the buffer is
   const int set = (int)(slot - g_rings[dev].slots);
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, &plan, hip_stream,
+  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, listed ? list : nullptr,
+               compact, list_bytes, &plan, hip_stream,
                g_dev[dev].queue_sets + set * kQueueSetInts, reinterpret_cast<uint32_t*>(dev_mem), ++slot->call,
                {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
   slot->stream = stream;
@@ -339,12 +346,16 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   if (int rc = prepare_device_locked(&dev)) return rc;  // first call on a device: looks up its scratch address
   unsigned char* base = static_cast<unsigned char*>(g_dev[dev].static_scratch);
   static thread_local std::vector<unsigned char> image;  // host memory; grows to the largest plan seen
-  image.resize(plan.image_bytes);
+  image.resize(std::max(plan.image_bytes, (size_t)kListBytes));
   // the compact list, when there is one and the scratch has room to stage it behind the rest
-  CompactPlan compact;
+  CompactPlan compact{};
   size_t compact_bytes = 0;
-  if (compact_plan(cache, &plan, &compact, image.data(), plan.image_bytes, &compact_bytes) &&
-      compact_bytes <= kStaticScratchBytes - plan.image_bytes - plan.total_bytes) {
+  const bool compacted = compact_plan(cache, &plan, &compact, image.data(), plan.image_bytes, &compact_bytes);
+  // a short one travels in the main kernel's arguments
+  const bool listed = compacted && compact_bytes <= (size_t)kListBytes && compact.ref_bytes == 2;
+  if (listed) {
+    // nothing to upload
+  } else if (compacted && compact_bytes <= kStaticScratchBytes - plan.image_bytes - plan.total_bytes) {
     if (int rc = static_scratch_expand(base + plan.off_items, base + plan.image_bytes + plan.total_bytes, compact, image.data(),
                                        compact_bytes, hip_stream))
       return rc;
@@ -356,8 +367,8 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   // stored and, of the partial slots, exactly the rows that items of this call write first.
   // (The heads of the work queues, which must, live in their own small array, and every
   // launch leaves them zero.)
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, base + plan.image_bytes, base, &plan,
-               hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, base + plan.image_bytes, base,
+               listed ? image.data() : nullptr, compact, listed ? compact_bytes : 0, &plan, hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
   bool main_launched = false;
   return launch_attn(a, &main_launched);
 }

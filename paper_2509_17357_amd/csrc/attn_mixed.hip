@@ -92,7 +92,25 @@ struct AttnParams {
   unsigned done_value;
   int q_base[kQueues];
   int q_len[kQueues];
+  CompactPlan compact;  // of a list in the launch's arguments (items is not read then)
 };
+
+// A compact list (2-byte references) as a kernel argument.  Arguments lie in device memory: a work-group has them in
+// LDS 0.6 us after it starts (all 256 at once, 1 KiB as well as 3.7), where a 64-byte record of host memory takes 1.6 us,
+// and 2 next to streaming CUs.  A work-group's first record is there 2.0 us after its start (2.7 from host memory), the
+// later ones with their tickets; and the entry point that cannot allocate needs no launch that builds
+// the records first.  Measured, us a pass: 64 decodes through that entry point 113.7 -> 112.6, 11 of them 26.3 -> 23.2;
+// 16 decodes with a workspace 30.1 -> 28.9, fp8 chunk next to 48 decodes 97.2 -> 95.5.
+// Two sizes, because the host writes all of the arguments: 4 KiB cost it 1.5 us more than 1.5 KiB.
+template <int BYTES>
+struct ItemList {
+  static constexpr int kVecs = BYTES / 16;
+  u32x4 v[kVecs];
+};
+struct NoList {
+  static constexpr int kVecs = 0;
+};
+static_assert(sizeof(AttnParams) <= 256 && sizeof(AttnParams) % 8 == 0, "the arguments with a list are 4 KiB");
 
 // Narrow items: S^T row r of a 32-row MFMA tile holds key perm32(r) of the 32-key sub-tile
 // (bits 2 and 3 swapped), see the file comment.
@@ -365,7 +383,7 @@ constexpr int attn_lds_bytes() {
   constexpr int wide_lds = FP8 ? 3 * stage + 3 * tile / 2 : 4 * stage;  // stages (fp8: three, and three tiles of codes)
   constexpr int narrow_lds = kWaves * (2 * (D / 16) * 1024 + (FP8 ? 512 : 0)) + kWaves * 2 * kNarrowRows * 4;
   constexpr int lds = wide_lds > narrow_lds ? wide_lds : narrow_lds;
-  static_assert(lds % 128 == 0 && lds + 256 <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes and queue table)");
+  static_assert(lds % 128 == 0 && lds + 256 + kListBytes <= 160 * 1024, "LDS budget (the buffers, then the item loop's mailboxes, queue table and list)");
   return lds;
 }
 
@@ -373,6 +391,7 @@ constexpr int attn_lds_bytes() {
 // alternates between them, so one barrier per item separates writing and reading), then for
 // lane k = 0 .. 7 the dynamic part of queue (xcc + k) mod 8 as (items, first item).
 constexpr int kLoopLdsBytes = 2 * 64 + 2 * 4 * kQueues;
+// and then the compact list, where the launch has one.
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
@@ -382,6 +401,14 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 // none at all.
 __device__ __forceinline__ int static_items(const AttnParams& p, int x) {
   return min(p.q_len[x], ((int)gridDim.x - x + kQueues - 1) / kQueues);
+}
+
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
 }
 
 // What wave 0 needs to take the next item, and the mailbox that the next record goes to.
@@ -440,10 +467,44 @@ __device__ __forceinline__ int resolve_item(const AttnParams& p, Feed& f, int he
   }
 }
 constexpr int kNotYet = -2;  // WorkItem::wide of a mailbox that waits for its record
-// Copies the record of item idx (idx < 0: a record whose field 9, WorkItem::wide, is -1) to the
-// mailbox.  By DMA: the transfer passes no register, so only the wait for it (vmcnt, then a
-// barrier for the other waves) has to be placed.
+// Writes the record of a list's item to the mailbox, complete on return; u and ref are uniform.
+__device__ __forceinline__ void post_item(const AttnParams& p, const Feed& f, const CompactUnit& u, unsigned ref, int lane) {
+  const WorkItem w = expand_unit(p.compact, u, ref);
+  const int* const wf = reinterpret_cast<const int*>(&w);
+  int rec = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) rec = lane == i ? wf[i] : rec;
+  if (lane < 16) asm volatile("ds_write_b32 %0, %1" ::"v"(f.mail + f.turn + 4 * lane), "v"(rec) : "memory");
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+// Posts the record of item idx (idx < 0: a record whose field 9, WorkItem::wide, is -1) in the
+// mailbox.  LIST: expanded from the compact list behind the mailboxes, complete on return.
+// Otherwise copied from p.items by DMA: the transfer passes no register, so only the wait for it (vmcnt,
+// then a barrier for the other waves) has to be placed.
+template <bool LIST>
 __device__ __forceinline__ void fetch_record(const AttnParams& p, const Feed& f, int idx, int lane) {
+  if constexpr (LIST) {
+    if (idx < 0) {
+      if (lane == 9) asm volatile("ds_write_b32 %0, %1" ::"v"(f.mail + f.turn + 4 * lane), "v"(-1) : "memory");
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      return;
+    }
+    const unsigned units = f.mail + kLoopLdsBytes;
+    unsigned ref = units + p.compact.n_units * (unsigned)sizeof(CompactUnit) + 2u * (unsigned)idx;
+    asm volatile("ds_read_u16 %0, %0\n\ts_waitcnt lgkmcnt(0)" : "+v"(ref)::"memory");
+    ref = (unsigned)__builtin_amdgcn_readfirstlane((int)ref);
+    int word;  // lane i: word i & 7 of the unit
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(word)
+                 : "v"(units + unit_of_ref(p.compact, ref) * (unsigned)sizeof(CompactUnit) + 4 * (lane & 7))
+                 : "memory");
+    CompactUnit u;
+    int* const uw = reinterpret_cast<int*>(&u);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) uw[i] = __builtin_amdgcn_readlane(word, i);
+    post_item(p, f, u, ref, lane);
+    return;
+  }
   typedef const __attribute__((address_space(1))) int global_int;
   global_int* r = idx >= 0 ? (global_int*)(p.items + idx) : (global_int*)no_item;
   if (lane < 16) __builtin_amdgcn_global_load_lds(r + lane, (lds_byte*)(uintptr_t)(f.mail + f.turn), 4, 0, 0);
@@ -532,14 +593,6 @@ template <int N>
 __device__ __forceinline__ void lds_land1(u32x4& x) {
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "i"(N) : "memory");
 }
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
 // Read the NOPS 1-KiB operand planes of this lane (plane n at addr + 1024 n).
 template <int NOPS>
 __device__ __forceinline__ void lds_read_planes(u32x4 (&x)[NOPS], unsigned addr) {
@@ -623,7 +676,7 @@ __device__ __forceinline__ void lds_write_b64(unsigned addr, u32x2 v) {
 //          201 tokens behind 3000, G = 8, next to 48 decodes: 117.4 -> 111.4 us a pass).
 // For an fp8 cache the scale of K enters the exponent constant, that of V the normalisation.
 enum { kPool, kCopy, kCodes };
-template <int D, int MODE>
+template <int D, int MODE, class List>
 __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsigned char* smem) {
   constexpr bool FP8 = MODE != kPool, CODES = MODE == kCodes;
   constexpr int NSTEP = D / 16, NDT = D / 16;  // K (and V) operands of a 32-key sub-tile
@@ -787,7 +840,7 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
   int head = 0;
   bool early = false, asked = false;  // wave 0: a ticket was requested ahead; the record is on its way or there
   auto ask_next = [&]() {
-    fetch_record(p, feed, resolve_item(p, feed, head, lane), lane);
+    fetch_record<(List::kVecs > 0)>(p, feed, resolve_item(p, feed, head, lane), lane);
     asked = true;
   };
   int bt_next = 0;
@@ -1565,42 +1618,66 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
 // in index order and stalls on the first XCD without a free CU, which couples the per-XCD
 // orders of a plain one-item-per-work-group launch; a resident work-group asks for its next
 // item when it is done with the last, whichever XCD's queue still has one.
-template <int D, bool FP8>
-__global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
+template <int D, bool FP8, class List>
+__global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List list) {
   extern __shared__ __align__(1024) unsigned char smem[];
+  constexpr bool LIST = List::kVecs > 0;
   static_assert(kQueues == 8, "XCC_ID is masked to three bits");
   // hardware register XCC_ID (id 20), bits 3:0: the XCD this work-group runs on
   const int xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (kQueues - 1);
   int* const dyn = reinterpret_cast<int*>(smem + attn_lds_bytes<D, FP8>() + 128);
   Feed feed{(unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>(), 0, xcc, 0};
-  int next = -1;  // wave 0: the item this work-group starts with
+  // The record of the item that this work-group starts with is asked for first; the queue table and the list, which
+  // the items after it need, are set up meanwhile by other waves.
+  const int q0 = blockIdx.x & (kQueues - 1), i0 = blockIdx.x / kQueues;
+  bool posted = i0 < p.q_len[q0];  // the next record is in the mailbox already
   if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
-    const int lane = threadIdx.x;
-    const int y = (xcc + lane) & (kQueues - 1);
+    if (posted) {
+      const int lane = threadIdx.x, idx = p.q_base[q0] + i0;
+      if constexpr (LIST) {
+        // uniform addresses: scalar loads of the arguments
+        const unsigned* const words = reinterpret_cast<const unsigned*>(&list);
+        const unsigned ref = words[p.compact.n_units * (int)(sizeof(CompactUnit) / 4) + (idx >> 1)] >> 16 * (idx & 1) & 0xffffu;
+        CompactUnit u;
+        unsigned* const uw = reinterpret_cast<unsigned*>(&u);
 #pragma unroll
-    for (int x = 0; x < kQueues; ++x) {
-      const int n_static = static_items(p, x), i = blockIdx.x / kQueues;
-      if ((blockIdx.x & (kQueues - 1)) == (unsigned)x && i < n_static) next = p.q_base[x] + i;
-      if (lane < kQueues && x == y) {
-        dyn[2 * lane] = p.q_len[x] - n_static;
-        dyn[2 * lane + 1] = p.q_base[x] + n_static;
+        for (int i = 0; i < 8; ++i) uw[i] = words[unit_of_ref(p.compact, ref) * 8 + i];
+        post_item(p, feed, u, ref, lane);
+      } else {
+        fetch_record<false>(p, feed, idx, lane);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
     }
+  } else {
+    const int lane = threadIdx.x - (kThreads - 64);
+    if (lane >= 0 && lane < kQueues) {
+      const int y = (xcc + lane) & (kQueues - 1), n_static = static_items(p, y);
+      dyn[2 * lane] = p.q_len[y] - n_static;
+      dyn[2 * lane + 1] = p.q_base[y] + n_static;
+    }
+    if constexpr (LIST) {
+      const int v = threadIdx.x - 64;
+      if (v < List::kVecs)
+        *reinterpret_cast<u32x4*>(smem + attn_lds_bytes<D, FP8>() + kLoopLdsBytes + v * 16) = list.v[v];
+    }
   }
-  bool posted = false;  // the next record is in the mailbox already
+  bool first = true;
   for (;;) {
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));  // recomputed per item
+    if (first) __syncthreads();  // queue table, list and the first record, if there is one
     // wave 0 takes the next item and posts its record
-    if (!posted && __builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) == 0) {
       const int lane = tid;
-      if (next < 0) next = resolve_item(p, feed, request_item(p, feed, lane), lane);
-      else feed.left = __builtin_amdgcn_readfirstlane(queue_part(feed, lane).len);
-      fetch_record(p, feed, next, lane);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      next = -1;
+      if (!posted) {
+        fetch_record<LIST>(p, feed, resolve_item(p, feed, request_item(p, feed, lane), lane), lane);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      } else if (first) {
+        feed.left = __builtin_amdgcn_readfirstlane(queue_part(feed, lane).len);
+      }
     }
-    __syncthreads();  // the record is there, and every wave is done with the last item's LDS
+    if (!first || !posted) __syncthreads();  // the record is there, and every wave is done with the last item's LDS
+    first = false;
     const WorkItem it = unpack_record(read_mail(feed, feed.turn, tid & 63));
     feed.turn ^= 64;
     posted = false;
@@ -1609,12 +1686,12 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p) {
     if (it.wide) {
       if constexpr (FP8) {
         if (it.wide >= 2) {
-          posted = run_wide<D, kCopy>(p, feed, smem);
+          posted = run_wide<D, kCopy, List>(p, feed, smem);
         } else {
-          posted = run_wide<D, kCodes>(p, feed, smem);
+          posted = run_wide<D, kCodes, List>(p, feed, smem);
         }
       } else {
-        posted = run_wide<D, kPool>(p, feed, smem);
+        posted = run_wide<D, kPool, List>(p, feed, smem);
       }
     } else {
       run_narrow<D, FP8>(p, it, smem);
@@ -1674,11 +1751,18 @@ __global__ __launch_bounds__(kStageThreads) void kv_stage_kernel(AttnParams p) {
   }
 }
 
+template <int D, bool FP8, class List>
+const void* attn_kernel() {
+  auto kern = attn_mixed_kernel<D, FP8, List>;
+  return reinterpret_cast<const void*>(kern);
+}
+
 template <int D, bool FP8>
 int prepare_typed() {
-  auto kern = attn_mixed_kernel<D, FP8>;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             attn_lds_bytes<D, FP8>() + kLoopLdsBytes) == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
+  constexpr int lds = attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
+  for (const void* kern : {attn_kernel<D, FP8, NoList>(), attn_kernel<D, FP8, ItemList<kShortListBytes>>(), attn_kernel<D, FP8, ItemList<kListBytes>>()})
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds + kListBytes) != hipSuccess) return CRONUS_ERR_HIP;
+  return CRONUS_OK;
 }
 
 // Launches of one call, in order: the fp8 copy (if any sequence has one), the main kernel.  prepare_attn_kernels() must have run on this device.  The
@@ -1702,12 +1786,20 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
     }
   }
   if (pl.n_items > 0) {
-    auto kern = attn_mixed_kernel<D, FP8>;
-    if (timed)
-      hipExtLaunchKernelGGL(kern, dim3((unsigned)pl.n_workgroups), dim3(kThreads), lds, s, ev(0), ev(1), 0, p);
-    else
-      hipLaunchKernelGGL(kern, dim3((unsigned)pl.n_workgroups), dim3(kThreads), lds, s, p);
-    if (hipGetLastError() != hipSuccess) return CRONUS_ERR_HIP;
+    const void* const kern = !a.list                             ? attn_kernel<D, FP8, NoList>()
+                             : a.list_bytes <= kShortListBytes ? attn_kernel<D, FP8, ItemList<kShortListBytes>>()
+                                                               : attn_kernel<D, FP8, ItemList<kListBytes>>();
+    const int list_lds = !a.list ? 0 : a.list_bytes <= kShortListBytes ? kShortListBytes : kListBytes;
+    NoList none;
+    void* args[] = {const_cast<AttnParams*>(&p), a.list ? const_cast<void*>(a.list) : &none};
+    const dim3 grid((unsigned)pl.n_workgroups);
+    const hipError_t launched =
+        timed ? hipExtLaunchKernel(kern, grid, dim3(kThreads), args, lds + list_lds, s, ev(0), ev(1), 0)
+              : hipLaunchKernel(kern, grid, dim3(kThreads), args, lds + list_lds, s);
+    if (launched != hipSuccess) {
+      (void)hipGetLastError();
+      return CRONUS_ERR_HIP;
+    }
     *main_launched = true;
   }
   // results of key spans are merged by the main kernel itself; the outer stop event follows it
@@ -1727,41 +1819,22 @@ __global__ __launch_bounds__(256) void plan_upload_kernel(UploadChunk c, u32x4* 
   if (i < n_vec) dst[i] = c.v[i];
 }
 
-// Work items from the compact form of the list, one thread per item.  A list that fits in the
-// arguments is expanded by one launch (64 decodes, 512 items: 3 KiB, one launch where the
-// records took eleven of 2 us each); a longer one is uploaded first.
-__device__ __forceinline__ void expand_one(const CompactPlan& m, const unsigned char* src, WorkItem* items) {
+// Work items from the compact form of a list that is too long for the main kernel's arguments (it has
+// been uploaded), one thread per item.
+__global__ __launch_bounds__(256) void plan_expand_kernel(const unsigned char* src, CompactPlan m, WorkItem* items) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= m.n_items) return;
   const unsigned char* refs = src + (size_t)m.n_units * sizeof(CompactUnit);
   const uint32_t ref = m.ref_bytes == 2 ? reinterpret_cast<const uint16_t*>(refs)[i] : reinterpret_cast<const uint32_t*>(refs)[i];
   items[i] = expand_item(m, reinterpret_cast<const CompactUnit*>(src), ref);
 }
-__global__ __launch_bounds__(256) void plan_expand_args_kernel(UploadChunk c, CompactPlan m, WorkItem* items) {
-  // the arguments lie in host memory: one coalesced read of all of them, then LDS
-  __shared__ u32x4 list[kUploadVecs];
-  if (threadIdx.x < kUploadVecs) list[threadIdx.x] = c.v[threadIdx.x];
-  __syncthreads();
-  expand_one(m, reinterpret_cast<const unsigned char*>(list), items);
-}
-__global__ __launch_bounds__(256) void plan_expand_kernel(const unsigned char* src, CompactPlan m, WorkItem* items) {
-  expand_one(m, src, items);
-}
 
 }  // namespace
 
 int static_scratch_expand(void* items, void* staging, const CompactPlan& m, const void* host_src, size_t bytes, void* stream) {
-  const dim3 grid((unsigned)((m.n_items + 255) / 256));
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  WorkItem* out = static_cast<WorkItem*>(items);
-  if (bytes <= sizeof(UploadChunk)) {
-    UploadChunk c;
-    memcpy(&c, host_src, bytes);
-    hipLaunchKernelGGL(plan_expand_args_kernel, grid, dim3(256), 0, s, c, m, out);
-  } else {
-    if (int rc = static_scratch_upload(staging, host_src, bytes, stream)) return rc;
-    hipLaunchKernelGGL(plan_expand_kernel, grid, dim3(256), 0, s, static_cast<const unsigned char*>(staging), m, out);
-  }
+  if (int rc = static_scratch_upload(staging, host_src, bytes, stream)) return rc;
+  hipLaunchKernelGGL(plan_expand_kernel, dim3((unsigned)((m.n_items + 255) / 256)), dim3(256), 0, static_cast<hipStream_t>(stream),
+                     static_cast<const unsigned char*>(staging), m, static_cast<WorkItem*>(items));
   return hipGetLastError() == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
 }
 
@@ -1832,6 +1905,7 @@ int launch_attn(const AttnLaunch& a, bool* main_launched) {
     p.q_base[x] = pl.q_base[x];
     p.q_len[x] = pl.q_len[x];
   }
+  p.compact = a.compact;
   p.stage_seqs = reinterpret_cast<const StageSeq*>(image + pl.off_stage);
   p.stage_k = ws + pl.off_stage_k;
   p.stage_v = ws + pl.off_stage_v;

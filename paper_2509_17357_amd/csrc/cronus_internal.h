@@ -54,11 +54,11 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
-// Compact form of the work list, for the entry point that uploads it as kernel arguments: the
-// items of one tile of a sequence differ only by KV head and key span, so an item is a number
-// (unit * n_kv_heads + kv_head) * max_split + span (2 bytes when all fit) and a unit holds the
-// rest.  expand_item() is the one definition of what an item then is: the device builds the
-// records with it, and the host accepts the compact form only if it gives back every record.
+// Compact form of the work list: the items of one tile of a sequence differ only by KV head and
+// key span, so an item is a number (unit << head_bits | kv_head) << span_bits | span (2 bytes
+// when all fit) and a unit holds the rest.  expand_unit() is the one definition of what an item then is:
+// the device builds the records with it, and the host accepts the compact form only if it gives back
+// every record.  No divisions: the device expands an item each time that a work-group takes one.
 #if defined(__HIP__)
 #define CRONUS_HOST_DEVICE __host__ __device__
 #else
@@ -69,18 +69,18 @@ struct CompactUnit {
   uint32_t tile;      // tile of the chunk | head group << 24
   uint32_t per;       // keys per span | wide << 31
   uint32_t partial;   // first partial slot of KV head 0 | slots per KV head << 16
-  uint32_t merge;     // merge group of KV head 0 | groups per KV head << 16
+  uint32_t merge;     // merge group of KV head 0 | groups per KV head << 12 | spans << 24
 };
 static_assert(sizeof(CompactUnit) == 32, "two 16-byte vectors");
 struct CompactPlan {
-  int32_t n_items, n_units, n_kv_heads, max_split;
+  int32_t n_items, n_units, head_bits, span_bits;
   int32_t group_heads, heads_per_kv, wide_tok, ref_bytes;  // ref_bytes: 2 or 4
 };
-CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
-  const uint32_t span = ref % (uint32_t)c.max_split, rest = ref / (uint32_t)c.max_split;
-  const int32_t kvh = (int32_t)(rest % (uint32_t)c.n_kv_heads);
-  const CompactUnit u = units[rest / (uint32_t)c.n_kv_heads];
+CRONUS_HOST_DEVICE inline uint32_t unit_of_ref(const CompactPlan& c, uint32_t ref) { return ref >> (c.head_bits + c.span_bits); }
+CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const CompactUnit& u, uint32_t ref) {
+  const int32_t span = (int32_t)(ref & ((1u << c.span_bits) - 1)), kvh = (int32_t)(ref >> c.span_bits & ((1u << c.head_bits) - 1));
   const int32_t first_head = (int32_t)(u.tile >> 24) * c.group_heads, per = (int32_t)(u.per & 0x7fffffffu);
+  const int32_t n_split = (int32_t)(u.merge >> 24);
   const bool wide = u.per >> 31;
   WorkItem w;
   w.seq = u.seq;
@@ -89,12 +89,12 @@ CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const Compa
   w.n_heads = c.heads_per_kv - first_head < c.group_heads ? c.heads_per_kv - first_head : c.group_heads;
   w.q_tok0 = (int32_t)(u.tile & 0xffffffu) * c.wide_tok;
   w.n_tok = u.chunk_len - w.q_tok0 < c.wide_tok ? u.chunk_len - w.q_tok0 : c.wide_tok;
-  const int32_t kv_total = u.prefix_len + w.q_tok0 + w.n_tok, n_split = (kv_total - 1) / per + 1;
-  w.kv_begin = (int32_t)span * per;
+  const int32_t kv_total = u.prefix_len + w.q_tok0 + w.n_tok;
+  w.kv_begin = span * per;
   w.kv_end = kv_total - w.kv_begin < per ? kv_total : w.kv_begin + per;
   w.first_partial = (int32_t)(u.partial & 0xffffu) + kvh * (int32_t)(u.partial >> 16);
-  w.partial = n_split > 1 ? w.first_partial + (int32_t)span * (wide ? kWaves : 1) : -1;
-  w.merge_key = n_split * kMaxMergeGroups + (int32_t)(u.merge & 0xffffu) + kvh * (int32_t)(u.merge >> 16);
+  w.partial = n_split > 1 ? w.first_partial + span * (wide ? kWaves : 1) : -1;
+  w.merge_key = n_split * kMaxMergeGroups + (int32_t)(u.merge & 0xfffu) + kvh * (int32_t)(u.merge >> 12 & 0xfffu);
   w.wide = wide;
   w.prefix_len = u.prefix_len;
   w.chunk_len = u.chunk_len;
@@ -102,6 +102,12 @@ CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const Compa
   w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
   return w;
 }
+CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
+  return expand_unit(c, units[unit_of_ref(c, ref)], ref);
+}
+// A list of at most this many bytes and with 2-byte references travels in the main kernel's own arguments (up to
+// kShortListBytes in a smaller set of them).  More do not fit in 4 KiB next to the other arguments.
+constexpr int kListBytes = 3840, kShortListBytes = 1280;
 
 // Rows whose partial results (split over key spans) are combined, for inspection (the kernels
 // find what they need in the work items):
@@ -173,8 +179,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
 void write_plan(const Plan* plan, void* host_buf);
 // The same list in compact form ([CompactUnit x n_units | references], *bytes of buf used, a
 // multiple of 16), when it can be expressed (it holds every record) and fits in `capacity`.
-// Checking every record costs the host less than the launches it saves (host time of a static
-// call, records / compact: 512 items 66 / 26 us, 1024 110 / 49, 2800 246 / 119).
+// Checking every record costs the host less than the launches it saves the static entry point (host time of a
+// call there, records / compact: 512 items 66 / 26 us, 1024 110 / 49, 2800 246 / 119); the other one pays 1.6 us more for
+// 264 items and 2.9 for 552 than for writing the records to host memory.
 bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c, void* buf, size_t capacity, size_t* bytes);
 
 struct AttnLaunch {
@@ -186,6 +193,10 @@ struct AttnLaunch {
   float sm_scale;
   void* workspace;  // device; holds the partial results at plan->off_partials
   const void* plan_image;  // device-visible [WorkItem | MergeItem | StageSeq] image at the plan's offsets
+  const void* list;  // host, kListBytes long; the compact list that takes the place of the image's items (copied by
+                     // the launch), or nullptr
+  CompactPlan compact;
+  size_t list_bytes;
   const Plan* plan;
   void* stream;
   int* queue_set;  // device; this call's set of queue heads (kQueueSetInts ints, all zero between launches)
@@ -215,9 +226,8 @@ int static_scratch_resolve(void** device_ptr);
 // static device array, zero when the library is loaded; every launch leaves its set zero).
 int queue_sets_resolve(int** device_ptr);
 int static_scratch_upload(void* dst, const void* host_src, size_t bytes, void* stream);
-// Enqueues the launches that build the work items of a compact list at `items` (device); a list
-// that does not fit in the arguments of one launch goes through `staging` (device, 16-byte
-// aligned, `bytes` bytes).
+// Enqueues the launches that build the work items of a compact list at `items` (device), through `staging`
+// (device, 16-byte aligned, `bytes` bytes): for a list of more than kListBytes.
 int static_scratch_expand(void* items, void* staging, const CompactPlan& c, const void* host_src, size_t bytes, void* stream);
 // second may be null
 int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,

@@ -42,7 +42,9 @@ struct Scratch {
   struct Run { int32_t begin, len; float shortest; };  // a contiguous run of one group's tiles in a queue
   std::vector<Run> runs[kXcds];
   int32_t wide_tok;                    // tokens per wide tile of the last plan
-  std::vector<int32_t> unit_base;      // compact_plan: first unit of every sequence
+  // compact_plan: the unit of every item (tiles of a sequence back to back, head group by head group), and their number
+  std::vector<int32_t> wide_unit, narrow_unit;
+  long long n_units;
   std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
   std::vector<float> row_keys;         // keys of the narrow rows, one entry per sequence
   struct Busy { double until; long long cus; };
@@ -419,6 +421,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   sc.seqs.resize((size_t)n_seqs);
   sc.wide.clear();
   sc.narrow.clear();
+  sc.wide_unit.clear();
+  sc.narrow_unit.clear();
   sc.wide_cost.clear();
   sc.groups.clear();
   sc.merges.clear();
@@ -466,7 +470,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     }
   }
 
-  auto add_narrow = [&](int s, int kvh, int head0, int nh, int q_tok0, int n_tok, int kv_total) {
+  auto add_narrow = [&](int s, int kvh, int head0, int nh, int q_tok0, int n_tok, int kv_total, int32_t unit) {
     const NarrowSplit split = split_of(kv_total, span);
     int n_split = split.n;
     int per_item = split.per;
@@ -490,24 +494,28 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       w.merge_key = merge_key;
       w.wide = 0;
       sc.narrow.push_back(w);
+      sc.narrow_unit.push_back(unit);
     }
   };
 
+  long long next_unit = 0;
   for (int s = 0; s < n_seqs; ++s) {
     const int P = prefix_lens[s], C = chunk_lens[s];
     sc.seqs[(size_t)s] = SeqInfo{P, C, q_off, (P + C + kBlock - 1) / kBlock};
     q_off += C;
     if (C == 0) continue;
+    const int seq_tiles = (C + wide_tok - 1) / wide_tok;
+    const int32_t unit0 = (int32_t)std::min<long long>(next_unit, 1 << 30);  // (that many are never used)
+    next_unit += (long long)seq_tiles * n_groups;
     for (int kvh = 0; kvh < Hkv; ++kvh) {
       for (int gidx = 0; gidx < n_groups; ++gidx) {
         const int head0 = kvh * G + gidx * group;
         const int nh = std::min(group, G - gidx * group);
         if (C * group <= kNarrowRows) {
-          add_narrow(s, kvh, head0, nh, 0, C, P + C);
+          add_narrow(s, kvh, head0, nh, 0, C, P + C, unit0 + gidx);
           continue;
         }
         int32_t wide_tag = 1;
-        const int seq_tiles = (C + wide_tok - 1) / wide_tok;
         if (fp8 && (seq_tiles >= kStageMinTiles || (seq_tiles >= kStageMinTilesLong && P + C >= kStageLongKeys))) {
           const int32_t nb = (P + C + kBlock - 1) / kBlock;
           const bool listed = !sc.stages.empty() && sc.stages.back().seq == s;
@@ -523,7 +531,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         for (int t0 = 0; t0 < C; t0 += wide_tok) {
           const int nt = std::min(wide_tok, C - t0);
           if (nt * group <= kNarrowRows) {
-            add_narrow(s, kvh, head0, nh, t0, nt, P + t0 + nt);
+            add_narrow(s, kvh, head0, nh, t0, nt, P + t0 + nt, unit0 + gidx * seq_tiles + t0 / wide_tok);
             continue;
           }
           // A tile whose keys alone would keep one CU busy for much longer than a CU's fair
@@ -569,6 +577,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
             w.wide = wide_tag;
             const float cost = (float)(w.kv_end - w.kv_begin) * t.cost_per_key;
             sc.wide.push_back(w);
+            sc.wide_unit.push_back(unit0 + gidx * seq_tiles + t.t0 / wide_tok);
             sc.wide_cost.push_back(cost);
             g.cost += cost;
           }
@@ -700,6 +709,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       q[k++] = ref;
     }
   }
+  sc.n_units = next_unit;
   const size_t n_slots = sc.wide.size() + sc.narrow.size();
   {
     int32_t base = 0;
@@ -764,48 +774,51 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
   const int Hkv = cache->num_kv_heads, G = cache->num_q_heads / Hkv;
   const int group = std::min(G, kNarrowRows), n_groups = (G + group - 1) / group;
   if (n_groups > 255) return false;
-  long long n_units = 0;
-  sc.unit_base.resize(sc.seqs.size());
-  for (size_t s = 0; s < sc.seqs.size(); ++s) {
-    sc.unit_base[s] = (int32_t)std::min<long long>(n_units, 1 << 30);
-    const long long tiles = (sc.seqs[s].chunk_len + sc.wide_tok - 1) / sc.wide_tok;
-    if (tiles >= 1 << 24) return false;
-    n_units += tiles * n_groups;
-  }
-  if (plan->n_items <= 0 || n_units > (long long)(capacity / sizeof(CompactUnit))) return false;
-  auto unit_of = [&](const WorkItem& w) {
-    const SeqInfo& si = sc.seqs[(size_t)w.seq];
-    const int32_t tiles = (si.chunk_len + sc.wide_tok - 1) / sc.wide_tok, g = (w.head0 - w.kv_head * G) / group;
-    return (size_t)(sc.unit_base[(size_t)w.seq] + g * tiles + w.q_tok0 / sc.wide_tok);
-  };
+  const long long n_units = sc.n_units;
+  if (plan->n_items <= 0 || n_units > (long long)(capacity / sizeof(CompactUnit)) ||
+      (unsigned long long)n_units * sizeof(CompactUnit) + 2ull * (unsigned long long)plan->n_items > capacity)
+    return false;
   CompactUnit* units = static_cast<CompactUnit*>(buf);
   std::memset(units, 0, (size_t)n_units * sizeof(CompactUnit));
   uint32_t max_split = 1;
+  static_assert(kMaxMergeGroups <= 1 << 12, "a merge group fits in 12 bits");
   // the first span of KV head 0 fills a unit, that of KV head 1 shows the steps between heads
-  for (const auto* list : {&sc.wide, &sc.narrow})
-    for (const WorkItem& w : *list) {
+  for (const bool wide : {true, false}) {
+    const auto& list = wide ? sc.wide : sc.narrow;
+    const auto& unit = wide ? sc.wide_unit : sc.narrow_unit;
+    for (size_t k = 0; k < list.size(); ++k) {
+      const WorkItem& w = list[k];
       if (w.kv_begin != 0 || w.kv_head > 1) continue;
-      CompactUnit& u = units[unit_of(w)];
+      CompactUnit& u = units[(size_t)unit[k]];
       const SeqInfo& si = sc.seqs[(size_t)w.seq];
       const bool split = w.partial >= 0;
-      const uint32_t merge = (uint32_t)(w.merge_key % kMaxMergeGroups);
+      const uint32_t merge = (uint32_t)(w.merge_key % kMaxMergeGroups), n_split = split ? (uint32_t)(w.merge_key / kMaxMergeGroups) : 1u;
+      if (n_split > 0xffu) return false;
       if (w.kv_head == 0) {
         u = CompactUnit{w.seq, si.prefix_len, si.chunk_len, si.q_off,
                         (uint32_t)(w.q_tok0 / sc.wide_tok) | (uint32_t)((w.head0 / group) << 24),
                         (uint32_t)w.kv_end | (w.wide ? 1u << 31 : 0u), split ? (uint32_t)w.first_partial : 0u,
-                        split ? merge : 0u};
-        if (split) max_split = std::max(max_split, (uint32_t)(w.merge_key / kMaxMergeGroups));
+                        (split ? merge : 0u) | n_split << 24};
+        max_split = std::max(max_split, n_split);
         if (u.partial > 0xffffu) return false;
       } else if (split) {
-        const int64_t dp = (int64_t)w.first_partial - (u.partial & 0xffffu), dm = (int64_t)merge - (u.merge & 0xffffu);
-        if (dp < 0 || dp > 0xffff || dm < 0 || dm > 0xffff) return false;
+        const int64_t dp = (int64_t)w.first_partial - (u.partial & 0xffffu), dm = (int64_t)merge - (u.merge & 0xfffu);
+        if (dp < 0 || dp > 0xffff || dm < 0 || dm > 0xfff) return false;
         u.partial |= (uint32_t)dp << 16;
-        u.merge |= (uint32_t)dm << 16;
+        u.merge |= (uint32_t)dm << 12;
       }
     }
-  const unsigned long long numbers = (unsigned long long)n_units * Hkv * max_split;
+  }
+  auto bits_of = [](uint32_t n) {  // the least b with n <= 2^b
+    int32_t b = 0;
+    while ((uint64_t)1 << b < n) ++b;
+    return b;
+  };
+  const int32_t head_bits = bits_of((uint32_t)Hkv), span_bits = bits_of(max_split);
+  if (head_bits + span_bits > 30) return false;
+  const unsigned long long numbers = (unsigned long long)n_units << (head_bits + span_bits);
   if (numbers > 0x7fffffffull) return false;
-  *c = CompactPlan{(int32_t)plan->n_items, (int32_t)n_units, Hkv, (int32_t)max_split, group, G, sc.wide_tok,
+  *c = CompactPlan{(int32_t)plan->n_items, (int32_t)n_units, head_bits, span_bits, group, G, sc.wide_tok,
                    numbers <= 0x10000ull ? 2 : 4};
   const size_t off = (size_t)n_units * sizeof(CompactUnit);
   *bytes = align_up(off + (size_t)plan->n_items * c->ref_bytes, 16);
@@ -815,10 +828,9 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
   for (int x = 0; x < kQueues; ++x)
     for (const int32_t q : sc.queue[x]) {
       const WorkItem& w = q >= 0 ? sc.wide[(size_t)q] : sc.narrow[(size_t)~q];
-      const size_t unit = unit_of(w);
-      const uint32_t per = units[unit].per & 0x7fffffffu;
-      if (per == 0) return false;
-      const uint32_t ref = (uint32_t)((unit * (size_t)Hkv + w.kv_head) * max_split + (uint32_t)w.kv_begin / per);
+      const uint32_t unit = (uint32_t)(q >= 0 ? sc.wide_unit[(size_t)q] : sc.narrow_unit[(size_t)~q]);
+      const uint32_t span = w.partial < 0 ? 0u : (uint32_t)(w.partial - w.first_partial) / (q >= 0 ? kWaves : 1);
+      const uint32_t ref = (unit << head_bits | (uint32_t)w.kv_head) << span_bits | span;
       const WorkItem e = expand_item(*c, units, ref);
       if (e.seq != w.seq || e.kv_head != w.kv_head || e.head0 != w.head0 || e.n_heads != w.n_heads || e.q_tok0 != w.q_tok0 ||
           e.n_tok != w.n_tok || e.kv_begin != w.kv_begin || e.kv_end != w.kv_end || e.partial != w.partial || e.wide != w.wide ||
