@@ -93,6 +93,7 @@ struct AttnParams {
   int q_base[kQueues];
   int q_len[kQueues];
   CompactPlan compact;  // of a list in the launch's arguments (items is not read then)
+  int n_seqs;
 };
 
 // A compact list (2-byte references) as a kernel argument.  Arguments lie in device memory: a work-group has them in
@@ -111,6 +112,8 @@ struct NoList {
   static constexpr int kVecs = 0;
 };
 static_assert(sizeof(AttnParams) <= 256 && sizeof(AttnParams) % 8 == 0, "the arguments with a list are 4 KiB");
+
+constexpr int kNonTemporal = 2;  // cache policy operand of a transfer: the instruction's nt bit
 
 // Narrow items: S^T row r of a 32-row MFMA tile holds key perm32(r) of the 32-key sub-tile
 // (bits 2 and 3 swapped), see the file comment.
@@ -1342,6 +1345,23 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   };
   auto pin_table = [&]() { asm volatile("" : "+v"(bt_reg)); };  // wait for them here, not at each use
   load_table(0);
+  // K/V that one item reads is read non-temporally: it passes the 256 MB cache in front of the HBM by, which otherwise
+  // takes in every line that streams past (us a pass: 256 decodes of 1 .. 8 k keys 814 -> 742, 6.6 TB/s where it was 5.95;
+  // 64 of 100 .. 4000 through the static entry point 112.6 -> 100.2; four chunks next to 64 151.9 -> 144.7; fp8, a chunk next
+  // to 48, 95.5 -> 91.2; decodes of 2000 keys, cold: 4 of them 20.5 -> 19.2, 16 37.2 -> 32.8.  What is lost is the second pass
+  // over a cache that fits there: 16 such decodes over and over 29.5 -> 31.3).  K/V that other
+  // items read as well is better kept there (64 decodes of 4 k keys, groups of 8 on the same blocks: 60 us, 81
+  // non-temporally; with only the first half or quarter of the blocks shared 116 and 149, 110 and 136).  So a span that has the
+  // block at three quarters of its keys in common with one of the 16 sequences next in the batch is read the ordinary way
+  // (looking costs at most 0.4 us an item: 256 decodes of the same 2 k keys 139 -> 143), and so
+  // are head groups that share a KV head.  A policy only: an entry past a row's end that happens to be equal costs nothing but time.
+  int near_blk = -1, own_blk;
+  {
+    const int col = (it.kv_begin + (it.kv_end - it.kv_begin) / 4 * 3) >> 4;
+    const int other = it.seq + (lane & 16 ? (lane & 7) + 1 : -(lane & 7) - 1);
+    own_blk = bt[col];
+    if (lane < 32 && !(lane & 8) && other >= 0 && other < p.n_seqs) near_blk = p.block_tables[(long long)other * p.max_blocks + col];
+  }
   asm volatile("" ::: "memory");
   // Lanes without a row of their own ask for nothing (a decode has G valid rows of 32).
 #pragma unroll
@@ -1381,35 +1401,38 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(vop[t * NDB + db]), as_bf16x8(pp[t]), o[db], 0, 0, 0);
   };
 
+  auto shared = [&]() {
+    return __builtin_amdgcn_ballot_w64(near_blk == own_blk) != 0 || gi_n * p.n_kv_heads != p.n_q_heads;
+  };
   if constexpr (!FP8) {
     // K/V chunks go global -> LDS by DMA, one 16-byte chunk per lane per instruction, into
     // this wave's private planes; each lane later reads back exactly the chunk it fetched,
     // so LDS only serves as storage for loads in flight (no registers are tied up).
     lds_byte* wl = (lds_byte*)smem + wave * WAVE_LDS;
     const unsigned rd_addr = (unsigned)(unsigned long long)wl + lane * 16;  // LDS byte address
-    auto issue_k = [&](int j) {
+    auto issue_k = [&](auto nt, int j) -> void {
       const long long b0 = __builtin_amdgcn_readlane(bt_reg, 2 * (j & 31));
       const long long b1 = __builtin_amdgcn_readlane(bt_reg, 2 * (j & 31) + 1);
       const unsigned char* g =
           p.k_pool + (((pr >> 4) ? b1 : b0) * p.n_kv_heads + it.kv_head) * head_stride + k_lane_off;
 #pragma unroll
-      for (int st = 0; st < NSTEP; ++st) __builtin_amdgcn_global_load_lds(g + st * 512, wl + st * 1024, 16, 0, 0);
+      for (int st = 0; st < NSTEP; ++st) __builtin_amdgcn_global_load_lds(g + st * 512, wl + st * 1024, 16, 0, decltype(nt)::value);
     };
-    auto issue_v = [&](int j) {
+    auto issue_v = [&](auto nt, int j) -> void {
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const long long b = __builtin_amdgcn_readlane(bt_reg, 2 * (j & 31) + t);
         const unsigned char* g = p.v_pool + (b * p.n_kv_heads + it.kv_head) * head_stride + v_lane_off;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
-          __builtin_amdgcn_global_load_lds(g + db * 512, wl + (NSTEP + t * NDB + db) * 1024, 16, 0, 0);
+          __builtin_amdgcn_global_load_lds(g + db * 512, wl + (NSTEP + t * NDB + db) * 1024, 16, 0, decltype(nt)::value);
       }
     };
-    const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;  // sub-tiles wave, wave+4, ...
+    const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;  // sub-tiles wave, wave+8, ...
+    auto stream = [&](auto nt) -> void {
     if (n_iter > 0) {
-      pin_table();
-      issue_k(0);
-      issue_v(0);
+      issue_k(nt, 0);
+      issue_v(nt, 0);
     }
     pin_q();
     for (int j = 0; j < n_iter; ++j) {
@@ -1425,14 +1448,18 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
           load_table(j + 1);
           pin_table();
         }
-        issue_k(j + 1);  // the K planes are free again
+        issue_k(nt, j + 1);  // the K planes are free again
       }
       softmax(s, pp, u);
       if (has_next) wait_vmcnt<NSTEP>(); else wait_vmcnt<0>();  // V(j) landed
       lds_read_planes<NSTEP>(vop, rd_addr + NSTEP * 1024);
       compute_pv(vop, pp, u);
-      if (has_next) issue_v(j + 1);
+      if (has_next) issue_v(nt, j + 1);
     }
+    };
+    pin_table();
+    if (shared()) stream(std::integral_constant<int, 0>{});
+    else stream(std::integral_constant<int, kNonTemporal>{});
   } else {
     // fp8: the two blocks of a sub-tile are copied whole, 16 bytes per lane, into block
     // images in this wave's LDS (K: 2 x 16*D bytes, the second image 128 bytes further so
@@ -1448,7 +1475,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     const unsigned wl_addr = (unsigned)(unsigned long long)wl;
     const unsigned k_rd = wl_addr + (pr >> 4) * (BLKB + 128) + (half * 16 + (pr & 15)) * 8;
     const unsigned v_rd = wl_addr + KSET + (half * D + pr) * 8;
-    auto issue = [&](int j) {
+    auto issue = [&](auto nt, int j) -> void {
       if ((j & 31) == 0) {
         if (j) load_table(j);
         pin_table();
@@ -1460,7 +1487,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
         const unsigned char* g = p.k_pool + (b * p.n_kv_heads + it.kv_head) * BLKB + lane * 16;
 #pragma unroll
         for (int i = 0; i < NIB; ++i)
-          __builtin_amdgcn_global_load_lds(g + i * 1024, set + blk * (BLKB + 128) + i * 1024, 16, 0, 0);
+          __builtin_amdgcn_global_load_lds(g + i * 1024, set + blk * (BLKB + 128) + i * 1024, 16, 0, decltype(nt)::value);
       }
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) {
@@ -1468,7 +1495,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
         const unsigned char* g = p.v_pool + (b * p.n_kv_heads + it.kv_head) * BLKB + lane * 16;
 #pragma unroll
         for (int i = 0; i < NIB; ++i)
-          __builtin_amdgcn_global_load_lds(g + i * 1024, set + KSET + blk * BLKB + i * 1024, 16, 0, 0);
+          __builtin_amdgcn_global_load_lds(g + i * 1024, set + KSET + blk * BLKB + i * 1024, 16, 0, decltype(nt)::value);
       }
     };
     auto read_k = [&](u32x4 (&x)[NSTEP], int j) {
@@ -1488,8 +1515,9 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
       for (int n = 0; n < NSTEP; ++n) x[n] = fp8x8_to_bf16x8(r[n]);
     };
     const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;
-    if (n_iter > 0) issue(0);
-    if (n_iter > 1) issue(1);
+    auto stream = [&](auto nt) -> void {
+    if (n_iter > 0) issue(nt, 0);
+    if (n_iter > 1) issue(nt, 1);
     pin_q();
     for (int j = 0; j < n_iter; ++j) {
       const int u = wave + kWaves * j;
@@ -1502,9 +1530,13 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
       softmax(s, pp, u);
       if (more) wait_vmcnt<2 * NIK>(); else wait_vmcnt<0>();     // V(j) landed
       read_v(vop, j);
-      if (j + 2 < n_iter) issue(j + 2);                          // this set is free again
+      if (j + 2 < n_iter) issue(nt, j + 2);                          // this set is free again
       compute_pv(vop, pp, u);
     }
+    };
+    pin_table();
+    if (shared()) stream(std::integral_constant<int, 0>{});
+    else stream(std::integral_constant<int, kNonTemporal>{});
   }
 
   // Combine the waves, which covered different keys: each parks the valid rows of its O in
@@ -1906,6 +1938,7 @@ int launch_attn(const AttnLaunch& a, bool* main_launched) {
     p.q_len[x] = pl.q_len[x];
   }
   p.compact = a.compact;
+  p.n_seqs = pl.n_seqs;
   p.stage_seqs = reinterpret_cast<const StageSeq*>(image + pl.off_stage);
   p.stage_k = ws + pl.off_stage_k;
   p.stage_v = ws + pl.off_stage_v;
