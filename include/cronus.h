@@ -173,6 +173,17 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
                       float sm_scale, void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
+ * cronus_iteration - a whole iteration (section 4.4) in one call: what cronus_kv_append_pair(cache, first, second, ...) and
+ * then cronus_attn_mixed(cache, q, out, ...) do with these arguments, the same bits.  Knowing both halves, it keeps
+ * the placed rows out of the GPU's caches where the iteration is bound by streaming the decodes' K/V.
+ * Errors: those of the two calls; nothing is enqueued when either would be refused.
+ */
+int cronus_iteration(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
+                     const void* q, void* out, const int32_t* prefix_lens, const int32_t* chunk_lens,
+                     const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, float sm_scale,
+                     void* workspace, size_t workspace_bytes, void* hip_stream);
+
+/*
  * cronus_attn_mixed_static - cronus_attn_mixed for callers that cannot allocate: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
  * without the workspace, same kernels, same results; the call allocates no device or pinned

@@ -23,7 +23,7 @@ CRONUS_ERR_HIP = 4
 CRONUS_KV_BF16 = 0
 CRONUS_KV_FP8_E4M3 = 1
 
-EXPORTS = ("cronus_kv_append", "cronus_kv_append_pair", "cronus_kv_gather", "cronus_attn_mixed", "cronus_attn_mixed_static",
+EXPORTS = ("cronus_kv_append", "cronus_kv_append_pair", "cronus_kv_gather", "cronus_attn_mixed", "cronus_iteration", "cronus_attn_mixed_static",
            "cronus_attn_mixed_workspace_bytes",
            "cronus_attn_mixed_plan_stats", "cronus_attn_mixed_plan_items", "cronus_balancer_split",
            "cronus_profile_events", "cronus_probe_mfma", "cronus_probe_mfma_16x16x32", "cronus_probe_mfma_sink_floats", "cronus_status_string",
@@ -82,6 +82,8 @@ def lib() -> ctypes.CDLL:
         L.cronus_balancer_split.restype = ctypes.c_int
         L.cronus_attn_mixed.argtypes = [cp, vp, vp, vp, vp, vp, i32, i32, ctypes.c_float, vp, ctypes.c_size_t, vp]
         L.cronus_attn_mixed.restype = ctypes.c_int
+        L.cronus_iteration.argtypes = [cp, rp, rp, vp, vp, vp, vp, vp, i32, i32, ctypes.c_float, vp, ctypes.c_size_t, vp]
+        L.cronus_iteration.restype = ctypes.c_int
         L.cronus_attn_mixed_static.argtypes = [cp, vp, vp, vp, vp, vp, i32, i32, ctypes.c_float, vp]
         L.cronus_attn_mixed_static.restype = ctypes.c_int
         L.cronus_attn_mixed_workspace_bytes.argtypes = [cp, i32p, i32p, i32]
@@ -195,13 +197,14 @@ def cronus_kv_append(cache: cronus_kv_cache, k_src, v_src, cu_tokens, start_pos,
     return rc
 
 
+def _kv_rows(k, v, cu, pos, n):
+    return cronus_kv_rows(_ptr(k), _ptr(v), _ptr(cu), _ptr(pos), int(n))
+
+
 def cronus_kv_append_pair(cache: cronus_kv_cache, first, second, block_tables, max_blocks_per_seq: int, n_seqs: int,
                           stream: int = 0, check=True) -> int:
     """first, second: (k_src, v_src, cu_tokens, start_pos, n_tokens) each, device tensors (or addresses)."""
-    k, v, cu, pos, n = first
-    a = cronus_kv_rows(_ptr(k), _ptr(v), _ptr(cu), _ptr(pos), int(n))
-    k, v, cu, pos, n = second
-    b = cronus_kv_rows(_ptr(k), _ptr(v), _ptr(cu), _ptr(pos), int(n))
+    a, b = _kv_rows(*first), _kv_rows(*second)
     rc = lib().cronus_kv_append_pair(ctypes.byref(cache), ctypes.byref(a), ctypes.byref(b), _ptr(block_tables),
                                      int(max_blocks_per_seq), int(n_seqs), stream)
     if check and rc != CRONUS_OK:
@@ -311,6 +314,23 @@ def cronus_attn_mixed(cache: cronus_kv_cache, q, out, prefix_lens, chunk_lens, b
                                  int(workspace_bytes), stream)
     if check and rc != CRONUS_OK:
         raise CronusError(rc, "cronus_attn_mixed")
+    return rc
+
+
+def cronus_iteration(cache: cronus_kv_cache, first, second, q, out, prefix_lens, chunk_lens, block_tables,
+                     max_blocks_per_seq: int, sm_scale: float, workspace, workspace_bytes: int, stream: int = 0,
+                     check=True) -> int:
+    """cronus_kv_append_pair of `first` and `second`, then cronus_attn_mixed."""
+    a, b = _kv_rows(*first), _kv_rows(*second)
+    p, pp = _lens(prefix_lens)
+    c, cp = _lens(chunk_lens)
+    if p.size != c.size:
+        raise ValueError("prefix_lens and chunk_lens differ in length")
+    rc = lib().cronus_iteration(ctypes.byref(cache), ctypes.byref(a), ctypes.byref(b), _ptr(q), _ptr(out), pp, cp,
+                                _ptr(block_tables), int(max_blocks_per_seq), int(p.size), float(sm_scale),
+                                _ptr(workspace), int(workspace_bytes), stream)
+    if check and rc != CRONUS_OK:
+        raise CronusError(rc, "cronus_iteration")
     return rc
 
 

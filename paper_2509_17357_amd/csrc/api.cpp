@@ -147,19 +147,27 @@ int cronus_kv_append(const cronus_kv_cache* cache, const void* k_src, const void
   return launch_kv_append(cache, &rows, nullptr, block_tables, max_blocks_per_seq, n_seqs, hip_stream);
 }
 
-int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
-                          const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* hip_stream) {
+// Checks two sets of rows; then *first is null when there is none, *second when there are not two.
+static int check_rows(const cronus_kv_cache* cache, const cronus_kv_rows** first, const cronus_kv_rows** second,
+                      const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs) {
   if (int rc = check_cache(cache)) return rc;
-  if (!first || !second || n_seqs < 0 || max_blocks_per_seq <= 0) return CRONUS_ERR_INVALID_ARG;
-  for (const cronus_kv_rows* r : {first, second}) {
+  if (!*first || !*second || n_seqs < 0 || max_blocks_per_seq <= 0) return CRONUS_ERR_INVALID_ARG;
+  for (const cronus_kv_rows* r : {*first, *second}) {
     if (r->n_tokens < 0) return CRONUS_ERR_INVALID_ARG;
     if (r->n_tokens > 0 && n_seqs > 0 && (!r->k_src || !r->v_src || !r->cu_tokens || !r->start_pos || !block_tables))
       return CRONUS_ERR_INVALID_ARG;
   }
-  if (first->n_tokens == 0) std::swap(first, second);
-  if (first->n_tokens == 0 || n_seqs == 0) return CRONUS_OK;
-  return launch_kv_append(cache, first, second->n_tokens > 0 ? second : nullptr, block_tables, max_blocks_per_seq, n_seqs,
-                          hip_stream);
+  if ((*first)->n_tokens == 0) std::swap(*first, *second);
+  if ((*second)->n_tokens == 0 || n_seqs == 0) *second = nullptr;
+  if ((*first)->n_tokens == 0 || n_seqs == 0) *first = nullptr;
+  return CRONUS_OK;
+}
+
+int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
+                          const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* hip_stream) {
+  if (int rc = check_rows(cache, &first, &second, block_tables, max_blocks_per_seq, n_seqs)) return rc;
+  if (!first) return CRONUS_OK;
+  return launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream);
 }
 
 int cronus_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, const int32_t* cu_tokens,
@@ -261,16 +269,40 @@ int check_attn_args(const cronus_kv_cache* cache, const void* q, const void* out
   return CRONUS_OK;
 }
 
-}  // namespace
+// Whether an iteration places its rows past the caches: where streaming the decodes' K/V takes at least twice as
+// long as the products of the chunks, and 20 us.  Such an iteration is bound by the HBM, which then also takes back what
+// the scatter left behind; elsewhere the chunk tiles read the rows from the cache.  (us a pass, cached / past the
+// caches: 4 chunks next to 64 decodes, streaming 95 us and products 36, 140.3 / 129.8; a chunk next to 49, 41 and 13, 69.4 / 65.8; fp8,
+// 53 and 17, 90.1 / 87.0; 82 decodes, 68 and 0.4, 82.2 / 79.7.  The other side: 66 and 36 122.6 / 122.6, 105 and 121
+// 226 / 229, 24 and 113 172.3 / 174.2, 0 and 771 799 / 808; 8 and 1 32.2 / 32.8.)
+bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens, int32_t n_seqs) {
+  const int group = std::min(cache->num_q_heads / cache->num_kv_heads, kNarrowRows);
+  double stream_us = 0, product_us = 0;
+  for (int s = 0; s < n_seqs; ++s) {
+    const double P = prefix_lens[s], C = chunk_lens[s];
+    if (C * group > kNarrowRows) product_us += C * P + C * (C + 1) / 2;
+    else if (C > 0) stream_us += P + C;
+  }
+  const double elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2;
+  stream_us *= 2.0 * elem_bytes * cache->num_kv_heads * cache->head_dim / 6e6;  // 6 TB/s
+  product_us *= 4.0 * cache->num_q_heads * cache->head_dim / 1.2e9;             // 1.2 PFLOP/s
+  return stream_us >= 20 && stream_us >= 2 * product_us;
+}
 
-int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, const int32_t* prefix_lens,
-                      const int32_t* chunk_lens, const int32_t* block_tables, int32_t max_blocks_per_seq,
-                      int32_t n_seqs, float sm_scale, void* workspace, size_t workspace_bytes, void* hip_stream) {
+// cronus_attn_mixed behind the placing of the rows of `first` and `second` (null: none).
+int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const void* q, void* out,
+               const int32_t* prefix_lens, const int32_t* chunk_lens, const int32_t* block_tables, int32_t max_blocks_per_seq,
+               int32_t n_seqs, float sm_scale, void* workspace, size_t workspace_bytes, void* hip_stream) {
+  auto place = [&]() -> int {
+    if (!first) return CRONUS_OK;
+    return launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream,
+                            rows_past_cache(cache, prefix_lens, chunk_lens, n_seqs));
+  };
   long long total_q = 0;
   if (int rc = check_attn_args(cache, q, out, prefix_lens, chunk_lens, block_tables, max_blocks_per_seq, n_seqs,
                                sm_scale, &total_q))
     return rc;
-  if (total_q == 0) return CRONUS_OK;
+  if (total_q == 0) return place();
 
   Plan plan;
   const int n_cus = device_cus();
@@ -290,6 +322,7 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, co
   if (int rc = prepare_device_locked(&dev)) return rc;
   Slot* slot = acquire_slot(dev, plan.image_bytes, stream, lock);
   if (!slot) return CRONUS_ERR_HIP;
+  if (int rc = place()) return rc;  // the plan buffer has not been used
   unsigned char* const host = static_cast<unsigned char*>(slot->host);
   unsigned char* const dev_mem = static_cast<unsigned char*>(slot->dev);
   // a short list travels in the launch's arguments, which the device reads sooner than host memory
@@ -316,6 +349,24 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, co
     slot->state = Slot::kFree;
   }
   return rc;
+}
+
+}  // namespace
+
+int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out, const int32_t* prefix_lens,
+                      const int32_t* chunk_lens, const int32_t* block_tables, int32_t max_blocks_per_seq,
+                      int32_t n_seqs, float sm_scale, void* workspace, size_t workspace_bytes, void* hip_stream) {
+  return attn_mixed(cache, nullptr, nullptr, q, out, prefix_lens, chunk_lens, block_tables, max_blocks_per_seq, n_seqs, sm_scale,
+                    workspace, workspace_bytes, hip_stream);
+}
+
+int cronus_iteration(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const void* q,
+                     void* out, const int32_t* prefix_lens, const int32_t* chunk_lens, const int32_t* block_tables,
+                     int32_t max_blocks_per_seq, int32_t n_seqs, float sm_scale, void* workspace, size_t workspace_bytes,
+                     void* hip_stream) {
+  if (int rc = check_rows(cache, &first, &second, block_tables, max_blocks_per_seq, n_seqs)) return rc;
+  return attn_mixed(cache, first, second, q, out, prefix_lens, chunk_lens, block_tables, max_blocks_per_seq, n_seqs, sm_scale,
+                    workspace, workspace_bytes, hip_stream);
 }
 
 int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* out, const int32_t* prefix_lens,

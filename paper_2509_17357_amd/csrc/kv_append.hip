@@ -77,12 +77,19 @@ struct AppendRows {
   const int* start_pos;
 };
 
+template <bool PAST_CACHE, class T>
+__device__ __forceinline__ void store_chunk(void* p, T v) {
+  if constexpr (PAST_CACHE) __builtin_nontemporal_store(v, static_cast<T*>(p));
+  else *static_cast<T*>(p) = v;
+}
+
 // Work-group g of a set's part of the grid's x dimension serves sequence s = the last one with
 // first_group(s) <= g, where first_group(s) = cu_tokens[s] / 16 + 2 s, and within it the
 // j-th cache block the rows touch, j = g - first_group(s).  A sequence with n rows
 // touches at most n / 16 + 2 blocks, which is what this numbering reserves; work-groups
 // past the last touched block have nothing to do.  Host side: n_tokens/16 + 2 n_seqs + 1 work-groups a set.
-template <bool FP8>
+// PAST_CACHE: whole chunks are stored non-temporally (the caller's rule: cronus_iteration).
+template <bool FP8, bool PAST_CACHE>
 __global__ __launch_bounds__(256) void kv_append_kernel(
     AppendRows first, AppendRows second, int first_groups, void* __restrict__ k_pool, void* __restrict__ v_pool,
     const float* __restrict__ k_scale, const float* __restrict__ v_scale, const int* __restrict__ block_tables,
@@ -118,12 +125,12 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
   if (mine) {
     const long long k_off = head_base + ((long long)dc * 16 + slot) * 8;
     if constexpr (!FP8) {
-      *reinterpret_cast<u32x4*>(static_cast<unsigned short*>(k_pool) + k_off) = kk;
+      store_chunk<PAST_CACHE>(static_cast<unsigned short*>(k_pool) + k_off, kk);
     } else {
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = __uint_as_float((e & 1) ? (kk[e >> 1] & 0xffff0000u) : (kk[e >> 1] << 16));
-      *reinterpret_cast<u32x2*>(static_cast<unsigned char*>(k_pool) + k_off) = quant_e4m3_x8(x, make_quantiser(k_scale[head]));
+      store_chunk<PAST_CACHE>(static_cast<unsigned char*>(k_pool) + k_off, quant_e4m3_x8(x, make_quantiser(k_scale[head])));
     }
   }
   // ---- V: through LDS; thread (dc, kc, jj) then owns the chunk of d = 8 dc + jj, slots 8 kc .. 8 kc + 7
@@ -148,7 +155,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
           u32x4 o;
 #pragma unroll
           for (int x = 0; x < 4; ++x) o[x] = el[2 * x] | (el[2 * x + 1] << 16);
-          *reinterpret_cast<u32x4*>(vp) = o;
+          store_chunk<PAST_CACHE>(vp, o);
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
@@ -161,7 +168,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
         const u32x2 packed = quant_e4m3_x8(x, make_quantiser(v_scale[head]));
         unsigned char* vp = static_cast<unsigned char*>(v_pool) + v_off;
         if (c_hi - c_lo == 8) {
-          *reinterpret_cast<u32x2*>(vp) = packed;
+          store_chunk<PAST_CACHE>(vp, packed);
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(
 }  // namespace
 
 int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
-                     const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* stream) {
+                     const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* stream, bool past_cache) {
   auto groups_of = [&](const cronus_kv_rows* r) { return r ? (long long)r->n_tokens / 16 + 2LL * n_seqs + 1 : 0; };
   const long long groups = groups_of(first) + groups_of(second);
   if (groups > 0x7fffffffLL || cache->num_kv_heads > 65535) return CRONUS_ERR_INVALID_ARG;
@@ -185,7 +192,9 @@ int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, 
              : AppendRows{};
   };
   const dim3 grid((unsigned)groups, (unsigned)cache->num_kv_heads);
-  auto kernel = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? kv_append_kernel<true> : kv_append_kernel<false>;
+  const bool fp8 = cache->kv_dtype == CRONUS_KV_FP8_E4M3;
+  auto kernel = past_cache ? (fp8 ? kv_append_kernel<true, true> : kv_append_kernel<false, true>)
+                           : (fp8 ? kv_append_kernel<true, false> : kv_append_kernel<false, false>);
   hipLaunchKernelGGL(kernel, grid, dim3(256), 0, static_cast<hipStream_t>(stream), rows_of(first), rows_of(second),
                      (int)groups_of(first), cache->k_cache, cache->v_cache, cache->k_scale, cache->v_scale, block_tables,
                      max_blocks_per_seq, n_seqs, cache->num_kv_heads, cache->head_dim);

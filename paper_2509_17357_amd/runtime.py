@@ -4,9 +4,10 @@ every computation through the C ABI (binding.py).  No oracle, no fallback.
 The hot path of one iteration (Cronus section 4.2 and 4.4) is, in order:
   1. ingest_prefix  - cronus_kv_append of the transferred prefix KV of the continuation
                       chunks (start_pos = 0)
-  2. append_new     - cronus_kv_append of this iteration's K/V rows (start_pos = prefix); a step does
-                      1 and 2 in one launch (place_rows, cronus_kv_append_pair)
-  3. attention      - cronus_attn_mixed over chunks and decodes
+  2. append_new     - cronus_kv_append of this iteration's K/V rows (start_pos = prefix); place_rows does
+                      1 and 2 in one launch (cronus_kv_append_pair)
+  3. attention      - cronus_attn_mixed over chunks and decodes; a step is one call for all three
+                      (cronus_iteration)
 The contexts of the decode requests were cached by earlier iterations; here they are
 placed by setup_decode_context(), which is set-up, not part of the iteration.
 """
@@ -145,13 +146,14 @@ class DeviceIteration:
         return B.cronus_kv_append(self.cache, self.new_k, self.new_v, self.cu_new, self.prefix_pos,
                                   self.block_tables, b.max_blocks, b.n_seqs, self.n_new_tokens, self._stream())
 
+    def _rows(self):
+        return ((self.prefix_k, self.prefix_v, self.cu_prefix, self.zero_pos, self.n_prefix_tokens),
+                (self.new_k, self.new_v, self.cu_new, self.prefix_pos, self.n_new_tokens))
+
     def place_rows(self, stream=None):
         """ingest_prefix and append_new in one launch (the rows go to different slots)."""
         b = self.batch
-        return B.cronus_kv_append_pair(self.cache,
-                                       (self.prefix_k, self.prefix_v, self.cu_prefix, self.zero_pos, self.n_prefix_tokens),
-                                       (self.new_k, self.new_v, self.cu_new, self.prefix_pos, self.n_new_tokens),
-                                       self.block_tables, b.max_blocks, b.n_seqs,
+        return B.cronus_kv_append_pair(self.cache, *self._rows(), self.block_tables, b.max_blocks, b.n_seqs,
                                        self._stream() if stream is None else stream)
 
     def ensure_workspace(self):
@@ -172,7 +174,8 @@ class DeviceIteration:
                                    self._stream() if stream is None else stream)
 
     def step(self):
-        """One pass of the whole hot path (after setup_decode_context())."""
-        stream = self._stream()  # looked up once: 1.9 us each time
-        self.place_rows(stream)
-        self.attention(stream)
+        """One pass of the whole hot path (after setup_decode_context()): place_rows and attention in one call."""
+        b = self.batch
+        self.ensure_workspace()
+        B.cronus_iteration(self.cache, *self._rows(), self.q, self.out, b.prefix_lens, b.chunk_lens, self.block_tables,
+                           b.max_blocks, self.sm_scale, self.workspace, self.workspace_bytes, self._stream())
