@@ -154,10 +154,9 @@ int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* fi
  *                  one is accepted where it holds what versions up to 505 needed for these
  *                  lengths: chunk tiles are then cut into fewer key spans, and results can
  *                  differ in the last bf16 bit
- * The work list is built on the host during the call.  A list of at most 3.75 KiB in compact form
- * (80 decodes of 8 KV heads, uncut) travels in the main kernel's arguments; a longer one is read by
- * the kernels from pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
- * demand, never freed; the ninth call in flight waits on the host for one of them, either way).  A call
+ * The work list is built on the host during the call and read by the kernels from
+ * pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
+ * demand, never freed; the ninth call in flight waits on the host for one of them).  A call
  * captured into a HIP graph keeps its buffer for good, since replays read it: later calls use
  * the others, and fail with CRONUS_ERR_HIP once eight calls have been captured
  * (cronus_attn_mixed_static keeps none).  The main
@@ -176,7 +175,8 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * cronus_iteration - a whole iteration (section 4.4) in one call: what cronus_kv_append_pair(cache, first, second, ...) and
  * then cronus_attn_mixed(cache, q, out, ...) do with these arguments, the same bits.  Knowing both halves, it keeps
  * the placed rows out of the GPU's caches where the iteration is bound by streaming the decodes' K/V.
- * Errors: those of the two calls; nothing is enqueued when either would be refused.
+ * Errors: those of the two calls.  Null pointers, negative lengths and unsupported shapes are found before anything is
+ * enqueued; the rows have been placed when the attention is refused for its lengths or its workspace, as by the two calls.
  */
 int cronus_iteration(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
                      const void* q, void* out, const int32_t* prefix_lens, const int32_t* chunk_lens,

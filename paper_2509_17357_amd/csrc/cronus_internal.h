@@ -105,7 +105,7 @@ CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const Compa
 CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
   return expand_unit(c, units[unit_of_ref(c, ref)], ref);
 }
-// A list of at most this many bytes and with 2-byte references travels in the main kernel's own arguments (up to
+// A static call's list of at most this many bytes and with 2-byte references travels in the main kernel's own arguments (up to
 // kShortListBytes in a smaller set of them).  More do not fit in 4 KiB next to the other arguments.
 constexpr int kListBytes = 3840, kShortListBytes = 1280;
 
@@ -180,8 +180,9 @@ void write_plan(const Plan* plan, void* host_buf);
 // The same list in compact form ([CompactUnit x n_units | references], *bytes of buf used, a
 // multiple of 16), when it can be expressed (it holds every record) and fits in `capacity`.
 // Checking every record costs the host less than the launches it saves the static entry point (host time of a
-// call there, records / compact: 512 items 66 / 26 us, 1024 110 / 49, 2800 246 / 119); the other one pays 1.6 us more for
-// 264 items and 2.9 for 552 than for writing the records to host memory.
+// call there, records / compact: 512 items 66 / 26 us, 1024 110 / 49, 2800 246 / 119).  The other one writes its
+// records to host memory: a compact list as an argument saves it 0.5 us of device time a launch, but costs the host 1.6 us more for
+// 264 items, 2.9 for 552 and 8 on a first pass.
 bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c, void* buf, size_t capacity, size_t* bytes);
 
 struct AttnLaunch {

