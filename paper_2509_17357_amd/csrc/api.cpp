@@ -436,6 +436,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 507; }  // 0.5.7: smaller workspaces accepted again; whole prompts uncut; first reference before the steady loop
+int cronus_version(void) { return 508; }  // 0.5.8: decode K/V past the cache; cronus_iteration; the static list in the arguments
 
 }  // extern "C"

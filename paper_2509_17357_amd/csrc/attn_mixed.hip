@@ -96,12 +96,11 @@ struct AttnParams {
   int n_seqs;
 };
 
-// A compact list (2-byte references) as a kernel argument.  Arguments lie in device memory: a work-group has them in
+// A compact list (2-byte references) as a kernel argument of a call of the static entry point, which otherwise needs a
+// launch of 4.6 us that builds the records first.  Arguments lie in device memory: a work-group has them in
 // LDS 0.6 us after it starts (all 256 at once, 1 KiB as well as 3.7), where a 64-byte record of host memory takes 1.6 us,
-// and 2 next to streaming CUs.  A work-group's first record is there 2.0 us after its start (2.7 from host memory), the
-// later ones with their tickets; and the entry point that cannot allocate needs no launch that builds
-// the records first.  Measured, us a pass: 64 decodes through that entry point 113.7 -> 112.6, 11 of them 26.3 -> 23.2;
-// 16 decodes with a workspace 30.1 -> 28.9, fp8 chunk next to 48 decodes 97.2 -> 95.5.
+// and 2 next to streaming CUs; the first record is there 2.0 us after the start.  Measured, us a pass: 64 decodes
+// 113.7 -> 112.6, 11 of them 26.3 -> 23.2, 9 of 65 .. 786 keys 21.4 -> 18.3.
 // Two sizes, because the host writes all of the arguments: 4 KiB cost it 1.5 us more than 1.5 KiB.
 template <int BYTES>
 struct ItemList {
