@@ -25,7 +25,7 @@
  *     consumed before the call returns.
  *   - Return value: a cronus_status.  Arguments are checked on the host before
  *     anything is launched: INVALID_ARG, UNSUPPORTED and WORKSPACE mean that nothing has
- *     been enqueued.  CRONUS_ERR_HIP reports a failed HIP runtime call; one-time set-up
+ *     been enqueued (cronus_iteration: except its rows, for a workspace that is too small).  CRONUS_ERR_HIP reports a failed HIP runtime call; one-time set-up
  *     (kernel attributes, the plan buffers) precedes the first launch of a call, but a
  *     failed launch or event record can leave earlier kernels of the same call enqueued,
  *     and the outputs of that call are then undefined.
@@ -175,8 +175,9 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * cronus_iteration - a whole iteration (section 4.4) in one call: what cronus_kv_append_pair(cache, first, second, ...) and
  * then cronus_attn_mixed(cache, q, out, ...) do with these arguments, the same bits.  Knowing both halves, it keeps
  * the placed rows out of the GPU's caches where the iteration is bound by streaming the decodes' K/V.
- * Errors: those of the two calls.  Null pointers, negative lengths and unsupported shapes are found before anything is
- * enqueued; the rows have been placed when the attention is refused for its lengths or its workspace, as by the two calls.
+ * Errors: those of the two calls, found before anything is enqueued, with two exceptions: the rows have been placed, and the
+ * attention has not been enqueued, when CRONUS_ERR_WORKSPACE reports a workspace that is too small (the plan that tells is built while the
+ * rows are placed) and when CRONUS_ERR_HIP reports the attention's set-up.
  */
 int cronus_iteration(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
                      const void* q, void* out, const int32_t* prefix_lens, const int32_t* chunk_lens,

@@ -289,6 +289,8 @@ bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, c
   return stream_us >= 20 && stream_us >= 2 * product_us;
 }
 
+bool workspace_refused(const void* workspace) { return !workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u); }
+
 // cronus_attn_mixed behind the placing of the rows of `first` and `second` (null: none).
 int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const void* q, void* out,
                const int32_t* prefix_lens, const int32_t* chunk_lens, const int32_t* block_tables, int32_t max_blocks_per_seq,
@@ -297,8 +299,15 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   if (int rc = check_attn_args(cache, q, out, prefix_lens, chunk_lens, block_tables, max_blocks_per_seq, n_seqs,
                                sm_scale, &total_q))
     return rc;
-  // before the plan is built, so that the device works meanwhile (whole prompts, a first pass 446 -> 400 us)
   if (first) {
+    // What build_plan and the workspace refuse: no row is placed for these lengths, whose scatter would read the table
+    // beyond the sequence's own entries.
+    if (total_q > 0) {
+      for (int s = 0; s < n_seqs; ++s)
+        if ((long long)prefix_lens[s] + chunk_lens[s] > (long long)max_blocks_per_seq * kBlock) return CRONUS_ERR_INVALID_ARG;
+      if (workspace_refused(workspace)) return CRONUS_ERR_WORKSPACE;
+    }
+    // before the plan is built, so that the device works meanwhile (whole prompts, a first pass: 446 us with the plan first, 400)
     if (int rc = launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream,
                                   rows_past_cache(cache, prefix_lens, chunk_lens, n_seqs)))
       return rc;
@@ -308,7 +317,7 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   Plan plan;
   const int n_cus = device_cus();
   if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, n_cus, &plan)) return rc;
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return CRONUS_ERR_WORKSPACE;
+  if (workspace_refused(workspace)) return CRONUS_ERR_WORKSPACE;
   // a workspace that served these lengths before the tiles were cut finer still does
   if (workspace_bytes < plan.total_bytes) {
     if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, n_cus, &plan, true, 0, true)) return rc;

@@ -136,3 +136,40 @@ def test_error_paths_forced_from_the_host():
         # valid arguments, no device: the set-up that precedes the first launch reports it
         assert call(c, fake, fake, [40], [3], fake, fake, need) == B.CRONUS_ERR_HIP
         assert B.cronus_kv_append(c, fake, fake, fake, fake, fake, 4, 1, 5, check=False) == B.CRONUS_ERR_HIP
+
+
+def test_iteration_errors_forced_from_the_host():
+    """cronus_iteration refuses before it places a row what the host can see: both calls' arguments, lengths that do not fit the
+    table (their rows would go to other sequences' blocks), a workspace that is missing or misaligned.  (Without a GPU a call that gets as far as a
+    launch ends in CRONUS_ERR_HIP, so these codes also show that nothing was launched.)"""
+    import torch
+    fake = 0x7F0000001000
+    c = B.make_cache(fake, fake, 100, 8, 2, 64)
+    rows, none = (fake, fake, fake, fake, 3), (None, None, None, None, 0)
+
+    def call(P, C, cache=c, first=rows, second=rows, q=fake, out=fake, bt=fake, ws=fake, ws_bytes=1 << 20, max_blocks=4, scale=0.125):
+        return B.cronus_iteration(cache, first, second, q, out, P, C, bt, max_blocks, scale, ws, ws_bytes, check=False)
+
+    bad = B.CRONUS_ERR_INVALID_ARG
+    for first, second in ((rows, rows), (rows, none), (none, rows)):
+        assert call([62], [3], first=first, second=second) == bad                 # 65 keys > 4 blocks
+        assert call([40, 65], [3, 0], first=first, second=second) == bad          # a skipped sequence's too
+        assert call([2147483647], [2147483647], first=first, second=second) == bad
+        assert call([62], [3], first=first, second=second, ws=None) == bad
+        assert call([40], [3], first=first, second=second, ws=None) == B.CRONUS_ERR_WORKSPACE
+        assert call([40], [3], first=first, second=second, ws=fake + 8) == B.CRONUS_ERR_WORKSPACE
+        for kw in (dict(q=None), dict(out=None), dict(bt=None), dict(scale=0.0), dict(scale=float("nan")), dict(max_blocks=0),
+                   dict(cache=B.make_cache(None, fake, 100, 8, 2, 64))):
+            assert call([40], [3], first=first, second=second, **kw) == bad, kw
+        assert call([-1], [3], first=first, second=second) == bad and call([40], [-3], first=first, second=second) == bad
+        assert call([40], [3], first=first, second=second, cache=B.make_cache(fake, fake, 100, 8, 2, 96)) == B.CRONUS_ERR_UNSUPPORTED
+    for k in range(4):  # a null pointer in a set that has rows; a negative count
+        broken = tuple(None if i == k else fake for i in range(4)) + (3,)
+        assert call([40], [3], first=broken) == bad and call([40], [3], second=broken) == bad
+    assert call([40], [3], first=(fake, fake, fake, fake, -1)) == bad
+    assert call([], []) == B.CRONUS_OK and call([40, 7], [0, 0], first=none, second=none, ws=None, ws_bytes=0) == B.CRONUS_OK  # nothing to do
+    assert call([40], [3], first=none, second=none, ws_bytes=0) == B.CRONUS_ERR_WORKSPACE
+    if not torch.cuda.is_available():
+        assert call([40], [3]) == B.CRONUS_ERR_HIP       # valid, no device
+        assert call([61], [3]) == B.CRONUS_ERR_HIP       # exactly four blocks
+        assert call([40, 99], [0, 0]) == B.CRONUS_ERR_HIP  # no query rows: only the rows are placed, as by cronus_kv_append_pair

@@ -81,6 +81,13 @@ def test_replays_and_refusals():
     fresh(it)
     before = state(it)
     assert call(None, it.workspace_bytes) == B.CRONUS_ERR_INVALID_ARG and same(state(it), before)
+    # refused on the host, with nothing enqueued: a sequence longer than its row of the table, no workspace
+    long = b.prefix_lens.copy()
+    long[-1] = 16 * b.max_blocks
+    for P, ws, code in ((long, it.workspace, B.CRONUS_ERR_INVALID_ARG), (b.prefix_lens, None, B.CRONUS_ERR_WORKSPACE)):
+        assert B.cronus_iteration(it.cache, *it._rows(), it.q, it.out, P, b.chunk_lens, it.block_tables, b.max_blocks, it.sm_scale, ws,
+                                  it.workspace_bytes, it._stream(), check=False) == code
+        assert same(state(it), before)
     assert call(it.q, 256) == B.CRONUS_ERR_WORKSPACE  # found when the plan is built: the rows are there, the output is not
     got = state(it)
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and np.array_equal(got[2], before[2])
