@@ -34,7 +34,7 @@
  *     serialised by one lock (not held while a call waits for a plan buffer).
  *   - Block ids in block tables are NOT checked on the device: an id outside
  *     [0, num_blocks) or two rows mapped to one slot in a single call is undefined
- *     behaviour.  Table entries past ceil(len/16) are never used and may hold
+ *     behaviour.  Table entries past ceil(len/16) are never read and may hold
  *     anything; cache slots past a sequence's length are never used as data.
  *
  * Paged cache layout (block_size = 16 tokens; E = element: bf16 = 2 bytes, or one

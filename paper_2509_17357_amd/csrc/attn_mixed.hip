@@ -93,7 +93,6 @@ struct AttnParams {
   int q_base[kQueues];
   int q_len[kQueues];
   CompactPlan compact;  // of a list in the launch's arguments (items is not read then)
-  int n_seqs;
 };
 
 // A compact list (2-byte references) as a kernel argument of a call of the static entry point, which otherwise needs a
@@ -469,9 +468,11 @@ __device__ __forceinline__ int resolve_item(const AttnParams& p, Feed& f, int he
   }
 }
 constexpr int kNotYet = -2;  // WorkItem::wide of a mailbox that waits for its record
-// Writes the record of a list's item to the mailbox, complete on return; u and ref are uniform.
+// Writes the record of a list's item to the mailbox, complete on return; u and ref are uniform.  The peers of a narrow item
+// are left to run_narrow, which has the units at hand: in their place (>= 0) stands the item's own unit.
 __device__ __forceinline__ void post_item(const AttnParams& p, const Feed& f, const CompactUnit& u, unsigned ref, int lane) {
-  const WorkItem w = expand_unit(p.compact, u, ref);
+  WorkItem w = expand_unit(p.compact, u, ref);
+  if (!w.wide && w.peers == 0) w.peers = (int)unit_of_ref(p.compact, ref);
   const int* const wf = reinterpret_cast<const int*>(&w);
   int rec = 0;
 #pragma unroll
@@ -1290,7 +1291,7 @@ __device__ __forceinline__ void lds_read4_b64(u32x2 (&x)[4], unsigned addr) {
       : "memory");
 }
 
-template <int D, bool FP8>
+template <int D, bool FP8, bool LIST>
 __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& it, unsigned char* smem) {
   constexpr int NSTEP = D / 16, NDB = D / 32;
   constexpr int ESZ = FP8 ? 1 : 2;
@@ -1300,7 +1301,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   asm volatile("" : "+v"(tid));  // recomputed per item: lane terms kept across the item loop would cost the loops registers
   const int lane = tid & 63, half = lane >> 5, c32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, it.n_blocks};
+  const SeqInfo si = {it.prefix_len, it.chunk_len, it.q_off, (it.prefix_len + it.chunk_len + kBlock - 1) / kBlock};
   const int gi_n = it.n_heads;
   const int rows_valid = it.n_tok * gi_n;  // <= 32
   const int kv_len = si.prefix_len + si.chunk_len;
@@ -1355,15 +1356,28 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   // over a cache that fits there: 16 such decodes over and over 29.5 -> 31.3).  K/V that other
   // items read as well is better kept there (64 decodes of 4 k keys, groups of 8 on the same blocks: 60 us, 81
   // non-temporally; with only the first half or quarter of the blocks shared 116 and 149, 110 and 136).  So a span that has the
-  // block at three quarters of its keys in common with one of the 16 sequences next in the batch is read the ordinary way
+  // block at three quarters of its keys in common with one of its peers, the 16 sequences next in the batch that have this column, is read the ordinary way
   // (looking costs at most 0.4 us an item: 256 decodes of the same 2 k keys 139 -> 143), and so
-  // are head groups that share a KV head.  A policy only: an entry past a row's end that happens to be equal costs nothing but time.
-  int near_blk = -1, own_blk;
+  // are head groups that share a KV head.
+  int peer_blk = -1, own_blk;
   {
-    const int col = (it.kv_begin + (it.kv_end - it.kv_begin) / 4 * 3) >> 4;
-    const int other = it.seq + (lane & 16 ? (lane & 7) + 1 : -(lane & 7) - 1);
+    const int col = peer_column(it.kv_begin, it.kv_end), offset = peer_offset(lane & 15);
     own_blk = bt[col];
-    if (lane < 32 && !(lane & 8) && other >= 0 && other < p.n_seqs) near_blk = p.block_tables[(long long)other * p.max_blocks + col];
+    bool look = lane < 2 * kPeers;
+    if constexpr (LIST) {
+      const int unit = it.peers + offset;
+      look = look && it.peers >= 0 && unit >= 0 && unit < p.compact.n_units;
+      const unsigned units = (unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
+      u32x4 v;  // the first half of the unit
+      asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(v)
+                   : "v"(units + (look ? unit : 0) * (unsigned)sizeof(CompactUnit))
+                   : "memory");
+      look = look && is_peer(CompactUnit{(int)v[0], (int)v[1], (int)v[2], (int)v[3], 0, 0, 0, 0}, it.seq, offset, col);
+    } else {
+      look = look && (max(it.peers, 0) >> (lane & 15) & 1);
+    }
+    if (look) peer_blk = p.block_tables[(long long)(it.seq + offset) * p.max_blocks + col];
   }
   asm volatile("" ::: "memory");
   // Lanes without a row of their own ask for nothing (a decode has G valid rows of 32).
@@ -1405,7 +1419,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   };
 
   auto shared = [&]() {
-    return __builtin_amdgcn_ballot_w64(near_blk == own_blk) != 0 || gi_n * p.n_kv_heads != p.n_q_heads;
+    return it.peers < 0 || __builtin_amdgcn_ballot_w64(peer_blk == own_blk) != 0;
   };
   if constexpr (!FP8) {
     // K/V chunks go global -> LDS by DMA, one 16-byte chunk per lane per instruction, into
@@ -1729,7 +1743,7 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
         posted = run_wide<D, kPool, List>(p, feed, smem);
       }
     } else {
-      run_narrow<D, FP8>(p, it, smem);
+      run_narrow<D, FP8, LIST>(p, it, smem);
     }
   }
   // No queue has an item left for this work-group.  The last work-group of the launch to get
@@ -1941,7 +1955,6 @@ int launch_attn(const AttnLaunch& a, bool* main_launched) {
     p.q_len[x] = pl.q_len[x];
   }
   p.compact = a.compact;
-  p.n_seqs = pl.n_seqs;
   p.stage_seqs = reinterpret_cast<const StageSeq*>(image + pl.off_stage);
   p.stage_k = ws + pl.off_stage_k;
   p.stage_v = ws + pl.off_stage_v;

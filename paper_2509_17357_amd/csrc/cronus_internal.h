@@ -7,6 +7,12 @@
 
 #include "cronus.h"
 
+#if defined(__HIP__)
+#define CRONUS_HOST_DEVICE __host__ __device__
+#else
+#define CRONUS_HOST_DEVICE
+#endif
+
 namespace cronus {
 
 constexpr int kBlock = 16;          // tokens per KV block (N_size of Algorithm 1)
@@ -47,23 +53,32 @@ struct WorkItem {
                      // waves split keys; -1: nothing to do (a work-group's "no item left" marker)
   // copy of the sequence's record, so that a work-group needs one dependent load less
   // before it can address Q and the block table
-  int32_t prefix_len, chunk_len, q_off, n_blocks;
+  int32_t prefix_len, chunk_len, q_off;
+  union {
+    int32_t n_blocks;  // wide: as in the sequence's record
+    int32_t peers;     // narrow: < 0: other items of the launch read its K/V too; else a bit for each sequence near by
+                       // whose table has the item's column (peer_column, peer_offset)
+  };
   // partial >= 0: first partial slot of the item's row group, and n_split * kMaxMergeGroups +
   // the group's index among those of the launch
   int32_t first_partial, merge_key;
 };
 static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
+// A narrow item whose K/V no other item reads keeps it out of the caches.  Whether decodes share blocks is seen in the block
+// tables only: the item compares its block at three quarters of its keys with that of the kPeers sequences on either side
+// in the batch, where they attend in this launch and have as many blocks (no other entry of their rows is read).
+constexpr int kPeers = 8;
+CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) { return (kv_begin + (kv_end - kv_begin) / 4 * 3) / kBlock; }
+CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeers ? bit - kPeers : bit - kPeers + 1; }
+// What the host knows of it: no other head group reads the same KV head.
+CRONUS_HOST_DEVICE inline bool may_be_read_once(int32_t n_heads, int32_t heads_per_kv) { return n_heads == heads_per_kv; }
+
 // Compact form of the work list: the items of one tile of a sequence differ only by KV head and
 // key span, so an item is a number (unit << head_bits | kv_head) << span_bits | span (2 bytes
 // when all fit) and a unit holds the rest.  expand_unit() is the one definition of what an item then is:
 // the device builds the records with it, and the host accepts the compact form only if it gives back
 // every record.  No divisions: the device expands an item each time that a work-group takes one.
-#if defined(__HIP__)
-#define CRONUS_HOST_DEVICE __host__ __device__
-#else
-#define CRONUS_HOST_DEVICE
-#endif
 struct CompactUnit {
   int32_t seq, prefix_len, chunk_len, q_off;
   uint32_t tile;      // tile of the chunk | head group << 24
@@ -99,11 +114,26 @@ CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const Compa
   w.prefix_len = u.prefix_len;
   w.chunk_len = u.chunk_len;
   w.q_off = u.q_off;
-  w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
+  if (wide) w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
+  else w.peers = may_be_read_once(w.n_heads, c.heads_per_kv) ? 0 : -1;  // no peers yet
   return w;
 }
+// Units lie in the order of their sequences, so a decode's peers are found beside its own unit, where the sequences
+// between them have one unit each.
+CRONUS_HOST_DEVICE inline bool is_peer(const CompactUnit& v, int32_t seq, int32_t offset, int32_t column) {
+  return v.seq == seq + offset && column * kBlock < v.prefix_len + v.chunk_len;
+}
 CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
-  return expand_unit(c, units[unit_of_ref(c, ref)], ref);
+  const int32_t unit = (int32_t)unit_of_ref(c, ref);
+  WorkItem w = expand_unit(c, units[unit], ref);
+  if (!w.wide && w.peers == 0) {
+    const int32_t column = peer_column(w.kv_begin, w.kv_end);
+    for (int32_t b = 0; b < 2 * kPeers; ++b) {
+      const int32_t v = unit + peer_offset(b);
+      if (v >= 0 && v < c.n_units && is_peer(units[v], w.seq, peer_offset(b), column)) w.peers |= 1 << b;
+    }
+  }
+  return w;
 }
 // A static call's list of at most this many bytes and with 2-byte references travels in the main kernel's own arguments (up to
 // kShortListBytes in a smaller set of them).  More do not fit in 4 KiB next to the other arguments.

@@ -45,6 +45,7 @@ struct Scratch {
   // compact_plan: the unit of every item (tiles of a sequence back to back, head group by head group), and their number
   std::vector<int32_t> wide_unit, narrow_unit;
   long long n_units;
+  std::vector<int32_t> unit_seq, unit_keys, peers;  // build_plan: for WorkItem::peers
   std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
   std::vector<float> row_keys;         // keys of the narrow rows, one entry per sequence
   struct Busy { double until; long long cus; };
@@ -470,6 +471,37 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     }
   }
 
+  // Sequence and keys of every unit, with kPeers empty places on either side, for WorkItem::peers (as expand_item finds them).
+  if (n_groups == 1) {
+    sc.unit_seq.assign(kPeers, 0);
+    sc.unit_keys.assign(kPeers, 0);
+    for (int s = 0; s < n_seqs; ++s) {
+      const int32_t C = chunk_lens[s];
+      for (int32_t t = C; t > 0; t -= wide_tok) {
+        sc.unit_seq.push_back(s);
+        sc.unit_keys.push_back(prefix_lens[s] + C);
+      }
+    }
+    sc.unit_seq.insert(sc.unit_seq.end(), kPeers, 0);
+    sc.unit_keys.insert(sc.unit_keys.end(), kPeers, 0);
+  }
+  auto peers_of = [&](int32_t s, int32_t unit, int32_t kv_begin, int32_t kv_end) {
+    typedef int32_t Four __attribute__((vector_size(16)));
+    static_assert(kPeers == 8, "two vectors a side");
+    const int32_t first_key = peer_column(kv_begin, kv_end) * kBlock;
+    const Four places{0, 1, 2, 3}, bits{1, 2, 4, 8};
+    Four mask{0, 0, 0, 0};
+    for (int v = 0; v < 4; ++v) {
+      Four seq, keys;  // of the units 4 v .. 4 v + 3 places from the first (the unit itself is left out)
+      const size_t at = (size_t)unit + 4 * v + (v >= 2);
+      std::memcpy(&seq, sc.unit_seq.data() + at, sizeof(seq));
+      std::memcpy(&keys, sc.unit_keys.data() + at, sizeof(keys));
+      mask |= (keys > first_key) & (seq == places + (s + peer_offset(4 * v))) & (bits << 4 * v);
+    }
+    return mask[0] | mask[1] | mask[2] | mask[3];
+  };
+
+  int32_t peers_unit = -1;  // whose spans sc.peers is of: the same for every KV head
   auto add_narrow = [&](int s, int kvh, int head0, int nh, int q_tok0, int n_tok, int kv_total, int32_t unit) {
     const NarrowSplit split = split_of(kv_total, span);
     int n_split = split.n;
@@ -484,11 +516,18 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       sc.merges.push_back(MergeItem{(int32_t)n_partials, n_split, s, kvh, head0, nh, q_tok0, n_tok, 0, n_tok * nh, 1, 0});
       n_merge_rows += (int64_t)n_tok * nh;
     }
+    const bool once = may_be_read_once(nh, G);
+    if (once && (unit != peers_unit || n_split != (int)sc.peers.size())) {
+      peers_unit = unit;
+      sc.peers.resize((size_t)n_split);
+      for (int i = 0; i < n_split; ++i) sc.peers[(size_t)i] = peers_of(s, unit, i * per_item, std::min(kv_total, (i + 1) * per_item));
+    }
     for (int i = 0; i < n_split; ++i) {
       WorkItem w{};
       w.seq = s; w.kv_head = kvh; w.head0 = head0; w.n_heads = nh; w.q_tok0 = q_tok0; w.n_tok = n_tok;
       w.kv_begin = i * per_item;
       w.kv_end = std::min(kv_total, (i + 1) * per_item);
+      w.peers = once ? sc.peers[(size_t)i] : -1;
       w.partial = n_split > 1 ? (int32_t)(n_partials++) : -1;
       w.first_partial = first_partial;
       w.merge_key = merge_key;
@@ -758,7 +797,7 @@ void write_plan(const Plan* plan, void* host_buf) {
       w.prefix_len = si.prefix_len;
       w.chunk_len = si.chunk_len;
       w.q_off = si.q_off;
-      w.n_blocks = si.n_blocks;
+      if (w.wide) w.n_blocks = si.n_blocks;
       wi[i++] = w;
     }
   }
@@ -831,7 +870,7 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
       const uint32_t unit = (uint32_t)(q >= 0 ? sc.wide_unit[(size_t)q] : sc.narrow_unit[(size_t)~q]);
       const uint32_t span = w.partial < 0 ? 0u : (uint32_t)(w.partial - w.first_partial) / (q >= 0 ? kWaves : 1);
       const uint32_t ref = (unit << head_bits | (uint32_t)w.kv_head) << span_bits | span;
-      const WorkItem e = expand_item(*c, units, ref);
+      const WorkItem e = expand_unit(*c, units[unit], ref);  // (its peers follow from the other units)
       if (e.seq != w.seq || e.kv_head != w.kv_head || e.head0 != w.head0 || e.n_heads != w.n_heads || e.q_tok0 != w.q_tok0 ||
           e.n_tok != w.n_tok || e.kv_begin != w.kv_begin || e.kv_end != w.kv_end || e.partial != w.partial || e.wide != w.wide ||
           (w.partial >= 0 && (e.first_partial != w.first_partial || e.merge_key != w.merge_key)))

@@ -1,0 +1,77 @@
+"""Which sequences' block tables a narrow item looks at (WorkItem::peers, under AddressSanitizer and
+UndefinedBehaviorSanitizer): only entries that the header says are read, that is below ceil(len / 16) of a sequence that
+attends in the call, and among decodes all of the eight on either side that have the column."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2509_17357_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def plan_of(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path_factory.mktemp("policy") / "policy_check")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-g", "-ffp-contract=off", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=all", "-Wno-unknown-pragmas", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(ROOT, "tests", "native", "policy_check_main.cpp"), os.path.join(CSRC, "plan.cpp"),
+                    "-o", exe], check=True)
+    env = dict(os.environ)
+    env.pop("LD_PRELOAD", None)  # the sanitizer runtime must come first in the library list
+
+    def run(hq, hkv, d, cus, seqs):
+        text = " ".join(map(str, [hq, hkv, d, cus, len(seqs)] + [x for s in seqs for x in s]))
+        r = subprocess.run([exe], input=text + "\n", capture_output=True, text=True, env=env)
+        assert r.returncode == 0, r.stderr[-3000:]
+        lines = r.stdout.splitlines()
+        items = np.array([ln.split() for ln in lines[1:]], dtype=np.int64).reshape(-1, 7)
+        assert int(lines[0]) == items.shape[0]
+        return items
+    return run
+
+
+OFFSETS = list(range(-8, 0)) + list(range(1, 9))
+
+
+def look(items, seqs):
+    """(seq, column, sequences looked at) of every item that looks."""
+    for seq, _, _, _, begin, end, peers in items.tolist():
+        if peers >= 0:
+            yield seq, (begin + (end - begin) // 4 * 3) // 16, {seq + OFFSETS[b] for b in range(32) if peers >> b & 1}
+
+
+def test_only_entries_in_use_are_looked_at(plan_of):
+    rng = np.random.default_rng(8)
+    looked = 0
+    for i in range(60):
+        n = int(rng.integers(1, 60))
+        hq, hkv, d = [(8, 2, 64), (32, 8, 128), (28, 4, 128), (64, 8, 128), (8, 8, 64)][i % 5]
+        P = rng.integers(0, int(rng.choice([50, 3000, 20000])), n)
+        C = np.where(rng.random(n) < 0.7, 1, rng.integers(0, int(rng.choice([3, 30, 700])), n))
+        seqs = list(zip(P.tolist(), C.tolist()))
+        for seq, col, others in look(plan_of(hq, hkv, d, int(rng.choice([1, 64, 256])), seqs), seqs):
+            for o in others:
+                assert 0 <= o < n and seqs[o][1] > 0 and 16 * col < sum(seqs[o]), (i, seq, col, o)
+            looked += len(others)
+    assert looked > 1000
+
+
+@pytest.mark.parametrize("n, keys", [(1, 40), (3, 5000), (20, 700), (64, 4000), (257, 8000)])
+def test_decodes_look_at_every_neighbour_that_has_the_column(plan_of, n, keys):
+    rng = np.random.default_rng(n)
+    seqs = [(int(p), 1) for p in rng.integers(1, keys, n)]
+    items = plan_of(32, 8, 128, 256, seqs)
+    assert len({tuple(x) for x in items[:, [0, 1, 4]].tolist()}) == len(items)
+    for seq, col, others in look(items, seqs):
+        assert others == {o for o in range(max(0, seq - 8), min(n, seq + 9)) if o != seq and 16 * col < sum(seqs[o])}
+    assert (items[:, 6] >= 0).all()
+
+
+def test_head_groups_that_share_a_kv_head_do_not_look(plan_of):
+    assert (plan_of(64, 1, 128, 256, [(900, 1)] * 5)[:, 6] < 0).all()
