@@ -1358,7 +1358,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   // non-temporally; with only the first half or quarter of the blocks shared 116 and 149, 110 and 136).  So a span that has the
   // block at three quarters of its keys in common with one of its peers, the 16 sequences next in the batch that have this column, is read the ordinary way
   // (looking costs at most 0.4 us an item: 256 decodes of the same 2 k keys 139 -> 143), and so
-  // are head groups that share a KV head.
+  // are head groups that share a KV head and the tail of a chunk, whose tiles read the same keys.
   int peer_blk = -1, own_blk;
   {
     const int col = peer_column(it.kv_begin, it.kv_end), offset = peer_offset(lane & 15);

@@ -71,8 +71,11 @@ static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 constexpr int kPeers = 8;
 CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) { return (kv_begin + (kv_end - kv_begin) / 4 * 3) / kBlock; }
 CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeers ? bit - kPeers : bit - kPeers + 1; }
-// What the host knows of it: no other head group reads the same KV head.
-CRONUS_HOST_DEVICE inline bool may_be_read_once(int32_t n_heads, int32_t heads_per_kv) { return n_heads == heads_per_kv; }
+// What the host knows of it: no other head group reads the same KV head, and the item is not the tail of a chunk, whose tiles
+// read the same keys.
+CRONUS_HOST_DEVICE inline bool may_be_read_once(int32_t n_tok, int32_t chunk_len, int32_t n_heads, int32_t heads_per_kv) {
+  return n_tok == chunk_len && n_heads == heads_per_kv;
+}
 
 // Compact form of the work list: the items of one tile of a sequence differ only by KV head and
 // key span, so an item is a number (unit << head_bits | kv_head) << span_bits | span (2 bytes
@@ -115,7 +118,7 @@ CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const Compa
   w.chunk_len = u.chunk_len;
   w.q_off = u.q_off;
   if (wide) w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
-  else w.peers = may_be_read_once(w.n_heads, c.heads_per_kv) ? 0 : -1;  // no peers yet
+  else w.peers = may_be_read_once(w.n_tok, w.chunk_len, w.n_heads, c.heads_per_kv) ? 0 : -1;  // no peers yet
   return w;
 }
 // Units lie in the order of their sequences, so a decode's peers are found beside its own unit, where the sequences

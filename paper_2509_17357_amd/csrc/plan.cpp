@@ -516,7 +516,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       sc.merges.push_back(MergeItem{(int32_t)n_partials, n_split, s, kvh, head0, nh, q_tok0, n_tok, 0, n_tok * nh, 1, 0});
       n_merge_rows += (int64_t)n_tok * nh;
     }
-    const bool once = may_be_read_once(nh, G);
+    const bool once = may_be_read_once(n_tok, chunk_lens[s], nh, G);
     if (once && (unit != peers_unit || n_split != (int)sc.peers.size())) {
       peers_unit = unit;
       sc.peers.resize((size_t)n_split);

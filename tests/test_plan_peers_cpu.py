@@ -75,3 +75,11 @@ def test_decodes_look_at_every_neighbour_that_has_the_column(plan_of, n, keys):
 
 def test_head_groups_that_share_a_kv_head_do_not_look(plan_of):
     assert (plan_of(64, 1, 128, 256, [(900, 1)] * 5)[:, 6] < 0).all()
+
+
+def test_the_tail_of_a_chunk_does_not_look(plan_of):
+    """Its keys are those of the chunk's tiles; a short chunk that is one item does look."""
+    for heads, seqs in (((32, 8, 128), [(6000, 516), (900, 1), (50, 7)]), ((28, 4, 128), [(0, 36 * 5 + 3)] * 4), ((8, 2, 64), [(300, 65)])):
+        items = plan_of(*heads, 256, seqs)
+        tails = items[:, 3] < np.array([seqs[s][1] for s in items[:, 0]])
+        assert tails.any() and (items[tails, 6] < 0).all() and (items[~tails, 6] >= 0).all()
