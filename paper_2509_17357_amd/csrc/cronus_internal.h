@@ -56,7 +56,7 @@ struct WorkItem {
   int32_t prefix_len, chunk_len, q_off;
   union {
     int32_t n_blocks;  // wide: as in the sequence's record
-    int32_t peers;     // narrow: < 0: other items of the launch read its K/V too; else a bit for each sequence near by
+    int32_t peers;     // narrow: < 0: its K/V is read the ordinary way; else a bit for each sequence near by
                        // whose table has the item's column (peer_column, peer_offset)
   };
   // partial >= 0: first partial slot of the item's row group, and n_split * kMaxMergeGroups +
@@ -65,17 +65,19 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
-// A narrow item whose K/V no other item reads keeps it out of the caches.  Whether decodes share blocks is seen in the block
+// A narrow item whose K/V no other item reads keeps it out of the caches.  The host knows of the others where there are more head
+// groups of a KV head than one, and where the item is the tail of a chunk, whose tiles read the same keys.  Whether decodes share blocks is seen in the block
 // tables only: the item compares its block at three quarters of its keys with that of the kPeers sequences on either side
 // in the batch, where they attend in this launch and have as many blocks (no other entry of their rows is read).
 constexpr int kPeers = 8;
 CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) { return (kv_begin + (kv_end - kv_begin) / 4 * 3) / kBlock; }
 CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeers ? bit - kPeers : bit - kPeers + 1; }
-// What the host knows of it: no other head group reads the same KV head, and the item is not the tail of a chunk, whose tiles
-// read the same keys.
-CRONUS_HOST_DEVICE inline bool may_be_read_once(int32_t n_tok, int32_t chunk_len, int32_t n_heads, int32_t heads_per_kv) {
-  return n_tok == chunk_len && n_heads == heads_per_kv;
-}
+// The K/V of a launch's decodes passes the caches from this many bytes on.  Less may still lie there from its last use (the
+// eight L2s hold 32 MB).  us a pass, ordinary / past the caches, over the same three batches in turn and cold:
+// 2 decodes of 1000 keys (8 MB) 15.6 / 17.8 and 18.6 / 18.3, 4 of 2000 (33 MB) 17.4 / 19.3 and 20.8 / 20.1, 8 of 1500
+// (49 MB) 20.6 / 21.7 and 23.8 / 22.5, 16 of 1000 (66 MB) 21.6 / 22.9 and 26.0 / 23.9, 12 of 2000 (98 MB) 33.2 / 32.6 and 36.0 / 33.4,
+// 16 of 2000 (131 MB) 36.1 / 32.6 and 36.8 / 33.0.  The line lies where the two together are even.
+constexpr long long kPastCacheBytes = 40'000'000;
 
 // Compact form of the work list: the items of one tile of a sequence differ only by KV head and
 // key span, so an item is a number (unit << head_bits | kv_head) << span_bits | span (2 bytes
@@ -93,6 +95,7 @@ static_assert(sizeof(CompactUnit) == 32, "two 16-byte vectors");
 struct CompactPlan {
   int32_t n_items, n_units, head_bits, span_bits;
   int32_t group_heads, heads_per_kv, wide_tok, ref_bytes;  // ref_bytes: 2 or 4
+  int32_t past_cache;                                      // Plan::past_cache
 };
 CRONUS_HOST_DEVICE inline uint32_t unit_of_ref(const CompactPlan& c, uint32_t ref) { return ref >> (c.head_bits + c.span_bits); }
 CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const CompactUnit& u, uint32_t ref) {
@@ -118,7 +121,7 @@ CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const Compa
   w.chunk_len = u.chunk_len;
   w.q_off = u.q_off;
   if (wide) w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
-  else w.peers = may_be_read_once(w.n_tok, w.chunk_len, w.n_heads, c.heads_per_kv) ? 0 : -1;  // no peers yet
+  else w.peers = c.past_cache && w.n_tok == u.chunk_len ? 0 : -1;  // no peers yet
   return w;
 }
 // Units lie in the order of their sequences, so a decode's peers are found beside its own unit, where the sequences
@@ -178,6 +181,7 @@ struct Plan {
   int64_t n_items = 0, n_wide = 0, n_partials = 0, n_merge = 0, n_merge_rows = 0;
   int32_t n_seqs = 0;
   int32_t wide_rows = 0;  // rows per wide tile (compile-time choice of the kernel instance)
+  int32_t past_cache = 0;  // 1: the decodes' K/V passes the caches (WorkItem::peers; one head group, kPastCacheBytes)
   int32_t n_stage_seqs = 0;
   int64_t n_stage_blocks = 0;
   // The work items form kQueues queues, stored one after the other: queue x is items

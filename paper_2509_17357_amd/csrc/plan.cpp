@@ -162,7 +162,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // keys read by narrow items, to size the spans, and the cost of the wide tiles in the
   // planner's unit (one key of a full wide tile = wide_rows / 128, one key of a narrow
   // item = 1/2), to size the spans that long wide tiles are cut into
-  long long narrow_keys = 0;
+  long long narrow_keys = 0, decode_keys = 0;
   double wide_cost_total = 0;
   long long wide_tiles = 0;
   for (int s = 0; s < n_seqs; ++s) {
@@ -170,8 +170,10 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     if (P < 0 || C < 0) return CRONUS_ERR_INVALID_ARG;
     if (P + C > (long long)max_blocks_per_seq * kBlock) return CRONUS_ERR_INVALID_ARG;
     if (C == 0) continue;
-    if (C * group <= kNarrowRows) narrow_keys += (P + C) * Hkv * n_groups;
-    else {
+    if (C * group <= kNarrowRows) {
+      narrow_keys += (P + C) * Hkv * n_groups;
+      decode_keys += P + C;
+    } else {
       const long long rem = C % wide_tok;
       if (rem && rem * group <= kNarrowRows) narrow_keys += (P + C) * Hkv * n_groups;
       const long long full = C / wide_tok;  // full tiles end at P + wide_tok, P + 2 wide_tok, ...
@@ -472,7 +474,9 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   }
 
   // Sequence and keys of every unit, with kPeers empty places on either side, for WorkItem::peers (as expand_item finds them).
-  if (n_groups == 1) {
+  const bool past_cache =
+      n_groups == 1 && decode_keys * 2 * Hkv * D * (cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2) >= kPastCacheBytes;
+  if (past_cache) {
     sc.unit_seq.assign(kPeers, 0);
     sc.unit_keys.assign(kPeers, 0);
     for (int s = 0; s < n_seqs; ++s) {
@@ -516,7 +520,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       sc.merges.push_back(MergeItem{(int32_t)n_partials, n_split, s, kvh, head0, nh, q_tok0, n_tok, 0, n_tok * nh, 1, 0});
       n_merge_rows += (int64_t)n_tok * nh;
     }
-    const bool once = may_be_read_once(n_tok, chunk_lens[s], nh, G);
+    const bool once = past_cache && n_tok == chunk_lens[s];
     if (once && (unit != peers_unit || n_split != (int)sc.peers.size())) {
       peers_unit = unit;
       sc.peers.resize((size_t)n_split);
@@ -761,6 +765,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   plan->n_workgroups = (int32_t)std::min<size_t>(n_slots, (size_t)std::max(n_cus, 1));
 
   plan->n_seqs = n_seqs;
+  plan->past_cache = past_cache;
   plan->wide_rows = wide_rows;
   plan->n_items = (int64_t)n_slots;
   plan->n_wide = (int64_t)sc.wide.size();
@@ -858,7 +863,7 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
   const unsigned long long numbers = (unsigned long long)n_units << (head_bits + span_bits);
   if (numbers > 0x7fffffffull) return false;
   *c = CompactPlan{(int32_t)plan->n_items, (int32_t)n_units, head_bits, span_bits, group, G, sc.wide_tok,
-                   numbers <= 0x10000ull ? 2 : 4};
+                   numbers <= 0x10000ull ? 2 : 4, plan->past_cache};
   const size_t off = (size_t)n_units * sizeof(CompactUnit);
   *bytes = align_up(off + (size_t)plan->n_items * c->ref_bytes, 16);
   if (*bytes > capacity) return false;

@@ -1,5 +1,5 @@
 // Host-only driver for how the K/V of narrow items is read (plan.cpp: WorkItem::peers): reads batches from stdin
-//   <Hq> <Hkv> <D> <n_cus> <n_seqs> P0 C0 P1 C1 ...
+//   <Hq> <Hkv> <D> <fp8 0|1> <n_cus> <n_seqs> P0 C0 P1 C1 ...
 // and prints, for each, "<narrow items>" and then a line "seq kv_head q_tok0 n_tok kv_begin kv_end peers" for every one.
 #include <cstdio>
 #include <iostream>
@@ -13,8 +13,8 @@ int wide_rows_for(int, int) { return kWaves * 32; }
 
 int main() {
   using namespace cronus;
-  int hq, hkv, d, n_cus, n;
-  while (std::cin >> hq >> hkv >> d >> n_cus >> n) {
+  int hq, hkv, d, fp8, n_cus, n;
+  while (std::cin >> hq >> hkv >> d >> fp8 >> n_cus >> n) {
     std::vector<int32_t> P((size_t)n), C((size_t)n);
     for (int i = 0; i < n; ++i) std::cin >> P[(size_t)i] >> C[(size_t)i];
     cronus_kv_cache c{};
@@ -23,6 +23,7 @@ int main() {
     c.num_kv_heads = hkv;
     c.head_dim = d;
     c.block_size = 16;
+    c.kv_dtype = fp8 ? CRONUS_KV_FP8_E4M3 : CRONUS_KV_BF16;
     Plan plan;
     if (build_plan(&c, P.data(), C.data(), n, 0x7fffffff / 16, n_cus, &plan)) return 1;
     std::vector<unsigned char> image(plan.image_bytes);  // exactly sized

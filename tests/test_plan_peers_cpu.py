@@ -1,6 +1,7 @@
 """Which sequences' block tables a narrow item looks at (WorkItem::peers, under AddressSanitizer and
 UndefinedBehaviorSanitizer): only entries that the header says are read, that is below ceil(len / 16) of a sequence that
-attends in the call, and among decodes all of the eight on either side that have the column."""
+attends in the call, and among decodes all of the eight on either side that have the column.  And which items look at none:
+those whose K/V other items of the launch read, and all of a launch whose decodes' K/V is small."""
 import os
 import shutil
 import subprocess
@@ -25,8 +26,8 @@ def plan_of(tmp_path_factory):
     env = dict(os.environ)
     env.pop("LD_PRELOAD", None)  # the sanitizer runtime must come first in the library list
 
-    def run(hq, hkv, d, cus, seqs):
-        text = " ".join(map(str, [hq, hkv, d, cus, len(seqs)] + [x for s in seqs for x in s]))
+    def run(hq, hkv, d, cus, seqs, fp8=0):
+        text = " ".join(map(str, [hq, hkv, d, fp8, cus, len(seqs)] + [x for s in seqs for x in s]))
         r = subprocess.run([exe], input=text + "\n", capture_output=True, text=True, env=env)
         assert r.returncode == 0, r.stderr[-3000:]
         lines = r.stdout.splitlines()
@@ -62,10 +63,10 @@ def test_only_entries_in_use_are_looked_at(plan_of):
     assert looked > 1000
 
 
-@pytest.mark.parametrize("n, keys", [(1, 40), (3, 5000), (20, 700), (64, 4000), (257, 8000)])
+@pytest.mark.parametrize("n, keys", [(1, 30000), (3, 20000), (20, 2000), (64, 4000), (257, 8000)])
 def test_decodes_look_at_every_neighbour_that_has_the_column(plan_of, n, keys):
     rng = np.random.default_rng(n)
-    seqs = [(int(p), 1) for p in rng.integers(1, keys, n)]
+    seqs = [(int(p), 1) for p in rng.integers(keys // 100, keys, n)]
     items = plan_of(32, 8, 128, 256, seqs)
     assert len({tuple(x) for x in items[:, [0, 1, 4]].tolist()}) == len(items)
     for seq, col, others in look(items, seqs):
@@ -74,12 +75,25 @@ def test_decodes_look_at_every_neighbour_that_has_the_column(plan_of, n, keys):
 
 
 def test_head_groups_that_share_a_kv_head_do_not_look(plan_of):
-    assert (plan_of(64, 1, 128, 256, [(900, 1)] * 5)[:, 6] < 0).all()
+    assert (plan_of(64, 1, 128, 256, [(90000, 1)] * 5)[:, 6] < 0).all()
 
 
 def test_the_tail_of_a_chunk_does_not_look(plan_of):
     """Its keys are those of the chunk's tiles; a short chunk that is one item does look."""
-    for heads, seqs in (((32, 8, 128), [(6000, 516), (900, 1), (50, 7)]), ((28, 4, 128), [(0, 36 * 5 + 3)] * 4), ((8, 2, 64), [(300, 65)])):
+    for heads, seqs in (((32, 8, 128), [(6000, 516), (9900, 1), (50, 7)]), ((28, 4, 128), [(0, 36 * 5 + 3)] * 4 + [(20000, 1)]), ((8, 2, 64), [(300, 65), (90000, 1)])):
         items = plan_of(*heads, 256, seqs)
         tails = items[:, 3] < np.array([seqs[s][1] for s in items[:, 0]])
         assert tails.any() and (items[tails, 6] < 0).all() and (items[~tails, 6] >= 0).all()
+
+
+@pytest.mark.parametrize("fp8, heads, below", [(0, (32, 8, 128), 9765), (0, (8, 2, 64), 78125), (0, (28, 4, 128), 19531), (1, (64, 8, 128), 19531), (1, (8, 1, 64), 312500)])
+def test_small_launches_keep_their_kv_in_the_caches(plan_of, fp8, heads, below):
+    """`below` keys of decodes are the most that take less than 40 MB."""
+    row = 2 * heads[1] * heads[2] * (1 if fp8 else 2)
+    assert below * row <= 40e6 < (below + 1) * row
+    for chunks in ([], [(700, 300), (0, 1000)]):  # whose keys do not count
+        for keys in (below - (below * row == 40e6), below + 1):
+            n = keys // 3
+            peers = plan_of(*heads, 256, [(n - 1, 1), (n - 1, 1)] + chunks + [(keys - 2 * n - 1, 1)], fp8)
+            decodes = peers[peers[:, 3] == 1]
+            assert len(decodes) and ((decodes[:, 6] >= 0) == (keys > below)).all(), keys
