@@ -127,7 +127,10 @@ class DeviceIteration:
         return self._cache
 
     def _stream(self):
-        return torch.cuda.current_stream(self.device).cuda_stream
+        # what torch.cuda.current_stream(device).cuda_stream gives, without the Stream object around it (1.9 us): a step looks it up
+        # before its first launch
+        index = self.device.index
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
     def setup_decode_context(self):
         """Set-up: the KV that earlier iterations of the decode requests left in the cache."""

@@ -99,3 +99,25 @@ def test_replays_and_refusals():
         torch.cuda.synchronize()
         graph.replay()
         assert same(state(it), want), k
+
+
+@pytest.mark.parametrize("device", ["cuda:0", "cuda"])
+def test_a_step_runs_on_the_current_stream(device):
+    shape, P, C = CASES["halves and edges"]
+    it = DeviceIteration(W.custom_batch(shape, P, C, seed=77), device=device, pool_fill=0x5A)
+    it.load_device_inputs()
+    it.setup_decode_context()
+    it.step()
+    want = state(it)
+    assert it._stream() == torch.cuda.current_stream(it.device).cuda_stream
+    side = torch.cuda.Stream()
+    fresh(it)
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        assert it._stream() == side.cuda_stream
+        it.step()
+        done = torch.cuda.Event()
+        done.record()
+    assert it._stream() == torch.cuda.current_stream(it.device).cuda_stream
+    torch.cuda.current_stream().wait_event(done)
+    assert same(state(it), want)
