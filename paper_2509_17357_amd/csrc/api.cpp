@@ -269,26 +269,6 @@ int check_attn_args(const cronus_kv_cache* cache, const void* q, const void* out
   return CRONUS_OK;
 }
 
-// Whether an iteration places its rows past the caches: where streaming the decodes' K/V takes at least twice as
-// long as the products of the chunks, and 20 us.  Such an iteration is bound by the HBM, which then also takes back what
-// the scatter left behind; elsewhere the chunk tiles read the rows from the cache.  (us a pass, cached / past the
-// caches: 4 chunks next to 64 decodes, streaming 95 us and products 36, 140.3 / 129.8; a chunk next to 49, 41 and 13, 69.4 / 65.8; fp8,
-// 53 and 17, 90.1 / 87.0; 82 decodes, 68 and 0.4, 82.2 / 79.7.  The other side: 66 and 36 122.6 / 122.6, 105 and 121
-// 226 / 229, 24 and 113 172.3 / 174.2, 0 and 771 799 / 808; 8 and 1 32.2 / 32.8.)
-bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens, int32_t n_seqs) {
-  const int group = std::min(cache->num_q_heads / cache->num_kv_heads, kNarrowRows);
-  double stream_us = 0, product_us = 0;
-  for (int s = 0; s < n_seqs; ++s) {
-    const double P = prefix_lens[s], C = chunk_lens[s];
-    if (C * group > kNarrowRows) product_us += C * P + C * (C + 1) / 2;
-    else if (C > 0) stream_us += P + C;
-  }
-  const double elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2;
-  stream_us *= 2.0 * elem_bytes * cache->num_kv_heads * cache->head_dim / 6e6;  // 6 TB/s
-  product_us *= 4.0 * cache->num_q_heads * cache->head_dim / 1.2e9;             // 1.2 PFLOP/s
-  return stream_us >= 20 && stream_us >= 2 * product_us;
-}
-
 bool workspace_refused(const void* workspace) { return !workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u); }
 
 // cronus_attn_mixed behind the placing of the rows of `first` and `second` (null: none).

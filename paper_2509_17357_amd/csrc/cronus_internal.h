@@ -222,6 +222,9 @@ void write_plan(const Plan* plan, void* host_buf);
 // 264 items, 2.9 for 552 and 8 on a first pass.
 bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c, void* buf, size_t capacity, size_t* bytes);
 
+// Whether the rows of such an iteration are stored past the caches (cronus_iteration).
+bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens, int32_t n_seqs);
+
 struct AttnLaunch {
   const cronus_kv_cache* cache;
   const void* q;

@@ -886,4 +886,26 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
   return true;
 }
 
+// Whether an iteration places its rows past the caches: where streaming the decodes' K/V takes at least twice as
+// long as the products of the chunks, and 20 us.  Such an iteration is bound by the HBM, which then also takes back what
+// the scatter left behind; elsewhere the chunk tiles read the rows from the cache.  us a pass, cached / past the
+// caches, behind the times of streaming and products.  This side: 4 chunks next to 64 decodes, 95 and 36, 140.3 / 129.8; a chunk next to 49, 41 and 13,
+// 69.4 / 65.8; fp8, 53 and 17, 90.1 / 87.0; a chunk of 256 behind 256 next to 24, 33 and 1, 44.5 / 42.5; 512 behind 1500 next to 32, 44 and 12,
+// 80.0 / 69.0; fp8, 100 behind 1000 next to 32, 27 and 3, 52.2 / 50.4; decodes alone, whose rows are few, 22 32.2 / 32.1, 27 45.2 / 45.3,
+// 38 43.2 / 42.9, 55 72.6 / 72.0.  The other side: 66 and 36 122.6 / 122.6, 105 and 121 226 / 229, 24 and 113 172.3 / 174.2,
+// 0 and 771 799 / 808; 8 and 1 32.2 / 32.8.  (A ratio of 1.6, fp8, 55 and 34, still gained: 108.6 / 106.7.)
+bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens, int32_t n_seqs) {
+  const int group = std::min(cache->num_q_heads / cache->num_kv_heads, kNarrowRows);
+  double stream_us = 0, product_us = 0;
+  for (int s = 0; s < n_seqs; ++s) {
+    const double P = prefix_lens[s], C = chunk_lens[s];
+    if (C * group > kNarrowRows) product_us += C * P + C * (C + 1) / 2;
+    else if (C > 0) stream_us += P + C;
+  }
+  const double elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2;
+  stream_us *= 2.0 * elem_bytes * cache->num_kv_heads * cache->head_dim / 6e6;  // 6 TB/s
+  product_us *= 4.0 * cache->num_q_heads * cache->head_dim / 1.2e9;             // 1.2 PFLOP/s
+  return stream_us >= 20 && stream_us >= 2 * product_us;
+}
+
 }  // namespace cronus

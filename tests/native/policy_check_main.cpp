@@ -1,6 +1,6 @@
-// Host-only driver for how the K/V of narrow items is read (plan.cpp: WorkItem::peers): reads batches from stdin
+// Host-only driver for what passes the caches (plan.cpp: WorkItem::peers, rows_past_cache): reads batches from stdin
 //   <Hq> <Hkv> <D> <fp8 0|1> <n_cus> <n_seqs> P0 C0 P1 C1 ...
-// and prints, for each, "<narrow items>" and then a line "seq kv_head q_tok0 n_tok kv_begin kv_end peers" for every one.
+// and prints, for each, "<narrow items> <rows past the caches 0|1>" and then a line "seq kv_head q_tok0 n_tok kv_begin kv_end peers" for every one.
 #include <cstdio>
 #include <iostream>
 #include <vector>
@@ -29,7 +29,7 @@ int main() {
     std::vector<unsigned char> image(plan.image_bytes);  // exactly sized
     write_plan(&plan, image.data());
     const WorkItem* w = reinterpret_cast<const WorkItem*>(image.data() + plan.off_items);
-    std::printf("%lld\n", (long long)(plan.n_items - plan.n_wide));
+    std::printf("%lld %d\n", (long long)(plan.n_items - plan.n_wide), (int)rows_past_cache(&c, P.data(), C.data(), n));
     for (long long i = 0; i < plan.n_items; ++i)
       if (!w[i].wide)
         std::printf("%d %d %d %d %d %d %d\n", w[i].seq, w[i].kv_head, w[i].q_tok0, w[i].n_tok, w[i].kv_begin, w[i].kv_end, w[i].peers);

@@ -15,13 +15,14 @@ pytestmark = pytest.mark.gpu
 # streaming at 6 TB/s takes 20 us from 29 297 decode keys of 8 KV heads x 128 on
 CASES = {
     "few decodes": (W.SHAPE_8B, [5, 16, 31, 700, 2999, 15], [1] * 6),
-    "just below the rule": (W.SHAPE_8B, [9764, 9765, 9765], [1, 1, 1]),
-    "just above the rule": (W.SHAPE_8B, [9765, 9765, 9765], [1, 1, 1]),
+    "just below the rule": (W.SHAPE_8B, [9764, 9764, 9765], [1, 1, 1]),
+    "just above the rule": (W.SHAPE_8B, [9764, 9765, 9765], [1, 1, 1]),
     "streaming, chunk and prefix": (W.SHAPE_8B, [1003, 20000, 20000], [37, 1, 1]),
     "streaming, fp8": (W.HeadShape(16, 8, 128, "fp8"), [250, 40000, 30000, 0], [70, 1, 1, 17]),
     "streaming, D 64": (W.HeadShape(8, 8, 64), [100, 60000, 17], [65, 1, 1]),
     "halves and edges": (W.SHAPE_8B, [3, 8, 24, 40, 0, 100], [5, 8, 16, 40, 1, 33]),
     "fp8, D 64": (W.HeadShape(8, 4, 64, "fp8"), [15, 17, 0, 100], [2, 1, 65, 31]),
+    "fp8, bf16 copy": (W.HeadShape(16, 2, 64, "fp8"), [100, 40], [520, 1]),
     "whole prompts": (W.SHAPE_8B, [0, 0], [130, 47]),
     "skipped sequence": (W.SHAPE_8B, [50, 60, 70], [1, 0, 20]),
     "no query rows": (W.SHAPE_8B, [50, 60], [0, 0]),
@@ -62,6 +63,8 @@ def test_iteration_equals_append_and_attention(name):
     if name == "shared blocks":  # the decode's first blocks are those that the chunk's prefix is placed in
         it.block_tables[1, :4] = it.block_tables[0, :4]
         fresh(it)
+    if name == "fp8, bf16 copy":
+        assert B.cronus_attn_mixed_plan_stats(it.cache, it.batch.prefix_lens, it.batch.chunk_lens)["copy_blocks"] > 0
     it.place_rows()
     it.attention()
     want = state(it)

@@ -32,7 +32,8 @@ def plan_of(tmp_path_factory):
         assert r.returncode == 0, r.stderr[-3000:]
         lines = r.stdout.splitlines()
         items = np.array([ln.split() for ln in lines[1:]], dtype=np.int64).reshape(-1, 7)
-        assert int(lines[0]) == items.shape[0]
+        n_items, run.rows_past = map(int, lines[0].split())
+        assert n_items == items.shape[0]
         return items
     return run
 
@@ -97,3 +98,22 @@ def test_small_launches_keep_their_kv_in_the_caches(plan_of, fp8, heads, below):
             peers = plan_of(*heads, 256, [(n - 1, 1), (n - 1, 1)] + chunks + [(keys - 2 * n - 1, 1)], fp8)
             decodes = peers[peers[:, 3] == 1]
             assert len(decodes) and ((decodes[:, 6] >= 0) == (keys > below)).all(), keys
+
+
+# (heads, fp8, sequences, whether the rows are stored past the caches): 6 TB/s of streaming, 1.2 PFLOP/s of products
+ROWS = [((32, 8, 128), 0, [(9763, 1), (9764, 1), (9766, 1)], 0),      # 29 296 keys, 19.9994 us
+        ((32, 8, 128), 0, [(9764, 1), (9764, 1), (9766, 1)], 1),      # 29 297, 20.00009
+        ((64, 8, 128), 1, [(58592, 1)], 0), ((64, 8, 128), 1, [(58593, 1)], 1),
+        ((8, 8, 64), 0, [(58592, 1)], 0), ((8, 8, 64), 0, [(58593, 1)], 1),
+        # products of 1024 tokens: 4 x 32 x 128 x (1024 P + 1024 x 1025 / 2) / 1.2e9 = 19.9998 and 20.014 us, streaming of 58 594 keys 40.0002
+        ((32, 8, 128), 0, [(58593, 1), (918, 1024)], 1), ((32, 8, 128), 0, [(58593, 1), (919, 1024)], 0),
+        ((32, 8, 128), 0, [(58593, 1), (918, 1024), (5000, 0)], 1),   # a skipped sequence does not count
+        ((32, 8, 128), 0, [(40000, 8)], 1), ((32, 8, 128), 0, [(40000, 9)], 0),  # 32 rows stream, 36 are a tile
+        ((64, 1, 128), 0, [(300000, 1)], 1), ((32, 8, 128), 0, [(100, 700), (0, 40)], 0), ((32, 8, 128), 0, [(100, 0)], 0)]
+
+
+@pytest.mark.parametrize("case", range(len(ROWS)))
+def test_which_iterations_place_their_rows_past_the_caches(plan_of, case):
+    heads, fp8, seqs, past = ROWS[case]
+    plan_of(*heads, 256, seqs, fp8)
+    assert plan_of.rows_past == past
