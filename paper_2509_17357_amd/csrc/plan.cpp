@@ -45,7 +45,8 @@ struct Scratch {
   // compact_plan: the unit of every item (tiles of a sequence back to back, head group by head group), and their number
   std::vector<int32_t> wide_unit, narrow_unit;
   long long n_units;
-  std::vector<int32_t> unit_seq, unit_keys, peers;  // build_plan: for WorkItem::peers
+  std::vector<int32_t> unit_seq, unit_keys;  // build_plan: for WorkItem::peers
+  std::vector<uint32_t> peers;
   std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
   std::vector<float> row_keys;         // keys of the narrow rows, one entry per sequence
   struct Busy { double until; long long cus; };
@@ -491,18 +492,18 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   }
   auto peers_of = [&](int32_t s, int32_t unit, int32_t kv_begin, int32_t kv_end) {
     typedef int32_t Four __attribute__((vector_size(16)));
-    static_assert(kPeers == 8, "two vectors a side");
+    static_assert(kPeers == 16, "four vectors a side");
     const int32_t first_key = peer_column(kv_begin, kv_end) * kBlock;
     const Four places{0, 1, 2, 3}, bits{1, 2, 4, 8};
     Four mask{0, 0, 0, 0};
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < 8; ++v) {
       Four seq, keys;  // of the units 4 v .. 4 v + 3 places from the first (the unit itself is left out)
-      const size_t at = (size_t)unit + 4 * v + (v >= 2);
+      const size_t at = (size_t)unit + 4 * v + (v >= 4);
       std::memcpy(&seq, sc.unit_seq.data() + at, sizeof(seq));
       std::memcpy(&keys, sc.unit_keys.data() + at, sizeof(keys));
       mask |= (keys > first_key) & (seq == places + (s + peer_offset(4 * v))) & (bits << 4 * v);
     }
-    return mask[0] | mask[1] | mask[2] | mask[3];
+    return (uint32_t)(mask[0] | mask[1] | mask[2] | mask[3]);
   };
 
   int32_t peers_unit = -1;  // whose spans sc.peers is of: the same for every KV head
@@ -531,7 +532,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       w.seq = s; w.kv_head = kvh; w.head0 = head0; w.n_heads = nh; w.q_tok0 = q_tok0; w.n_tok = n_tok;
       w.kv_begin = i * per_item;
       w.kv_end = std::min(kv_total, (i + 1) * per_item);
-      w.peers = once ? sc.peers[(size_t)i] : -1;
+      w.peers = once ? sc.peers[(size_t)i] : 0;
       w.partial = n_split > 1 ? (int32_t)(n_partials++) : -1;
       w.first_partial = first_partial;
       w.merge_key = merge_key;
