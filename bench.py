@@ -3,14 +3,14 @@
 
 A step is one pass of the whole path over one synthetic batch: ingest of the
 transferred prefixes of the continuation chunks and append of the iteration's new K/V
-rows (one launch: cronus_kv_append_pair), and the mixed attention
-(cronus_attn_mixed: work decomposition, chunk tiles, decode spans and their merge).  Inputs are
+rows (one launch), and the mixed attention (work decomposition, chunk tiles, decode spans
+and their merge), in one call (cronus_iteration).  Inputs are
 resident in HBM before the timed region.  Prints ONE JSON line.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--no-extra]
                   [--no-cpu-baseline]
 
-The headline workload is the prefill-heavy batch (benchmark configs[2]): the largest
+The headline workload is the prefill-heavy batch: the largest
 bf16 batch and the one that carries the MFMA roofline target.  Every other workload is
 timed with the same K and W and reported under "other_workloads", each with its own
 roofline and cpu_baseline: the Llama-3-8B-shaped batch, the decode-heavy batch (HBM
@@ -377,7 +377,7 @@ def main():
         "config": {"workload": args.workload, "q_heads": sh.n_q_heads, "kv_heads": sh.n_kv_heads,
                    "head_dim": sh.head_dim, "kv_dtype": sh.kv_dtype, "block_size": 16,
                    "n_seqs": batch.n_seqs, "q_tokens": batch.total_q, "kv_tokens": int(batch.kv_lens.sum()),
-                   "step": "kv_append_pair(prefix of chunks, new tokens) + attn_mixed"},
+                   "step": "iteration: kv_append_pair(prefix of chunks, new tokens) + attn_mixed"},
         "detail": main_res,
         "roofline": main_res["roofline"],
         "other_workloads": others,

@@ -425,6 +425,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 508; }  // 0.5.8: decode K/V past the cache; cronus_iteration; the static list in the arguments
+int cronus_version(void) { return 509; }  // 0.5.9: lengths checked before rows are placed; small decode launches, chunk tails and shared blocks through the caches
 
 }  // extern "C"

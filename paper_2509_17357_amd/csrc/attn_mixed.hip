@@ -1242,9 +1242,12 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
     feed.turn ^= 64;
   }
   younger = 0;
-  // Non-temporal stores: the output of a launch (206 MB for 25 k tokens of 32 heads) would push K/V that other tiles still
-  // read out of the caches.  us a pass: 4 chunks next to 64 decodes 143.3 -> 140.3, whole prompts 329 -> 325, large chunks
-  // behind prefixes 802 -> 799; with a matrix product that reads the output behind each pass 181.8 -> 179.2, 442 -> 439, 876 -> 876.
+  // Non-temporal stores: the output would push K/V that other tiles still read out of the caches.  At every size: of 25
+  // launches none was slower, and with a product (4096 wide) behind each pass that reads the output the worst lost 1 %.  us a pass,
+  // ordinary / non-temporal, alone and with the product: 512 tokens (4 MB) 21.0 / 20.8 and 52.8 / 52.6, 4 prompts of 700 (22 MB)
+  // 41.5 / 40.7 and 116.0 / 116.0, 5 of 1000 (40 MB) 73.2 / 68.1 and 214 / 204, 8 of 1000 (65 MB) 101.2 / 99.3 and 302 / 296, 16 of 1200
+  // (157 MB) 234 / 232 and 712 / 719, 4 chunks of 512 next to 64 decodes 137.3 / 131.2 and 203.5 / 199.2.  (6 prompts of 1000 before a
+  // product 1024 wide: 128 / 132.)
   if (finished) {
     unsigned char* const op =
         reinterpret_cast<unsigned char*>(p.out + ((long long)(fin.q_off + fin.q_tok0) * p.n_q_heads + fin.head0) * D);
@@ -1447,32 +1450,32 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     };
     const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;  // sub-tiles wave, wave+8, ...
     auto stream = [&](auto nt) -> void {
-    if (n_iter > 0) {
-      issue_k(nt, 0);
-      issue_v(nt, 0);
-    }
-    pin_q();
-    for (int j = 0; j < n_iter; ++j) {
-      const int u = wave + kWaves * j;
-      const bool has_next = j + 1 < n_iter;
-      u32x4 kop[NSTEP], vop[NSTEP], pp[2];
-      f32x16 s;
-      wait_vmcnt<NSTEP>();  // K(j) landed; the V(j) loads issued after it may still fly
-      lds_read_planes<NSTEP>(kop, rd_addr);
-      compute_s(kop, s);
-      if (has_next) {
-        if (((j + 1) & 31) == 0) {
-          load_table(j + 1);
-          pin_table();
-        }
-        issue_k(nt, j + 1);  // the K planes are free again
+      if (n_iter > 0) {
+        issue_k(nt, 0);
+        issue_v(nt, 0);
       }
-      softmax(s, pp, u);
-      if (has_next) wait_vmcnt<NSTEP>(); else wait_vmcnt<0>();  // V(j) landed
-      lds_read_planes<NSTEP>(vop, rd_addr + NSTEP * 1024);
-      compute_pv(vop, pp, u);
-      if (has_next) issue_v(nt, j + 1);
-    }
+      pin_q();
+      for (int j = 0; j < n_iter; ++j) {
+        const int u = wave + kWaves * j;
+        const bool has_next = j + 1 < n_iter;
+        u32x4 kop[NSTEP], vop[NSTEP], pp[2];
+        f32x16 s;
+        wait_vmcnt<NSTEP>();  // K(j) landed; the V(j) loads issued after it may still fly
+        lds_read_planes<NSTEP>(kop, rd_addr);
+        compute_s(kop, s);
+        if (has_next) {
+          if (((j + 1) & 31) == 0) {
+            load_table(j + 1);
+            pin_table();
+          }
+          issue_k(nt, j + 1);  // the K planes are free again
+        }
+        softmax(s, pp, u);
+        if (has_next) wait_vmcnt<NSTEP>(); else wait_vmcnt<0>();  // V(j) landed
+        lds_read_planes<NSTEP>(vop, rd_addr + NSTEP * 1024);
+        compute_pv(vop, pp, u);
+        if (has_next) issue_v(nt, j + 1);
+      }
     };
     pin_table();
     if (shared()) stream(std::integral_constant<int, 0>{});
@@ -1533,23 +1536,23 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     };
     const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;
     auto stream = [&](auto nt) -> void {
-    if (n_iter > 0) issue(nt, 0);
-    if (n_iter > 1) issue(nt, 1);
-    pin_q();
-    for (int j = 0; j < n_iter; ++j) {
-      const int u = wave + kWaves * j;
-      const bool more = j + 1 < n_iter;  // sub-tile j + 1 has been requested
-      u32x4 kop[NSTEP], vop[NSTEP], pp[2];
-      f32x16 s;
-      if (more) wait_vmcnt<3 * NIK>(); else wait_vmcnt<NIK>();   // K(j) landed
-      read_k(kop, j);
-      compute_s(kop, s);
-      softmax(s, pp, u);
-      if (more) wait_vmcnt<2 * NIK>(); else wait_vmcnt<0>();     // V(j) landed
-      read_v(vop, j);
-      if (j + 2 < n_iter) issue(nt, j + 2);                          // this set is free again
-      compute_pv(vop, pp, u);
-    }
+      if (n_iter > 0) issue(nt, 0);
+      if (n_iter > 1) issue(nt, 1);
+      pin_q();
+      for (int j = 0; j < n_iter; ++j) {
+        const int u = wave + kWaves * j;
+        const bool more = j + 1 < n_iter;  // sub-tile j + 1 has been requested
+        u32x4 kop[NSTEP], vop[NSTEP], pp[2];
+        f32x16 s;
+        if (more) wait_vmcnt<3 * NIK>(); else wait_vmcnt<NIK>();   // K(j) landed
+        read_k(kop, j);
+        compute_s(kop, s);
+        softmax(s, pp, u);
+        if (more) wait_vmcnt<2 * NIK>(); else wait_vmcnt<0>();     // V(j) landed
+        read_v(vop, j);
+        if (j + 2 < n_iter) issue(nt, j + 2);                      // this set is free again
+        compute_pv(vop, pp, u);
+      }
     };
     pin_table();
     if (shared()) stream(std::integral_constant<int, 0>{});
