@@ -92,7 +92,7 @@ struct AttnParams {
   unsigned done_value;
   int q_base[kQueues];
   int q_len[kQueues];
-  CompactPlan compact;  // of a list in the launch's arguments (items is not read then); past_cache: of every launch
+  CompactPlan compact;  // of a list in the launch's arguments (items is not read then)
 };
 
 // A compact list (2-byte references) as a kernel argument of a call of the static entry point, which otherwise needs a
@@ -469,10 +469,10 @@ __device__ __forceinline__ int resolve_item(const AttnParams& p, Feed& f, int he
 }
 constexpr int kNotYet = -2;  // WorkItem::wide of a mailbox that waits for its record
 // Writes the record of a list's item to the mailbox, complete on return; u and ref are uniform.  The peers of a narrow item
-// are left to run_narrow, which has the units at hand: in their place stands the item's own unit.
+// are left to run_narrow, which has the units at hand: in their place (>= 0) stands the item's own unit.
 __device__ __forceinline__ void post_item(const AttnParams& p, const Feed& f, const CompactUnit& u, unsigned ref, int lane) {
   WorkItem w = expand_unit(p.compact, u, ref);
-  if (!w.wide) w.peers = unit_of_ref(p.compact, ref);
+  if (!w.wide && w.peers == 0) w.peers = (int)unit_of_ref(p.compact, ref);
   const int* const wf = reinterpret_cast<const int*>(&w);
   int rec = 0;
 #pragma unroll
@@ -1358,18 +1358,17 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   // chunks next to 64 151.9 -> 144.7; fp8, a chunk next to 48, 95.5 -> 91.2).  K/V that other
   // items read as well is better kept there (64 decodes of 4 k keys, groups of 8 on the same blocks: 60 us, 81
   // non-temporally; with only the first half or quarter of the blocks shared 116 and 149, 110 and 136).  So a span that has the
-  // block at three quarters of its keys in common with one of its peers, the 32 sequences next in the batch that have this column,
+  // block at three quarters of its keys in common with one of its peers, the 31 sequences next in the batch that have this column,
   // is read the ordinary way (looking costs at most 0.4 us an item: 256 decodes of the same 2 k keys 139 -> 143), and so are
   // head groups that share a KV head and the tail of a chunk, whose tiles read the same keys.
-  const bool once = may_pass_cache(p.compact.past_cache, it);
   int peer_blk = -1, own_blk;
   {
-    const int col = peer_column(it.kv_begin, it.kv_end), offset = peer_offset(lane & (2 * kPeers - 1));
+    const int col = peer_column(it.kv_begin, it.kv_end), offset = peer_offset(c32);
     own_blk = bt[col];
-    bool look = once && lane < 2 * kPeers;
+    bool look = lane < kPeers;
     if constexpr (LIST) {
-      const int unit = (int)it.peers + offset;
-      look = look && unit >= 0 && unit < p.compact.n_units;
+      const int unit = it.peers + offset;
+      look = look && it.peers >= 0 && unit >= 0 && unit < p.compact.n_units;
       const unsigned units = (unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
       u32x4 v;  // the first half of the unit
       asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
@@ -1378,7 +1377,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
                    : "memory");
       look = look && is_peer(CompactUnit{(int)v[0], (int)v[1], (int)v[2], (int)v[3], 0, 0, 0, 0}, it.seq, offset, col);
     } else {
-      look = look && (it.peers >> (lane & (2 * kPeers - 1)) & 1);
+      look = look && (max(it.peers, 0) >> c32 & 1);
     }
     if (look) peer_blk = p.block_tables[(long long)(it.seq + offset) * p.max_blocks + col];
   }
@@ -1422,7 +1421,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   };
 
   auto shared = [&]() {
-    return !once || __builtin_amdgcn_ballot_w64(peer_blk == own_blk) != 0;
+    return it.peers < 0 || __builtin_amdgcn_ballot_w64(peer_blk == own_blk) != 0;
   };
   if constexpr (!FP8) {
     // K/V chunks go global -> LDS by DMA, one 16-byte chunk per lane per instruction, into
@@ -1958,7 +1957,6 @@ int launch_attn(const AttnLaunch& a, bool* main_launched) {
     p.q_len[x] = pl.q_len[x];
   }
   p.compact = a.compact;
-  p.compact.past_cache = pl.past_cache;
   p.stage_seqs = reinterpret_cast<const StageSeq*>(image + pl.off_stage);
   p.stage_k = ws + pl.off_stage_k;
   p.stage_v = ws + pl.off_stage_v;

@@ -56,8 +56,8 @@ struct WorkItem {
   int32_t prefix_len, chunk_len, q_off;
   union {
     int32_t n_blocks;  // wide: as in the sequence's record
-    uint32_t peers;    // narrow: a bit for each sequence near by whose table has the item's column (peer_column,
-                       // peer_offset); looked at where may_pass_cache holds
+    int32_t peers;     // narrow: < 0: its K/V is read the ordinary way; else a bit for each sequence near by whose table has
+                       // the item's column (peer_column, peer_offset)
   };
   // partial >= 0: first partial slot of the item's row group, and n_split * kMaxMergeGroups +
   // the group's index among those of the launch
@@ -67,14 +67,15 @@ static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
 // A narrow item whose K/V no other item reads keeps it out of the caches.  The host knows of the others where there are more head
 // groups of a KV head than one, and where the item is the tail of a chunk, whose tiles read the same keys.  Whether decodes share blocks is seen in the block
-// tables only: the item compares its block at three quarters of its keys with that of the kPeers sequences on either side
+// tables only: the item compares its block at three quarters of its keys with that of the 16 sequences before and the 15 behind it
 // in the batch, where they attend in this launch and have as many blocks (no other entry of their rows is read).  As many as a
-// record has bits for: with 8 on either side, 64 decodes of the same 4 k keys in groups of 7, nine places apart, took 101 us instead of 71,
+// record has bits for (the sign says whether to look; a flag among the kernel's arguments cost each narrow item a scalar load, 0.5 us):
+// with 8 on either side, 64 decodes of the same 4 k keys in groups of 7, nine places apart, took 101 us instead of 71,
 // and 8 prefixes dealt at random 84 instead of 75.
-constexpr int kPeers = 16;
+constexpr int kPeersBefore = 16, kPeers = 31;
 CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) { return (kv_begin + (kv_end - kv_begin) / 4 * 3) / kBlock; }
-CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeers ? bit - kPeers : bit - kPeers + 1; }
-CRONUS_HOST_DEVICE inline bool may_pass_cache(int32_t past_cache, const WorkItem& w) { return past_cache && w.n_tok == w.chunk_len; }  // past_cache: the plan's
+CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeersBefore ? bit - kPeersBefore : bit - kPeersBefore + 1; }
+
 // The K/V of a launch's decodes passes the caches from this many bytes on.  Less may still lie there from its last use (the
 // eight L2s hold 32 MB).  us a pass, ordinary / past the caches, over the same three batches in turn and cold:
 // 2 decodes of 1000 keys (8 MB) 15.6 / 17.8 and 18.6 / 18.3, 4 of 2000 (33 MB) 17.4 / 19.3 and 20.8 / 20.1, 8 of 1500
@@ -124,7 +125,7 @@ CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const Compa
   w.chunk_len = u.chunk_len;
   w.q_off = u.q_off;
   if (wide) w.n_blocks = (u.prefix_len + u.chunk_len + kBlock - 1) / kBlock;
-  else w.peers = 0;
+  else w.peers = c.past_cache && w.n_tok == u.chunk_len ? 0 : -1;  // no peers yet
   return w;
 }
 // Units lie in the order of their sequences, so a decode's peers are found beside its own unit, where the sequences
@@ -135,11 +136,11 @@ CRONUS_HOST_DEVICE inline bool is_peer(const CompactUnit& v, int32_t seq, int32_
 CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
   const int32_t unit = (int32_t)unit_of_ref(c, ref);
   WorkItem w = expand_unit(c, units[unit], ref);
-  if (!w.wide && may_pass_cache(c.past_cache, w)) {
+  if (!w.wide && w.peers == 0) {
     const int32_t column = peer_column(w.kv_begin, w.kv_end);
-    for (int32_t b = 0; b < 2 * kPeers; ++b) {
+    for (int32_t b = 0; b < kPeers; ++b) {
       const int32_t v = unit + peer_offset(b);
-      if (v >= 0 && v < c.n_units && is_peer(units[v], w.seq, peer_offset(b), column)) w.peers |= 1u << b;
+      if (v >= 0 && v < c.n_units && is_peer(units[v], w.seq, peer_offset(b), column)) w.peers |= 1 << b;
     }
   }
   return w;

@@ -45,8 +45,7 @@ struct Scratch {
   // compact_plan: the unit of every item (tiles of a sequence back to back, head group by head group), and their number
   std::vector<int32_t> wide_unit, narrow_unit;
   long long n_units;
-  std::vector<int32_t> unit_seq, unit_keys;  // build_plan: for WorkItem::peers
-  std::vector<uint32_t> peers;
+  std::vector<int32_t> unit_seq, unit_keys, peers;  // build_plan: for WorkItem::peers
   std::vector<uint8_t> whole;          // by sequence: narrow rows that are not cut for want of arrival counters (else empty)
   std::vector<float> row_keys;         // keys of the narrow rows, one entry per sequence
   struct Busy { double until; long long cus; };
@@ -474,12 +473,12 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
     }
   }
 
-  // Sequence and keys of every unit, with kPeers empty places on either side, for WorkItem::peers (as expand_item finds them).
+  // Sequence and keys of every unit, with 16 empty places on either side, for WorkItem::peers (as expand_item finds them).
   const bool past_cache =
       n_groups == 1 && decode_keys * 2 * Hkv * D * (cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2) >= kPastCacheBytes;
   if (past_cache) {
-    sc.unit_seq.assign(kPeers, 0);
-    sc.unit_keys.assign(kPeers, 0);
+    sc.unit_seq.assign(kPeersBefore, 0);
+    sc.unit_keys.assign(kPeersBefore, 0);
     for (int s = 0; s < n_seqs; ++s) {
       const int32_t C = chunk_lens[s];
       for (int32_t t = C; t > 0; t -= wide_tok) {
@@ -487,12 +486,12 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
         sc.unit_keys.push_back(prefix_lens[s] + C);
       }
     }
-    sc.unit_seq.insert(sc.unit_seq.end(), kPeers, 0);
-    sc.unit_keys.insert(sc.unit_keys.end(), kPeers, 0);
+    sc.unit_seq.insert(sc.unit_seq.end(), kPeersBefore, 0);
+    sc.unit_keys.insert(sc.unit_keys.end(), kPeersBefore, 0);
   }
   auto peers_of = [&](int32_t s, int32_t unit, int32_t kv_begin, int32_t kv_end) {
     typedef int32_t Four __attribute__((vector_size(16)));
-    static_assert(kPeers == 16, "four vectors a side");
+    static_assert(kPeersBefore == 16 && kPeers == 31, "four vectors a side, without the last place");
     const int32_t first_key = peer_column(kv_begin, kv_end) * kBlock;
     const Four places{0, 1, 2, 3}, bits{1, 2, 4, 8};
     Four mask{0, 0, 0, 0};
@@ -503,7 +502,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       std::memcpy(&keys, sc.unit_keys.data() + at, sizeof(keys));
       mask |= (keys > first_key) & (seq == places + (s + peer_offset(4 * v))) & (bits << 4 * v);
     }
-    return (uint32_t)(mask[0] | mask[1] | mask[2] | mask[3]);
+    return (mask[0] | mask[1] | mask[2] | mask[3]) & 0x7fffffff;
   };
 
   int32_t peers_unit = -1;  // whose spans sc.peers is of: the same for every KV head
@@ -532,7 +531,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       w.seq = s; w.kv_head = kvh; w.head0 = head0; w.n_heads = nh; w.q_tok0 = q_tok0; w.n_tok = n_tok;
       w.kv_begin = i * per_item;
       w.kv_end = std::min(kv_total, (i + 1) * per_item);
-      w.peers = once ? sc.peers[(size_t)i] : 0;
+      w.peers = once ? sc.peers[(size_t)i] : -1;
       w.partial = n_split > 1 ? (int32_t)(n_partials++) : -1;
       w.first_partial = first_partial;
       w.merge_key = merge_key;

@@ -1,7 +1,7 @@
 // Host-only driver for what passes the caches (plan.cpp: WorkItem::peers, rows_past_cache): reads batches from stdin
 //   <Hq> <Hkv> <D> <fp8 0|1> <n_cus> <n_seqs> P0 C0 P1 C1 ...
 // and prints, for each, "<narrow items> <rows past the caches 0|1>" and then a line "seq kv_head q_tok0 n_tok kv_begin kv_end
-// looks peers" for every one (looks: whether the kernel looks at the peers at all).
+// peers" for every one.
 #include <cstdio>
 #include <iostream>
 #include <vector>
@@ -33,8 +33,8 @@ int main() {
     std::printf("%lld %d\n", (long long)(plan.n_items - plan.n_wide), (int)rows_past_cache(&c, P.data(), C.data(), n));
     for (long long i = 0; i < plan.n_items; ++i)
       if (!w[i].wide)
-        std::printf("%d %d %d %d %d %d %d %u\n", w[i].seq, w[i].kv_head, w[i].q_tok0, w[i].n_tok, w[i].kv_begin, w[i].kv_end,
-                    (int)may_pass_cache(plan.past_cache, w[i]), w[i].peers);
+        std::printf("%d %d %d %d %d %d %d\n", w[i].seq, w[i].kv_head, w[i].q_tok0, w[i].n_tok, w[i].kv_begin, w[i].kv_end,
+                    w[i].peers);
   }
   return 0;
 }
