@@ -1352,7 +1352,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   };
   auto pin_table = [&]() { asm volatile("" : "+v"(bt_reg)); };  // wait for them here, not at each use
   load_table(0);
-  // K/V that one item reads is read non-temporally where the launch's decodes have much of it (kPastCacheBytes): it passes the
+  // K/V that one item reads is read non-temporally where the launch has much of it, or long products (kPastCacheBytes, kPastCacheProductsUs): it passes the
   // 256 MB cache in front of the HBM by, which otherwise takes in every line that streams past (us a pass: 256 decodes of
   // 1 .. 8 k keys 814 -> 742, 6.6 TB/s where it was 5.95; 64 of 100 .. 4000 through the static entry point 112.6 -> 100.2; four
   // chunks next to 64 151.9 -> 144.7; fp8, a chunk next to 48, 95.5 -> 91.2).  K/V that other

@@ -82,6 +82,12 @@ CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeers
 // (49 MB) 20.6 / 21.7 and 23.8 / 22.5, 16 of 1000 (66 MB) 21.6 / 22.9 and 26.0 / 23.9, 12 of 2000 (98 MB) 33.2 / 32.6 and 36.0 / 33.4,
 // 16 of 2000 (131 MB) 36.1 / 32.6 and 36.8 / 33.0.  The line lies where the two together are even.
 constexpr long long kPastCacheBytes = 40'000'000;
+// And whatever there is of it where the chunks' products take this long (at 1.2 PFLOP/s): the decodes are not what such a launch
+// waits for, and their K/V would push out what the chunk tiles read again.  us a pass, ordinary / past the caches: 4 decodes of 2000
+// next to 500 tokens behind 8000 (products 56 us) 99.6 / 98.2, next to 3 x 400 behind 4000 (69) 118.4 / 117.8; fp8, 8 of 1100 next to 4 whole prompts
+// of 700 (27) 75.0 / 72.0.  The other side: 4 of 2000 next to 64 tokens behind 200 (0.2) 17.2 / 18.8; 7 heads a KV head, 8 of 1100 next to
+// 256 behind 1000 (4) 30.0 / 30.7; 8 of 1100 next to 4 whole prompts of 700 (13) 46.2 / 46.9.
+constexpr double kPastCacheProductsUs = 20;
 
 // Compact form of the work list: the items of one tile of a sequence differ only by KV head and
 // key span, so an item is a number (unit << head_bits | kv_head) << span_bits | span (2 bytes
@@ -185,7 +191,7 @@ struct Plan {
   int64_t n_items = 0, n_wide = 0, n_partials = 0, n_merge = 0, n_merge_rows = 0;
   int32_t n_seqs = 0;
   int32_t wide_rows = 0;  // rows per wide tile (compile-time choice of the kernel instance)
-  int32_t past_cache = 0;  // 1: the decodes' K/V passes the caches (WorkItem::peers; one head group, kPastCacheBytes)
+  int32_t past_cache = 0;  // 1: the decodes' K/V passes the caches (WorkItem::peers; one head group, kPastCacheBytes or kPastCacheProductsUs)
   int32_t n_stage_seqs = 0;
   int64_t n_stage_blocks = 0;
   // The work items form kQueues queues, stored one after the other: queue x is items

@@ -121,6 +121,11 @@ static double rounds_us(const std::vector<float>& row_keys, long long copies, lo
   return list_us(loads, cus);
 }
 
+// Time of the chunks' products over `pairs` visible (query, key) pairs a head, at 1.2 PFLOP/s.
+static double products_us(const cronus_kv_cache* cache, double pairs) {
+  return pairs * 4.0 * cache->num_q_heads * cache->head_dim / 1.2e9;
+}
+
 int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens,
                int32_t n_seqs, int32_t max_blocks_per_seq, int n_cus, Plan* plan, bool allow_stage,
                size_t scratch_limit, bool lean) {
@@ -163,7 +168,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
   // planner's unit (one key of a full wide tile = wide_rows / 128, one key of a narrow
   // item = 1/2), to size the spans that long wide tiles are cut into
   long long narrow_keys = 0, decode_keys = 0;
-  double wide_cost_total = 0;
+  double wide_cost_total = 0, chunk_pairs = 0;
   long long wide_tiles = 0;
   for (int s = 0; s < n_seqs; ++s) {
     const long long P = prefix_lens[s], C = chunk_lens[s];
@@ -174,6 +179,7 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
       narrow_keys += (P + C) * Hkv * n_groups;
       decode_keys += P + C;
     } else {
+      chunk_pairs += (double)C * (double)P + 0.5 * (double)C * (double)(C + 1);
       const long long rem = C % wide_tok;
       if (rem && rem * group <= kNarrowRows) narrow_keys += (P + C) * Hkv * n_groups;
       const long long full = C / wide_tok;  // full tiles end at P + wide_tok, P + 2 wide_tok, ...
@@ -475,7 +481,8 @@ int build_plan(const cronus_kv_cache* cache, const int32_t* prefix_lens, const i
 
   // Sequence and keys of every unit, with 16 empty places on either side, for WorkItem::peers (as expand_item finds them).
   const bool past_cache =
-      n_groups == 1 && decode_keys * 2 * Hkv * D * (cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2) >= kPastCacheBytes;
+      n_groups == 1 && (decode_keys * 2 * Hkv * D * (cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2) >= kPastCacheBytes ||
+                        (decode_keys > 0 && products_us(cache, chunk_pairs) >= kPastCacheProductsUs));
   if (past_cache) {
     sc.unit_seq.assign(kPeersBefore, 0);
     sc.unit_keys.assign(kPeersBefore, 0);
@@ -904,7 +911,7 @@ bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, c
   }
   const double elem_bytes = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? 1 : 2;
   stream_us *= 2.0 * elem_bytes * cache->num_kv_heads * cache->head_dim / 6e6;  // 6 TB/s
-  product_us *= 4.0 * cache->num_q_heads * cache->head_dim / 1.2e9;             // 1.2 PFLOP/s
+  product_us = products_us(cache, product_us);
   return stream_us >= 20 && stream_us >= 2 * product_us;
 }
 

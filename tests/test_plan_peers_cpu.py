@@ -1,7 +1,7 @@
 """Which sequences' block tables a narrow item looks at (WorkItem::peers, under AddressSanitizer and
 UndefinedBehaviorSanitizer): only entries that the header says are read, that is below ceil(len / 16) of a sequence that
 attends in the call, and among decodes all of the sixteen before and the fifteen behind it that have the column.  And which items look at none:
-those whose K/V other items of the launch read, and all of a launch whose decodes' K/V is small."""
+those whose K/V other items of the launch read, and all of a launch whose decodes' K/V and chunks are small."""
 import os
 import shutil
 import subprocess
@@ -92,7 +92,7 @@ def test_small_launches_keep_their_kv_in_the_caches(plan_of, fp8, heads, below):
     """`below` keys of decodes are the most that take less than 40 MB."""
     row = 2 * heads[1] * heads[2] * (1 if fp8 else 2)
     assert below * row <= 40e6 < (below + 1) * row
-    for chunks in ([], [(700, 300), (0, 1000)]):  # whose keys do not count
+    for chunks in ([], [(70, 300), (0, 200)]):  # whose keys do not count
         for keys in (below - (below * row == 40e6), below + 1):
             n = keys // 3
             peers = plan_of(*heads, 256, [(n - 1, 1), (n - 1, 1)] + chunks + [(keys - 2 * n - 1, 1)], fp8)
@@ -117,3 +117,17 @@ def test_which_iterations_place_their_rows_past_the_caches(plan_of, case):
     heads, fp8, seqs, past = ROWS[case]
     plan_of(*heads, 256, seqs, fp8)
     assert plan_of.rows_past == past
+
+
+@pytest.mark.parametrize("heads, fp8, chunk", [((32, 8, 128), 0, (918, 1024)), ((64, 8, 128), 1, (918, 512)), ((8, 2, 64), 0, (2000, 3000))])
+def test_decodes_next_to_long_products_keep_out_of_the_caches(plan_of, heads, fp8, chunk):
+    """Products of 20 us at 1.2 PFLOP/s, with one decode of few keys next to them."""
+    us = lambda P, C: 4 * heads[0] * heads[2] * (C * P + C * (C + 1) / 2) / 1.2e9
+    P, C = chunk
+    while us(P, C) < 20:
+        P += 1
+    while us(P - 1, C) >= 20:
+        P -= 1
+    for p, past in ((P - 1, False), (P, True)):
+        items = plan_of(*heads, 256, [(500, 1), (p, C)], fp8)
+        assert ((items[items[:, 3] == 1][:, 6] >= 0) == past).all(), p
