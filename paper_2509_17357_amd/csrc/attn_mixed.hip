@@ -1365,19 +1365,19 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   {
     const int col = peer_column(it.kv_begin, it.kv_end), offset = peer_offset(c32);
     own_blk = bt[col];
-    bool look = lane < kPeers;
+    bool look;
     if constexpr (LIST) {
-      const int unit = it.peers + offset;
-      look = look && it.peers >= 0 && unit >= 0 && unit < p.compact.n_units;
+      const unsigned unit = (unsigned)(it.peers + offset);
+      look = (lane < kPeers) & (it.peers >= 0) & (unit < (unsigned)p.compact.n_units);
       const unsigned units = (unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
       u32x4 v;  // the first half of the unit
       asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)"
                    : "=&v"(v)
-                   : "v"(units + (look ? unit : 0) * (unsigned)sizeof(CompactUnit))
+                   : "v"(units + (look ? unit : 0u) * (unsigned)sizeof(CompactUnit))
                    : "memory");
-      look = look && is_peer(CompactUnit{(int)v[0], (int)v[1], (int)v[2], (int)v[3], 0, 0, 0, 0}, it.seq, offset, col);
+      look = look & is_peer(CompactUnit{(int)v[0], (int)v[1], (int)v[2], (int)v[3], 0, 0, 0, 0}, it.seq, offset, col);
     } else {
-      look = look && (max(it.peers, 0) >> c32 & 1);
+      look = (lane < kPeers) & (max(it.peers, 0) >> c32 & 1);
     }
     if (look) peer_blk = p.block_tables[(long long)(it.seq + offset) * p.max_blocks + col];
   }

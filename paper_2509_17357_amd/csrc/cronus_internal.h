@@ -73,7 +73,9 @@ static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 // with 8 on either side, 64 decodes of the same 4 k keys in groups of 7, nine places apart, took 101 us instead of 71,
 // and 8 prefixes dealt at random 84 instead of 75.
 constexpr int kPeersBefore = 16, kPeers = 31;
-CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) { return (kv_begin + (kv_end - kv_begin) / 4 * 3) / kBlock; }
+CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) {
+  return (int32_t)(((uint32_t)kv_begin + (uint32_t)(kv_end - kv_begin) / 4 * 3) / kBlock);
+}
 CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeersBefore ? bit - kPeersBefore : bit - kPeersBefore + 1; }
 
 // The K/V of a launch's decodes passes the caches from this many bytes on.  Less may still lie there from its last use (the
@@ -137,7 +139,7 @@ CRONUS_HOST_DEVICE inline WorkItem expand_unit(const CompactPlan& c, const Compa
 // Units lie in the order of their sequences, so a decode's peers are found beside its own unit, where the sequences
 // between them have one unit each.
 CRONUS_HOST_DEVICE inline bool is_peer(const CompactUnit& v, int32_t seq, int32_t offset, int32_t column) {
-  return v.seq == seq + offset && column * kBlock < v.prefix_len + v.chunk_len;
+  return (v.seq == seq + offset) & (column * kBlock < v.prefix_len + v.chunk_len);
 }
 CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const CompactUnit* units, uint32_t ref) {
   const int32_t unit = (int32_t)unit_of_ref(c, ref);
