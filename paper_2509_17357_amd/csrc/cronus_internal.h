@@ -78,12 +78,13 @@ CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) 
 }
 CRONUS_HOST_DEVICE inline int32_t peer_offset(int32_t bit) { return bit < kPeersBefore ? bit - kPeersBefore : bit - kPeersBefore + 1; }
 
-// The K/V of a launch's decodes passes the caches from this many bytes on.  Less may still lie there from its last use (the
-// eight L2s hold 32 MB).  us a pass, ordinary / past the caches, over the same three batches in turn and cold:
-// 2 decodes of 1000 keys (8 MB) 15.6 / 17.8 and 18.6 / 18.3, 4 of 2000 (33 MB) 17.4 / 19.3 and 20.8 / 20.1, 8 of 1500
-// (49 MB) 20.6 / 21.7 and 23.8 / 22.5, 16 of 1000 (66 MB) 21.6 / 22.9 and 26.0 / 23.9, 12 of 2000 (98 MB) 33.2 / 32.6 and 36.0 / 33.4,
-// 16 of 2000 (131 MB) 36.1 / 32.6 and 36.8 / 33.0.  The line lies where the two together are even.
-constexpr long long kPastCacheBytes = 40'000'000;
+// The K/V of a launch's decodes passes the caches from this many bytes on: less of it may still lie there from its last use, three such
+// batches in turn fit into 256 MB.  us a pass, ordinary / past the caches, over the same three batches in turn and cold:
+// 2 decodes of 1000 keys (8 MB) 15.6 / 17.8 and 18.6 / 18.3, 4 of 2000 (33 MB) 17.4 / 19.3 and 20.8 / 20.1, 76 of 150 (47 MB) 29.9 / 31.2 and
+// 34.0 / 32.5, 8 of 1500 (49 MB) 20.6 / 21.7 and 23.8 / 22.5, 128 of 130 (68 MB) 42.6 / 45.4 and 48.0 / 46.0, 100 of 200 (82 MB) 39.5 / 40.8
+// and 43.7 / 41.9, 33 of 700 (95 MB) 34.3 / 34.5 and 37.9 / 35.2, 12 of 2000 (98 MB) 33.2 / 32.6 and 36.0 / 33.4, 200 of 120 (98 MB) 63.8 / 62.5 and
+// 66.1 / 63.2, 16 of 2000 (131 MB) 36.1 / 32.6 and 36.8 / 33.0.  Cold batches below the line give up 4 to 8 % for it.
+constexpr long long kPastCacheBytes = 90'000'000;
 // And whatever there is of it where the chunks' products take this long (at 1.2 PFLOP/s): the decodes are not what such a launch
 // waits for, and their K/V would push out what the chunk tiles read again.  us a pass, ordinary / past the caches: 4 decodes of 2000
 // next to 500 tokens behind 8000 (products 56 us) 99.6 / 98.2, next to 3 x 400 behind 4000 (69) 118.4 / 117.8; fp8, 8 of 1100 next to 4 whole prompts

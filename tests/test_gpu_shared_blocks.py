@@ -37,11 +37,11 @@ def test_shared_blocks_give_the_same_bits(shape, n, keys):
         assert np.array_equal(bits_from_bf16_tensor(it.out), want)
 
 
-@pytest.mark.parametrize("shape, n, keys", [(W.SHAPE_8B, 20, 701), (W.HeadShape(16, 8, 128, "fp8"), 18, 1300), (W.HeadShape(8, 4, 64), 40, 1000)])
+@pytest.mark.parametrize("shape, n, keys", [(W.SHAPE_8B, 33, 701), (W.HeadShape(16, 8, 128, "fp8"), 36, 1300), (W.HeadShape(8, 4, 64), 90, 1000)])
 def test_shared_blocks_of_large_launches(shape, n, keys):
-    """The same where the launch's K/V is large enough (40 MB) to be read non-temporally at all, with the records in host memory
+    """The same where the launch's K/V is large enough (90 MB) to be read non-temporally at all, with the records in host memory
     and with the list in the arguments."""
-    assert n * keys * 2 * shape.n_kv_heads * shape.head_dim * (1 if shape.kv_dtype == "fp8" else 2) >= 40e6
+    assert n * keys * 2 * shape.n_kv_heads * shape.head_dim * (1 if shape.kv_dtype == "fp8" else 2) >= 90e6
     it = DeviceIteration(W.custom_batch(shape, [keys - 1] * n, [1] * n, seed=9750 + n), pool_fill=0x5A)
     it.load_device_inputs()
     for t in (it.ctx_k, it.ctx_v, it.new_k, it.new_v):
