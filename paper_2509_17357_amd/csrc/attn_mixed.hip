@@ -1352,15 +1352,16 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   };
   auto pin_table = [&]() { asm volatile("" : "+v"(bt_reg)); };  // wait for them here, not at each use
   load_table(0);
-  // K/V that one item reads is read non-temporally where the launch has much of it, or long products (kPastCacheBytes, kPastCacheProductsUs): it passes the
-  // 256 MB cache in front of the HBM by, which otherwise takes in every line that streams past (us a pass: 256 decodes of
-  // 1 .. 8 k keys 814 -> 742, 6.6 TB/s where it was 5.95; 64 of 100 .. 4000 through the static entry point 112.6 -> 100.2; four
-  // chunks next to 64 151.9 -> 144.7; fp8, a chunk next to 48, 95.5 -> 91.2).  K/V that other
+  // K/V that one item reads is read non-temporally where the launch has much of it, or long products (kPastCacheBytes,
+  // kPastCacheProductsUs): it passes the 256 MB cache in front of the HBM by, which otherwise takes in every line that streams
+  // past (us a pass: 256 decodes of 1 .. 8 k keys 814 -> 742, 6.6 TB/s where it was 5.95; 64 of 100 .. 4000 through the static
+  // entry point 112.6 -> 100.2; four chunks next to 64 151.9 -> 144.7; fp8, a chunk next to 48, 95.5 -> 91.2).  K/V that other
   // items read as well is better kept there (64 decodes of 4 k keys, groups of 8 on the same blocks: 60 us, 81
   // non-temporally; with only the first half or quarter of the blocks shared 116 and 149, 110 and 136).  So a span that has the
-  // block at three quarters of its keys in common with one of its peers, the 31 sequences next in the batch that have this column,
-  // is read the ordinary way (looking costs at most 0.4 us an item: 256 decodes of the same 2 k keys 139 -> 143), and so are
-  // head groups that share a KV head and the tail of a chunk, whose tiles read the same keys.
+  // block at three quarters of its keys in common with one of its peers, the 31 sequences next in the batch that have this
+  // column, is read the ordinary way (looking costs at most 0.4 us an item: 256 decodes of the same 2 k keys 139 -> 143; no
+  // branches, which cost as much again), and so are head groups that share a KV head and the tail of a chunk, whose tiles
+  // read the same keys.
   int peer_blk = -1, own_blk;
   {
     const int col = peer_column(it.kv_begin, it.kv_end), offset = peer_offset(c32);

@@ -65,13 +65,13 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "one work item = one 64-byte line");
 
-// A narrow item whose K/V no other item reads keeps it out of the caches.  The host knows of the others where there are more head
-// groups of a KV head than one, and where the item is the tail of a chunk, whose tiles read the same keys.  Whether decodes share blocks is seen in the block
-// tables only: the item compares its block at three quarters of its keys with that of the 16 sequences before and the 15 behind it
-// in the batch, where they attend in this launch and have as many blocks (no other entry of their rows is read).  As many as a
-// record has bits for (the sign says whether to look; a flag among the kernel's arguments cost each narrow item a scalar load, 0.5 us):
-// with 8 on either side, 64 decodes of the same 4 k keys in groups of 7, nine places apart, took 101 us instead of 71,
-// and 8 prefixes dealt at random 84 instead of 75.
+// A narrow item whose K/V no other item reads keeps it out of the caches.  The host knows of the others where there are more
+// head groups of a KV head than one, and where the item is the tail of a chunk, whose tiles read the same keys.  Whether
+// decodes share blocks is seen in the block tables only: the item compares its block at three quarters of its keys with that
+// of the 16 sequences before and the 15 behind it in the batch, where they attend in this launch and have as many blocks (no
+// other entry of their rows is read).  As many as a record has bits for; the sign says whether to look (a flag among the
+// kernel's arguments cost each narrow item a scalar load, 0.5 us).  With 8 on either side, 64 decodes of the same 4 k keys in
+// groups of 7, nine places apart, took 101 us instead of 71, and 8 prefixes dealt at random 84 instead of 75.
 constexpr int kPeersBefore = 16, kPeers = 31;
 CRONUS_HOST_DEVICE inline int32_t peer_column(int32_t kv_begin, int32_t kv_end) {
   return (int32_t)(((uint32_t)kv_begin + (uint32_t)(kv_end - kv_begin) / 4 * 3) / kBlock);
