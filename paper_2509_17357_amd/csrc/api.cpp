@@ -287,11 +287,20 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
         if ((long long)prefix_lens[s] + chunk_lens[s] > (long long)max_blocks_per_seq * kBlock) return CRONUS_ERR_INVALID_ARG;
       if (workspace_refused(workspace)) return CRONUS_ERR_WORKSPACE;
     }
+  }
+  auto place_rows = [&] {
+    return launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream,
+                            rows_past_cache(cache, prefix_lens, chunk_lens, n_seqs));
+  };
+  const bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, chunk_lens, n_seqs);
+  auto refused = [&](int rc) {  // after the checks, with the attention not enqueued: the rows are placed all the same
+    const int placed = in_launch ? place_rows() : CRONUS_OK;
+    return placed ? placed : rc;
+  };
+  if (first && !in_launch) {
     // before the plan is built, so that the device works meanwhile (whole prompts, a first pass:
     // 400 us, 446 with the plan first)
-    if (int rc = launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream,
-                                  rows_past_cache(cache, prefix_lens, chunk_lens, n_seqs)))
-      return rc;
+    if (int rc = place_rows()) return rc;
   }
   if (total_q == 0) return CRONUS_OK;
 
@@ -303,22 +312,23 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   if (workspace_bytes < plan.total_bytes) {
     if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, n_cus, &plan, true, 0, true)) return rc;
   }
-  if (workspace_bytes < plan.total_bytes) return CRONUS_ERR_WORKSPACE;
+  if (workspace_bytes < plan.total_bytes) return refused(CRONUS_ERR_WORKSPACE);
   if (plan.n_items > 0x7fffffffLL) return CRONUS_ERR_INVALID_ARG;
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   std::unique_lock<std::mutex> lock(g_mu);
   // everything that can fail without a launch comes first: kernel attributes, the plan buffer
   int dev = 0;
-  if (int rc = prepare_device_locked(&dev)) return rc;
+  if (int rc = prepare_device_locked(&dev)) return refused(rc);
   Slot* slot = acquire_slot(dev, plan.image_bytes, stream, lock);
-  if (!slot) return CRONUS_ERR_HIP;
+  if (!slot) return refused(CRONUS_ERR_HIP);
   unsigned char* const host = static_cast<unsigned char*>(slot->host);
   unsigned char* const dev_mem = static_cast<unsigned char*>(slot->dev);
   write_plan(&plan, host + kSlotHeader);
   // the set of queue heads that belongs to this plan buffer: free again when the buffer is
   const int set = (int)(slot - g_rings[dev].slots);
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, nullptr, {}, 0, &plan, hip_stream,
+  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, nullptr, {}, 0,
+               in_launch ? first : nullptr, prefix_lens, chunk_lens, &plan, hip_stream,
                g_dev[dev].queue_sets + set * kQueueSetInts, reinterpret_cast<uint32_t*>(dev_mem), ++slot->call,
                {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
   slot->stream = stream;
@@ -402,7 +412,7 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   // (The heads of the work queues, which must, live in their own small array, and every
   // launch leaves them zero.)
   AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, base + plan.image_bytes, base,
-               listed ? image.data() : nullptr, compact, listed ? compact_bytes : 0, &plan, hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+               listed ? image.data() : nullptr, compact, listed ? compact_bytes : 0, nullptr, nullptr, nullptr, &plan, hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
   bool main_launched = false;
   return launch_attn(a, &main_launched);
 }

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "cronus_internal.h"
+#include "e4m3_quant.h"
 
 // Scratch of cronus_attn_mixed_static (the entry point for callers that cannot allocate): the
 // plan image and the partial results of one call.  Each GPU that loads the library holds its
@@ -109,6 +110,17 @@ struct ItemList {
 struct NoList {
   static constexpr int kVecs = 0;
 };
+// The new rows of an iteration of narrow items, which its attention launch places itself (map_rows, place_rows_read).
+struct NewRows {
+  static constexpr int kVecs = 0;
+  const unsigned short* k;
+  const unsigned short* v;
+  const int* cu_tokens;
+  const int* start_pos;
+  int n_rows, n_seqs;  // at most kMaxNewRows each
+  int kv_len[kMaxNewRows];  // keys that each sequence's items read
+};
+static_assert(kMaxNewRows == 64, "a lane for each row and for each sequence");
 static_assert(sizeof(AttnParams) <= 256 && sizeof(AttnParams) % 8 == 0, "the arguments with a list are 4 KiB");
 
 constexpr int kNonTemporal = 2;  // cache policy operand of a transfer: the instruction's nt bit
@@ -1271,6 +1283,101 @@ __device__ __forceinline__ bool run_wide(const AttnParams& p, Feed& feed, unsign
   }
 }
 
+// ------------------------------------------------------------ new rows of a decode iteration
+// A row of one KV head in the lanes of a wave: the first D / 8 lanes hold the chunks of K, the next those of V.
+template <int D>
+__device__ __forceinline__ u32x4 load_row(const AttnParams& p, const NewRows& rows, int row, int kv_head, int lane) {
+  constexpr int CH = D / 8;
+  if (lane >= 2 * CH) return u32x4{0, 0, 0, 0};
+  return *reinterpret_cast<const u32x4*>((lane >= CH ? rows.v : rows.k) + ((long long)row * p.n_kv_heads + kv_head) * D + (lane & (CH - 1)) * 8);
+}
+// Stores it in its slot, as kv_append_kernel does: K as 16-byte chunks (fp8: 8 codes), V element by element.
+template <int D, bool FP8>
+__device__ __forceinline__ void store_row(const AttnParams& p, u32x4 x, int kv_head, int blk, int slot, int lane) {
+  constexpr int CH = D / 8;
+  if (lane >= 2 * CH) return;
+  const bool is_v = lane >= CH;
+  const int ch = lane & (CH - 1);
+  const long long base = ((long long)blk * p.n_kv_heads + kv_head) * (16 * D);
+  const long long at = base + (is_v ? ((slot >> 3) * D + ch * 8) * 8 + (slot & 7) : (ch * 16 + slot) * 8);
+  unsigned char* const pool = const_cast<unsigned char*>(is_v ? p.v_pool : p.k_pool);
+  if constexpr (!FP8) {
+    unsigned short* const to = reinterpret_cast<unsigned short*>(pool) + at;
+    if (is_v) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) to[8 * e] = (unsigned short)(x[e >> 1] >> 16 * (e & 1));
+    } else {
+      *reinterpret_cast<u32x4*>(to) = x;
+    }
+  } else {
+    float f[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = __uint_as_float((e & 1) ? (x[e >> 1] & 0xffff0000u) : (x[e >> 1] << 16));
+    const codes8 c = quant_e4m3_x8(f, make_quantiser((is_v ? p.v_scale : p.k_scale)[kv_head]));
+    unsigned char* const to = pool + at;
+    if (is_v) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) to[8 * e] = (unsigned char)(c[e >> 2] >> 8 * (e & 3));
+    } else {
+      *reinterpret_cast<codes8*>(to) = c;
+    }
+  }
+}
+
+// Each wave that is about to read a block which holds new rows stores those rows first (place_rows_read), its own sequence's
+// or another's, so no work-group waits for another; who reads the same block elsewhere stores the same bytes.  A wave's loads
+// see the stores before them, and no line of the block can lie stale in the caches, since whoever read it before on this CU
+// or XCD in this launch had stored its rows there too.  Rows that no item reads (past the length of
+// their sequence, or of a sequence without query rows) are dealt out to the work-groups when they start.
+// One wave: leaves (block, slot) of every row, block -1: none, in LDS at `list`, and behind them whether row s is that of sequence s.
+template <int D, bool FP8>
+__device__ __forceinline__ void map_rows(const AttnParams& p, const NewRows& rows, unsigned list, int lane) {
+  const int lo = rows.cu_tokens[min(lane, rows.n_seqs)], hi = rows.cu_tokens[min(lane + 1, rows.n_seqs)];
+  const int start = rows.start_pos[min(lane, rows.n_seqs - 1)], kv_len = rows.kv_len[lane];
+  int seq = lane < rows.n_seqs ? lane : -1, pos = start, len = kv_len;  // of row `lane`, where every sequence has one
+  const bool in_order = __builtin_amdgcn_ballot_w64(lane < rows.n_seqs && ((lo != lane) | (hi != lane + 1))) == 0;
+  if (!in_order) {
+    seq = -1;
+    for (int s = 0; s < rows.n_seqs; ++s) {
+      const int first = __builtin_amdgcn_readlane(lo, s);
+      if (lane >= first && lane < __builtin_amdgcn_readlane(hi, s)) {
+        seq = s;
+        pos = __builtin_amdgcn_readlane(start, s) + lane - first;
+        len = __builtin_amdgcn_readlane(kv_len, s);
+      }
+    }
+  }
+  if (lane >= rows.n_rows) seq = -1;
+  int blk = -1;
+  if (seq >= 0) blk = p.block_tables[(long long)seq * p.max_blocks + (pos >> 4)];
+  asm volatile("ds_write_b64 %0, %1" ::"v"(list + 8 * lane), "v"(u32x2{(unsigned)blk, (unsigned)(pos & 15)}) : "memory");
+  if (lane == 0) asm volatile("ds_write_b32 %0, %1 offset:%2" ::"v"(list), "v"((int)in_order), "i"(8 * kMaxNewRows) : "memory");
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  unsigned long long unread = __builtin_amdgcn_ballot_w64(seq >= 0 && pos >= len);
+  for (; unread != 0; unread &= unread - 1) {
+    const int row = __builtin_ctzll(unread), b = __builtin_amdgcn_readlane(blk, row);
+    for (int h = (int)(blockIdx.x + gridDim.x - (unsigned)row % gridDim.x) % (int)gridDim.x; h < p.n_kv_heads; h += gridDim.x)
+      if (b >= 0) store_row<D, FP8>(p, load_row<D>(p, rows, row, h, lane), h, b, __builtin_amdgcn_readlane(pos, row) & 15, lane);
+  }
+}
+// A wave is about to read the n blocks in the first lanes of `blocks`: stores the rows in them.  own: the chunks of row
+// own_row, requested ahead (own_row < 0: none).
+template <int D, bool FP8>
+__device__ __forceinline__ void place_rows_read(const AttnParams& p, const NewRows& rows, unsigned list, int kv_head, int blocks, int n,
+                                                int own_row, u32x4 own, int lane) {
+  u32x2 at;
+  asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(at) : "v"(list + 8 * lane) : "memory");
+  for (int i = 0; i < n; ++i) {
+    const int b = __builtin_amdgcn_readlane(blocks, i);
+    for (unsigned long long here = __builtin_amdgcn_ballot_w64((int)at[0] == b); here != 0; here &= here - 1) {
+      const int row = __builtin_ctzll(here);
+      u32x4 x = own;
+      if (row != own_row) x = load_row<D>(p, rows, row, kv_head, lane);
+      store_row<D, FP8>(p, x, kv_head, b, __builtin_amdgcn_readlane((int)at[1], row), lane);
+    }
+  }
+}
+
 // --------------------------------------------------------- narrow (decode-like) item
 // Operand chunks of 8 bytes picked out of a block image in LDS (fp8 codes).
 template <int O0, int O1, int O2, int O3, int O4, int O5, int O6, int O7>
@@ -1294,8 +1401,8 @@ __device__ __forceinline__ void lds_read4_b64(u32x2 (&x)[4], unsigned addr) {
       : "memory");
 }
 
-template <int D, bool FP8, bool LIST>
-__device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& it, unsigned char* smem) {
+template <int D, bool FP8, bool LIST, bool PLACES>
+__device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& it, const NewRows& rows, unsigned char* smem) {
   constexpr int NSTEP = D / 16, NDB = D / 32;
   constexpr int ESZ = FP8 ? 1 : 2;
   constexpr int WAVE_LDS = 2 * NSTEP * 1024 + (FP8 ? 512 : 0);  // per-wave LDS: K planes then V planes; fp8: two sets of block images
@@ -1351,7 +1458,28 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
     bt_reg = bt[min(((it.kv_begin + 32 * uu) >> 4) + (lane & 1), last_blk)];
   };
   auto pin_table = [&]() { asm volatile("" : "+v"(bt_reg)); };  // wait for them here, not at each use
+  const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;  // sub-tiles wave, wave+8, ...
+  const unsigned row_list = (unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
+  int own_row = -1;  // a decode's row lies in its last sub-tile
+  u32x4 own{0, 0, 0, 0};
+  auto place_rows = [&](int j0) {  // of sub-tiles j0 .. j0 + 31, whose entries have been pinned
+    if constexpr (PLACES) {
+      const int last = min(n_iter - j0, 32);
+      const int n = last <= 0 ? 0 : 2 * last - (it.kv_begin + 32 * (wave + kWaves * (j0 + last - 1)) + 16 >= it.kv_end);
+      place_rows_read<D, FP8>(p, rows, row_list, it.kv_head, bt_reg, n, own_row, own, lane);
+    }
+  };
   load_table(0);
+  if constexpr (PLACES) {
+    if (it.kv_end == kv_len && wave == ((n_sub - 1) & (kWaves - 1)) && rows.n_rows == rows.n_seqs) {
+      int in_order;
+      asm volatile("ds_read_b32 %0, %1 offset:%2\n\ts_waitcnt lgkmcnt(0)" : "=&v"(in_order) : "v"(row_list), "i"(8 * kMaxNewRows) : "memory");
+      if (__builtin_amdgcn_readfirstlane(in_order)) {
+        own_row = it.seq;
+        own = load_row<D>(p, rows, own_row, it.kv_head, lane);
+      }
+    }
+  }
   // K/V that one item reads is read non-temporally where the launch has much of it, or long products (kPastCacheBytes,
   // kPastCacheProductsUs): it passes the 256 MB cache in front of the HBM by, which otherwise takes in every line that streams
   // past (us a pass: 256 decodes of 1 .. 8 k keys 814 -> 742, 6.6 TB/s where it was 5.95; 64 of 100 .. 4000 through the static
@@ -1448,7 +1576,6 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
           __builtin_amdgcn_global_load_lds(g + db * 512, wl + (NSTEP + t * NDB + db) * 1024, 16, 0, decltype(nt)::value);
       }
     };
-    const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;  // sub-tiles wave, wave+8, ...
     auto stream = [&](auto nt) -> void {
       if (n_iter > 0) {
         issue_k(nt, 0);
@@ -1467,6 +1594,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
           if (((j + 1) & 31) == 0) {
             load_table(j + 1);
             pin_table();
+            place_rows(j + 1);
           }
           issue_k(nt, j + 1);  // the K planes are free again
         }
@@ -1478,6 +1606,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
       }
     };
     pin_table();
+    place_rows(0);
     if (shared()) stream(std::integral_constant<int, 0>{});
     else stream(std::integral_constant<int, kNonTemporal>{});
   } else {
@@ -1499,6 +1628,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
       if ((j & 31) == 0) {
         if (j) load_table(j);
         pin_table();
+        if (j) place_rows(j);
       }
       lds_byte* set = wl + (j & 1) * SET;
 #pragma unroll
@@ -1534,7 +1664,6 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
 #pragma unroll
       for (int n = 0; n < NSTEP; ++n) x[n] = fp8x8_to_bf16x8(r[n]);
     };
-    const int n_iter = n_sub > wave ? (n_sub - wave + kWaves - 1) / kWaves : 0;
     auto stream = [&](auto nt) -> void {
       if (n_iter > 0) issue(nt, 0);
       if (n_iter > 1) issue(nt, 1);
@@ -1555,6 +1684,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
       }
     };
     pin_table();
+    place_rows(0);
     if (shared()) stream(std::integral_constant<int, 0>{});
     else stream(std::integral_constant<int, kNonTemporal>{});
   }
@@ -1674,6 +1804,7 @@ template <int D, bool FP8, class List>
 __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List list) {
   extern __shared__ __align__(1024) unsigned char smem[];
   constexpr bool LIST = List::kVecs > 0;
+  constexpr bool PLACES = std::is_same_v<List, NewRows>;  // narrow items only
   static_assert(kQueues == 8, "XCC_ID is masked to three bits");
   // hardware register XCC_ID (id 20), bits 3:0: the XCD this work-group runs on
   const int xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (kQueues - 1);
@@ -1707,6 +1838,9 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
       dyn[2 * lane] = p.q_len[y] - n_static;
       dyn[2 * lane + 1] = p.q_base[y] + n_static;
     }
+    if constexpr (PLACES) {
+      if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 1) map_rows<D, FP8>(p, list, feed.mail + kLoopLdsBytes, threadIdx.x - 64);
+    }
     if constexpr (LIST) {
       const int v = threadIdx.x - 64;
       if (v < List::kVecs)
@@ -1735,7 +1869,9 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
     posted = false;
     if (it.wide < 0) break;
     if (it.n_tok <= 0 || it.n_heads <= 0) continue;
-    if (it.wide) {
+    if constexpr (PLACES) {
+      run_narrow<D, FP8, false, true>(p, it, list, smem);
+    } else if (it.wide) {
       if constexpr (FP8) {
         if (it.wide >= 2) {
           posted = run_wide<D, kCopy, List>(p, feed, smem);
@@ -1746,7 +1882,7 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
         posted = run_wide<D, kPool, List>(p, feed, smem);
       }
     } else {
-      run_narrow<D, FP8, LIST>(p, it, smem);
+      run_narrow<D, FP8, LIST, false>(p, it, NewRows{}, smem);
     }
   }
   // No queue has an item left for this work-group.  The last work-group of the launch to get
@@ -1812,7 +1948,7 @@ const void* attn_kernel() {
 template <int D, bool FP8>
 int prepare_typed() {
   constexpr int lds = attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
-  for (const void* kern : {attn_kernel<D, FP8, NoList>(), attn_kernel<D, FP8, ItemList<kShortListBytes>>(), attn_kernel<D, FP8, ItemList<kListBytes>>()})
+  for (const void* kern : {attn_kernel<D, FP8, NoList>(), attn_kernel<D, FP8, NewRows>(), attn_kernel<D, FP8, ItemList<kShortListBytes>>(), attn_kernel<D, FP8, ItemList<kListBytes>>()})
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds + kListBytes) != hipSuccess) return CRONUS_ERR_HIP;
   return CRONUS_OK;
 }
@@ -1838,12 +1974,19 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
     }
   }
   if (pl.n_items > 0) {
-    const void* const kern = !a.list                             ? attn_kernel<D, FP8, NoList>()
+    const void* const kern = a.rows                              ? attn_kernel<D, FP8, NewRows>()
+                             : !a.list                           ? attn_kernel<D, FP8, NoList>()
                              : a.list_bytes <= kShortListBytes ? attn_kernel<D, FP8, ItemList<kShortListBytes>>()
                                                                : attn_kernel<D, FP8, ItemList<kListBytes>>();
-    const int list_lds = !a.list ? 0 : a.list_bytes <= kShortListBytes ? kShortListBytes : kListBytes;
+    const int list_lds = a.rows ? 8 * kMaxNewRows + 16 : !a.list ? 0 : a.list_bytes <= kShortListBytes ? kShortListBytes : kListBytes;
     NoList none;
-    void* args[] = {const_cast<AttnParams*>(&p), a.list ? const_cast<void*>(a.list) : &none};
+    NewRows rows{};
+    if (a.rows) {
+      rows = NewRows{static_cast<const unsigned short*>(a.rows->k_src), static_cast<const unsigned short*>(a.rows->v_src), a.rows->cu_tokens,
+                     a.rows->start_pos, a.rows->n_tokens, pl.n_seqs, {}};
+      for (int i = 0; i < pl.n_seqs; ++i) rows.kv_len[i] = a.chunk_lens[i] > 0 ? a.prefix_lens[i] + a.chunk_lens[i] : 0;
+    }
+    void* args[] = {const_cast<AttnParams*>(&p), a.rows ? static_cast<void*>(&rows) : a.list ? const_cast<void*>(a.list) : &none};
     const dim3 grid((unsigned)pl.n_workgroups);
     const hipError_t launched =
         timed ? hipExtLaunchKernel(kern, grid, dim3(kThreads), args, lds + list_lds, s, ev(0), ev(1), 0)

@@ -238,6 +238,16 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
 // Whether the rows of such an iteration are stored past the caches (cronus_iteration).
 bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens, int32_t n_seqs);
 
+// An iteration of narrow items only (decodes) with one set of at most this many rows, and as many sequences, places them in its
+// attention launch: one lane a row, and a block is compared with all rows at once.  One launch less (2.5 us) and no wait for its
+// last work-group.  us a pass, two launches / one: a decode of 5000 keys 16.6 / 14.8, 4 of 1340 .. 3086 17.3 / 15.0, 10 of 68 .. 1037
+// (7 heads a KV head) 14.9 / 12.8, 16 of 281 .. 2407 30.1 / 29.2, 30 of 296 .. 659 18.5 / 16.5, 38 of 155 .. 1333 (8 heads) 32.6 / 30.1,
+// 54 of 143 21.9 / 21.1; fp8, 4 of 65 .. 1194 15.2 / 12.2, 54 of 722 .. 1341 36.1 / 35.3; 24 drawn sets of 1 .. 54 decodes 14 % less on average,
+// none slower.  Chunk tiles read too many rows to store them each for itself.
+constexpr int kMaxNewRows = 64;
+bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* chunk_lens,
+                    int32_t n_seqs);
+
 struct AttnLaunch {
   const cronus_kv_cache* cache;
   const void* q;
@@ -251,6 +261,9 @@ struct AttnLaunch {
                      // the launch), or nullptr
   CompactPlan compact;
   size_t list_bytes;
+  const cronus_kv_rows* rows;  // rows that the main kernel places (rows_in_launch, and no list), or nullptr
+  const int32_t* prefix_lens;  // of the call, where there are such rows
+  const int32_t* chunk_lens;
   const Plan* plan;
   void* stream;
   int* queue_set;  // device; this call's set of queue heads (kQueueSetInts ints, all zero between launches)
