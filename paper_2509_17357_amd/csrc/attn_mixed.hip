@@ -1800,11 +1800,13 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
 // in index order and stalls on the first XCD without a free CU, which couples the per-XCD
 // orders of a plain one-item-per-work-group launch; a resident work-group asks for its next
 // item when it is done with the last, whichever XCD's queue still has one.
-template <int D, bool FP8, class List>
+// NARROW: an instance for launches without chunk tiles (main_kernel).
+template <int D, bool FP8, class List, bool NARROW>
 __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List list) {
   extern __shared__ __align__(1024) unsigned char smem[];
   constexpr bool LIST = List::kVecs > 0;
-  constexpr bool PLACES = std::is_same_v<List, NewRows>;  // narrow items only
+  constexpr bool PLACES = std::is_same_v<List, NewRows>;
+  static_assert(NARROW || !PLACES, "chunk tiles do not place rows");
   static_assert(kQueues == 8, "XCC_ID is masked to three bits");
   // hardware register XCC_ID (id 20), bits 3:0: the XCD this work-group runs on
   const int xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (kQueues - 1);
@@ -1871,6 +1873,8 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
     if (it.n_tok <= 0 || it.n_heads <= 0) continue;
     if constexpr (PLACES) {
       run_narrow<D, FP8, false, true>(p, it, list, smem);
+    } else if constexpr (NARROW) {
+      run_narrow<D, FP8, LIST, false>(p, it, NewRows{}, smem);
     } else if (it.wide) {
       if constexpr (FP8) {
         if (it.wide >= 2) {
@@ -1939,16 +1943,32 @@ __global__ __launch_bounds__(kStageThreads) void kv_stage_kernel(AttnParams p) {
   }
 }
 
-template <int D, bool FP8, class List>
+template <int D, bool FP8, class List, bool NARROW>
 const void* attn_kernel() {
-  auto kern = attn_mixed_kernel<D, FP8, List>;
+  auto kern = attn_mixed_kernel<D, FP8, List, NARROW>;
   return reinterpret_cast<const void*>(kern);
+}
+
+// The instance of the main kernel for a launch: what comes with the arguments, and whether its items are all narrow.  The
+// instances without chunk tiles have registers to spare (D = 128: 223 instead of 256, 2 instead of 60 .. 160 scalars spilled, no
+// scratch), and an item costs fewer instructions: us a pass, with / without the tiles, static calls of 13 decodes of 697 .. 2049 keys
+// 21.28 / 20.71, 35 of 196 .. 1967 37.3 / 36.6, 49 of 682 .. 1246 46.1 / 45.3; 217 of 100 62.6 / 61.9, fp8, 214 of 564 .. 1396 107.8 / 107.0;
+// 20 such launches 0.9 % less on average.
+enum Extra { kPlain, kShort, kLong, kRows };
+template <int D, bool FP8>
+const void* main_kernel(Extra extra, bool narrow) {
+  if (extra == kRows) return attn_kernel<D, FP8, NewRows, true>();
+  if (extra == kShort) return narrow ? attn_kernel<D, FP8, ItemList<kShortListBytes>, true>() : attn_kernel<D, FP8, ItemList<kShortListBytes>, false>();
+  if (extra == kLong) return narrow ? attn_kernel<D, FP8, ItemList<kListBytes>, true>() : attn_kernel<D, FP8, ItemList<kListBytes>, false>();
+  return narrow ? attn_kernel<D, FP8, NoList, true>() : attn_kernel<D, FP8, NoList, false>();
 }
 
 template <int D, bool FP8>
 int prepare_typed() {
   constexpr int lds = attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
-  for (const void* kern : {attn_kernel<D, FP8, NoList>(), attn_kernel<D, FP8, NewRows>(), attn_kernel<D, FP8, ItemList<kShortListBytes>>(), attn_kernel<D, FP8, ItemList<kListBytes>>()})
+  for (const void* kern : {main_kernel<D, FP8>(kPlain, false), main_kernel<D, FP8>(kShort, false), main_kernel<D, FP8>(kLong, false),
+                           main_kernel<D, FP8>(kPlain, true), main_kernel<D, FP8>(kShort, true), main_kernel<D, FP8>(kLong, true),
+                           main_kernel<D, FP8>(kRows, true)})
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds + kListBytes) != hipSuccess) return CRONUS_ERR_HIP;
   return CRONUS_OK;
 }
@@ -1974,11 +1994,9 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
     }
   }
   if (pl.n_items > 0) {
-    const void* const kern = a.rows                              ? attn_kernel<D, FP8, NewRows>()
-                             : !a.list                           ? attn_kernel<D, FP8, NoList>()
-                             : a.list_bytes <= kShortListBytes ? attn_kernel<D, FP8, ItemList<kShortListBytes>>()
-                                                               : attn_kernel<D, FP8, ItemList<kListBytes>>();
-    const int list_lds = a.rows ? 8 * kMaxNewRows + 16 : !a.list ? 0 : a.list_bytes <= kShortListBytes ? kShortListBytes : kListBytes;
+    const Extra extra = a.rows ? kRows : !a.list ? kPlain : a.list_bytes <= kShortListBytes ? kShort : kLong;
+    const void* const kern = main_kernel<D, FP8>(extra, pl.n_wide == 0);
+    const int list_lds = extra == kRows ? 8 * kMaxNewRows + 16 : extra == kShort ? kShortListBytes : extra == kLong ? kListBytes : 0;
     NoList none;
     NewRows rows{};
     if (a.rows) {
