@@ -22,7 +22,12 @@ constexpr int kNarrowRows = 32;     // one MFMA column tile: a decode's (token, 
 constexpr int kWideKvTile = 64;     // keys staged in LDS per step of a wide (chunk) tile
 constexpr int kNarrowKvStep = 32 * kWaves;  // keys covered by the waves of a narrow item per step
 constexpr int kQueues = 8;          // work queues of a launch: one per XCD of an MI355X (each XCD has its own L2)
-constexpr int kCounterStride = 16;  // int32 between the queue heads of a set: one 64-byte line each
+// int32 between the queue heads of a set: 256 bytes, so that no two lie in one 128-byte line.  Every ticket and look of the 256
+// work-groups goes to memory, whose lines take them one at a time, and with 64 bytes two queues and all looks at either shared a
+// line.  us a pass at 64 / 128 / 256 / 512 / 1024 bytes: 16 decodes of 281 .. 2407 29.3 / 25.3 / 25.1 / 25.2 / 25.2, 40 of 2717 .. 5329
+// (7 heads a KV head) 71.9 / 69.8 / 69.8 / 69.9 / 69.9, 4 chunks of 512 next to 64 decodes 127.0 / 124.1 / 124.3 / 124.0 / 124.3, fp8, a chunk
+// of 201 next to 48 87.1 / 84.8 / 84.6 / 84.7 / 84.6; launches with no more items than work-groups take no tickets: no difference.
+constexpr int kCounterStride = 64;
 // Row groups whose results are merged from key spans, per launch at most: each has kWaves arrival
 // counters in the set.  A launch with more rows to split leaves its shortest ones whole (build_plan).
 constexpr int kMaxMergeGroups = 4096;
