@@ -327,7 +327,8 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   write_plan(&plan, host + kSlotHeader);
   // the set of queue heads that belongs to this plan buffer: free again when the buffer is
   const int set = (int)(slot - g_rings[dev].slots);
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader, nullptr, {}, 0,
+  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader,
+               plan.n_items <= std::min<int64_t>(kFewItems, plan.n_workgroups) ? reinterpret_cast<const WorkItem*>(host + kSlotHeader + plan.off_items) : nullptr, nullptr, {}, 0,
                in_launch ? first : nullptr, prefix_lens, chunk_lens, &plan, hip_stream,
                g_dev[dev].queue_sets + set * kQueueSetInts, reinterpret_cast<uint32_t*>(dev_mem), ++slot->call,
                {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
@@ -412,7 +413,7 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   // (The heads of the work queues, which must, live in their own small array, and every
   // launch leaves them zero.)
   AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, base + plan.image_bytes, base,
-               listed ? image.data() : nullptr, compact, listed ? compact_bytes : 0, nullptr, nullptr, nullptr, &plan, hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+               nullptr, listed ? image.data() : nullptr, compact, listed ? compact_bytes : 0, nullptr, nullptr, nullptr, &plan, hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
   bool main_launched = false;
   return launch_attn(a, &main_launched);
 }

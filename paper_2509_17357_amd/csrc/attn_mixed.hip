@@ -110,6 +110,15 @@ struct ItemList {
 struct NoList {
   static constexpr int kVecs = 0;
 };
+// The records of a launch of at most kFewItems items, by work-group, as a kernel argument: one load of device memory, where a
+// record of host memory is there 2.2 us after the start.  A work-group runs its one item; there are no queues.
+struct Records {
+  static constexpr int kMost = kFewItems, kVecs = 0;
+  int word[kMost][16];
+};
+struct NoRecords {
+  static constexpr int kMost = 0;
+};
 // The new rows of an iteration of narrow items, which its attention launch places itself (map_rows, place_rows_read).
 struct NewRows {
   static constexpr int kVecs = 0;
@@ -121,6 +130,7 @@ struct NewRows {
   int kv_len[kMaxNewRows];  // keys that each sequence's items read
 };
 static_assert(kMaxNewRows == 64, "a lane for each row and for each sequence");
+static_assert(sizeof(AttnParams) + sizeof(NewRows) + sizeof(Records) <= 4096, "arguments of a kernel");
 static_assert(sizeof(AttnParams) <= 256 && sizeof(AttnParams) % 8 == 0, "the arguments with a list are 4 KiB");
 
 constexpr int kNonTemporal = 2;  // cache policy operand of a transfer: the instruction's nt bit
@@ -1801,12 +1811,13 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
 // orders of a plain one-item-per-work-group launch; a resident work-group asks for its next
 // item when it is done with the last, whichever XCD's queue still has one.
 // NARROW: an instance for launches without chunk tiles (main_kernel).
-template <int D, bool FP8, class List, bool NARROW>
-__global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List list) {
+template <int D, bool FP8, class List, bool NARROW, class Recs>
+__global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List list, Recs records) {
   extern __shared__ __align__(1024) unsigned char smem[];
   constexpr bool LIST = List::kVecs > 0;
   constexpr bool PLACES = std::is_same_v<List, NewRows>;
   static_assert(NARROW || !PLACES, "chunk tiles do not place rows");
+  using Arg = std::conditional_t<(Recs::kMost > 0), Recs, List>;  // (each instance has a run_wide of its own: the compiler's host pass wants that)
   static_assert(kQueues == 8, "XCC_ID is masked to three bits");
   // hardware register XCC_ID (id 20), bits 3:0: the XCD this work-group runs on
   const int xcc = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & (kQueues - 1);
@@ -1815,7 +1826,7 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
   // The record of the item that this work-group starts with is asked for first; the queue table and the list, which
   // the items after it need, are set up meanwhile by other waves.
   const int q0 = blockIdx.x & (kQueues - 1), i0 = blockIdx.x / kQueues;
-  bool posted = i0 < p.q_len[q0];  // the next record is in the mailbox already
+  bool posted = Recs::kMost > 0 || i0 < p.q_len[q0];  // the next record is in the mailbox already
   if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
     if (posted) {
       const int lane = threadIdx.x, idx = p.q_base[q0] + i0;
@@ -1828,6 +1839,10 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
 #pragma unroll
         for (int i = 0; i < 8; ++i) uw[i] = words[unit_of_ref(p.compact, ref) * 8 + i];
         post_item(p, feed, u, ref, lane);
+      } else if constexpr (Recs::kMost > 0) {
+        const int word = records.word[blockIdx.x][lane & 15];
+        if (lane < 16) asm volatile("ds_write_b32 %0, %1" ::"v"(feed.mail + feed.turn + 4 * lane), "v"(word) : "memory");
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       } else {
         fetch_record<false>(p, feed, idx, lane);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1878,12 +1893,12 @@ __global__ __launch_bounds__(kThreads) void attn_mixed_kernel(AttnParams p, List
     } else if (it.wide) {
       if constexpr (FP8) {
         if (it.wide >= 2) {
-          posted = run_wide<D, kCopy, List>(p, feed, smem);
+          posted = run_wide<D, kCopy, Arg>(p, feed, smem);
         } else {
-          posted = run_wide<D, kCodes, List>(p, feed, smem);
+          posted = run_wide<D, kCodes, Arg>(p, feed, smem);
         }
       } else {
-        posted = run_wide<D, kPool, List>(p, feed, smem);
+        posted = run_wide<D, kPool, Arg>(p, feed, smem);
       }
     } else {
       run_narrow<D, FP8, LIST, false>(p, it, NewRows{}, smem);
@@ -1943,9 +1958,9 @@ __global__ __launch_bounds__(kStageThreads) void kv_stage_kernel(AttnParams p) {
   }
 }
 
-template <int D, bool FP8, class List, bool NARROW>
+template <int D, bool FP8, class List, bool NARROW, class Recs = NoRecords>
 const void* attn_kernel() {
-  auto kern = attn_mixed_kernel<D, FP8, List, NARROW>;
+  auto kern = attn_mixed_kernel<D, FP8, List, NARROW, Recs>;
   return reinterpret_cast<const void*>(kern);
 }
 
@@ -1954,10 +1969,12 @@ const void* attn_kernel() {
 // scratch), and an item costs fewer instructions: us a pass, with / without the tiles, static calls of 13 decodes of 697 .. 2049 keys
 // 21.28 / 20.71, 35 of 196 .. 1967 37.3 / 36.6, 49 of 682 .. 1246 46.1 / 45.3; 217 of 100 62.6 / 61.9, fp8, 214 of 564 .. 1396 107.8 / 107.0;
 // 20 such launches 0.9 % less on average.
-enum Extra { kPlain, kShort, kLong, kRows };
+enum Extra { kPlain, kFew, kShort, kLong, kRows, kFewRows };
 template <int D, bool FP8>
 const void* main_kernel(Extra extra, bool narrow) {
   if (extra == kRows) return attn_kernel<D, FP8, NewRows, true>();
+  if (extra == kFewRows) return attn_kernel<D, FP8, NewRows, true, Records>();
+  if (extra == kFew) return narrow ? attn_kernel<D, FP8, NoList, true, Records>() : attn_kernel<D, FP8, NoList, false, Records>();
   if (extra == kShort) return narrow ? attn_kernel<D, FP8, ItemList<kShortListBytes>, true>() : attn_kernel<D, FP8, ItemList<kShortListBytes>, false>();
   if (extra == kLong) return narrow ? attn_kernel<D, FP8, ItemList<kListBytes>, true>() : attn_kernel<D, FP8, ItemList<kListBytes>, false>();
   return narrow ? attn_kernel<D, FP8, NoList, true>() : attn_kernel<D, FP8, NoList, false>();
@@ -1966,10 +1983,11 @@ const void* main_kernel(Extra extra, bool narrow) {
 template <int D, bool FP8>
 int prepare_typed() {
   constexpr int lds = attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
-  for (const void* kern : {main_kernel<D, FP8>(kPlain, false), main_kernel<D, FP8>(kShort, false), main_kernel<D, FP8>(kLong, false),
-                           main_kernel<D, FP8>(kPlain, true), main_kernel<D, FP8>(kShort, true), main_kernel<D, FP8>(kLong, true),
-                           main_kernel<D, FP8>(kRows, true)})
-    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds + kListBytes) != hipSuccess) return CRONUS_ERR_HIP;
+  for (const Extra extra : {kPlain, kFew, kShort, kLong, kRows, kFewRows})
+    for (const bool narrow : {false, true}) {
+      const void* const kern = main_kernel<D, FP8>(extra, narrow);
+      if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds + kListBytes) != hipSuccess) return CRONUS_ERR_HIP;
+    }
   return CRONUS_OK;
 }
 
@@ -1994,9 +2012,10 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
     }
   }
   if (pl.n_items > 0) {
-    const Extra extra = a.rows ? kRows : !a.list ? kPlain : a.list_bytes <= kShortListBytes ? kShort : kLong;
+    const bool few = a.records != nullptr;
+    const Extra extra = a.rows ? (few ? kFewRows : kRows) : a.list ? (a.list_bytes <= kShortListBytes ? kShort : kLong) : few ? kFew : kPlain;
     const void* const kern = main_kernel<D, FP8>(extra, pl.n_wide == 0);
-    const int list_lds = extra == kRows ? 8 * kMaxNewRows + 16 : extra == kShort ? kShortListBytes : extra == kLong ? kListBytes : 0;
+    const int list_lds = a.rows ? 8 * kMaxNewRows + 16 : extra == kShort ? kShortListBytes : extra == kLong ? kListBytes : 0;
     NoList none;
     NewRows rows{};
     if (a.rows) {
@@ -2004,7 +2023,19 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
                      a.rows->start_pos, a.rows->n_tokens, pl.n_seqs, {}};
       for (int i = 0; i < pl.n_seqs; ++i) rows.kv_len[i] = a.chunk_lens[i] > 0 ? a.prefix_lens[i] + a.chunk_lens[i] : 0;
     }
-    void* args[] = {const_cast<AttnParams*>(&p), a.rows ? static_cast<void*>(&rows) : a.list ? const_cast<void*>(a.list) : &none};
+    Records records;
+    if (few) {
+      // each work-group's item, of the queue of the XCD that it probably runs on while that has one
+      int next[kQueues] = {0};
+      for (int b = 0; b < (int)pl.n_items; ++b) {
+        int x = b % kQueues;
+        for (int y = 0; y < kQueues && next[x] == pl.q_len[x]; ++y) x = (x + 1) % kQueues;
+        std::memcpy(records.word[b], a.records + pl.q_base[x] + next[x]++, sizeof(WorkItem));
+      }
+    }
+    NoRecords no_records;
+    void* args[] = {const_cast<AttnParams*>(&p), a.rows ? static_cast<void*>(&rows) : a.list ? const_cast<void*>(a.list) : &none,
+                    few ? static_cast<void*>(&records) : &no_records};
     const dim3 grid((unsigned)pl.n_workgroups);
     const hipError_t launched =
         timed ? hipExtLaunchKernel(kern, grid, dim3(kThreads), args, lds + list_lds, s, ev(0), ev(1), 0)
@@ -2116,7 +2147,7 @@ int launch_attn(const AttnLaunch& a, bool* main_launched) {
   p.merge_counters = a.queue_set + (kQueues + 1) * kCounterStride;
   for (int x = 0; x < kQueues; ++x) {
     p.q_base[x] = pl.q_base[x];
-    p.q_len[x] = pl.q_len[x];
+    p.q_len[x] = a.records ? 0 : pl.q_len[x];  // (records in the arguments: no queues)
   }
   p.compact = a.compact;
   p.stage_seqs = reinterpret_cast<const StageSeq*>(image + pl.off_stage);

@@ -162,6 +162,12 @@ CRONUS_HOST_DEVICE inline WorkItem expand_item(const CompactPlan& c, const Compa
 // A static call's list of at most this many bytes and with 2-byte references travels in the main kernel's own arguments (up to
 // kShortListBytes in a smaller set of them).  More do not fit in 4 KiB next to the other arguments.
 constexpr int kListBytes = 3840, kShortListBytes = 1280;
+// A call of cronus_attn_mixed or cronus_iteration with at most this many items passes their records in the main kernel's arguments
+// (3 KiB; new rows and the other arguments take 0.6 of the 4 KiB that there are).  us a pass, records in host memory / in the
+// arguments: 12 items, a chunk of 64 next to 4 decodes 12.9 / 11.4; 3 decodes, 7 heads a KV head 11.2 / 8.4; a decode of 300, 8 KV heads
+// 10.6 / 9.2; 40 items, 5 decodes 10.9 / 9.6; 8 of 64 .. 700, 7 heads 13.0 / 10.4; two chunk tiles a KV head next to 2 decodes 14.9 / 13.5.  Room for
+// 16, 32 or 48: 12 items 11.6 / 11.8 / 11.7.
+constexpr int kFewItems = 48;
 
 // Rows whose partial results (split over key spans) are combined, for inspection (the kernels
 // find what they need in the work items):
@@ -262,6 +268,7 @@ struct AttnLaunch {
   float sm_scale;
   void* workspace;  // device; holds the partial results at plan->off_partials
   const void* plan_image;  // device-visible [WorkItem | MergeItem | StageSeq] image at the plan's offsets
+  const WorkItem* records;  // host; the items of a launch of at most kFewItems, which travel in the arguments, or nullptr
   const void* list;  // host, kListBytes long; the compact list that takes the place of the image's items (copied by
                      // the launch), or nullptr
   CompactPlan compact;
