@@ -437,6 +437,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 509; }  // 0.5.9: lengths checked before rows are placed; small decode launches, chunk tails and shared blocks through the caches
+int cronus_version(void) { return 510; }  // 0.5.10: decode iterations place their rows in the attention launch; small launches carry their records; large gathers read past the caches
 
 }  // extern "C"

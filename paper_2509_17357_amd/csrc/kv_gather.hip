@@ -18,9 +18,22 @@ template <int ESZ> struct ChunkOf;
 template <> struct ChunkOf<2> { typedef unsigned int type __attribute__((ext_vector_type(4))); };
 template <> struct ChunkOf<1> { typedef unsigned int type __attribute__((ext_vector_type(2))); };
 
+// From this many bytes of rows on, the blocks of a bf16 cache are read non-temporally: what leaves the instance is not read again,
+// and its lines would take the place of the rows being written.  Less of it may still lie in the 256 MB cache from its last
+// use.  us a hand-off (gather, then scatter; three in turn), ordinary / non-temporal: 26 MB 22.9 / 23.5, 28 24.2 / 25.1, 33 28.8 / 28.5, 34 30.9 / 29.4,
+// 45 40.2 / 36.3, 60 52.8 / 47.9, 80 67.2 / 62.6, 110 96.6 / 86.6, 150 122.9 / 119.7, 193 137.6 / 134.4, 260 210.0 / 209.2, 400 319.1 / 318.9.
+// (fp8: within 1 % on both sides of it.  Non-temporal stores of the rows: 0.86-0.94 at 33-193 MB.)
+constexpr long long kPastCacheRowBytes = 32'000'000;
+
+template <bool PAST_CACHE, class T>
+__device__ __forceinline__ T load_chunk(const unsigned char* p) {
+  if constexpr (PAST_CACHE) return __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
+  else return *reinterpret_cast<const T*>(p);
+}
+
 // Work-group g of grid.x serves the last sequence s with cu_tokens[s]/16 + 2 s <= g and
 // the (g - that)-th cache block its rows touch; grid.x = n_tokens/16 + 2 n_seqs + 1.
-template <int ESZ>
+template <int ESZ, bool PAST_CACHE>
 __global__ __launch_bounds__(256) void kv_gather_kernel(
     const unsigned char* __restrict__ k_pool, const unsigned char* __restrict__ v_pool,
     unsigned char* __restrict__ k_dst, unsigned char* __restrict__ v_dst, const int* __restrict__ cu_tokens,
@@ -50,7 +63,7 @@ __global__ __launch_bounds__(256) void kv_gather_kernel(
 
   // ---- V: chunk t of the block = (kc, d), kc = t / D, d = t % D
   if (t < 2 * head_dim) {
-    const Chunk c = *reinterpret_cast<const Chunk*>(v_pool + head_base + (long long)t * CB);
+    const Chunk c = load_chunk<PAST_CACHE, Chunk>(v_pool + head_base + (long long)t * CB);
     unsigned char* row = vt[t];
 #pragma unroll
     for (int w = 0; w < CB / 4; ++w) {
@@ -61,7 +74,7 @@ __global__ __launch_bounds__(256) void kv_gather_kernel(
   }
   // ---- K: chunk (dc, slot) as stored
   if (mine) {
-    const Chunk c = *reinterpret_cast<const Chunk*>(k_pool + head_base + ((long long)dc * 16 + slot) * CB);
+    const Chunk c = load_chunk<PAST_CACHE, Chunk>(k_pool + head_base + ((long long)dc * 16 + slot) * CB);
     *reinterpret_cast<Chunk*>(k_dst + dst_off) = c;
   }
   __syncthreads();
@@ -96,13 +109,12 @@ int launch_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, con
   auto vp = static_cast<const unsigned char*>(cache->v_cache);
   auto kd = static_cast<unsigned char*>(k_dst);
   auto vd = static_cast<unsigned char*>(v_dst);
-  if (cache->kv_dtype == CRONUS_KV_FP8_E4M3) {
-    hipLaunchKernelGGL(kv_gather_kernel<1>, grid, dim3(256), 0, s, kp, vp, kd, vd, cu_tokens, start_pos,
-                       block_tables, max_blocks_per_seq, n_seqs, cache->num_kv_heads, cache->head_dim);
-  } else {
-    hipLaunchKernelGGL(kv_gather_kernel<2>, grid, dim3(256), 0, s, kp, vp, kd, vd, cu_tokens, start_pos,
-                       block_tables, max_blocks_per_seq, n_seqs, cache->num_kv_heads, cache->head_dim);
-  }
+  const bool past_cache = (long long)n_tokens * cache->num_kv_heads * cache->head_dim * 4 >= kPastCacheRowBytes;
+  auto kernel = cache->kv_dtype == CRONUS_KV_FP8_E4M3 ? kv_gather_kernel<1, false>
+                : past_cache                          ? kv_gather_kernel<2, true>
+                                                      : kv_gather_kernel<2, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, kp, vp, kd, vd, cu_tokens, start_pos, block_tables, max_blocks_per_seq, n_seqs,
+                     cache->num_kv_heads, cache->head_dim);
   return hipGetLastError() == hipSuccess ? CRONUS_OK : CRONUS_ERR_HIP;
 }
 
