@@ -155,7 +155,8 @@ int cronus_kv_append_pair(const cronus_kv_cache* cache, const cronus_kv_rows* fi
  *                  lengths: chunk tiles are then cut into fewer key spans, and results can
  *                  differ in the last bf16 bit
  * The work list is built on the host during the call and read by the kernels from
- * pinned, device-mapped host memory that the library owns (a ring of 8 buffers, grown on
+ * pinned, device-mapped host memory that the library owns (at most 48 items: from the
+ * kernel's arguments, a copy; a ring of 8 buffers, grown on
  * demand, never freed; the ninth call in flight waits on the host for one of them).  A call
  * captured into a HIP graph keeps its buffer for good, since replays read it: later calls use
  * the others, and fail with CRONUS_ERR_HIP once eight calls have been captured
@@ -175,6 +176,7 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * cronus_iteration - a whole iteration (section 4.4) in one call: what cronus_kv_append_pair(cache, first, second, ...) and
  * then cronus_attn_mixed(cache, q, out, ...) do with these arguments, the same bits.  Knowing both halves, it keeps
  * the placed rows out of the GPU's caches where the iteration is bound by streaming the decodes' K/V.
+ * Rows of an iteration of decodes (one set of at most 64 rows, at most 64 sequences) are placed by the attention launch itself.
  * Errors: those of the two calls, found before anything is enqueued, with two exceptions: the rows have been placed, and the
  * attention has not been enqueued, when CRONUS_ERR_WORKSPACE reports a workspace that is too small (the plan that tells is built while the
  * rows are placed) and when CRONUS_ERR_HIP reports the attention's set-up.
