@@ -269,6 +269,16 @@ int check_attn_args(const cronus_kv_cache* cache, const void* q, const void* out
   return CRONUS_OK;
 }
 
+// Whether an array that the rows are read from shares memory with [p, p + bytes).
+bool read_from(const cronus_kv_cache* cache, const cronus_kv_rows* rows, int32_t n_seqs, const void* p, size_t bytes) {
+  auto meets = [&](const void* src, size_t n) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(src), b = reinterpret_cast<uintptr_t>(p);
+    return a < b + bytes && b < a + n;
+  };
+  const size_t values = (size_t)rows->n_tokens * cache->num_kv_heads * cache->head_dim * 2, ints = (size_t)n_seqs * sizeof(int32_t);
+  return meets(rows->k_src, values) || meets(rows->v_src, values) || meets(rows->cu_tokens, ints + sizeof(int32_t)) || meets(rows->start_pos, ints);
+}
+
 bool workspace_refused(const void* workspace) { return !workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u); }
 
 // cronus_attn_mixed behind the placing of the rows of `first` and `second` (null: none).
@@ -292,7 +302,10 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
     return launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream,
                             rows_past_cache(cache, prefix_lens, chunk_lens, n_seqs));
   };
-  const bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, chunk_lens, n_seqs);
+  // (rows that lie in what the attention writes are read before it starts)
+  const bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, chunk_lens, n_seqs) &&
+                         !read_from(cache, first, n_seqs, out, (size_t)total_q * cache->num_q_heads * cache->head_dim * 2) &&
+                         !read_from(cache, first, n_seqs, workspace, workspace_bytes);
   auto refused = [&](int rc) {  // after the checks, with the attention not enqueued: the rows are placed all the same
     const int placed = in_launch ? place_rows() : CRONUS_OK;
     return placed ? placed : rc;

@@ -101,3 +101,45 @@ def test_rows_placed_in_the_launch(name):
         for _ in range(3):
             got = run(graph.replay)
             assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and np.array_equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("where", ["out", "workspace"])
+def test_rows_that_lie_in_what_the_attention_writes(where):
+    """As with the two calls, the rows and their counts may lie in the output or in the workspace: they are read first."""
+    shape, P = G4, [5000, 900, 17, 31, 2000, 3100, 255, 256]
+    n, C = len(P), [1] * len(P)
+    it = DeviceIteration(W.custom_batch(shape, P, C, seed=92), pool_fill=0)
+    it.load_device_inputs()
+    it.setup_decode_context()
+    pools = it.k_pool.clone(), it.v_pool.clone()
+    ws = torch.zeros(B.cronus_attn_mixed_workspace_bytes(it.cache, P, C) + (1 << 20), dtype=torch.uint8, device=it.device)
+    out = torch.zeros_like(it.q)
+    area = (out if where == "out" else ws).view(torch.uint8).reshape(-1)
+    arrays, at = [], 0
+    for a in (it.new_k, it.new_v, it.cu_new, it.prefix_pos):
+        size = a.numel() * a.element_size()
+        arrays.append((a, area[at:at + size].view(a.dtype).reshape(a.shape)))
+        at += (size + 15) // 16 * 16
+    assert at <= area.numel()
+
+    def run(f):
+        it.k_pool.copy_(pools[0])
+        it.v_pool.copy_(pools[1])
+        for a, moved in arrays:
+            moved.copy_(a)
+        f(*(moved for _, moved in arrays))
+        torch.cuda.synchronize()
+        return it.k_pool.clone(), it.v_pool.clone(), bits_from_bf16_tensor(out).copy()
+
+    def two_calls(k, v, cu, start):
+        B.cronus_kv_append(it.cache, k, v, cu, start, it.block_tables, it.batch.max_blocks, n, n)
+        B.cronus_attn_mixed(it.cache, it.q, out, P, C, it.block_tables, it.batch.max_blocks, it.sm_scale, ws, ws.numel())
+
+    def one_call(k, v, cu, start):
+        B.cronus_iteration(it.cache, (k, v, cu, start, n), (None, None, None, None, 0), it.q, out, P, C, it.block_tables, it.batch.max_blocks,
+                           it.sm_scale, ws, ws.numel())
+
+    want = run(two_calls)
+    for _ in range(3):
+        got = run(one_call)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and np.array_equal(got[2], want[2])

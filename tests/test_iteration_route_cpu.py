@@ -1,0 +1,46 @@
+"""What cronus_iteration enqueues, on the host: api.cpp and plan.cpp as they are, with stubs for the launches and the HIP calls
+(tests/native/iteration_check_main.cpp).  A decode iteration's rows are placed by the attention launch itself or by a scatter in
+front of it; the results are the same bits, so only the route can tell which of the two ran."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2509_17357_amd", "csrc")
+SCATTER, PLACED = "0 rows attention", "0 attention+rows"
+K, V, CU, START, OUT, WS = (0x100000000 * (i + 1) for i in range(6))
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    cxx, rocm = shutil.which("g++"), os.environ.get("ROCM_PATH", "/opt/rocm")
+    if cxx is None or not os.path.exists(os.path.join(rocm, "include", "hip", "hip_runtime.h")):
+        pytest.skip("no host C++ compiler or no HIP headers")
+    out = str(tmp_path_factory.mktemp("iteration") / "iteration_check")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-w", "-D__HIP_PLATFORM_AMD__",
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", os.path.join(rocm, "include"),
+                    os.path.join(ROOT, "tests", "native", "iteration_check_main.cpp"), os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "plan.cpp"),
+                    os.path.join(CSRC, "balancer.cpp"), "-o", out], check=True)
+    return out
+
+
+def route(exe, P, C, heads=(32, 8, 128), fp8=False, failure="none", rows=None, second=0, k=K, v=V, cu=CU, start=START, out=OUT, ws=WS, ws_bytes=1 << 28):
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0")
+    env.pop("LD_PRELOAD", None)  # the sanitizer runtime must come first in the library list
+    args = [*heads, int(fp8), failure, sum(C) if rows is None else rows, second, k, v, cu, start, out, ws, ws_bytes, len(P)]
+    r = subprocess.run([exe, *map(str, args), *(str(x) for pc in zip(P, C) for x in pc)], capture_output=True, text=True, env=env, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr[-3000:]
+    return r.stdout.strip()
+
+
+def test_rows_that_lie_in_what_the_attention_writes(exe):
+    """They are read before it starts, by the scatter, whichever of their arrays it is; next to it they may lie."""
+    P, C = [100, 600, 40], [1, 1, 1]
+    row, head_row = 3 * 8 * 128 * 2, 3 * 32 * 128 * 2
+    assert route(exe, P, C) == PLACED
+    for area, bytes_ in ((OUT, head_row), (WS, 1 << 28)):
+        for name, size in (("k", row), ("v", row), ("cu", 16), ("start", 12)):
+            for at, want in ((area - size, PLACED), (area - size + 1, SCATTER), (area, SCATTER), (area + bytes_ - 1, SCATTER), (area + bytes_, PLACED)):
+                assert route(exe, P, C, **{name: at}) == want, (name, hex(at))
