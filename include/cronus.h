@@ -180,7 +180,7 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * unless k_src, v_src, cu_tokens or start_pos lie in out or in the workspace.
  * Errors: those of the two calls, found before anything is enqueued, with two exceptions: the rows have been placed, and the
  * attention has not been enqueued, when CRONUS_ERR_WORKSPACE reports a workspace that is too small (the plan that tells is built while the
- * rows are placed) and when CRONUS_ERR_HIP reports the attention's set-up.
+ * rows are placed) and when CRONUS_ERR_HIP reports the attention's set-up or its launch.
  */
 int cronus_iteration(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
                      const void* q, void* out, const int32_t* prefix_lens, const int32_t* chunk_lens,

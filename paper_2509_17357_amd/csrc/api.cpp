@@ -355,7 +355,7 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
     lock.lock();
     slot->state = Slot::kFree;
   }
-  return rc;
+  return main_launched ? rc : refused(rc);
 }
 
 }  // namespace

@@ -44,3 +44,13 @@ def test_rows_that_lie_in_what_the_attention_writes(exe):
         for name, size in (("k", row), ("v", row), ("cu", 16), ("start", 12)):
             for at, want in ((area - size, PLACED), (area - size + 1, SCATTER), (area, SCATTER), (area + bytes_ - 1, SCATTER), (area + bytes_, PLACED)):
                 assert route(exe, P, C, **{name: at}) == want, (name, hex(at))
+
+
+@pytest.mark.parametrize("rows", ["placed in the launch", "scattered"])
+def test_rows_are_placed_where_the_attention_is_not_enqueued(exe, rows):
+    """Errors that are found after the checks leave the rows placed, whichever route they were to take."""
+    P, C = ([100, 9000, 40], [1, 1, 1]) if rows == "placed in the launch" else ([100, 9000], [50, 1])
+    assert route(exe, P, C) == (PLACED if rows == "placed in the launch" else SCATTER)
+    assert route(exe, P, C, ws_bytes=256) == "3 rows"
+    for failure in ("setup", "buffer", "launch"):
+        assert route(exe, P, C, failure=failure) == "4 rows"
