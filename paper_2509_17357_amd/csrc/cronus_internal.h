@@ -308,6 +308,7 @@ int static_scratch_upload(void* dst, const void* host_src, size_t bytes, void* s
 // Enqueues the launches that build the work items of a compact list at `items` (device), through `staging`
 // (device, 16-byte aligned, `bytes` bytes): for a list of more than kListBytes.
 int static_scratch_expand(void* items, void* staging, const CompactPlan& c, const void* host_src, size_t bytes, void* stream);
+constexpr int kMaxScatterHeads = 65535;  // KV heads that the scatter and the gather accept: their grids' y dimension
 // second may be null; past_cache: the rows do not stay in the caches (non-temporal stores)
 int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second,
                      const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* stream,

@@ -144,7 +144,7 @@ int launch_kv_append(const cronus_kv_cache* cache, const cronus_kv_rows* first, 
                      const int32_t* block_tables, int32_t max_blocks_per_seq, int32_t n_seqs, void* stream, bool past_cache) {
   auto groups_of = [&](const cronus_kv_rows* r) { return r ? (long long)r->n_tokens / 16 + 2LL * n_seqs + 1 : 0; };
   const long long groups = groups_of(first) + groups_of(second);
-  if (groups > 0x7fffffffLL || cache->num_kv_heads > 65535) return CRONUS_ERR_INVALID_ARG;
+  if (groups > 0x7fffffffLL || cache->num_kv_heads > kMaxScatterHeads) return CRONUS_ERR_INVALID_ARG;
   auto rows_of = [](const cronus_kv_rows* r) {
     return r ? AppendRows{static_cast<const unsigned short*>(r->k_src), static_cast<const unsigned short*>(r->v_src),
                           r->cu_tokens, r->start_pos}

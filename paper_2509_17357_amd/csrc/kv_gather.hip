@@ -102,7 +102,7 @@ int launch_kv_gather(const cronus_kv_cache* cache, void* k_dst, void* v_dst, con
                      const int32_t* start_pos, const int32_t* block_tables, int32_t max_blocks_per_seq,
                      int32_t n_seqs, int32_t n_tokens, void* stream) {
   const long long groups = (long long)n_tokens / 16 + 2LL * n_seqs + 1;
-  if (groups > 0x7fffffffLL || cache->num_kv_heads > 65535) return CRONUS_ERR_INVALID_ARG;
+  if (groups > 0x7fffffffLL || cache->num_kv_heads > kMaxScatterHeads) return CRONUS_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const dim3 grid((unsigned)groups, (unsigned)cache->num_kv_heads);
   auto kp = static_cast<const unsigned char*>(cache->k_cache);

@@ -918,6 +918,7 @@ bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, c
 bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* chunk_lens,
                     int32_t n_seqs) {
   if (!first || second || first->n_tokens > kMaxNewRows || n_seqs > kMaxNewRows) return false;
+  if (cache->num_kv_heads > kMaxScatterHeads) return false;  // (the scatter refuses them)
   const int group = std::min(cache->num_q_heads / cache->num_kv_heads, kNarrowRows);
   for (int s = 0; s < n_seqs; ++s)
     if ((long long)chunk_lens[s] * group > kNarrowRows) return false;

@@ -39,7 +39,7 @@ int queue_sets_resolve(int** p) { return *p = queue_sets, CRONUS_OK; }
 int static_scratch_upload(void*, const void*, size_t, void*) { std::abort(); }
 int static_scratch_expand(void*, void*, const CompactPlan&, const void*, size_t, void*) { std::abort(); }
 int launch_kv_append(const cronus_kv_cache* c, const cronus_kv_rows*, const cronus_kv_rows*, const int32_t*, int32_t, int32_t, void*, bool) {
-  if (c->num_kv_heads > 65535) return CRONUS_ERR_INVALID_ARG;  // as kv_append.hip, whose grid has no more
+  if (c->num_kv_heads > kMaxScatterHeads) return CRONUS_ERR_INVALID_ARG;  // as kv_append.hip
   enqueued += " rows";
   return CRONUS_OK;
 }

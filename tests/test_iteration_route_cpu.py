@@ -54,3 +54,9 @@ def test_rows_are_placed_where_the_attention_is_not_enqueued(exe, rows):
     assert route(exe, P, C, ws_bytes=256) == "3 rows"
     for failure in ("setup", "buffer", "launch"):
         assert route(exe, P, C, failure=failure) == "4 rows"
+
+
+def test_more_heads_than_the_scatter_takes_are_refused(exe):
+    assert route(exe, [20], [1], heads=(65535, 65535, 64)).startswith("0 ")
+    for P, C in (([20], [1]), ([20], [50])):
+        assert route(exe, P, C, heads=(65536, 65536, 64)) == "1"
