@@ -176,7 +176,7 @@ int cronus_attn_mixed(const cronus_kv_cache* cache, const void* q, void* out,
  * cronus_iteration - a whole iteration (section 4.4) in one call: what cronus_kv_append_pair(cache, first, second, ...) and
  * then cronus_attn_mixed(cache, q, out, ...) do with these arguments, the same bits.  Knowing both halves, it keeps
  * the placed rows out of the GPU's caches where the iteration is bound by streaming the decodes' K/V.
- * Rows of an iteration of decodes (one set of at most 64 rows, at most 64 sequences) are placed by the attention launch itself,
+ * Rows of an iteration of at most 64 decodes (one set with a row for each, up to some contexts) are placed by the attention launch itself,
  * unless k_src, v_src, cu_tokens or start_pos lie in out or in the workspace.
  * Errors: those of the two calls, found before anything is enqueued, with two exceptions: the rows have been placed, and the
  * attention has not been enqueued, when CRONUS_ERR_WORKSPACE reports a workspace that is too small (the plan that tells is built while the

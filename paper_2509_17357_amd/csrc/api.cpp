@@ -302,8 +302,9 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
     return launch_kv_append(cache, first, second, block_tables, max_blocks_per_seq, n_seqs, hip_stream,
                             rows_past_cache(cache, prefix_lens, chunk_lens, n_seqs));
   };
+  const int n_cus = device_cus();
   // (rows that lie in what the attention writes are read before it starts)
-  const bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, chunk_lens, n_seqs) &&
+  const bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, prefix_lens, chunk_lens, n_seqs, n_cus) &&
                          !read_from(cache, first, n_seqs, out, (size_t)total_q * cache->num_q_heads * cache->head_dim * 2) &&
                          !read_from(cache, first, n_seqs, workspace, workspace_bytes);
   auto refused = [&](int rc) {  // after the checks, with the attention not enqueued: the rows are placed all the same
@@ -318,7 +319,6 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   if (total_q == 0) return CRONUS_OK;
 
   Plan plan;
-  const int n_cus = device_cus();
   if (int rc = build_plan(cache, prefix_lens, chunk_lens, n_seqs, max_blocks_per_seq, n_cus, &plan)) return rc;
   if (workspace_refused(workspace)) return CRONUS_ERR_WORKSPACE;
   // a workspace that served these lengths before the tiles were cut finer still does

@@ -119,7 +119,7 @@ struct Records {
 struct NoRecords {
   static constexpr int kMost = 0;
 };
-// The new rows of an iteration of narrow items, which its attention launch places itself (map_rows, place_rows_read).
+// The new rows of an iteration of decodes, which its attention launch places itself (rows_in_launch, map_rows, place_rows_read).
 struct NewRows {
   static constexpr int kVecs = 0;
   const unsigned short* k;
@@ -1334,6 +1334,7 @@ __device__ __forceinline__ void store_row(const AttnParams& p, u32x4 x, int kv_h
   }
 }
 
+// The host asks for this where there is one row for each decode (rows_in_launch), but whose they are and where they go is the device's to tell.
 // Each wave that is about to read a block which holds new rows stores those rows first (place_rows_read), its own sequence's
 // or another's, so no work-group waits for another; who reads the same block elsewhere stores the same bytes.  A wave's loads
 // see the stores before them, and no line of the block can lie stale in the caches, since whoever read it before on this CU
@@ -1472,6 +1473,7 @@ __device__ __forceinline__ void run_narrow(const AttnParams& p, const WorkItem& 
   const unsigned row_list = (unsigned)(unsigned long long)(lds_byte*)smem + attn_lds_bytes<D, FP8>() + kLoopLdsBytes;
   int own_row = -1;  // a decode's row lies in its last sub-tile
   u32x4 own{0, 0, 0, 0};
+  // (The planner's spans are at most 5120 keys, 20 sub-tiles a wave, in the launches that rows_in_launch chooses: one call an item.)
   auto place_rows = [&](int j0) {  // of sub-tiles j0 .. j0 + 31, whose entries have been pinned
     if constexpr (PLACES) {
       const int last = min(n_iter - j0, 32);

@@ -249,15 +249,21 @@ bool compact_plan(const cronus_kv_cache* cache, const Plan* plan, CompactPlan* c
 // Whether the rows of such an iteration are stored past the caches (cronus_iteration).
 bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, const int32_t* chunk_lens, int32_t n_seqs);
 
-// An iteration of narrow items only (decodes) with one set of at most this many rows, and as many sequences, places them in its
-// attention launch: one lane a row, and a block is compared with all rows at once.  One launch less (2.5 us) and no wait for its
-// last work-group.  us a pass, two launches / one: a decode of 5000 keys 16.6 / 14.8, 4 of 1340 .. 3086 17.3 / 15.0, 10 of 68 .. 1037
-// (7 heads a KV head) 14.9 / 12.8, 16 of 281 .. 2407 30.1 / 29.2, 30 of 296 .. 659 18.5 / 16.5, 38 of 155 .. 1333 (8 heads) 32.6 / 30.1,
-// 54 of 143 21.9 / 21.1; fp8, 4 of 65 .. 1194 15.2 / 12.2, 54 of 722 .. 1341 36.1 / 35.3; 24 drawn sets of 1 .. 54 decodes 14 % less on average,
-// none slower.  Chunk tiles read too many rows to store them each for itself.
-constexpr int kMaxNewRows = 64;
-bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* chunk_lens,
-                    int32_t n_seqs);
+// An iteration of at most this many decodes whose one set has a row for each places them in its attention launch: one lane a row, and
+// a block is compared with all rows at once.  One launch less and no wait for its last work-group: 1.5 .. 3 us a pass, two launches / one:
+// a decode of 8000 keys 18.2 / 16.4, 16 of 500 .. 1500 21.2 / 19.9 (7 heads a KV head 17.5 / 15.3), 64 of 20 .. 250 20.9 / 19.4 (D = 64, 2 KV heads
+// 12.7 / 10.1); fp8, 8 of 300 .. 2000 15.9 / 13.6, 64 of 500 .. 1000 32.3 / 31.1.
+// The compares come before an item's first requests, about 0.4 us an item and 0.5 us per 1000 keys of what a CU works on, so the rows of launches
+// with more than kPlacingKeysPerCu keys a CU, a row counting as kPlacingRowKeys, are scattered: 64 of 4000 .. 8000, 8 KV heads, would take 247.8 / 250.7,
+// 64 of 500 .. 1000, 32 KV heads 142.0 / 148.4 (fp8 95.8 / 103.6), 32 of 500 .. 3000 146.4 / 150.6.  Of 187 sets of 1 .. 64 decodes, 2 .. 64 KV heads,
+// 134 are within the line, 0.99 .. 1.37 times as fast as with a scatter (10 % less time on average), and of the others none would gain more than 1.3 us.
+// Rows that are not one a sequence are stored one after the other by whoever reads their block, so they are scattered too: one KV head a query
+// head, 2 chunks of 32 15.7 / 27.3; 4 heads, 16 chunks of 4 22.7 / 26.3, 8 of 8 18.5 / 20.9 (but 8 of 2 18.3 / 16.9); 64 rows of one sequence
+// next to a decode 10.9 / 22.8, and 10.8 / 35.0 where no item reads them; decodes of which half have a row 54.1 / 56.0.  (The host knows
+// their number only: 20 rows of one sequence next to 20 decodes pass for theirs, and take 25.5 / 30.6.)
+constexpr int kMaxNewRows = 64, kPlacingRowKeys = 900, kPlacingKeysPerCu = 4400;
+bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* prefix_lens,
+                    const int32_t* chunk_lens, int32_t n_seqs, int n_cus);
 
 struct AttnLaunch {
   const cronus_kv_cache* cache;

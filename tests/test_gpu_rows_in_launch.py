@@ -1,7 +1,8 @@
-"""Decode iterations place their rows in the attention launch (one set, at most 64 rows and sequences, narrow items only): the bits
-of cronus_kv_append followed by cronus_attn_mixed, in the cache and in the output, on either side of that rule.  Rows one a
-sequence in order, and otherwise: several or none of a sequence, rows past its length or of a sequence without query rows
-(no item reads them), rows that other sequences read too, at the first and last slot of a block, in spans that are not the
+"""Decode iterations place their rows in the attention launch (one set with a row for each of at most 64 decodes): the bits
+of cronus_kv_append followed by cronus_attn_mixed, in the cache and in the output, on either side of that rule (SCATTERED: the cases
+beyond it, which tests/test_iteration_route_cpu.py checks).  Rows one a
+sequence in order, and, since the counts are on the device, otherwise: several or none of a sequence, rows past its length or of a sequence
+without query rows (no item reads them), rows that other sequences read too, at the first and last slot of a block, in spans that are not the
 last, in rows that stay whole (table entries are loaded more than once), more (row, KV head) pairs than work-groups."""
 import numpy as np
 import pytest
@@ -36,7 +37,18 @@ CASES = {
     "read by others": (G4, [40, 41, 42, 600], [1] * 4, "shared"),
     "read by others, fp8": (FP8, [40, 41, 42, 600], [1] * 4, "shared"),
     "left whole": (W.HeadShape(1040, 1040, 64), [8250, 8210, 8195, 8400], [1] * 4, ([1, 30, 1, 1], [8250, 8190, 8195, 100])),
+    # as many rows as decodes, but not one of each
+    "of one sequence": (G4, [100] * 20, [1] * 20, ([20] + [0] * 19, [77] + [100] * 19)),
+    "of one sequence, D 64": (D64, [900, 40, 600], [1] * 3, ([0, 3, 0], [900, 38, 600])),
+    "out of order": (G4, [100, 30, 7, 900], [1] * 4, ([1, 0, 2, 1], [100, 30, 6, 900])),
+    "in other spans": (G7, [3000, 600] + [50] * 25, [1] * 27, ([20, 7] + [0] * 25, [1015, 250] + [0] * 25)),
+    "past the length": (G4, [100, 600, 40, 80] + [33] * 11, [1] * 15, ([3, 2, 9, 1] + [0] * 11, [120, 601, 33, 0] + [0] * 11)),
+    "fp8, past the length": (FP8, [100, 600, 40] + [17] * 14, [1] * 17, ([5, 11, 1] + [0] * 14, [99, 590, 45] + [0] * 14)),
+    "fewer rows than counted": (G4, [100, 600, 40], [1] * 3, ([1, 1, 0], [100, 600, 40])),
+    "more heads than work-groups": (W.HeadShape(1040, 1040, 64), [100], [1], ([1], [120])),
 }
+SCATTERED = ("65", "few work-groups", "short chunks", "some without rows", "rows in other spans", "rows past the length", "fp8, rows past the length",
+             "left whole", "fewer rows than counted")
 
 
 @pytest.mark.parametrize("name", CASES)

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from test_gpu_rows_in_launch import CASES, SCATTERED
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2509_17357_amd", "csrc")
 SCATTER, PLACED = "0 rows attention", "0 attention+rows"
@@ -60,3 +62,32 @@ def test_more_heads_than_the_scatter_takes_are_refused(exe):
     assert route(exe, [20], [1], heads=(65535, 65535, 64)).startswith("0 ")
     for P, C in (([20], [1]), ([20], [50])):
         assert route(exe, P, C, heads=(65536, 65536, 64)) == "1"
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_route_of_the_cases_on_the_gpu(exe, name):
+    shape, P, C, given = CASES[name]
+    rows = sum(given[0]) if isinstance(given, tuple) else None
+    heads = shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+    assert route(exe, P, C, heads, shape.kv_dtype == "fp8", rows=rows) == (SCATTER if name in SCATTERED else PLACED)
+
+
+def test_rule_for_rows_in_the_launch(exe):
+    """One set, one row for each of at most 64 decodes, at most 4400 keys a CU (a row counts as 900, heads beyond 32 a KV head twice)."""
+    for n, want in ((1, PLACED), (63, PLACED), (64, PLACED), (65, SCATTER)):
+        assert route(exe, [100] * n, [1] * n) == want
+    P = [100, 600, 40]
+    assert route(exe, P, [1, 1, 1], rows=2) == route(exe, P, [1, 1, 1], rows=4) == SCATTER
+    assert route(exe, P, [1, 1, 1], rows=0, second=3) == PLACED
+    assert route(exe, P, [1, 1, 1], rows=3, second=3) == SCATTER
+    assert route(exe, P, [1, 2, 1]) == route(exe, P, [1, 2, 1], rows=3) == SCATTER
+    assert route(exe, P, [1, 0, 1]) == route(exe, P, [1, 0, 1], rows=3) == SCATTER
+    cus, row = 4400 * 256, 900
+    for heads, copies in (((32, 8, 128), 8), ((28, 4, 128), 4), ((48, 2, 64), 2), ((80, 2, 128), 4), ((64, 2, 64), 2), ((66, 2, 64), 4)):
+        for fp8 in (False, True):
+            keys = cus // copies - 16 * row  # of 16 decodes, at most
+            P = [keys // 16 - 1] * 15
+            last = keys - 15 * (keys // 16) - 1
+            assert route(exe, P + [last], [1] * 16, heads, fp8) == PLACED
+            assert route(exe, P + [last + 1], [1] * 16, heads, fp8) == SCATTER
+    assert route(exe, [1048575] * 64, [1] * 64, (64, 64, 64), ws_bytes=1 << 40) == SCATTER  # 2^32 keys
