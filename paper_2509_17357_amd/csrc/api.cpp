@@ -304,9 +304,9 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   };
   const int n_cus = device_cus();
   // (rows that lie in what the attention writes are read before it starts)
-  const bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, prefix_lens, chunk_lens, n_seqs, n_cus) &&
-                         !read_from(cache, first, n_seqs, out, (size_t)total_q * cache->num_q_heads * cache->head_dim * 2) &&
-                         !read_from(cache, first, n_seqs, workspace, workspace_bytes);
+  bool in_launch = total_q > 0 && rows_in_launch(cache, first, second, prefix_lens, chunk_lens, n_seqs, n_cus) &&
+                   !read_from(cache, first, n_seqs, out, (size_t)total_q * cache->num_q_heads * cache->head_dim * 2) &&
+                   !read_from(cache, first, n_seqs, workspace, workspace_bytes);
   auto refused = [&](int rc) {  // after the checks, with the attention not enqueued: the rows are placed all the same
     const int placed = in_launch ? place_rows() : CRONUS_OK;
     return placed ? placed : rc;
@@ -327,6 +327,10 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   }
   if (workspace_bytes < plan.total_bytes) return refused(CRONUS_ERR_WORKSPACE);
   if (plan.n_items > 0x7fffffffLL) return CRONUS_ERR_INVALID_ARG;
+  if (in_launch && plan.n_wide > 0) {  // the kernels that place rows have no chunk tiles; a decode's item is narrow, and the plan has the last word
+    if (int rc = place_rows()) return rc;
+    in_launch = false;
+  }
 
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   std::unique_lock<std::mutex> lock(g_mu);

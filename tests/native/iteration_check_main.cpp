@@ -2,7 +2,8 @@
 // launches a call enqueues, in order, and what it returns.  Arguments:
 //   <Hq> <Hkv> <D> <fp8 0|1> <failure> <rows of the first set> <of the second> <k_src> <v_src> <cu_tokens> <start_pos> <out>
 //   <workspace> <workspace bytes> <n_seqs> P0 C0 P1 C1 ...
-// failure: none, setup (kernel attributes), buffer (pinned memory), launch (main kernel).  Addresses are made up, never used.
+// failure: none, setup (kernel attributes), buffer (pinned memory), launch (main kernel), rule (rows_in_launch, which plan.cpp is
+// compiled with another name for, says yes to everything).  Addresses are made up, never used.
 // Prints the status and, for each launch, "rows" (scatter), "attention" or "attention+rows" (which places them itself).
 #include <hip/hip_runtime.h>
 
@@ -33,6 +34,11 @@ hipError_t hipHostGetDevicePointer(void** d, void* p, unsigned) { return *d = p,
 
 namespace cronus {
 int wide_rows_for(int, int) { return kWaves * 32; }
+bool rule_of_plan_cpp(const cronus_kv_cache*, const cronus_kv_rows*, const cronus_kv_rows*, const int32_t*, const int32_t*, int32_t, int);
+bool rows_in_launch(const cronus_kv_cache* c, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* P, const int32_t* C,
+                    int32_t n, int n_cus) {
+  return failure == "rule" || rule_of_plan_cpp(c, first, second, P, C, n, n_cus);
+}
 int prepare_attn_kernels() { return failure == "setup" ? CRONUS_ERR_HIP : CRONUS_OK; }
 int static_scratch_resolve(void** p) { return *p = queue_sets, CRONUS_OK; }
 int queue_sets_resolve(int** p) { return *p = queue_sets, CRONUS_OK; }

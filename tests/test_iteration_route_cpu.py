@@ -21,10 +21,11 @@ def exe(tmp_path_factory):
     if cxx is None or not os.path.exists(os.path.join(rocm, "include", "hip", "hip_runtime.h")):
         pytest.skip("no host C++ compiler or no HIP headers")
     out = str(tmp_path_factory.mktemp("iteration") / "iteration_check")
-    subprocess.run([cxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-w", "-D__HIP_PLATFORM_AMD__",
-                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", os.path.join(rocm, "include"),
-                    os.path.join(ROOT, "tests", "native", "iteration_check_main.cpp"), os.path.join(CSRC, "api.cpp"), os.path.join(CSRC, "plan.cpp"),
-                    os.path.join(CSRC, "balancer.cpp"), "-o", out], check=True)
+    flags = ["-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-w", "-D__HIP_PLATFORM_AMD__",
+             "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-isystem", os.path.join(rocm, "include")]
+    subprocess.run([cxx, *flags, "-Drows_in_launch=rule_of_plan_cpp", "-c", os.path.join(CSRC, "plan.cpp"), "-o", out + ".plan.o"], check=True)
+    subprocess.run([cxx, *flags, os.path.join(ROOT, "tests", "native", "iteration_check_main.cpp"), os.path.join(CSRC, "api.cpp"),
+                    os.path.join(CSRC, "balancer.cpp"), out + ".plan.o", "-o", out], check=True)
     return out
 
 
@@ -91,3 +92,10 @@ def test_rule_for_rows_in_the_launch(exe):
             assert route(exe, P + [last], [1] * 16, heads, fp8) == PLACED
             assert route(exe, P + [last + 1], [1] * 16, heads, fp8) == SCATTER
     assert route(exe, [1048575] * 64, [1] * 64, (64, 64, 64), ws_bytes=1 << 40) == SCATTER  # 2^32 keys
+
+
+def test_launches_with_chunk_tiles_never_place_rows(exe):
+    """Whatever the rule says: the kernels that place rows would run a tile as a narrow item."""
+    for P, C in (([100], [50]), ([100, 9000], [50, 1]), ([3000, 100], [200, 9])):
+        assert route(exe, P, C, failure="rule") == SCATTER
+    assert route(exe, [100, 9000], [2, 8], failure="rule") == PLACED
