@@ -111,7 +111,9 @@ struct NoList {
   static constexpr int kVecs = 0;
 };
 // The records of a launch of at most kFewItems items, by work-group, as a kernel argument: one load of device memory, where a
-// record of host memory is there 2.2 us after the start.  A work-group runs its one item; there are no queues.
+// record of host memory is there 2.2 us after the start.  A work-group's first item is its only one: the launch's queues are empty
+// (p.q_len 0), so it takes no ticket, posts the record that ends the item loop, and counts itself finished as in every launch, for the
+// plan buffer that the call holds all the same.
 struct Records {
   static constexpr int kMost = kFewItems, kVecs = 0;
   int word[kMost][16];
@@ -2025,8 +2027,9 @@ int launch_typed(const AttnLaunch& a, const AttnParams& p, bool* main_launched) 
                      a.rows->start_pos, a.rows->n_tokens, pl.n_seqs, {}};
       for (int i = 0; i < pl.n_seqs; ++i) rows.kv_len[i] = a.chunk_lens[i] > 0 ? a.prefix_lens[i] + a.chunk_lens[i] : 0;
     }
-    Records records;
+    Records records;  // the launch copies all of it
     if (few) {
+      std::memset(records.word + pl.n_items, 0, sizeof(records.word[0]) * (size_t)(kFewItems - pl.n_items));
       // each work-group's item, of the queue of the XCD that it probably runs on while that has one
       int next[kQueues] = {0};
       for (int b = 0; b < (int)pl.n_items; ++b) {
