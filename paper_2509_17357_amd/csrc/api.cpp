@@ -269,6 +269,22 @@ int check_attn_args(const cronus_kv_cache* cache, const void* q, const void* out
   return CRONUS_OK;
 }
 
+// What the launches of both attention entry points have in common; the caller holds g_mu.
+AttnLaunch attn_launch(const cronus_kv_cache* cache, const void* q, void* out, const int32_t* block_tables, int32_t max_blocks_per_seq,
+                       float sm_scale, const Plan& plan, void* hip_stream) {
+  AttnLaunch a{};
+  a.cache = cache;
+  a.q = q;
+  a.out = out;
+  a.block_tables = block_tables;
+  a.max_blocks_per_seq = max_blocks_per_seq;
+  a.sm_scale = sm_scale;
+  a.plan = &plan;
+  a.stream = hip_stream;
+  std::copy(g_ev, g_ev + 4, a.ev);
+  return a;
+}
+
 // Whether an array that the rows are read from shares memory with [p, p + bytes).
 bool read_from(const cronus_kv_cache* cache, const cronus_kv_rows* rows, int32_t n_seqs, const void* p, size_t bytes) {
   auto meets = [&](const void* src, size_t n) {
@@ -344,11 +360,17 @@ int attn_mixed(const cronus_kv_cache* cache, const cronus_kv_rows* first, const 
   write_plan(&plan, host + kSlotHeader);
   // the set of queue heads that belongs to this plan buffer: free again when the buffer is
   const int set = (int)(slot - g_rings[dev].slots);
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, workspace, dev_mem + kSlotHeader,
-               plan.n_items <= std::min<int64_t>(kFewItems, plan.n_workgroups) ? reinterpret_cast<const WorkItem*>(host + kSlotHeader + plan.off_items) : nullptr, nullptr, {}, 0,
-               in_launch ? first : nullptr, prefix_lens, chunk_lens, &plan, hip_stream,
-               g_dev[dev].queue_sets + set * kQueueSetInts, reinterpret_cast<uint32_t*>(dev_mem), ++slot->call,
-               {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+  AttnLaunch a = attn_launch(cache, q, out, block_tables, max_blocks_per_seq, sm_scale, plan, hip_stream);
+  a.workspace = workspace;
+  a.plan_image = dev_mem + kSlotHeader;
+  if (plan.n_items <= std::min<int64_t>(kFewItems, plan.n_workgroups))
+    a.records = reinterpret_cast<const WorkItem*>(host + kSlotHeader + plan.off_items);
+  if (in_launch) a.rows = first;
+  a.prefix_lens = prefix_lens;
+  a.chunk_lens = chunk_lens;
+  a.queue_set = g_dev[dev].queue_sets + set * kQueueSetInts;
+  a.done_flag = reinterpret_cast<uint32_t*>(dev_mem);
+  a.done_value = ++slot->call;
   slot->stream = stream;
   slot->state = is_capturing(stream) ? Slot::kLost : Slot::kPending;
   bool main_launched = false;
@@ -429,8 +451,15 @@ int cronus_attn_mixed_static(const cronus_kv_cache* cache, const void* q, void* 
   // stored and, of the partial slots, exactly the rows that items of this call write first.
   // (The heads of the work queues, which must, live in their own small array, and every
   // launch leaves them zero.)
-  AttnLaunch a{cache, q, out, block_tables, max_blocks_per_seq, sm_scale, base + plan.image_bytes, base,
-               nullptr, listed ? image.data() : nullptr, compact, listed ? compact_bytes : 0, nullptr, nullptr, nullptr, &plan, hip_stream, g_dev[dev].queue_sets + kSlots * kQueueSetInts, nullptr, 0, {g_ev[0], g_ev[1], g_ev[2], g_ev[3]}};
+  AttnLaunch a = attn_launch(cache, q, out, block_tables, max_blocks_per_seq, sm_scale, plan, hip_stream);
+  a.workspace = base + plan.image_bytes;
+  a.plan_image = base;
+  if (listed) {
+    a.list = image.data();
+    a.list_bytes = compact_bytes;
+  }
+  a.compact = compact;
+  a.queue_set = g_dev[dev].queue_sets + kSlots * kQueueSetInts;
   bool main_launched = false;
   return launch_attn(a, &main_launched);
 }
