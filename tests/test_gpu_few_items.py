@@ -27,6 +27,13 @@ CASES = {
     "chunks with tails": (G7, [30, 7], [50, 33], None),
     "tiles, fp8": (W.HeadShape(16, 2, 128, "fp8"), [500, 40], [90, 1], None),
     "tiles of an fp8 copy": (W.HeadShape(64, 1, 64, "fp8"), [100], [70], None),
+    # the longest spans of chunk tiles in so few items (196 steps of 64 keys; of an fp8 copy, 9), in each kernel that takes records
+    "long spans": (W.HeadShape(4, 1, 128), [100000], [300], 40),
+    "long spans, D 64": (W.HeadShape(4, 1, 64), [100000], [300], 40),
+    "long spans, fp8": (W.HeadShape(4, 1, 128, "fp8"), [100000], [300], 40),
+    "long spans, fp8, D 64": (W.HeadShape(4, 1, 64, "fp8"), [100000], [300], 40),
+    "long spans of an fp8 copy": (W.HeadShape(32, 1, 128, "fp8"), [1500], [128], 48),
+    "long spans of an fp8 copy, D 64": (W.HeadShape(32, 1, 64, "fp8"), [1500], [128], 48),
     "skipped sequences": (TWO, [9, 100, 3], [0, 1, 0], 2),
 }
 
@@ -42,6 +49,7 @@ def test_records_in_the_arguments(name):
     b = it.batch
     stats = B.cronus_attn_mixed_plan_stats(it.cache, P, C)
     assert stats["items"] == n_items if n_items else stats["items"] <= 48
+    assert (stats["copy_blocks"] > 0) == ("copy" in name)
     it.place_rows()
     pools = it.k_pool.clone(), it.v_pool.clone()
     B.cronus_attn_mixed_static(it.cache, it.q, it.out, P, C, it.block_tables, b.max_blocks, it.sm_scale)

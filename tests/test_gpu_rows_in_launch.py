@@ -3,7 +3,7 @@ of cronus_kv_append followed by cronus_attn_mixed, in the cache and in the outpu
 beyond it, which tests/test_iteration_route_cpu.py checks).  Rows one a
 sequence in order, and, since the counts are on the device, otherwise: several or none of a sequence, rows past its length or of a sequence
 without query rows (no item reads them), rows that other sequences read too, at the first and last slot of a block, in spans that are not the
-last, in rows that stay whole (table entries are loaded more than once), more (row, KV head) pairs than work-groups."""
+last, more (row, KV head) pairs than work-groups.  Beyond the rule also: rows that stay whole, for which table entries are loaded more than once."""
 import numpy as np
 import pytest
 import torch
@@ -99,11 +99,15 @@ def test_rows_placed_in_the_launch(name):
         got = run(one_call(a, b))
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
         assert np.array_equal(got[2], want[2])
-    if name in ("spans", "rows past the length"):
+    if name == "left whole":
+        items = B.cronus_attn_mixed_plan_items(it.cache, P, C)
+        assert (items[:, 7] - items[:, 6]).max() > 32 * 256  # a wave's 32 sub-tiles, for which it loads entries at once
+    if name in ("spans", "left whole"):
         # a workspace that is too small: the rows are there, the output is not
-        if B.cronus_attn_mixed_plan_stats(it.cache, P, C)["partials"] > 0:
-            got = run(lambda: B.cronus_iteration(it.cache, some, none, q, out, P, C, bt, mb, it.sm_scale, ws, 256, check=False))
-            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and (got[2] & 0x7fff == 0x7fc0).all()
+        assert B.cronus_attn_mixed_plan_stats(it.cache, P, C)["partials"] > 0
+        got = run(lambda: B.cronus_iteration(it.cache, some, none, q, out, P, C, bt, mb, it.sm_scale, ws, 256, check=False))
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and (got[2] & 0x7fff == 0x7fc0).all()
+    if name in ("spans", "past the length"):
         run(one_call(some, none))
         stream = torch.cuda.Stream()
         with torch.cuda.stream(stream):
