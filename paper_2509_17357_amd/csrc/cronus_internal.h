@@ -259,9 +259,11 @@ bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, c
 // 134 are within the line, 0.99 .. 1.37 times as fast as with a scatter (10 % less time on average), and of the others none would gain more than 1.3 us.
 // Rows that are not one a sequence are stored one after the other by whoever reads their block, so they are scattered too: one KV head a query
 // head, 2 chunks of 32 15.7 / 27.3; 4 heads, 16 chunks of 4 22.7 / 26.3, 8 of 8 18.5 / 20.9 (but 8 of 2 18.3 / 16.9); 64 rows of one sequence
-// next to a decode 10.9 / 22.8, and 10.8 / 35.0 where no item reads them; decodes of which half have a row 54.1 / 56.0.  (The host knows
+// next to a decode 10.9 / 22.8, and 10.8 / 35.0 where no item reads them; decodes of which half have a row 54.1 / 56.0.  Where sequences are skipped,
+// a row's sequence is looked for among all, one after the other: with half of the sequences or one skipped, 2 to 8 of 20 .. 3000 keys take
+// 0.73 .. 1.01 of what they take with a scatter, 16 up to 1.04, 32 1.08, 64 1.23, so they may be kPlacingSkippedSeqs at most.  (The host knows
 // their number only: 20 rows of one sequence next to 20 decodes pass for theirs, and take 25.5 / 30.6.)
-constexpr int kMaxNewRows = 64, kPlacingRowKeys = 900, kPlacingKeysPerCu = 4400;
+constexpr int kMaxNewRows = 64, kPlacingRowKeys = 900, kPlacingKeysPerCu = 4400, kPlacingSkippedSeqs = 8;
 bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* prefix_lens,
                     const int32_t* chunk_lens, int32_t n_seqs, int n_cus);
 

@@ -917,16 +917,20 @@ bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, c
 
 bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* prefix_lens,
                     const int32_t* chunk_lens, int32_t n_seqs, int n_cus) {
-  if (!first || second || n_seqs > kMaxNewRows || first->n_tokens != n_seqs) return false;
+  if (!first || second || n_seqs > kMaxNewRows) return false;
   if (cache->num_kv_heads > kMaxScatterHeads) return false;  // (the scatter refuses them)
   long long keys = 0;
+  int rows = 0;
   for (int s = 0; s < n_seqs; ++s) {
-    if (chunk_lens[s] != 1) return false;
+    if (chunk_lens[s] > 1) return false;
+    if (chunk_lens[s] == 0) continue;
+    ++rows;
     keys += prefix_lens[s] + 1LL;
   }
+  if (first->n_tokens != rows || (rows < n_seqs && n_seqs > kPlacingSkippedSeqs)) return false;
   const int q_heads = cache->num_q_heads / cache->num_kv_heads;
   const long long copies = (long long)cache->num_kv_heads * ((q_heads + kNarrowRows - 1) / kNarrowRows);
-  return (keys + kPlacingRowKeys * (long long)n_seqs) * copies <= kPlacingKeysPerCu * (long long)n_cus;
+  return (keys + kPlacingRowKeys * (long long)rows) * copies <= kPlacingKeysPerCu * (long long)n_cus;
 }
 
 }  // namespace cronus

@@ -44,11 +44,14 @@ CASES = {
     "in other spans": (G7, [3000, 600] + [50] * 25, [1] * 27, ([20, 7] + [0] * 25, [1015, 250] + [0] * 25)),
     "past the length": (G4, [100, 600, 40, 80] + [33] * 11, [1] * 15, ([3, 2, 9, 1] + [0] * 11, [120, 601, 33, 0] + [0] * 11)),
     "fp8, past the length": (FP8, [100, 600, 40] + [17] * 14, [1] * 17, ([5, 11, 1] + [0] * 14, [99, 590, 45] + [0] * 14)),
+    "skipped among 8": (G7, [100, 600, 15, 40, 2100, 31, 16, 5], [1, 0, 1, 1, 1, 0, 0, 1], ([1, 0, 1, 1, 1, 0, 0, 1], [100, 600, 15, 40, 2100, 31, 16, 5])),
+    "fp8, skipped among 3": (FP8, [100, 600, 15], [0, 1, 0], ([0, 1, 0], [100, 600, 15])),
+    "skipped among 9": (G4, [100, 600, 15, 40, 900, 31, 16, 5, 8], [1] * 8 + [0], ([1] * 8 + [0], [100, 600, 15, 40, 900, 31, 16, 5, 8])),
     "fewer rows than counted": (G4, [100, 600, 40], [1] * 3, ([1, 1, 0], [100, 600, 40])),
     "more heads than work-groups": (W.HeadShape(1040, 1040, 64), [100], [1], ([1], [120])),
 }
 SCATTERED = ("65", "few work-groups", "short chunks", "some without rows", "rows in other spans", "rows past the length", "fp8, rows past the length",
-             "left whole", "fewer rows than counted")
+             "left whole", "skipped among 9", "fewer rows than counted")
 
 
 @pytest.mark.parametrize("name", CASES)

@@ -74,7 +74,7 @@ def test_route_of_the_cases_on_the_gpu(exe, name):
 
 
 def test_rule_for_rows_in_the_launch(exe):
-    """One set, one row for each of at most 64 decodes, at most 4400 keys a CU (a row counts as 900, heads beyond 32 a KV head twice)."""
+    """One set, one row for each of at most 64 decodes (8 sequences where any is skipped), at most 4400 keys a CU (a row counts as 900, heads beyond 32 a KV head twice)."""
     for n, want in ((1, PLACED), (63, PLACED), (64, PLACED), (65, SCATTER)):
         assert route(exe, [100] * n, [1] * n) == want
     P = [100, 600, 40]
@@ -82,7 +82,9 @@ def test_rule_for_rows_in_the_launch(exe):
     assert route(exe, P, [1, 1, 1], rows=0, second=3) == PLACED
     assert route(exe, P, [1, 1, 1], rows=3, second=3) == SCATTER
     assert route(exe, P, [1, 2, 1]) == route(exe, P, [1, 2, 1], rows=3) == SCATTER
-    assert route(exe, P, [1, 0, 1]) == route(exe, P, [1, 0, 1], rows=3) == SCATTER
+    assert route(exe, P, [1, 0, 1]) == PLACED and route(exe, P, [1, 0, 1], rows=3) == SCATTER
+    for n, want in ((8, PLACED), (9, SCATTER)):
+        assert route(exe, [100] * n, [1] * (n - 1) + [0]) == route(exe, [100] * n, [0] * (n - 1) + [1]) == want
     cus, row = 4400 * 256, 900
     for heads, copies in (((32, 8, 128), 8), ((28, 4, 128), 4), ((48, 2, 64), 2), ((80, 2, 128), 4), ((64, 2, 64), 2), ((66, 2, 64), 4)):
         for fp8 in (False, True):
