@@ -483,6 +483,6 @@ const char* cronus_status_string(int status) {
   }
 }
 
-int cronus_version(void) { return 510; }  // 0.5.10: decode iterations place their rows in the attention launch; small launches carry their records; large gathers read past the caches
+int cronus_version(void) { return 511; }  // 0.5.11: decode iterations place their rows in the attention launch only where that is faster and the rows do not lie in what it writes
 
 }  // extern "C"

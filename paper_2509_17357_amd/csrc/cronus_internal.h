@@ -261,7 +261,7 @@ bool rows_past_cache(const cronus_kv_cache* cache, const int32_t* prefix_lens, c
 // head, 2 chunks of 32 15.7 / 27.3; 4 heads, 16 chunks of 4 22.7 / 26.3, 8 of 8 18.5 / 20.9 (but 8 of 2 18.3 / 16.9); 64 rows of one sequence
 // next to a decode 10.9 / 22.8, and 10.8 / 35.0 where no item reads them; decodes of which half have a row 54.1 / 56.0.  Where sequences are skipped,
 // a row's sequence is looked for among all, one after the other: with half of the sequences or one skipped, 2 to 8 of 20 .. 3000 keys take
-// 0.73 .. 1.01 of what they take with a scatter, 16 up to 1.04, 32 1.08, 64 1.23, so they may be kPlacingSkippedSeqs at most.  (The host knows
+// 0.73 .. 1.02 of what they take with a scatter, 16 up to 1.04, 32 1.08, 64 1.23, so they may be kPlacingSkippedSeqs at most.  (The host knows
 // their number only: 20 rows of one sequence next to 20 decodes pass for theirs, and take 25.5 / 30.6.)
 constexpr int kMaxNewRows = 64, kPlacingRowKeys = 900, kPlacingKeysPerCu = 4400, kPlacingSkippedSeqs = 8;
 bool rows_in_launch(const cronus_kv_cache* cache, const cronus_kv_rows* first, const cronus_kv_rows* second, const int32_t* prefix_lens,

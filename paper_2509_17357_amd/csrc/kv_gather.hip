@@ -22,6 +22,10 @@ template <> struct ChunkOf<1> { typedef unsigned int type __attribute__((ext_vec
 // and its lines would take the place of the rows being written.  Less of it may still lie in the 256 MB cache from its last
 // use.  us a hand-off (gather, then scatter; three in turn), ordinary / non-temporal: 26 MB 22.9 / 23.5, 28 24.2 / 25.1, 33 28.8 / 28.5, 34 30.9 / 29.4,
 // 45 40.2 / 36.3, 60 52.8 / 47.9, 80 67.2 / 62.6, 110 96.6 / 86.6, 150 122.9 / 119.7, 193 137.6 / 134.4, 260 210.0 / 209.2, 400 319.1 / 318.9.
+// A prefix that leaves straight after the iteration that computed it, with a copy of the rows behind: 33 26.8 / 26.8, 45 33.7 / 33.9, 60 41.3 / 41.9,
+// 80 55.4 / 55.4, 95 70.2 / 63.6, 110 86.3 / 76.5, 193 142.0 / 133.9, 240 176.9 / 183.9, 300 220.9 / 224.2, 400 295.0 / 293.5; with nothing before it 45 40.2 / 36.5,
+// 80 74.4 / 59.9, 193 162.3 / 150.5, 300 239.7 / 238.1; nothing but gathers 33 14.6 / 17.1, 45 20.9 / 21.6, 60 28.5 / 27.2, 80 38.8 / 34.3, 193 83.1 / 79.8.  What loses
+// are pools that all stay in the cache, gathered again and again, and the copy behind rows of about the cache's size.
 // (fp8: within 1 % on both sides of it.  Non-temporal stores of the rows: 0.86-0.94 at 33-193 MB.)
 constexpr long long kPastCacheRowBytes = 32'000'000;
 
